@@ -1,14 +1,18 @@
 // Stateless per-operation kernels (general shapes) and their C entry points.
 // Definitions: arXiv 1912.05234, Section 3 -- listings conv, mconv, sigmoid,
 // avgpool, backweights, backbias, backin, backavgpool.  Convolutions and fully
-// connected layers whose operands fit in LDS run as implicit GEMMs on the matrix
-// cores (cnn_igemm.h); the plain one-thread-per-output kernels below serve every
-// other shape.  The fused training step lives in cnn_fused.hip.
+// connected layers run as implicit GEMMs on the matrix cores (cnn_tile.h; the network's
+// own layers in kernels of their own); the plain one-thread-per-output kernels below serve
+// the `*_valu` calls, weight gradients without a workspace, and images beyond the 32-bit offsets
+// of the others.  The fused training step lives in cnn_fused.hip.
+#include <algorithm>
+#include <cmath>
 #include <mutex>
 
 #include "cnn_common.h"
 #include "cnn_igemm.h"
 #include "cnn_igemm_bf16.h"
+#include "cnn_tile.h"
 #include "cnn_col2im.h"
 #include "cnn_conv_wave.h"
 #include "cnn_fc_wave.h"
@@ -248,10 +252,11 @@ __global__ __launch_bounds__(TPB) void logistic_bwd_kernel(const float* __restri
 inline int launched() { return hipGetLastError() == hipSuccess ? CNN_OK : CNN_EHIP; }
 
 // ---- launch plans of the matrix-core kernels ----------------------------------------------------
-constexpr int LDS_LIMIT = 64 * 1024 - 512;  // bytes of dynamic LDS one workgroup may ask for
+constexpr int LDS_LIMIT = 64 * 1024 - 512;  // bytes of dynamic LDS a workgroup of the bf16 kernels may ask for
 constexpr int LDS_TARGET = 48 * 1024;       // preferred, so that three workgroups share a compute unit
-constexpr int WGRAD_LDS_TARGET = 36 * 1024; // both buffers of the weight gradient: four workgroups per compute unit
+constexpr int WGRAD_LDS_TARGET = 36 * 1024; // of their weight gradient: four workgroups per compute unit
 constexpr int CU_LDS = 160 * 1024;
+constexpr int TILE_LDS_LIMIT = 79 * 1024;   // of an image-tiled kernel: two workgroups per compute unit
 constexpr int NUM_CU = 256;
 constexpr int MAX_GROUP = 64;               // images per group
 constexpr int MAX_PARTIALS = 1024;          // workgroup columns (partial sums) of the weight gradient
@@ -264,292 +269,402 @@ unsigned resident_workgroups(size_t lds_bytes) {
   return (unsigned)(NUM_CU * per_cu);
 }
 
-// LDS cycles of the gathered-operand reads of the first two column tiles over the first K steps, in
-// a model of the 64 four-byte banks (measured: a 64-lane read of every second word costs what a read of
-// consecutive words costs, every fourth word twice as much): a wave's read is served in two halves of
-// 32 lanes, and a half takes as many cycles as the largest number of different words that fall into one bank.
-// Lane (q, j) of K step s reads word koff(4 s + q) + poff(16 tile + j).
-constexpr int LDS_BANKS = 64;
-int gather_read_cost(int LW, int LP, int LI, int KH, int KWP, int K, int OWP, int COLS, int P) {
-  const int steps = (K + 3) / 4 < 16 ? (K + 3) / 4 : 16;
-  int cost = 0;
-  for (int tile = 0; tile < 2; ++tile)
-    for (int s = 0; s < steps; ++s)
-      for (int half = 0; half < 2; ++half) {
-        int word[32], worst = 0;
-        for (int l = 0; l < 32; ++l) {
-          const int kk = 4 * s + 2 * half + (l >> 4), n = 16 * tile + (l & 15);
-          const int c = kk / (KH * KWP), rem = kk % (KH * KWP), img = n / COLS, r = n % COLS;
-          word[l] = (kk < K ? c * LP + (rem / KWP) * LW + rem % KWP : 0) + img * LI + (r / OWP) * LW + P * (r % OWP);
-        }
-        int per_bank[LDS_BANKS] = {0};  // different words per bank: each word counted at its first lane
-        for (int l = 0; l < 32; ++l) {
-          bool first = true;
-          for (int e = 0; e < l; ++e) first = first && word[e] != word[l];
-          if (first && ++per_bank[word[l] & (LDS_BANKS - 1)] > worst) worst = per_bank[word[l] & (LDS_BANKS - 1)];
-        }
-        cost += worst;
-      }
-  return cost;
-}
-
-// Row stride (floats) of a bordered plane: the natural one or up to eight floats more, whichever the
-// model above likes best.  (C1's input error, 24 + 2*4 = 32 columns: every row starts in the same
-// bank and the read takes 14 cycles instead of 2; 36 columns make it conflict-free.)  Remembered per
-// shape, since a call should not pay for the search.
-int bordered_row_stride(int SC, int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx, int P) {
+// ---- image-tiled kernels (cnn_tile.h) ------------------------------------------------------------------
+// The last plans made, by shape: choosing one costs tens of microseconds of host time, which a call should
+// not pay twice.  A plan is a pure function of its key (it holds no caller's pointer).
+template <typename PLAN, int KEYS>
+class PlanMemo {
   struct Entry {
-    int key[10], LW;
+    int key[KEYS];
+    PLAN plan;
   };
-  static Entry memo[16];
-  static int used = 0, next = 0;
-  static std::mutex guard;
-  const int key[10] = {SC, SH, SW, KH, KW, OH, OW, pady, padx, P};
-  std::lock_guard<std::mutex> lock(guard);
-  for (int i = 0; i < used; ++i) {
-    bool same = true;
-    for (int e = 0; e < 10; ++e) same = same && memo[i].key[e] == key[e];
-    if (same) return memo[i].LW;
-  }
-  const int base = SW + 2 * padx, rows = SH + 2 * pady, KWP = KW + P - 1, OWP = OW / P;
-  int best_lw = base, best_cost = -1;
-  for (int LW = base; LW <= base + 8; ++LW) {
-    const int LP = rows * LW, cost = gather_read_cost(LW, LP, SC * LP, KH, KWP, SC * KH * KWP, OWP, OH * OWP, P);
-    if (best_cost < 0 || cost < best_cost) best_cost = cost, best_lw = LW;
-  }
-  Entry& slot = memo[next];
-  next = (next + 1) % 16;
-  if (used < 16) ++used;
-  for (int e = 0; e < 10; ++e) slot.key[e] = key[e];
-  slot.LW = best_lw;
-  return best_lw;
-}
+  static constexpr int ENTRIES = 32;
+  Entry entry[ENTRIES];
+  int used = 0, next = 0;
+  std::mutex guard;
 
-struct ConvPlan {
-  igemm::ConvArgs a;
-  int tp = 0;  // pixel tiles per wave job; 0: the shape does not fit, use the plain kernel
-  unsigned grid = 0;
-  size_t lds_bytes = 0;
+ public:
+  template <typename MAKE>
+  PLAN get(const int (&key)[KEYS], MAKE make) {
+    {
+      std::lock_guard<std::mutex> lock(guard);
+      for (int i = 0; i < used; ++i)
+        if (std::equal(key, key + KEYS, entry[i].key)) return entry[i].plan;
+    }
+    const PLAN plan = make();
+    std::lock_guard<std::mutex> lock(guard);
+    Entry& slot = entry[next];
+    next = (next + 1) % ENTRIES;
+    if (used < ENTRIES) ++used;
+    std::copy(key, key + KEYS, slot.key);
+    slot.plan = plan;
+    return plan;
+  }
 };
 
-// dst[B][M][OH][OW] from src[B][SC][SH][SW] staged with a border of (pady, padx), P output pixels
-// per GEMM column.  tp = 0 when the operands do not fit in LDS.
-ConvPlan plan_conv_layout(const float* src, const float* w, const float* bias, float* dst, int B, int M,
-                          int SC, int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx, int flip,
-                          int P, long long LW) {
-  ConvPlan p;
-  igemm::ConvArgs& a = p.a;
-  a.src = src, a.w = w, a.bias = bias, a.dst = dst;
-  a.B = B, a.M = M, a.SC = SC, a.SH = SH, a.SW = SW, a.KH = KH, a.KW = KW, a.OH = OH, a.OW = OW;
-  a.pady = pady, a.padx = padx, a.flip = flip, a.zero_fill = (pady || padx) ? 1 : 0;
-  a.P = P, a.MR = M * P, a.KWP = KW + P - 1, a.OWP = OW / P;
-  const long long K = (long long)SC * KH * a.KWP, LP = (SH + 2LL * pady) * LW, LI = SC * LP;
-  const long long COLS = (long long)OH * a.OWP, MT = ((long long)a.MR + 15) / 16, NBK = (K + 15) / 16;
-  const long long R = a.MR < 16 ? a.MR : 16;
-  if ((MT * (R + 1) * 4 + 4) * (4 * NBK + 4) + 16 * MT + LI + 2 * COLS + 16 > LDS_LIMIT / 4) return p;  // not even one image
-  a.K = (int)K, a.LW = (int)LW, a.LP = (int)LP, a.LI = (int)LI, a.MT = (int)MT, a.R = (int)R, a.NBK = (int)NBK;
-  a.SP = igemm::row_stride(a.NBK);
-  auto bytes = [&](int nb) {
-    a.NB = nb;
-    return (long long)igemm::conv_lds(a).total * 4;
-  };
-  if (bytes(1) > LDS_LIMIT) return p;
-  // Images per group: enough for four column tiles, more when the batch is large, within the LDS
-  // target; among the admissible sizes the one that wastes the fewest matrix instructions on
-  // padding tiles and idle waves.
-  const int nb_tiles = (int)((64 + COLS - 1) / COLS);
-  int nb_want = (B + 2047) / 2048;
-  if (nb_want < nb_tiles) nb_want = nb_tiles;
-  if (nb_want > MAX_GROUP) nb_want = MAX_GROUP;
-  if (nb_want > B) nb_want = B;
+struct TileConvPlan {
+  tile::ConvArgs a;
+  int nt = 0, mt = 0;  // column and row tiles per wave; nt = 0: no unit fits in LDS
+  dim3 grid;
+  size_t lds_bytes = 0;
+  double cost = 0.0;
+};
+
+inline long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
+
+// Fills in one candidate, `res` workgroups per compute unit; false when it does not fit.  The cost is an estimate
+// of the kernel's clocks, linear in what a compute unit has to do: matrix instructions (32 clocks each, partly
+// hidden under the vector instructions of other waves), blocks of operand reads, staging and store instructions,
+// a fixed share per unit, and a memory round trip per unit that a workgroup takes.  The coefficients are a least
+// squares fit to 5000 timed plans of 40 shapes (7 % rms); the plan it picks is on average 1.4 % slower than the
+// fastest one of a shape.
+bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH, int TXC, int res) {
+  tile::ConvArgs& a = p.a;
+  a.P = P, a.MR = a.M * P, a.KWP = a.KW + P - 1;
+  const long long OWP = ceil_div(a.OW, P);
+  a.NB = NB, a.TH = TH, a.TXC = TXC;
+  a.groups = (int)ceil_div(a.B, NB), a.bands = (int)ceil_div(a.OH, TH), a.strips = (int)ceil_div(OWP, TXC);
+  if ((long long)a.groups * a.bands * a.strips > 0x3fffffff || (long long)NB * a.M * a.OH * a.OW >= tile::FAR_SIZE / 4) return false;
+  a.units = a.groups * a.bands * a.strips;
+  a.by_unit = tile::fast_div((long long)a.bands * a.strips), a.by_strip = tile::fast_div(a.strips), a.by_cc = tile::fast_div(a.SC);
+  a.RH = TH + a.KH - 1;
+  const bool border = a.pady || a.padx || a.strips > 1;
+  a.LW = border ? TXC * P + a.KW - 1 : a.SW;
+  a.RPI = a.LW <= 64 ? 64 / a.LW : 1;
+  // (by rows, the last instruction of a plane may bring rows past RH)
+  a.LP = border ? (int)ceil_div(a.RH, a.RPI) * a.RPI * a.LW : a.bands == 1 ? a.SH * a.SW : a.RH * a.LW;
+  const int MB = (int)ceil_div(a.MR, 16 * mt);
+  a.R = a.MR < 16 * mt ? a.MR : 16 * mt;
+  const int plane = a.SH * a.SW;
+  const double total = (double)a.units * MB;
+  if (res > 1 && total <= NUM_CU * (res - 1.0)) return false;
+  int gx = NUM_CU * res / MB > 0 ? NUM_CU * res / MB : 1;
+  if (gx > a.units) gx = a.units;
+  // channels per chunk: the fewest equal shares that fit, with all the weights in LDS or with each chunk's own
   double best = -1.0;
-  int best_nb = 1, best_tp = 1;
-  for (int nb = 1; nb <= nb_want; ++nb) {
-    const long long by = bytes(nb);
-    if (by > LDS_LIMIT || (by > LDS_TARGET && nb > nb_tiles)) break;
-    for (int tp = 1; tp <= 4; tp <<= 1) {
-      const long long PT = (nb * COLS + 15) / 16, jobs = ((PT + tp - 1) / tp) * MT;
-      const double used = (double)nb * COLS / 16.0 * MT, slots = (double)((jobs + 3) / 4) * 4 * tp;
-      const double score = used / slots * (1.0 + 0.005 * tp);  // near ties: share the dense operand
-      if (score >= best) best = score, best_nb = nb, best_tp = tp;
+  tile::ConvArgs keep = a;
+  for (int resident = 1; resident >= 0; --resident)
+    for (int chunks = resident ? 1 : 2; chunks <= a.SC && (chunks == 1 || NB == 1 || !border); ++chunks) {
+      a.CC = (int)ceil_div(a.SC, chunks);
+      if (ceil_div(a.SC, a.CC) != chunks) continue;
+      const long long K = (long long)a.CC * a.KH * a.KWP;
+      if (K > (1 << 16) || (long long)a.CC * a.LP * NB > TILE_LDS_LIMIT / 4) continue;
+      a.chunks = chunks, a.resident = resident, a.K = (int)K, a.NBK = (int)ceil_div(K, 16), a.LI = a.CC * a.LP;
+      // the sixteen columns of a tile are the same pixel of sixteen images when there are few pixels: images start in different banks
+      if (NB > 1 && a.OH * OWP < 16 && !border && a.LI % 8 == 0) a.LI += 4;
+      a.SP = igemm::row_stride(resident ? a.NBK * chunks : a.NBK), a.SK = igemm::row_stride(a.NBK);
+      const long long lds = (long long)tile::conv_lds(a).total * 4;
+      if (lds > TILE_LDS_LIMIT) continue;
+      a.linear = border ? 0
+                 : (a.bands == 1 ? (long long)a.SC * plane % 4 == 0 && (long long)a.CC * plane % 4 == 0 && a.LI % 4 == 0
+                                  : plane % 4 == 0 && a.LP % 4 == 0 && TH * a.SW % 4 == 0) ? 16 : 4;
+      const int by_lds = (int)(CU_LDS / (lds + 512)), by_regs = tile::conv_residency(nt, mt);
+      if (res > (by_lds < by_regs ? by_lds : by_regs)) break;
+      // workgroups of a compute unit, units it works off, units one workgroup takes in turn
+      const double wgs = total < (double)NUM_CU * res ? ceil(total / NUM_CU) : res;
+      const double per_cu = total > NUM_CU ? ceil(total / NUM_CU) : 1.0, turns = (double)ceil_div(a.units, gx) * chunks;
+      const double stage = 0.25 * NB * (!border && a.bands == 1 ? (double)ceil_div(a.CC * a.LP, 16 * a.linear) : a.CC * 1.0 * (!border ? ceil_div(a.LP, 16 * a.linear) : a.LW <= 64 ? ceil_div(a.RH, a.RPI) : a.RH * ceil_div(a.LW, 64)));
+      const double mfma = 128.0 * a.NBK * nt * mt, wt = a.R * 16.0 * a.NBK * chunks / tile::THREADS;
+      const int wide = P % 4 == 0 && a.OW % 4 == 0 ? 4 : P % 2 == 0 && a.OW % 2 == 0 ? 2 : 1;
+      const double unit = chunks * (mfma * (wgs == 1.0 ? 1.1 : wgs == 2.0 ? 0.6 : 0.5) + a.NBK * (80.0 * nt + 23.0) + stage * (border ? 50.0 : 82.0) + 430.0) +
+                          16.5 * nt * mt * 4 / wide + 83.0 * nt;
+      const double cost = 9300.0 + 500.0 * wgs + 290.0 * wt * (resident ? wgs : per_cu) + per_cu * unit + turns * (wgs == 1.0 ? 1970.0 : wgs == 2.0 ? 1820.0 : 1630.0);
+      if (best < 0.0 || cost < best) {
+        best = cost, keep = a;
+        p.lds_bytes = (size_t)lds;
+        p.grid = dim3((unsigned)gx, (unsigned)MB);
+      }
+      break;
     }
+  if (best < 0.0) return false;
+  a = keep;
+  p.cost = best;
+  p.nt = nt, p.mt = mt;
+  a.inv_p = 1.0f / P, a.inv_khkwp = 1.0f / (float)(a.KH * a.KWP), a.inv_kwp = 1.0f / (float)a.KWP;
+  a.inv_cols = 1.0f / (float)(TH * TXC), a.inv_txc = 1.0f / (float)TXC, a.inv_lw = 1.0f / (float)a.LW;
+  a.inv_kp = 1.0f / (float)(16 * a.NBK);
+  return true;
+}
+
+TileConvPlan search_tile_conv(int B, int M, int SC, int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx,
+                              int flip) {
+  TileConvPlan best;
+  if ((long long)SC * SH * SW > (1ll << 29) || (long long)SH * SW >= tile::FAR_SIZE / 4 || OH > (1 << 24) ||
+      (long long)M * SC * KH * KW >= tile::FAR_SIZE / 8 || ceil_div(M, 16) > 60000) return best;
+  TileConvPlan p;
+  tile::ConvArgs& a = p.a;
+  a.src = a.w = a.bias = nullptr, a.dst = nullptr;
+  a.B = B, a.M = M, a.SC = SC, a.SH = SH, a.SW = SW, a.KH = KH, a.KW = KW, a.OH = OH, a.OW = OW;
+  a.pady = pady, a.padx = padx, a.flip = flip;
+  auto consider = [&](int P, int mt, int nt, int NB, int TH, int TXC) {
+    for (int res = 1; res <= 4; ++res)
+      if (tile_conv_candidate(p, P, mt, nt, NB, TH, TXC, res) && (!best.nt || p.cost < best.cost)) best = p;
+  };
+  for (int P = 1; P <= OW && (P == 1 || (KW > 1 && P * M <= 16)); ++P) {
+    if ((P & (P - 1)) && P != 16 / M && OW % P) continue;  // powers of two (wide stores), divisors of the row, the one that fills the tile best
+    for (int mt = 1; mt <= (M > 16 ? 2 : 1); ++mt)
+      for (int nt = 1; nt <= 4; nt <<= 1) {
+        const long long OWP = ceil_div(OW, P), most = 64 * nt;
+        if (OWP > most) {
+          const int strips = (int)ceil_div(OWP, most);
+          consider(P, mt, nt, 1, 1, (int)ceil_div(OWP, strips));
+          continue;
+        }
+        const long long TH = most / OWP;
+        if (TH >= OH) {
+          const long long NB = most / (OH * OWP);
+          consider(P, mt, nt, (int)(NB < B ? NB : B), OH, (int)OWP);
+          if (NB > 1) consider(P, mt, nt, (int)(NB / 2 < B ? NB / 2 : B), OH, (int)OWP);
+        }
+        if (OH > 1) {
+          const int bands = (int)ceil_div(OH, TH < OH ? TH : OH - 1);
+          for (int f = 1; f <= 4; f <<= 1) consider(P, mt, nt, 1, (int)ceil_div(OH, (long long)bands * f), (int)OWP);
+        }
+      }
   }
-  a.NB = best_nb;
-  p.tp = best_tp;
-  a.groups = (B + a.NB - 1) / a.NB;
-  p.lds_bytes = (size_t)bytes(a.NB);
-  const unsigned resident = resident_workgroups(p.lds_bytes);
-  p.grid = (unsigned)a.groups < resident ? (unsigned)a.groups : resident;
-  // How a group reaches LDS: through registers that are loaded while the previous group is
-  // multiplied, as 16-byte items when the images are borderless multiples of four floats.
-  const long long per_image = (long long)SC * SH * SW, per_group = a.NB * per_image;
-  if (!a.zero_fill && per_image % 4 == 0) {
-    a.stage = igemm::STAGE_VECTOR;
-    a.passes = (int)((per_group / 4 + igemm::THREADS * igemm::PFV - 1) / (igemm::THREADS * igemm::PFV));
-  } else {
-    a.stage = igemm::STAGE_SCALAR;
-    a.passes = (int)((per_group + igemm::THREADS * igemm::PFS - 1) / (igemm::THREADS * igemm::PFS));
-  }
-  a.inv_sp = 1.0f / (float)a.SP, a.inv_r1 = 1.0f / (float)(a.R + 1), a.inv_p = 1.0f / (float)P;
-  a.inv_khkwp = 1.0f / (float)(KH * a.KWP), a.inv_kwp = 1.0f / (float)a.KWP;
-  a.inv_ohowp = 1.0f / (float)COLS, a.inv_owp = 1.0f / (float)a.OWP;
-  a.inv_sw = 1.0f / (float)SW, a.inv_sh = 1.0f / (float)SH;
+  return best;
+}
+
+TileConvPlan plan_tile_conv(const float* src, const float* w, const float* bias, float* dst, int B, int M, int SC,
+                            int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx, int flip) {
+  static PlanMemo<TileConvPlan, 12> memo;
+  TileConvPlan p = memo.get({B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip}, [&] {
+    return search_tile_conv(B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip);
+  });
+  p.a.src = src, p.a.w = w, p.a.bias = bias, p.a.dst = dst;
   return p;
 }
 
-// Bordered planes get the row stride the bank model prefers when the operands still fit with it.
-ConvPlan plan_conv_packed(const float* src, const float* w, const float* bias, float* dst, int B, int M,
-                          int SC, int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx, int flip,
-                          int P) {
-  const long long natural = SW + 2LL * padx, K = (long long)SC * KH * (KW + P - 1);
-  // the search works in int: only for planes that could fit in LDS at all
-  if ((pady || padx) && SC * (SH + 2LL * pady) * natural < LDS_LIMIT / 4 && K < (1 << 20)) {
-    const long long LW = bordered_row_stride(SC, SH, SW, KH, KW, OH, OW, pady, padx, P);
-    if (LW != natural) {
-      const ConvPlan p = plan_conv_layout(src, w, bias, dst, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip, P, LW);
-      if (p.tp) return p;
-    }
-  }
-  return plan_conv_layout(src, w, bias, dst, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip, P, natural);
+// More than 64 KB of dynamic LDS has to be asked for.
+template <typename ARGS>
+void launch_tiled(void (*kernel)(const ARGS), dim3 grid, size_t lds_bytes, hipStream_t stream, const ARGS& args) {
+  if (lds_bytes > 64 * 1024)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+  kernel<<<grid, tile::THREADS, lds_bytes, stream>>>(args);
 }
 
-// The packing factor: the largest divisor P of OW with M*P <= 16 whose operands fit in LDS (a wider
-// kernel row costs LDS for the weight table); 1 for kernels one column wide, where packing gains nothing.
-ConvPlan plan_conv(const float* src, const float* w, const float* bias, float* dst, int B, int M, int SC,
-                   int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx, int flip) {
-  if (KW > 1)
-    for (int P = 16 / M; P >= 2; --P) {
-      if (OW % P) continue;
-      const ConvPlan p = plan_conv_packed(src, w, bias, dst, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip, P);
-      if (p.tp) return p;
-    }
-  return plan_conv_packed(src, w, bias, dst, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip, 1);
+template <bool BORDER>
+void launch_tile_conv_as(const TileConvPlan& p, hipStream_t stream) {
+  switch (10 * p.mt + p.nt) {
+    case 11: launch_tiled(tile::conv_kernel<1, 1, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 12: launch_tiled(tile::conv_kernel<2, 1, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 14: launch_tiled(tile::conv_kernel<4, 1, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 21: launch_tiled(tile::conv_kernel<1, 2, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 22: launch_tiled(tile::conv_kernel<2, 2, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+    default: launch_tiled(tile::conv_kernel<4, 2, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+  }
 }
 
-int launch_conv(const ConvPlan& p, hipStream_t stream) {
-  switch (p.tp) {
-    case 4: igemm::conv_kernel<4><<<p.grid, igemm::THREADS, p.lds_bytes, stream>>>(p.a); break;
-    case 2: igemm::conv_kernel<2><<<p.grid, igemm::THREADS, p.lds_bytes, stream>>>(p.a); break;
-    default: igemm::conv_kernel<1><<<p.grid, igemm::THREADS, p.lds_bytes, stream>>>(p.a); break;
+int launch_tile_conv(const TileConvPlan& p, hipStream_t stream) {
+  if (p.a.linear)
+    launch_tile_conv_as<false>(p, stream);
+  else
+    launch_tile_conv_as<true>(p, stream);
+  return launched();
+}
+
+struct TileWgradPlan {
+  tile::WgradArgs a;
+  int nt = 0, mt = 0;
+  dim3 grid;
+  size_t lds_bytes = 0, workspace_bytes = 0, interface_bytes = 0;
+  double cost = 0.0;
+};
+
+// As above for the weight gradient; res = 0: one workgroup column, which needs no second kernel.  (Fit: 12600 plans,
+// 10 % rms, 5 % lost on average.)
+bool tile_wgrad_candidate(TileWgradPlan& p, int P, int mt, int nt, int NB, int TH, int res) {
+  tile::WgradArgs& a = p.a;
+  const int plane = a.H * a.W;
+  a.P = P, a.MR = a.Cout * P, a.KWP = a.KW + P - 1, a.WOP = (int)ceil_div(a.Wo, P);
+  a.K = a.Cin * a.KH * a.KWP, a.MT = (int)ceil_div(a.MR, 16), a.NT = (int)ceil_div(a.K, 16);
+  const int KHKWP = a.KH * a.KWP;
+  // taps of a workgroup: all of its tiles, or (packed) whole groups of KWP
+  a.TG = P == 1 ? 16 * nt : 16 * nt / a.KWP * a.KWP;
+  if (a.TG < 1) return false;
+  if (a.TG > a.K) a.TG = a.K;
+  a.NTG = (int)ceil_div(a.K, a.TG);
+  a.RS = a.Cout * a.Cin * a.KH * a.KW + a.Cout;
+  const int MB = (int)ceil_div(a.MT, mt);
+  a.NB = NB, a.TH = TH, a.groups = (int)ceil_div(a.B, NB), a.bands = (int)ceil_div(a.Ho, TH);
+  if ((long long)a.groups * a.bands > 0x3fffffff || (long long)NB * a.Cout * a.Ho * a.Wo >= tile::FAR_SIZE / 4) return false;
+  a.units = a.groups * a.bands;
+  // channels a group of 16 nt consecutive taps can touch
+  const long long cg = a.NTG == 1 ? a.Cin : (16LL * nt + KHKWP - 2) / KHKWP + 1;
+  a.CG = (int)(cg < a.Cin ? cg : a.Cin);
+  a.RH = a.bands == 1 ? a.H : TH + a.KH - 1;
+  if ((long long)NB * a.CG * a.RH * a.W > TILE_LDS_LIMIT / 4 || (long long)NB * TH * a.WOP > 4096) return false;
+  a.LP = a.RH * a.W, a.LI = a.CG * a.LP;
+  a.R = a.MR < 16 * mt ? a.MR : 16 * mt;
+  a.N = NB * TH * a.WOP, a.NBK = (a.N + 15) / 16, a.NPS = 16 * a.NBK + 4;
+  a.vec_x = plane % 4 == 0 && a.LP % 4 == 0 && (a.bands == 1 || TH * a.W % 4 == 0) ? 16 : 4;
+  if (a.bands == 1 && a.NTG == 1 && (long long)a.Cin * plane % 4 == 0) a.vec_x = 16;  // (runs of whole images)
+  const long long end = tile::wgrad_end_floats(nt, mt), all = tile::wgrad_lds(a).total, lds = 4 * (all > end ? all : end);
+  if (lds > TILE_LDS_LIMIT) return false;
+  const int regs = 4 * nt * mt + 3 * nt + 60;  // registers a wave needs, roughly
+  if (res > CU_LDS / (lds + 512) || res > 512 / regs) return false;
+  if (res > 1 && (double)a.units * MB * a.NTG <= NUM_CU * (res - 1.0)) return false;
+  int gx = NUM_CU * res / (MB * a.NTG);
+  if (gx < 1 || res == 0) gx = 1;
+  if (gx > a.units) gx = a.units;
+  const double total = (double)gx * MB * a.NTG, wgs = total > NUM_CU ? ceil(total / NUM_CU) : 1.0, share = total > NUM_CU ? total / NUM_CU : 1.0;
+  const double turns = (double)ceil_div(a.units, gx), blocks = (double)ceil_div(a.NBK, tile::WAVES), mfma = 128.0 * blocks * nt * mt;
+  const double x_instr = (double)NB * (a.bands == 1 ? ceil_div((long long)a.CG * a.LP, 16 * a.vec_x) : a.CG * ceil_div(a.LP, 16 * a.vec_x)), d_instr = (double)a.R * ceil_div(a.NBK, 4);
+  p.cost = 9500.0 + 256.0 * wgs * nt * mt +
+           turns * (share * (mfma * (wgs == 1.0 ? 2.0 : wgs == 2.0 ? 0.9 : 0.5) + blocks * (5.0 * nt + 320.0) + 19.0 * x_instr + 33.0 * d_instr) + 2000.0) +
+           (gx > 1 ? 6650.0 + 0.0097 * gx * a.RS + 2.4 * gx : 0.0);
+  p.nt = nt, p.mt = mt, p.lds_bytes = (size_t)lds;
+  p.grid = dim3((unsigned)gx, (unsigned)(MB * a.NTG));
+  p.workspace_bytes = gx > 1 ? (size_t)gx * a.RS * sizeof(float) : 0;
+  a.inv_khkwp = 1.0f / (float)KHKWP, a.inv_kwp = 1.0f / (float)a.KWP, a.inv_slots = 1.0f / (float)(TH * a.WOP), a.inv_wop = 1.0f / (float)a.WOP;
+  a.by_band = tile::fast_div(a.bands), a.by_p = tile::fast_div(P);
+  return true;
+}
+
+TileWgradPlan search_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
+  TileWgradPlan best, p;
+  tile::WgradArgs& a = p.a;
+  a.in = a.d_out = nullptr, a.out_k = a.out_b = nullptr;
+  a.B = B, a.Cin = Cin, a.H = H, a.W = W, a.Cout = Cout, a.KH = KH, a.KW = KW, a.Ho = H - KH + 1, a.Wo = W - KW + 1;
+  const long long K = (long long)Cin * KH * KW;
+  if ((long long)Cin * H * W > (1ll << 29) || (long long)H * W >= tile::FAR_SIZE / 4 || 16 * K > (1 << 22)) return best;
+  if (ceil_div(Cout, 16) * ceil_div(K, 16) > 60000) return best;
+  // up to two million multiply-adds on few images: one workgroup column, the second kernel would cost more than it saves
+  const bool tiny = B <= 64 && (double)B * Cout * a.Ho * a.Wo * K <= 2097152.0;
+  for (int P = 1; P <= a.Wo && (P == 1 || (KW > 1 && P * Cout <= 16)); ++P) {
+    if ((P & (P - 1)) && P != 16 / Cout && a.Wo % P) continue;
+    for (int mt = 1; mt <= (Cout > 16 ? 2 : 1); ++mt) {
+      const int NT = (int)ceil_div((long long)Cin * KH * (KW + P - 1), 16);
+      for (int nt : {1, 2, 3, 4, 6, 8, 12}) {
+        if (nt * mt > 16 || (nt > 1 && nt / 2 >= NT) || 16 * nt < KW + P - 1) continue;
+        auto consider = [&](int NB, int TH) {
+          for (int res = B > 64 ? 1 : 0; res <= (tiny ? 0 : 4); ++res)
+            if (tile_wgrad_candidate(p, P, mt, nt, NB, TH, res) && (!best.nt || p.cost < best.cost)) best = p;
+        };
+        const long long WOP = ceil_div(a.Wo, P);
+        for (int NB = 1; NB <= B && NB * a.Ho * WOP <= 1536; NB = NB < 4 ? NB + 1 : 2 * NB) consider(NB, a.Ho);
+        for (int TH = 1; TH < a.Ho && TH * WOP <= 1536; ++TH)
+          if (TH <= 4 || ceil_div(a.Ho, TH) != ceil_div(a.Ho, TH - 1)) consider(1, TH);
+      }
+    }
   }
+  return best;
+}
+
+// The workspace that callers have been asked for, and the shapes that the built-in scratch has been documented to
+// accept or to refuse, are part of the interface: a layout of one 16 x 16 tile per workgroup column, row tile and tap
+// tile, with as many columns as workgroups of whole images are resident.  0 for shapes whose images do not fit in
+// LDS.  The tiled kernels need less.
+size_t tile_layout_bytes(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
+  const long long Ho = H - KH + 1, Wo = W - KW + 1, per_image = (long long)Cin * H * W;
+  auto bytes_for = [&](int P) -> size_t {
+    const long long K = (long long)Cin * KH * (KW + P - 1), SPI = Ho * (Wo / P), MT = ceil_div((long long)Cout * P, 16), NT = ceil_div(K, 16);
+    const long long R = Cout * P < 16 ? Cout * P : 16, cx = per_image % 4 == 0 ? 256 : 64, cd = P == 1 && Ho * Wo % 4 == 0 ? 256 : 64;
+    if (2 * (per_image + 2 * SPI) > LDS_LIMIT / 4 || K > (1 << 20)) return 0;
+    auto lds = [&](long long nb) {
+      const long long blocks = ceil_div(nb * SPI, 16), total = 16 * blocks + 2 * ((R + 1) * (16 * blocks + 4) + ceil_div(nb * per_image, cx) * cx);
+      const long long handover = 16 * blocks + igemm::WAVES * 272;
+      return 4 * (total > handover ? total : handover);
+    };
+    if (SPI > 16 * cd || lds(1) > LDS_LIMIT) return 0;
+    long long nb = 1;
+    for (long long c = 2; c <= MAX_GROUP && c <= B && c <= ceil_div(B, MAX_PARTIALS) && lds(c) <= WGRAD_LDS_TARGET && c * SPI <= 16 * cd; ++c) nb = c;
+    long long gx = resident_workgroups((size_t)lds(nb)) / (MT * ceil_div(NT, 16));
+    gx = gx < 1 ? 1 : gx > MAX_PARTIALS ? MAX_PARTIALS : gx;
+    if (gx > ceil_div(B, nb)) gx = ceil_div(B, nb);
+    return (size_t)(gx * MT * (NT * 256 + 16)) * sizeof(float);
+  };
+  int best = 1;
+  long long best_cost = -1;
+  for (int P = 1; KW > 1 && P * Cout <= 16; ++P) {
+    if (Wo % P) continue;
+    const long long cost = ceil_div((long long)Cin * KH * (KW + P - 1), 16) * ceil_div(Ho * (Wo / P), 16);
+    if (best_cost < 0 || cost < best_cost) best_cost = cost, best = P;
+  }
+  for (int P = best; P >= 1; --P)
+    if (Wo % P == 0)
+      if (const size_t bytes = bytes_for(P)) return bytes;
+  return 0;
+}
+
+TileWgradPlan plan_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
+  static PlanMemo<TileWgradPlan, 7> memo;
+  return memo.get({B, Cin, H, W, Cout, KH, KW}, [&] {
+    TileWgradPlan p = search_tile_wgrad(B, Cin, H, W, Cout, KH, KW);
+    p.interface_bytes = tile_layout_bytes(B, Cin, H, W, Cout, KH, KW);
+    return p;
+  });
+}
+
+int launch_tile_wgrad(TileWgradPlan& p, const float* in, const float* d_out, float* d_k, float* d_bias, float* part,
+                      hipStream_t st) {
+  const int nk = p.a.RS - p.a.Cout, G = (int)p.grid.x;
+  p.a.in = in, p.a.d_out = d_out, p.a.out_k = G > 1 ? part : d_k, p.a.out_b = G > 1 ? part + nk : d_bias;
+#define CNN_TILE_WGRAD(NT, MT) \
+  case 100 * MT + NT: launch_tiled(tile::wgrad_kernel<NT, MT>, p.grid, p.lds_bytes, st, p.a); break
+  switch (100 * p.mt + p.nt) {
+    CNN_TILE_WGRAD(1, 1);
+    CNN_TILE_WGRAD(2, 1);
+    CNN_TILE_WGRAD(3, 1);
+    CNN_TILE_WGRAD(4, 1);
+    CNN_TILE_WGRAD(6, 1);
+    CNN_TILE_WGRAD(8, 1);
+    CNN_TILE_WGRAD(12, 1);
+    CNN_TILE_WGRAD(1, 2);
+    CNN_TILE_WGRAD(2, 2);
+    CNN_TILE_WGRAD(3, 2);
+    CNN_TILE_WGRAD(4, 2);
+    CNN_TILE_WGRAD(6, 2);
+    CNN_TILE_WGRAD(8, 2);
+    default: return CNN_EINVAL;
+  }
+#undef CNN_TILE_WGRAD
+  if (G == 1) return launched();
+  if (p.a.RS > 8192)
+    tile::reduce_rows_kernel<64><<<(unsigned)ceil_div(p.a.RS, 64), 1024, 0, st>>>(part, G, p.a.RS, nk, d_k, d_bias);
+  else
+    tile::reduce_rows_kernel<16><<<(unsigned)ceil_div(p.a.RS, 16), 1024, 0, st>>>(part, G, p.a.RS, nk, d_k, d_bias);
   return launched();
 }
 
 struct WgradPlan {
-  igemm::WgradArgs a;
-  bool fits = false;
-  bool one_wave_per_image = false;  // the shape of one of the network's convolutions: conv1:: / conv2::bwd_weight_kernel, gx workgroups
-  bool fc_rows = false;             // the shape of the network's fully connected layer: fc::bwd_weight_kernel, gx workgroups
-  unsigned gx = 0, gy = 0;
-  size_t lds_bytes = 0, workspace_bytes = 0;
+  // which kernel: cnn_tile.h by the plan in `tile`, or one of the network's own layers (gx workgroups that leave partial
+  // 16 x 16 tiles, MT x NT of them with P shifts, for igemm::wgrad_reduce_kernel)
+  enum { PLAIN, TILED, CONV1, CONV2, FC } kernel = PLAIN;
+  TileWgradPlan tile;
+  int P = 1, MT = 1, NT = 0;
+  unsigned gx = 0;
+  size_t workspace_bytes = 0;
 };
 
-WgradPlan plan_wgrad_packed(int B, int Cin, int H, int W, int Cout, int KH, int KW, int P) {
-  WgradPlan p;
-  igemm::WgradArgs& a = p.a;
-  a.in = nullptr, a.d_out = nullptr, a.part = nullptr;
-  a.B = B, a.Cin = Cin, a.H = H, a.W = W, a.Cout = Cout, a.KH = KH, a.KW = KW;
-  a.Ho = H - KH + 1, a.Wo = W - KW + 1;
-  a.P = P, a.MR = Cout * P, a.KWP = KW + P - 1, a.WOP = a.Wo / P;
-  const long long K = (long long)Cin * KH * a.KWP, HoWo = (long long)a.Ho * a.Wo, SPI = (long long)a.Ho * a.WOP;
-  const long long per_image = (long long)Cin * H * W;
-  if (2 * (per_image + 2 * SPI) > LDS_LIMIT / 4 || K > (1 << 20)) return p;
-  a.K = (int)K, a.MT = (a.MR + 15) / 16, a.NT = (int)((K + 15) / 16), a.NTG = (a.NT + 15) / 16;
-  a.KS = a.NT >= 3 ? 1 : a.NT == 2 ? 2 : 4;
-  a.R = a.MR < 16 ? a.MR : 16;
-  a.vec_x = per_image % 4 == 0 ? 1 : 0;
-  a.vec_d = (P == 1 && HoWo % 4 == 0) ? 1 : 0;
-  const int chunk_x = a.vec_x ? 256 : 64, chunk_d = a.vec_d ? 256 : 64;  // floats per staging load instruction
-  auto bytes = [&](int nb) {
-    a.NB = nb;
-    a.NBK = (int)((nb * SPI + 15) / 16);
-    a.NPS = igemm::error_row_stride(a.NBK);
-    a.XS = (int)((nb * per_image + chunk_x - 1) / chunk_x * chunk_x);
-    return (long long)igemm::wgrad_lds(a).total * 4;
-  };
-  if (SPI > 16LL * chunk_d || bytes(1) > LDS_LIMIT) return p;
-  int nb = 1;
-  const int nb_fill = (B + MAX_PARTIALS - 1) / MAX_PARTIALS;
-  // more images per group while the partial sums stay at MAX_PARTIALS columns, the two buffers stay
-  // within the LDS target and a row of the output error within sixteen load instructions
-  for (int c = 2; c <= MAX_GROUP && c <= B && c <= nb_fill && bytes(c) <= WGRAD_LDS_TARGET && c * SPI <= 16LL * chunk_d;
-       ++c)
-    nb = c;
-  p.lds_bytes = (size_t)bytes(nb);
-  a.groups = (B + nb - 1) / nb;
-  unsigned gx = resident_workgroups(p.lds_bytes) / (unsigned)(a.MT * a.NTG);
-  if (gx < 1) gx = 1;
-  if (gx > MAX_PARTIALS) gx = MAX_PARTIALS;
-  if (gx > (unsigned)a.groups) gx = (unsigned)a.groups;
-  p.gx = gx;
-  p.gy = (unsigned)(a.MT * a.NTG);
-  p.workspace_bytes = ((size_t)gx * a.MT * a.NT * 256 + (size_t)gx * a.MT * 16) * sizeof(float);
-  a.inv_p = 1.0f / (float)P, a.inv_khkwp = 1.0f / (float)(KH * a.KWP), a.inv_kwp = 1.0f / (float)a.KWP;
-  a.inv_spi = 1.0f / (float)SPI, a.inv_wop = 1.0f / (float)a.WOP;
-  p.fits = true;
-  return p;
-}
-
-// The packing factor that needs the fewest matrix instructions per image (column tiles x blocks of
-// pixel slots) among the divisors P of Wo with Cout*P <= 16; 1 for kernels one column wide.
 WgradPlan plan_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
+  WgradPlan p;
+  auto groups = [&](int images) {  // workgroups that take `images` images per round, at most two per compute unit
+    const unsigned g = (unsigned)ceil_div(B, images);
+    return g < 2u * NUM_CU ? g : 2u * NUM_CU;
+  };
   if (conv1::shape_fits(Cin, H, W, Cout, KH, KW)) {
-    WgradPlan p;
-    igemm::WgradArgs& a = p.a;
-    a.in = nullptr, a.d_out = nullptr, a.part = nullptr;
-    a.B = B, a.Cin = Cin, a.H = H, a.W = W, a.Cout = Cout, a.KH = KH, a.KW = KW;
-    a.P = 2, a.MT = 1, a.NT = 2;  // rows (map, x parity), columns the shifted taps: what the second kernel joins
-    p.fits = p.one_wave_per_image = true;
-    const unsigned groups = (unsigned)((B + conv1::WAVES_PER_GROUP - 1) / conv1::WAVES_PER_GROUP);
-    p.gx = groups < 2u * NUM_CU ? groups : 2u * NUM_CU;
-    p.gy = 1;
+    p.kernel = WgradPlan::CONV1;
+    p.P = 2, p.NT = 2;  // rows (map, x parity), columns the shifted taps: what the second kernel joins
+    p.gx = groups(conv1::WAVES_PER_GROUP);
     p.workspace_bytes = conv1::bwd_weight_workspace_bytes(p.gx);
-    return p;
-  }
-  if (H == 1 && W == 1 && KH == 1 && KW == 1 && fc::shape_fits(Cin, Cout)) {
-    WgradPlan p;
-    igemm::WgradArgs& a = p.a;
-    a.in = nullptr, a.d_out = nullptr, a.part = nullptr;
-    a.B = B, a.Cin = Cin, a.H = H, a.W = W, a.Cout = Cout, a.KH = KH, a.KW = KW;
-    a.P = 1, a.MT = 1, a.NT = fc::NT;  // what the second kernel needs to find the partial tiles
-    p.fits = p.fc_rows = true;
-    // a wave takes fc::AHEAD steps of four images per memory round trip
-    const int per_group = 4 * fc::AHEAD * fc::WGRAD_WAVES;
-    const unsigned groups = (unsigned)((B + per_group - 1) / per_group);
-    p.gx = groups < 2u * NUM_CU ? groups : 2u * NUM_CU;
-    p.gy = 1;
+  } else if (H == 1 && W == 1 && KH == 1 && KW == 1 && fc::shape_fits(Cin, Cout)) {
+    p.kernel = WgradPlan::FC;
+    p.NT = fc::NT;
+    p.gx = groups(4 * fc::AHEAD * fc::WGRAD_WAVES);  // a wave takes fc::AHEAD steps of four images per memory round trip
     p.workspace_bytes = fc::bwd_weight_workspace_bytes(p.gx);
-    return p;
-  }
-  if (conv2::shape_fits(Cin, H, W, Cout, KH, KW)) {
-    WgradPlan p;
-    igemm::WgradArgs& a = p.a;
-    a.in = nullptr, a.d_out = nullptr, a.part = nullptr;
-    a.B = B, a.Cin = Cin, a.H = H, a.W = W, a.Cout = Cout, a.KH = KH, a.KW = KW;
-    a.P = 1, a.MT = 1, a.NT = 10;  // what the second kernel needs to find the partial tiles
-    p.fits = p.one_wave_per_image = true;
-    const unsigned groups = (unsigned)((B + conv2::WAVES_PER_GROUP - 1) / conv2::WAVES_PER_GROUP);
-    p.gx = groups < 2u * NUM_CU ? groups : 2u * NUM_CU;  // two workgroups per compute unit are resident
-    p.gy = 1;
+  } else if (conv2::shape_fits(Cin, H, W, Cout, KH, KW)) {
+    p.kernel = WgradPlan::CONV2;
+    p.NT = 10;
+    p.gx = groups(conv2::WAVES_PER_GROUP);
     p.workspace_bytes = conv2::bwd_weight_workspace_bytes(p.gx);
-    return p;
+  } else {
+    p.tile = plan_tile_wgrad(B, Cin, H, W, Cout, KH, KW);
+    if (p.tile.nt) p.kernel = WgradPlan::TILED;
+    p.workspace_bytes = p.tile.workspace_bytes;
+    if (p.tile.nt && p.tile.interface_bytes > p.workspace_bytes) p.workspace_bytes = p.tile.interface_bytes;
   }
-  int best = 1;
-  if (KW > 1) {
-    const long long Ho = H - KH + 1, Wo = W - KW + 1;
-    long long best_cost = -1;
-    for (int P = 1; P * Cout <= 16; ++P) {
-      if (Wo % P) continue;
-      const long long cost = (((long long)Cin * KH * (KW + P - 1) + 15) / 16) * ((Ho * (Wo / P) + 15) / 16);
-      if (best_cost < 0 || cost < best_cost) best_cost = cost, best = P;
-    }
-  }
-  for (int P = best; P > 1; --P) {
-    if ((W - KW + 1) % P) continue;
-    const WgradPlan p = plan_wgrad_packed(B, Cin, H, W, Cout, KH, KW, P);
-    if (p.fits) return p;
-  }
-  return plan_wgrad_packed(B, Cin, H, W, Cout, KH, KW, 1);
+  return p;
 }
 
 // ---- reduced precision: the bf16 matrix-core kernel ------------------------------------------------
@@ -697,29 +812,19 @@ inline bool wgrad_args_ok(const float* in, const float* d_out, const float* d_k,
 
 // The matrix-core weight gradient: partial tiles per workgroup column into `part`, then the
 // fixed-order sum of the columns.
-int launch_wgrad(WgradPlan& p, const float* in, const float* d_out, float* d_k, float* d_bias, float* part,
-                 hipStream_t st) {
-  p.a.in = in, p.a.d_out = d_out, p.a.part = part;
-  const dim3 grid(p.gx, p.gy);
-  if (p.fc_rows)
-    fc::bwd_weight_kernel<<<p.gx, fc::WGRAD_THREADS, 0, st>>>(in, d_out, part, p.a.B);
-  else if (p.one_wave_per_image && p.a.Cin == 1)
-    conv1::bwd_weight_kernel<<<p.gx, conv1::THREADS, 0, st>>>(in, d_out, part, p.a.B);
-  else if (p.one_wave_per_image)
-    conv2::bwd_weight_kernel<<<p.gx, conv2::THREADS, 0, st>>>(in, d_out, part, p.a.B);
-  else if (p.a.vec_x && p.a.vec_d)
-    igemm::wgrad_kernel<16, 16><<<grid, igemm::THREADS, p.lds_bytes, st>>>(p.a);
-  else if (p.a.vec_x)
-    igemm::wgrad_kernel<16, 4><<<grid, igemm::THREADS, p.lds_bytes, st>>>(p.a);
-  else if (p.a.vec_d)
-    igemm::wgrad_kernel<4, 16><<<grid, igemm::THREADS, p.lds_bytes, st>>>(p.a);
-  else
-    igemm::wgrad_kernel<4, 4><<<grid, igemm::THREADS, p.lds_bytes, st>>>(p.a);
-  const igemm::WgradArgs& a = p.a;
-  const size_t outputs = (size_t)a.Cout * a.Cin * a.KH * a.KW + a.Cout;
+int launch_wgrad(WgradPlan& p, const float* in, const float* d_out, float* d_k, float* d_bias, int B, int Cin, int Cout,
+                 int KH, int KW, float* part, hipStream_t st) {
+  switch (p.kernel) {
+    case WgradPlan::TILED: return launch_tile_wgrad(p.tile, in, d_out, d_k, d_bias, part, st);
+    case WgradPlan::FC: fc::bwd_weight_kernel<<<p.gx, fc::WGRAD_THREADS, 0, st>>>(in, d_out, part, B); break;
+    case WgradPlan::CONV1: conv1::bwd_weight_kernel<<<p.gx, conv1::THREADS, 0, st>>>(in, d_out, part, B); break;
+    case WgradPlan::CONV2: conv2::bwd_weight_kernel<<<p.gx, conv2::THREADS, 0, st>>>(in, d_out, part, B); break;
+    default: return CNN_EINVAL;
+  }
+  const size_t outputs = (size_t)Cout * Cin * KH * KW + Cout;
   const int epw = outputs >= 2048 ? 16 : outputs >= 512 ? 8 : 4;  // outputs per workgroup of the second kernel
   igemm::wgrad_reduce_kernel<<<(unsigned)((outputs + epw - 1) / epw), igemm::THREADS, 0, st>>>(
-      a.part, (int)p.gx, a.MT, a.NT, a.Cout, a.Cin, a.KH, a.KW, a.P, epw, d_k, d_bias);
+      part, (int)p.gx, p.MT, p.NT, Cout, Cin, KH, KW, p.P, epw, d_k, d_bias);
   return launched();
 }
 
@@ -785,8 +890,8 @@ int cnn_conv_fwd(const float* in, const float* k, const float* bias, float* out,
         in, k, bias, out, B);
     return launched();
   }
-  const ConvPlan p = plan_conv(in, k, bias, out, B, Cout, Cin, H, W, KH, KW, H - KH + 1, W - KW + 1, 0, 0, 0);
-  if (p.tp) return launch_conv(p, (hipStream_t)hip_stream);
+  const TileConvPlan p = plan_tile_conv(in, k, bias, out, B, Cout, Cin, H, W, KH, KW, H - KH + 1, W - KW + 1, 0, 0, 0);
+  if (p.nt) return launch_tile_conv(p, (hipStream_t)hip_stream);
   const size_t total = (size_t)B * Cout * (H - KH + 1) * (W - KW + 1);
   conv_fwd_kernel<false><<<grid_for(total), TPB, 0, (hipStream_t)hip_stream>>>(in, k, bias, out, total, Cin,
                                                                                 H, W, Cout, KH, KW);
@@ -812,9 +917,9 @@ int cnn_conv_bwd_input(const float* d_out, const float* k, float* d_in, int B, i
         d_out, k, d_in, B);  // 128 KB of LDS: one workgroup per compute unit
     return launched();
   }
-  const ConvPlan p = plan_conv(d_out, k, nullptr, d_in, B, Cin, Cout, H - KH + 1, W - KW + 1, KH, KW, H, W,
-                               KH - 1, KW - 1, 1);
-  if (p.tp) return launch_conv(p, (hipStream_t)hip_stream);
+  const TileConvPlan p = plan_tile_conv(d_out, k, nullptr, d_in, B, Cin, Cout, H - KH + 1, W - KW + 1, KH, KW, H, W,
+                                        KH - 1, KW - 1, 1);
+  if (p.nt) return launch_tile_conv(p, (hipStream_t)hip_stream);
   const size_t total = (size_t)B * Cin * H * W;
   conv_bwd_input_kernel<false><<<grid_for(total), TPB, 0, (hipStream_t)hip_stream>>>(d_out, k, d_in, total,
                                                                                       Cin, H, W, Cout, KH, KW);
@@ -877,8 +982,8 @@ int cnn_conv_bwd_weight(const float* in, const float* d_out, float* d_k, float* 
   if (!wgrad_args_ok(in, d_out, d_k, d_bias, B, Cin, H, W, Cout, KH, KW)) return CNN_EINVAL;
   if (workspace && !aligned16(workspace)) return CNN_EINVAL;
   WgradPlan p = plan_wgrad(B, Cin, H, W, Cout, KH, KW);
-  if (p.fits && workspace && workspace_bytes >= p.workspace_bytes)
-    return launch_wgrad(p, in, d_out, d_k, d_bias, static_cast<float*>(workspace), (hipStream_t)hip_stream);
+  if (p.kernel != WgradPlan::PLAIN && (p.workspace_bytes == 0 || (workspace && workspace_bytes >= p.workspace_bytes)))
+    return launch_wgrad(p, in, d_out, d_k, d_bias, B, Cin, Cout, KH, KW, static_cast<float*>(workspace), (hipStream_t)hip_stream);
   return launch_wgrad_plain(in, d_out, d_k, d_bias, B, Cin, H, W, Cout, KH, KW, (hipStream_t)hip_stream);
 }
 
@@ -886,7 +991,7 @@ int cnn_conv_bwd_weight_static(const float* in, const float* d_out, float* d_k, 
                                int H, int W, int Cout, int KH, int KW, void* hip_stream) {
   if (!wgrad_args_ok(in, d_out, d_k, d_bias, B, Cin, H, W, Cout, KH, KW)) return CNN_EINVAL;
   WgradPlan p = plan_wgrad(B, Cin, H, W, Cout, KH, KW);
-  if (!p.fits)  // only the kernel without partial sums serves this shape: it needs no scratch at all
+  if (p.kernel == WgradPlan::PLAIN)  // only the kernel without partial sums serves this shape: it needs no scratch at all
     return launch_wgrad_plain(in, d_out, d_k, d_bias, B, Cin, H, W, Cout, KH, KW, (hipStream_t)hip_stream);
   if (p.workspace_bytes > sizeof(float) * SCRATCH_FLOATS) return CNN_ESCRATCH;
   float* part = nullptr;
@@ -894,7 +999,7 @@ int cnn_conv_bwd_weight_static(const float* in, const float* d_out, float* d_k, 
   if (rc != CNN_OK) return rc;
   // every partial tile and bias row the second kernel reads is written by the first one in the same
   // call, so nothing of the previous call's contents has to be cleared
-  return launch_wgrad(p, in, d_out, d_k, d_bias, part, (hipStream_t)hip_stream);
+  return launch_wgrad(p, in, d_out, d_k, d_bias, B, Cin, Cout, KH, KW, part, (hipStream_t)hip_stream);
 }
 
 size_t cnn_conv_bwd_weight_bf16_workspace_bytes(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
@@ -951,8 +1056,8 @@ int cnn_fc_fwd(const float* in, const float* w, const float* bias, float* out, i
     fc::forward_kernel<<<fc_groups(B), fc::THREADS, 0, (hipStream_t)hip_stream>>>(in, w, bias, out, B);
     return launched();
   }
-  const ConvPlan p = plan_conv(in, w, bias, out, B, O, I, 1, 1, 1, 1, 1, 1, 0, 0, 0);
-  if (p.tp) return launch_conv(p, (hipStream_t)hip_stream);
+  const TileConvPlan p = plan_tile_conv(in, w, bias, out, B, O, I, 1, 1, 1, 1, 1, 1, 0, 0, 0);
+  if (p.nt) return launch_tile_conv(p, (hipStream_t)hip_stream);
   const size_t total = (size_t)B * O;
   fc_fwd_kernel<<<grid_for(total), TPB, 0, (hipStream_t)hip_stream>>>(in, w, bias, out, total, I, O);
   return launched();
@@ -966,8 +1071,8 @@ int cnn_fc_bwd_input(const float* d_out, const float* w, float* d_in, int B, int
     fc::bwd_input_kernel<<<fc_groups(B), fc::THREADS, 0, (hipStream_t)hip_stream>>>(d_out, w, d_in, B);
     return launched();
   }
-  const ConvPlan p = plan_conv(d_out, w, nullptr, d_in, B, I, O, 1, 1, 1, 1, 1, 1, 0, 0, 1);
-  if (p.tp) return launch_conv(p, (hipStream_t)hip_stream);
+  const TileConvPlan p = plan_tile_conv(d_out, w, nullptr, d_in, B, I, O, 1, 1, 1, 1, 1, 1, 0, 0, 1);
+  if (p.nt) return launch_tile_conv(p, (hipStream_t)hip_stream);
   const size_t total = (size_t)B * I;
   fc_bwd_input_kernel<<<grid_for(total), TPB, 0, (hipStream_t)hip_stream>>>(d_out, w, d_in, total, I, O);
   return launched();
@@ -983,10 +1088,10 @@ int cnn_fc_bwd_weight(const float* in, const float* d_out, float* d_w, float* d_
     return CNN_EINVAL;
   if (!aligned16(in) || !aligned16(d_out) || !aligned16(d_w) || (d_bias && !aligned16(d_bias)))
     return CNN_EINVAL;
-  if (workspace && workspace_bytes >= cnn_fc_bwd_weight_workspace_bytes(B, I, O) &&
-      cnn_fc_bwd_weight_workspace_bytes(B, I, O) > 0)
-    return cnn_conv_bwd_weight(in, d_out, d_w, d_bias, B, I, 1, 1, O, 1, 1, workspace, workspace_bytes,
-                               hip_stream);
+  if (workspace && !aligned16(workspace)) return CNN_EINVAL;
+  WgradPlan p = plan_wgrad(B, I, 1, 1, O, 1, 1);
+  if (p.kernel != WgradPlan::PLAIN && (p.workspace_bytes == 0 || (workspace && workspace_bytes >= p.workspace_bytes)))
+    return launch_wgrad(p, in, d_out, d_w, d_bias, B, I, O, 1, 1, static_cast<float*>(workspace), (hipStream_t)hip_stream);
   const unsigned blocks = (unsigned)(O * I + (d_bias ? O : 0));
   fc_bwd_weight_kernel<<<blocks, TPB, 0, (hipStream_t)hip_stream>>>(in, d_out, d_w, d_bias, B, I, O);
   return launched();

@@ -1,0 +1,59 @@
+"""The image-tiled convolution kernels where their cutting can go wrong: ragged bands, strips of very wide images,
+channel chunks, several row blocks, packed columns that do not divide a row, one workgroup column, images beyond
+64 KB.  Against the plain kernels, which test_gpu_ops.py pins to the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1912_05234_amd import binding, inputs
+from parity import RTOL_ACT, assert_close
+
+pytestmark = pytest.mark.gpu
+
+# (B, Cin, H, W, Cout, KH, KW)
+CASES = [(2, 3, 9, 700, 5, 3, 3), (1, 1, 3, 2500, 1, 3, 3),            # strips (the second: no weight-gradient plan)
+         (2, 70, 17, 19, 70, 3, 3), (1, 300, 9, 9, 5, 3, 3),            # chunks, several row blocks and tap groups
+         (33, 3, 32, 32, 16, 5, 5), (70, 16, 28, 28, 32, 3, 3),         # bands with a ragged last one, two row tiles
+         (40, 2, 11, 7, 3, 2, 3), (5, 1, 13, 27, 2, 7, 7), (9, 2, 14, 7, 1, 5, 5),  # packed, ragged rows
+         (301, 4, 30, 13, 4, 3, 3), (1100, 5, 6, 9, 7, 1, 1),           # several images per unit, a ragged last group
+         (1, 18, 27, 34, 2, 5, 5), (6, 26, 16, 22, 1, 3, 3),            # one workgroup column (no second kernel)
+         (3, 12, 70, 60, 9, 4, 6)]
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_tiled_convolutions(case):
+    B, Cin, H, W, Cout, KH, KW = case
+    x = dev(inputs.make_signed((B, Cin, H, W), 71))
+    k = dev(inputs.make_signed((Cout, Cin, KH, KW), 72))
+    b = dev(inputs.make_signed((Cout,), 73))
+    d = dev(inputs.make_signed((B, Cout, H - KH + 1, W - KW + 1), 74))
+    assert_close(host(binding.conv_fwd(x, k, b)), host(binding.conv_fwd(x, k, b, valu=True)).astype(np.float64), RTOL_ACT, "tiled conv_fwd")
+    assert_close(host(binding.conv_bwd_input(d, k, H, W)), host(binding.conv_bwd_input(d, k, H, W, valu=True)).astype(np.float64),
+                 RTOL_ACT, "tiled conv_bwd_input")
+    d_k, d_b = binding.conv_bwd_weight(x, d)
+    p_k, p_b = binding.conv_bwd_weight(x, d, workspace=False)
+    assert_close(host(d_k), host(p_k).astype(np.float64), RTOL_ACT, "tiled conv_bwd_weight")
+    assert_close(host(d_b), host(p_b).astype(np.float64), RTOL_ACT, "tiled conv_bwd_bias")
+    again, none = binding.conv_bwd_weight(x, d, want_bias=False)
+    assert none is None and torch.equal(again, d_k)
+
+
+@pytest.mark.parametrize("B,I,O", [(300, 784, 100), (17, 4096, 40), (1000, 64, 16), (33, 250, 250), (1, 192, 11)])
+def test_tiled_fully_connected(B, I, O):
+    x, w, b = inputs.make_signed((B, I), 75), inputs.make_signed((O, I), 76), inputs.make_signed((O,), 77)
+    d = inputs.make_signed((B, O), 78)
+    x64, w64, d64 = x.astype(np.float64), w.astype(np.float64), d.astype(np.float64)
+    assert_close(host(binding.fc_fwd(dev(x), dev(w), dev(b))), x64 @ w64.T + b, RTOL_ACT, "tiled fc_fwd")
+    assert_close(host(binding.fc_bwd_input(dev(d), dev(w))), d64 @ w64, RTOL_ACT, "tiled fc_bwd_input")
+    d_w, d_b = binding.fc_bwd_weight(dev(x), dev(d))
+    assert_close(host(d_w), d64.T @ x64, RTOL_ACT, "tiled fc_bwd_weight")
+    assert_close(host(d_b), d64.sum(axis=0), RTOL_ACT, "tiled fc_bwd_bias")
