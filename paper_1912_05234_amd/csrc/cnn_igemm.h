@@ -1,6 +1,5 @@
 // What the implicit-GEMM convolution kernels share: matrix instruction, index arithmetic, LDS barrier, and the
-// second kernel of the weight gradients that leave partial 16 x 16 tiles (cnn_conv_wave.h, cnn_fc_wave.h,
-// cnn_igemm_bf16.h).  Definitions: arXiv 1912.05234, Section 3 -- listings conv / mconv (forward), backin (input
+// second kernel of the weight gradients that leave partial 16 x 16 tiles (cnn_conv_wave.h, cnn_fc_wave.h).  Definitions: arXiv 1912.05234, Section 3 -- listings conv / mconv (forward), backin (input
 // gradient), backweights and backbias (weight and bias gradients).
 //
 // Every operation is an implicit GEMM D[M x N] = A[M x K] * B[K x N] in 16 x 16 tiles; with

@@ -11,8 +11,8 @@
 
 #include "cnn_common.h"
 #include "cnn_igemm.h"
-#include "cnn_igemm_bf16.h"
 #include "cnn_tile.h"
+#include "cnn_tile_bf16.h"
 #include "cnn_col2im.h"
 #include "cnn_conv_wave.h"
 #include "cnn_fc_wave.h"
@@ -44,7 +44,7 @@ typedef float vec4 __attribute__((ext_vector_type(4)));
 // An operand as the arithmetic sees it: itself, or rounded to bfloat16 (nearest even).
 template <bool BF16>
 __device__ __forceinline__ float operand(float v) {
-  return BF16 ? __uint_as_float((unsigned)igemm16::to_bf16(v) << 16) : v;
+  return BF16 ? __uint_as_float((unsigned)tile16::to_bf16(v) << 16) : v;
 }
 
 // out[b,co,y,x] = bias[co] + sum_{ci,u,v} in[b,ci,y+u,x+v] * k[co,ci,u,v]
@@ -252,22 +252,9 @@ __global__ __launch_bounds__(TPB) void logistic_bwd_kernel(const float* __restri
 inline int launched() { return hipGetLastError() == hipSuccess ? CNN_OK : CNN_EHIP; }
 
 // ---- launch plans of the matrix-core kernels ----------------------------------------------------
-constexpr int LDS_LIMIT = 64 * 1024 - 512;  // bytes of dynamic LDS a workgroup of the bf16 kernels may ask for
-constexpr int LDS_TARGET = 48 * 1024;       // preferred, so that three workgroups share a compute unit
-constexpr int WGRAD_LDS_TARGET = 36 * 1024; // of their weight gradient: four workgroups per compute unit
 constexpr int CU_LDS = 160 * 1024;
 constexpr int TILE_LDS_LIMIT = 79 * 1024;   // of an image-tiled kernel: two workgroups per compute unit
 constexpr int NUM_CU = 256;
-constexpr int MAX_GROUP = 64;               // images per group
-constexpr int MAX_PARTIALS = 1024;          // workgroup columns (partial sums) of the weight gradient
-
-// Workgroups that keep every compute unit as full as the LDS use allows (at most eight each).
-unsigned resident_workgroups(size_t lds_bytes) {
-  size_t per_cu = CU_LDS / (lds_bytes + 512);
-  if (per_cu > 8) per_cu = 8;
-  if (per_cu < 1) per_cu = 1;
-  return (unsigned)(NUM_CU * per_cu);
-}
 
 // ---- image-tiled kernels (cnn_tile.h) ------------------------------------------------------------------
 // The last plans made, by shape: choosing one costs tens of microseconds of host time, which a call should
@@ -312,14 +299,8 @@ struct TileConvPlan {
 
 inline long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
 
-// Fills in one candidate, `res` workgroups per compute unit; false when it does not fit.  The cost is an estimate
-// of the kernel's clocks, linear in what a compute unit has to do: matrix instructions (32 clocks each, partly
-// hidden under the vector instructions of other waves), blocks of operand reads, staging and store instructions,
-// a fixed share per unit, and a memory round trip per unit that a workgroup takes.  The coefficients are a least
-// squares fit to 5000 timed plans of 40 shapes (7 % rms); the plan it picks is on average 1.4 % slower than the
-// fastest one of a shape.
-bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH, int TXC, int res) {
-  tile::ConvArgs& a = p.a;
+// The unit's geometry in `a`; false when it cannot be.
+bool tile_unit(tile::ConvArgs& a, int P, int mt, int NB, int TH, int TXC) {
   a.P = P, a.MR = a.M * P, a.KWP = a.KW + P - 1;
   const long long OWP = ceil_div(a.OW, P);
   a.NB = NB, a.TH = TH, a.TXC = TXC;
@@ -333,13 +314,41 @@ bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH,
   a.RPI = a.LW <= 64 ? 64 / a.LW : 1;
   // (by rows, the last instruction of a plane may bring rows past RH)
   a.LP = border ? (int)ceil_div(a.RH, a.RPI) * a.RPI * a.LW : a.bands == 1 ? a.SH * a.SW : a.RH * a.LW;
-  const int MB = (int)ceil_div(a.MR, 16 * mt);
   a.R = a.MR < 16 * mt ? a.MR : 16 * mt;
-  const int plane = a.SH * a.SW;
+  return true;
+}
+// Bytes per lane of the staging loads of borderless planes, 0 for staging by rows.
+int tile_linear(const tile::ConvArgs& a, bool border) {
+  if (border) return 0;
+  const long long plane = (long long)a.SH * a.SW;
+  return (a.bands == 1 ? a.SC * plane % 4 == 0 && a.CC * plane % 4 == 0 && a.LI % 4 == 0
+                       : plane % 4 == 0 && a.LP % 4 == 0 && a.TH * a.SW % 4 == 0) ? 16 : 4;
+}
+// Workgroups in x for `res` per compute unit and `gy` in y (res = 0: one).
+int tile_columns(int units, int gy, int res) {
+  const int gx = NUM_CU * res / gy > 0 ? NUM_CU * res / gy : 1;
+  return gx < units ? gx : units;
+}
+void tile_constants(tile::ConvArgs& a) {
+  a.inv_p = 1.0f / a.P, a.inv_khkwp = 1.0f / (float)(a.KH * a.KWP), a.inv_kwp = 1.0f / (float)a.KWP;
+  a.inv_cols = 1.0f / (float)(a.TH * a.TXC), a.inv_txc = 1.0f / (float)a.TXC, a.inv_lw = 1.0f / (float)a.LW;
+  a.inv_kp = 1.0f / (float)(16 * a.NBK);
+}
+
+// Fills in one candidate, `res` workgroups per compute unit; false when it does not fit.  The cost is an estimate
+// of the kernel's clocks, linear in what a compute unit has to do: matrix instructions (32 clocks each, partly
+// hidden under the vector instructions of other waves), blocks of operand reads, staging and store instructions,
+// a fixed share per unit, and a memory round trip per unit that a workgroup takes.  The coefficients are a least
+// squares fit to 5000 timed plans of 40 shapes (7 % rms); the plan it picks is on average 1.4 % slower than the
+// fastest one of a shape.
+bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH, int TXC, int res) {
+  tile::ConvArgs& a = p.a;
+  if (!tile_unit(a, P, mt, NB, TH, TXC)) return false;
+  const bool border = a.pady || a.padx || a.strips > 1;
+  const int MB = (int)ceil_div(a.MR, 16 * mt);
   const double total = (double)a.units * MB;
   if (res > 1 && total <= NUM_CU * (res - 1.0)) return false;
-  int gx = NUM_CU * res / MB > 0 ? NUM_CU * res / MB : 1;
-  if (gx > a.units) gx = a.units;
+  const int gx = tile_columns(a.units, MB, res);
   // channels per chunk: the fewest equal shares that fit, with all the weights in LDS or with each chunk's own
   double best = -1.0;
   tile::ConvArgs keep = a;
@@ -351,13 +360,11 @@ bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH,
       if (K > (1 << 16) || (long long)a.CC * a.LP * NB > TILE_LDS_LIMIT / 4) continue;
       a.chunks = chunks, a.resident = resident, a.K = (int)K, a.NBK = (int)ceil_div(K, 16), a.LI = a.CC * a.LP;
       // the sixteen columns of a tile are the same pixel of sixteen images when there are few pixels: images start in different banks
-      if (NB > 1 && a.OH * OWP < 16 && !border && a.LI % 8 == 0) a.LI += 4;
+      if (NB > 1 && a.TH * a.TXC < 16 && !border && a.LI % 8 == 0) a.LI += 4;
       a.SP = igemm::row_stride(resident ? a.NBK * chunks : a.NBK), a.SK = igemm::row_stride(a.NBK);
       const long long lds = (long long)tile::conv_lds(a).total * 4;
       if (lds > TILE_LDS_LIMIT) continue;
-      a.linear = border ? 0
-                 : (a.bands == 1 ? (long long)a.SC * plane % 4 == 0 && (long long)a.CC * plane % 4 == 0 && a.LI % 4 == 0
-                                  : plane % 4 == 0 && a.LP % 4 == 0 && TH * a.SW % 4 == 0) ? 16 : 4;
+      a.linear = tile_linear(a, border);
       const int by_lds = (int)(CU_LDS / (lds + 512)), by_regs = tile::conv_residency(nt, mt);
       if (res > (by_lds < by_regs ? by_lds : by_regs)) break;
       // workgroups of a compute unit, units it works off, units one workgroup takes in turn
@@ -380,56 +387,61 @@ bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH,
   a = keep;
   p.cost = best;
   p.nt = nt, p.mt = mt;
-  a.inv_p = 1.0f / P, a.inv_khkwp = 1.0f / (float)(a.KH * a.KWP), a.inv_kwp = 1.0f / (float)a.KWP;
-  a.inv_cols = 1.0f / (float)(TH * TXC), a.inv_txc = 1.0f / (float)TXC, a.inv_lw = 1.0f / (float)a.LW;
-  a.inv_kp = 1.0f / (float)(16 * a.NBK);
+  tile_constants(a);
   return true;
 }
 
-TileConvPlan search_tile_conv(int B, int M, int SC, int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx,
-                              int flip) {
-  TileConvPlan best;
+// The problem in `a`; false where the kernels' 32-bit offsets end.
+bool tile_args(tile::ConvArgs& a, int B, int M, int SC, int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx, int flip) {
   if ((long long)SC * SH * SW > (1ll << 29) || (long long)SH * SW >= tile::FAR_SIZE / 4 || OH > (1 << 24) ||
-      (long long)M * SC * KH * KW >= tile::FAR_SIZE / 8 || ceil_div(M, 16) > 60000) return best;
-  TileConvPlan p;
-  tile::ConvArgs& a = p.a;
+      (long long)M * SC * KH * KW >= tile::FAR_SIZE / 8 || ceil_div(M, 16) > 60000)
+    return false;
   a.src = a.w = a.bias = nullptr, a.dst = nullptr;
   a.B = B, a.M = M, a.SC = SC, a.SH = SH, a.SW = SW, a.KH = KH, a.KW = KW, a.OH = OH, a.OW = OW;
   a.pady = pady, a.padx = padx, a.flip = flip;
-  auto consider = [&](int P, int mt, int nt, int NB, int TH, int TXC) {
-    for (int res = 1; res <= 4; ++res)
-      if (tile_conv_candidate(p, P, mt, nt, NB, TH, TXC, res) && (!best.nt || p.cost < best.cost)) best = p;
-  };
-  for (int P = 1; P <= OW && (P == 1 || (KW > 1 && P * M <= 16)); ++P) {
+  return true;
+}
+// Hands every unit worth considering to `consider`: packing, row and column tiles, images, rows and columns, workgroups
+// per compute unit.
+template <typename CONSIDER>
+void tile_units(const tile::ConvArgs& a, CONSIDER consider) {
+  const int M = a.M, OH = a.OH, OW = a.OW, B = a.B;
+  for (int P = 1; P <= OW && (P == 1 || (a.KW > 1 && P * M <= 16)); ++P) {
     if ((P & (P - 1)) && P != 16 / M && OW % P) continue;  // powers of two (wide stores), divisors of the row, the one that fills the tile best
     for (int mt = 1; mt <= (M > 16 ? 2 : 1); ++mt)
       for (int nt = 1; nt <= 4; nt <<= 1) {
+        auto sizes = [&](int NB, long long TH, long long TXC) {
+          for (int res = 1; res <= 4; ++res) consider(P, mt, nt, NB, (int)TH, (int)TXC, res);
+        };
         const long long OWP = ceil_div(OW, P), most = 64 * nt;
         if (OWP > most) {
-          const int strips = (int)ceil_div(OWP, most);
-          consider(P, mt, nt, 1, 1, (int)ceil_div(OWP, strips));
+          sizes(1, 1, ceil_div(OWP, ceil_div(OWP, most)));
           continue;
         }
         const long long TH = most / OWP;
         if (TH >= OH) {
           const long long NB = most / (OH * OWP);
-          consider(P, mt, nt, (int)(NB < B ? NB : B), OH, (int)OWP);
-          if (NB > 1) consider(P, mt, nt, (int)(NB / 2 < B ? NB / 2 : B), OH, (int)OWP);
+          sizes((int)(NB < B ? NB : B), OH, OWP);
+          if (NB > 1) sizes((int)(NB / 2 < B ? NB / 2 : B), OH, OWP);
         }
         if (OH > 1) {
-          const int bands = (int)ceil_div(OH, TH < OH ? TH : OH - 1);
-          for (int f = 1; f <= 4; f <<= 1) consider(P, mt, nt, 1, (int)ceil_div(OH, (long long)bands * f), (int)OWP);
+          const long long bands = ceil_div(OH, TH < OH ? TH : OH - 1);
+          for (int f = 1; f <= 4; f <<= 1) sizes(1, ceil_div(OH, bands * f), OWP);
         }
       }
   }
-  return best;
 }
 
 TileConvPlan plan_tile_conv(const float* src, const float* w, const float* bias, float* dst, int B, int M, int SC,
                             int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx, int flip) {
   static PlanMemo<TileConvPlan, 12> memo;
   TileConvPlan p = memo.get({B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip}, [&] {
-    return search_tile_conv(B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip);
+    TileConvPlan best, c;
+    if (!tile_args(c.a, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip)) return best;
+    tile_units(c.a, [&](int P, int mt, int nt, int NB, int TH, int TXC, int res) {
+      if (tile_conv_candidate(c, P, mt, nt, NB, TH, TXC, res) && (!best.nt || c.cost < best.cost)) best = c;
+    });
+    return best;
   });
   p.a.src = src, p.a.w = w, p.a.bias = bias, p.a.dst = dst;
   return p;
@@ -504,9 +516,7 @@ bool tile_wgrad_candidate(TileWgradPlan& p, int P, int mt, int nt, int NB, int T
   const int regs = 4 * nt * mt + 3 * nt + 60;  // registers a wave needs, roughly
   if (res > CU_LDS / (lds + 512) || res > 512 / regs) return false;
   if (res > 1 && (double)a.units * MB * a.NTG <= NUM_CU * (res - 1.0)) return false;
-  int gx = NUM_CU * res / (MB * a.NTG);
-  if (gx < 1 || res == 0) gx = 1;
-  if (gx > a.units) gx = a.units;
+  const int gx = tile_columns(a.units, MB * a.NTG, res);
   const double total = (double)gx * MB * a.NTG, wgs = total > NUM_CU ? ceil(total / NUM_CU) : 1.0, share = total > NUM_CU ? total / NUM_CU : 1.0;
   const double turns = (double)ceil_div(a.units, gx), blocks = (double)ceil_div(a.NBK, tile::WAVES), mfma = 128.0 * blocks * nt * mt;
   const double x_instr = (double)NB * (a.bands == 1 ? ceil_div((long long)a.CG * a.LP, 16 * a.vec_x) : a.CG * ceil_div(a.LP, 16 * a.vec_x)), d_instr = (double)a.R * ceil_div(a.NBK, 4);
@@ -521,6 +531,45 @@ bool tile_wgrad_candidate(TileWgradPlan& p, int P, int mt, int nt, int NB, int T
   return true;
 }
 
+// The workspace that callers have been asked for, and the shapes that the built-in scratch has been documented to
+// accept or to refuse, are part of the interface: a layout of one 16 x 16 tile per workgroup column, row tile and tap
+// tile, with as many columns as workgroups of whole images are resident.  0 for shapes whose images do not fit in
+// LDS.  The tiled kernels need less.
+size_t tile_layout_bytes(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
+  constexpr int LDS_LIMIT = 64 * 1024 - 512, LDS_TARGET = 36 * 1024, MAX_GROUP = 64, MAX_COLUMNS = 1024;
+  const long long Ho = H - KH + 1, Wo = W - KW + 1, per_image = (long long)Cin * H * W;
+  auto bytes_for = [&](int P) -> size_t {
+    const long long K = (long long)Cin * KH * (KW + P - 1), SPI = Ho * (Wo / P), MT = ceil_div((long long)Cout * P, 16), NT = ceil_div(K, 16);
+    const long long R = Cout * P < 16 ? Cout * P : 16, cx = per_image % 4 == 0 ? 256 : 64, cd = P == 1 && Ho * Wo % 4 == 0 ? 256 : 64;
+    if (2 * (per_image + 2 * SPI) > LDS_LIMIT / 4 || K > (1 << 20)) return 0;
+    auto lds = [&](long long nb) {
+      const long long blocks = ceil_div(nb * SPI, 16), total = 16 * blocks + 2 * ((R + 1) * (16 * blocks + 4) + ceil_div(nb * per_image, cx) * cx);
+      const long long handover = 16 * blocks + igemm::WAVES * 272;
+      return 4 * (total > handover ? total : handover);
+    };
+    if (SPI > 16 * cd || lds(1) > LDS_LIMIT) return 0;
+    long long nb = 1;
+    for (long long c = 2; c <= MAX_GROUP && c <= B && c <= ceil_div(B, MAX_COLUMNS) && lds(c) <= LDS_TARGET && c * SPI <= 16 * cd; ++c) nb = c;
+    long long per_cu = CU_LDS / (lds(nb) + 512);
+    per_cu = per_cu > 8 ? 8 : per_cu < 1 ? 1 : per_cu;
+    long long gx = NUM_CU * per_cu / (MT * ceil_div(NT, 16));
+    gx = gx < 1 ? 1 : gx > MAX_COLUMNS ? MAX_COLUMNS : gx;
+    if (gx > ceil_div(B, nb)) gx = ceil_div(B, nb);
+    return (size_t)(gx * MT * (NT * 256 + 16)) * sizeof(float);
+  };
+  int best = 1;
+  long long best_cost = -1;
+  for (int P = 1; KW > 1 && P * Cout <= 16; ++P) {
+    if (Wo % P) continue;
+    const long long cost = ceil_div((long long)Cin * KH * (KW + P - 1), 16) * ceil_div(Ho * (Wo / P), 16);
+    if (best_cost < 0 || cost < best_cost) best_cost = cost, best = P;
+  }
+  for (int P = best; P >= 1; --P)
+    if (Wo % P == 0)
+      if (const size_t bytes = bytes_for(P)) return bytes;
+  return 0;
+}
+
 TileWgradPlan search_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
   TileWgradPlan best, p;
   tile::WgradArgs& a = p.a;
@@ -529,8 +578,13 @@ TileWgradPlan search_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, 
   const long long K = (long long)Cin * KH * KW;
   if ((long long)Cin * H * W > (1ll << 29) || (long long)H * W >= tile::FAR_SIZE / 4 || 16 * K > (1 << 22)) return best;
   if (ceil_div(Cout, 16) * ceil_div(K, 16) > 60000) return best;
-  // up to two million multiply-adds on few images: one workgroup column, the second kernel would cost more than it saves
-  const bool tiny = B <= 64 && (double)B * Cout * a.Ho * a.Wo * K <= 2097152.0;
+  // Few images beyond the LDS, for which the size query has always been zero: without a workspace only one workgroup
+  // column is possible, and where that reads for longer than the plain kernel takes (one workgroup per weight: about
+  // 4.4 clocks a pixel) the plain kernel stays.  From 30 us of the plain kernel on, partial sums pay in any case: 30
+  // images of 22 x 24 x 23, one tap, took it 33 us, one workgroup column would take 172, many columns take 13.
+  const double plain = 9600.0 + 4.4 * B * a.Ho * a.Wo * ceil_div(Cout * K, 8 * NUM_CU);
+  const bool tiny = B <= 64 && plain <= 72000.0 && (double)B * Cout * a.Ho * a.Wo * K <= 2097152.0 &&
+                    tile_layout_bytes(B, Cin, H, W, Cout, KH, KW) == 0;
   for (int P = 1; P <= a.Wo && (P == 1 || (KW > 1 && P * Cout <= 16)); ++P) {
     if ((P & (P - 1)) && P != 16 / Cout && a.Wo % P) continue;
     for (int mt = 1; mt <= (Cout > 16 ? 2 : 1); ++mt) {
@@ -548,43 +602,8 @@ TileWgradPlan search_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, 
       }
     }
   }
+  if (tiny && best.cost > plain) best.nt = 0, best.cost = plain;
   return best;
-}
-
-// The workspace that callers have been asked for, and the shapes that the built-in scratch has been documented to
-// accept or to refuse, are part of the interface: a layout of one 16 x 16 tile per workgroup column, row tile and tap
-// tile, with as many columns as workgroups of whole images are resident.  0 for shapes whose images do not fit in
-// LDS.  The tiled kernels need less.
-size_t tile_layout_bytes(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
-  const long long Ho = H - KH + 1, Wo = W - KW + 1, per_image = (long long)Cin * H * W;
-  auto bytes_for = [&](int P) -> size_t {
-    const long long K = (long long)Cin * KH * (KW + P - 1), SPI = Ho * (Wo / P), MT = ceil_div((long long)Cout * P, 16), NT = ceil_div(K, 16);
-    const long long R = Cout * P < 16 ? Cout * P : 16, cx = per_image % 4 == 0 ? 256 : 64, cd = P == 1 && Ho * Wo % 4 == 0 ? 256 : 64;
-    if (2 * (per_image + 2 * SPI) > LDS_LIMIT / 4 || K > (1 << 20)) return 0;
-    auto lds = [&](long long nb) {
-      const long long blocks = ceil_div(nb * SPI, 16), total = 16 * blocks + 2 * ((R + 1) * (16 * blocks + 4) + ceil_div(nb * per_image, cx) * cx);
-      const long long handover = 16 * blocks + igemm::WAVES * 272;
-      return 4 * (total > handover ? total : handover);
-    };
-    if (SPI > 16 * cd || lds(1) > LDS_LIMIT) return 0;
-    long long nb = 1;
-    for (long long c = 2; c <= MAX_GROUP && c <= B && c <= ceil_div(B, MAX_PARTIALS) && lds(c) <= WGRAD_LDS_TARGET && c * SPI <= 16 * cd; ++c) nb = c;
-    long long gx = resident_workgroups((size_t)lds(nb)) / (MT * ceil_div(NT, 16));
-    gx = gx < 1 ? 1 : gx > MAX_PARTIALS ? MAX_PARTIALS : gx;
-    if (gx > ceil_div(B, nb)) gx = ceil_div(B, nb);
-    return (size_t)(gx * MT * (NT * 256 + 16)) * sizeof(float);
-  };
-  int best = 1;
-  long long best_cost = -1;
-  for (int P = 1; KW > 1 && P * Cout <= 16; ++P) {
-    if (Wo % P) continue;
-    const long long cost = ceil_div((long long)Cin * KH * (KW + P - 1), 16) * ceil_div(Ho * (Wo / P), 16);
-    if (best_cost < 0 || cost < best_cost) best_cost = cost, best = P;
-  }
-  for (int P = best; P >= 1; --P)
-    if (Wo % P == 0)
-      if (const size_t bytes = bytes_for(P)) return bytes;
-  return 0;
 }
 
 TileWgradPlan plan_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
@@ -596,12 +615,22 @@ TileWgradPlan plan_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, in
   });
 }
 
+// The second kernel of a weight gradient with more than one workgroup column.
+int launch_reduce_rows(const float* part, int G, int RS, int nk, float* d_k, float* d_bias, hipStream_t st) {
+  if (G > 1 && RS > 8192)
+    tile::reduce_rows_kernel<64><<<(unsigned)ceil_div(RS, 64), 1024, 0, st>>>(part, G, RS, nk, d_k, d_bias);
+  else if (G > 1)
+    tile::reduce_rows_kernel<16><<<(unsigned)ceil_div(RS, 16), 1024, 0, st>>>(part, G, RS, nk, d_k, d_bias);
+  return launched();
+}
+
+template <bool ROUND>
 int launch_tile_wgrad(TileWgradPlan& p, const float* in, const float* d_out, float* d_k, float* d_bias, float* part,
                       hipStream_t st) {
   const int nk = p.a.RS - p.a.Cout, G = (int)p.grid.x;
   p.a.in = in, p.a.d_out = d_out, p.a.out_k = G > 1 ? part : d_k, p.a.out_b = G > 1 ? part + nk : d_bias;
 #define CNN_TILE_WGRAD(NT, MT) \
-  case 100 * MT + NT: launch_tiled(tile::wgrad_kernel<NT, MT>, p.grid, p.lds_bytes, st, p.a); break
+  case 100 * MT + NT: launch_tiled(tile::wgrad_kernel<NT, MT, ROUND>, p.grid, p.lds_bytes, st, p.a); break
   switch (100 * p.mt + p.nt) {
     CNN_TILE_WGRAD(1, 1);
     CNN_TILE_WGRAD(2, 1);
@@ -619,12 +648,7 @@ int launch_tile_wgrad(TileWgradPlan& p, const float* in, const float* d_out, flo
     default: return CNN_EINVAL;
   }
 #undef CNN_TILE_WGRAD
-  if (G == 1) return launched();
-  if (p.a.RS > 8192)
-    tile::reduce_rows_kernel<64><<<(unsigned)ceil_div(p.a.RS, 64), 1024, 0, st>>>(part, G, p.a.RS, nk, d_k, d_bias);
-  else
-    tile::reduce_rows_kernel<16><<<(unsigned)ceil_div(p.a.RS, 16), 1024, 0, st>>>(part, G, p.a.RS, nk, d_k, d_bias);
-  return launched();
+  return launch_reduce_rows(part, G, p.a.RS, nk, d_k, d_bias, st);
 }
 
 struct WgradPlan {
@@ -667,136 +691,238 @@ WgradPlan plan_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
   return p;
 }
 
-// ---- reduced precision: the bf16 matrix-core kernel ------------------------------------------------
-struct Conv16Plan {
-  igemm16::Args a;
-  int tp = 0;  // pixel tiles per wave job; 0: the shape does not fit, use the plain kernel
-  unsigned grid = 0;
+// ---- reduced precision: the image-tiled kernels with bf16 operands (cnn_tile_bf16.h) -----------------------
+struct Tile16ConvPlan {
+  tile16::ConvArgs a;
+  int nt = 0, mt = 0;
+  dim3 grid;
   size_t lds_bytes = 0;
+  double cost = 0.0;
 };
 
-Conv16Plan plan_conv16_packed(const float* src, const float* w, const float* bias, float* dst, int B, int M, int SC,
-                              int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx, int flip, int P) {
-  Conv16Plan p;
-  igemm16::Args& a = p.a;
-  a.src = src, a.w = w, a.bias = bias, a.dst = dst;
-  a.B = B, a.M = M, a.SC = SC, a.SH = SH, a.SW = SW, a.KH = KH, a.KW = KW, a.OH = OH, a.OW = OW;
-  a.pady = pady, a.padx = padx, a.flip = flip;
-  a.P = P, a.MR = M * P, a.KWP = KW + P - 1, a.OWP = OW / P;
-  const long long C8 = ((long long)SC + 7) & ~7LL, K = (long long)KH * a.KWP * C8, NBK = (K + 31) / 32;
-  const long long LW = SW + 2LL * padx, LPIX = (SH + 2LL * pady) * LW, MT = ((long long)a.MR + 15) / 16;
-  const long long COLS = (long long)OH * a.OWP;
-  // first in 64 bits: one image and the tables must fit before anything is narrowed to int
-  if (16 * MT * (64 * NBK + 16) + 16 * NBK + 64 * MT + 8 * COLS + 2 * LPIX * C8 + 64 > LDS_LIMIT) return p;
-  a.C8 = (int)C8, a.K = (int)K, a.NBK = (int)NBK, a.RS = (int)(64 * NBK + 16), a.LW = (int)LW, a.LPIX = (int)LPIX;
-  a.MT = (int)MT;
-  auto bytes = [&](int nb) {
-    a.NB = nb;
-    return (long long)igemm16::lds_layout(a).total;
-  };
-  if (bytes(1) > LDS_LIMIT) return p;
-  const int nb_tiles = (int)((64 + COLS - 1) / COLS);
-  int nb_want = (B + 2047) / 2048;
-  if (nb_want < nb_tiles) nb_want = nb_tiles;
-  if (nb_want > MAX_GROUP) nb_want = MAX_GROUP;
-  if (nb_want > B) nb_want = B;
+bool tile16_conv_candidate(Tile16ConvPlan& p, int P, int mt, int nt, int NB, int TH, int TXC, int res) {
+  tile::ConvArgs& a = p.a.t;
+  if (!tile_unit(a, P, mt, NB, TH, TXC)) return false;
+  const bool border = a.pady || a.padx || a.strips > 1;
+  const int MB = (int)ceil_div(a.MR, 16 * mt), eights = (int)ceil_div(a.SC, 8);
+  const double total = (double)a.units * MB;
+  if (res > 1 && total <= NUM_CU * (res - 1.0)) return false;
+  const int plane = a.SH * a.SW, gx = tile_columns(a.units, MB, res);
+  // planes are staged without their border, which lies around them in the items
+  // (rows an odd number of items apart when the columns of a tile are an even number apart: they start in different banks)
+  a.LW = border ? TXC * P + a.KW - 1 : a.SW;
+  if (border && P % 2 == 0) a.LW |= 1;
+  a.LP = a.bands == 1 ? plane : (a.RH < a.SH ? a.RH : a.SH) * a.SW;
+  p.a.LPIX = a.RH * a.LW;
+  p.a.RI = a.bands == 1 ? a.SH : a.RH, p.a.r0 = a.bands == 1 ? a.pady : 0;
+  p.a.CI = a.strips == 1 ? a.SW : TXC * P + a.KW - 1, p.a.c0 = a.strips == 1 ? a.padx : 0;
+  p.a.edges = (a.bands > 1 && a.pady) || a.strips > 1 || (a.bands > 1 && a.OH % TH) ? 1 : 0;
   double best = -1.0;
-  int best_nb = 1, best_tp = 1;
-  for (int nb = 1; nb <= nb_want; ++nb) {
-    const long long by = bytes(nb);
-    if (by > LDS_LIMIT || (by > LDS_TARGET && nb > nb_tiles)) break;
-    for (int tp = 1; tp <= 4; tp <<= 1) {
-      const long long PT = (nb * COLS + 15) / 16, jobs = ((PT + tp - 1) / tp) * MT;
-      const double used = (double)nb * COLS / 16.0 * MT, slots = (double)((jobs + 3) / 4) * 4 * tp;
-      // this kernel is bound by LDS reads, not by matrix slots: a job reads 1 KB of weights per
-      // block once for its tp tiles and 1 KB of pixels per tile
-      const double score = used / slots * tp / (tp + 1.0);
-      if (score >= best) best = score, best_nb = nb, best_tp = tp;
+  tile16::ConvArgs keep = p.a;
+  for (int resident = 1; resident >= 0; --resident)
+    for (int chunks = resident ? 1 : 2; chunks <= eights; ++chunks) {
+      p.a.C8 = (int)ceil_div(eights, chunks);
+      if (ceil_div(eights, p.a.C8) != chunks) continue;
+      a.CC = chunks == 1 ? a.SC : 8 * p.a.C8;
+      const long long K8 = (long long)a.KH * a.KWP * p.a.C8;
+      if (K8 > (1 << 14) || (long long)a.CC * a.LP * NB > TILE_LDS_LIMIT / 4) continue;
+      a.chunks = chunks, a.resident = resident, a.K = (int)(8 * K8), a.NBK = (int)ceil_div(K8, 4), a.LI = a.CC * a.LP;
+      p.a.RS = 64 * a.NBK * (resident ? chunks : 1) + 16;
+      const long long lds = tile16::conv_lds(p.a).total;
+      if (lds > TILE_LDS_LIMIT) continue;
+      a.linear = (a.bands == 1 ? (long long)a.SC * plane % 4 == 0 && (long long)a.CC * plane % 4 == 0
+                               : plane % 4 == 0 && (a.SW % 4 == 0 || (!a.pady && a.LP % 4 == 0 && TH * a.SW % 4 == 0))) ? 16 : 4;
+      const int by_lds = (int)(CU_LDS / (lds + 512)), by_regs = tile16::conv_residency(nt, mt);
+      if (res > (by_lds < by_regs ? by_lds : by_regs)) break;
+      const double wgs = total < (double)NUM_CU * res ? ceil(total / NUM_CU) : res;
+      const double per_cu = total > NUM_CU ? ceil(total / NUM_CU) : 1.0, turns = (double)ceil_div(a.units, gx) * chunks;
+      const double stage = 0.25 * (a.bands == 1 ? (double)NB * ceil_div(a.CC * a.LP, 16 * a.linear) : (double)a.CC * ceil_div(a.LP, 16 * a.linear));
+      const double turned = (double)ceil_div((long long)NB * p.a.C8 * p.a.RI * p.a.CI, tile::THREADS), wt = (a.R + 1.0) * a.NBK * 4 * chunks / tile::THREADS;
+      const int wide = P % 4 == 0 && a.OW % 4 == 0 ? 4 : P % 2 == 0 && a.OW % 2 == 0 ? 2 : 1;
+      const double unit = chunks * (a.NBK * (15.0 * nt + 1.5 * nt * mt + 18.0) + turned * 340.0 + stage * 40.0) + 16.0 * nt * mt * 4 / wide + 76.0 * nt;
+      const double cost = 11600.0 + 515.0 * wt * (resident ? wgs : per_cu) + per_cu * unit + turns * (wgs == 1.0 ? 4900.0 : wgs == 2.0 ? 4200.0 : 3600.0);
+      if (best < 0.0 || cost < best) {
+        best = cost, keep = p.a;
+        p.lds_bytes = (size_t)lds;
+        p.grid = dim3((unsigned)gx, (unsigned)MB);
+      }
+      break;
     }
-  }
-  a.NB = best_nb;
-  p.tp = best_tp;
-  a.groups = (B + a.NB - 1) / a.NB;
-  p.lds_bytes = (size_t)bytes(a.NB);
-  const unsigned resident = resident_workgroups(p.lds_bytes);
-  p.grid = (unsigned)a.groups < resident ? (unsigned)a.groups : resident;
-  a.inv_kp = 1.0f / (float)(32 * a.NBK), a.inv_c8 = 1.0f / (float)a.C8, a.inv_kwp = 1.0f / (float)a.KWP;
-  a.inv_cols = 1.0f / (float)COLS, a.inv_owp = 1.0f / (float)a.OWP, a.inv_p = 1.0f / (float)P, a.inv_chhw = 1.0f / (float)(C8 / 8 * SH * SW);
-  a.inv_hw = 1.0f / (float)(SH * SW), a.inv_sw = 1.0f / (float)SW;
+  if (best < 0.0) return false;
+  p.a = keep;
+  p.cost = best, p.nt = nt, p.mt = mt;
+  tile_constants(a);
+  p.a.inv_k8 = 1.0f / (float)(4 * a.NBK), p.a.inv_c8 = 1.0f / (float)p.a.C8, p.a.by_c8 = tile::fast_div(p.a.C8);
+  p.a.inv_plane = 1.0f / (float)(p.a.RI * p.a.CI), p.a.inv_ci = 1.0f / (float)p.a.CI;
+  return true;
+}
+
+Tile16ConvPlan plan_tile16_conv(const float* src, const float* w, const float* bias, float* dst, int B, int M, int SC,
+                                int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx, int flip) {
+  static PlanMemo<Tile16ConvPlan, 12> memo;
+  Tile16ConvPlan p = memo.get({B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip}, [&] {
+    Tile16ConvPlan best, c;
+    if (!tile_args(c.a.t, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip)) return best;
+    tile_units(c.a.t, [&](int P, int mt, int nt, int NB, int TH, int TXC, int res) {
+      if (tile16_conv_candidate(c, P, mt, nt, NB, TH, TXC, res) && (!best.nt || c.cost < best.cost)) best = c;
+    });
+    return best;
+  });
+  p.a.t.src = src, p.a.t.w = w, p.a.t.bias = bias, p.a.t.dst = dst;
   return p;
 }
 
-// Column packing as in the fp32 kernel (P pixels of a row per column, rows (m, sh)): among the
-// divisors P of OW with M*P <= 16 the one with the fewest 16-byte pixel reads per image, tiles x
-// K blocks; 1 for kernels one column wide.
-Conv16Plan plan_conv16(const float* src, const float* w, const float* bias, float* dst, int B, int M, int SC,
-                       int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx, int flip) {
-  Conv16Plan best = plan_conv16_packed(src, w, bias, dst, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip, 1);
-  if (KW == 1) return best;
-  auto cost = [&](const Conv16Plan& p) { return (double)OH * p.a.OWP / 16.0 * p.a.NBK; };
-  for (int P = 2; P * M <= 16; ++P) {
-    if (OW % P) continue;
-    const Conv16Plan p = plan_conv16_packed(src, w, bias, dst, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip, P);
-    if (p.tp && (!best.tp || cost(p) < cost(best))) best = p;
-  }
-  return best;
-}
-
-int launch_conv16(const Conv16Plan& p, hipStream_t stream) {
-  switch (p.tp) {
-    case 4: igemm16::conv_kernel<4><<<p.grid, igemm::THREADS, p.lds_bytes, stream>>>(p.a); break;
-    case 2: igemm16::conv_kernel<2><<<p.grid, igemm::THREADS, p.lds_bytes, stream>>>(p.a); break;
-    default: igemm16::conv_kernel<1><<<p.grid, igemm::THREADS, p.lds_bytes, stream>>>(p.a); break;
+template <bool BORDER>
+int launch_tile16_conv_as(const Tile16ConvPlan& p, hipStream_t stream) {
+  switch (10 * p.mt + p.nt) {
+    case 11: launch_tiled(tile16::conv_kernel<1, 1, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 12: launch_tiled(tile16::conv_kernel<2, 1, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 14: launch_tiled(tile16::conv_kernel<4, 1, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 21: launch_tiled(tile16::conv_kernel<1, 2, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 22: launch_tiled(tile16::conv_kernel<2, 2, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+    default: launch_tiled(tile16::conv_kernel<4, 2, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
   }
   return launched();
 }
 
-struct Wgrad16Plan {
-  igemm16::WArgs a;
-  bool fits = false;
-  unsigned gx = 0, gy = 0;
+int launch_tile16_conv(const Tile16ConvPlan& p, hipStream_t stream) {
+  const bool border = p.a.t.pady || p.a.t.padx || p.a.t.strips > 1;
+  return border ? launch_tile16_conv_as<true>(p, stream) : launch_tile16_conv_as<false>(p, stream);
+}
+
+struct Tile16WgradPlan {
+  tile16::WgradArgs a;
+  int nt = 0, mt = 0;
+  dim3 grid;
   size_t lds_bytes = 0, workspace_bytes = 0;
+  double cost = 0.0;
+};
+
+bool tile16_wgrad_candidate(Tile16WgradPlan& p, int P, int mt, int nt, int TH, int res) {
+  tile16::WgradArgs& a = p.a;
+  const int plane = a.H * a.W;
+  a.P = P, a.MR = a.Cout * P, a.KWP = a.KW + P - 1, a.WOP = a.Wo / P;
+  a.K = a.Cin * a.KH * a.KWP, a.MT = (int)ceil_div(a.MR, 16), a.NT = (int)ceil_div(a.K, 16);
+  const int KHKWP = a.KH * a.KWP, MB = (int)ceil_div(a.MT, mt);
+  a.TG = P == 1 ? 16 * nt : 16 * nt / a.KWP * a.KWP;
+  if (a.TG < 1) return false;
+  if (a.TG > a.K) a.TG = a.K;
+  a.NTG = (int)ceil_div(a.K, a.TG);
+  a.RS = a.Cout * a.Cin * a.KH * a.KW + a.Cout;
+  a.TH = TH, a.groups = (int)ceil_div(a.B, 8), a.bands = (int)ceil_div(a.Ho, TH);
+  if ((long long)a.groups * a.bands > 0x3fffffff) return false;
+  a.units = a.groups * a.bands;
+  const long long cg = a.NTG == 1 ? a.Cin : (a.TG + KHKWP - 2LL) / KHKWP + 1;
+  a.CG = (int)(cg < a.Cin ? cg : a.Cin);
+  const int R = a.MR < 16 * mt ? a.MR : 16 * mt;
+  a.CO = R / P;
+  a.RH = a.bands == 1 ? a.H : TH + a.KH - 1;
+  if ((long long)a.CG * a.RH * a.W > TILE_LDS_LIMIT / 32 || (long long)a.CO * TH * a.Wo > TILE_LDS_LIMIT / 32) return false;
+  a.LP = a.RH * a.W, a.LI = a.CG * a.LP;
+  a.DL = TH * a.Wo, a.DI = a.CO * a.DL, a.DP = a.DL | 1;
+  a.N = TH * a.WOP, a.NBK = (a.N + 3) / 4;
+  a.vec_x = plane % 4 == 0 && a.LP % 4 == 0 && (a.bands == 1 || TH * a.W % 4 == 0) ? 16 : 4;
+  if (a.bands == 1 && a.NTG == 1 && (long long)a.Cin * plane % 4 == 0) a.vec_x = 16;  // (runs of whole images)
+  const long long HoWo = (long long)a.Ho * a.Wo;
+  a.vec_d = a.bands == 1 ? (a.Cout * HoWo % 4 == 0 && a.CO * HoWo % 4 == 0 && 16 * mt / P * HoWo % 4 == 0 ? 16 : 4) : (HoWo % 4 == 0 && a.DL % 4 == 0 ? 16 : 4);
+  if (a.MT > mt && a.bands == 1 && a.Cout % a.CO * HoWo % 4) a.vec_d = 4;
+  const long long end = 4ll * tile::wgrad_end_floats(nt, mt), all = tile16::wgrad_lds(a).total, lds = all > end ? all : end;
+  if (lds > TILE_LDS_LIMIT) return false;
+  const int regs = 4 * nt * mt + 9 * nt + 8 * mt + 50;
+  if (res > CU_LDS / (lds + 512) || res > 512 / regs) return false;
+  if (res > 1 && (double)a.units * MB * a.NTG <= NUM_CU * (res - 1.0)) return false;
+  const int gx = tile_columns(a.units, MB * a.NTG, res);
+  const double total = (double)gx * MB * a.NTG, wgs = total > NUM_CU ? ceil(total / NUM_CU) : 1.0, share = total > NUM_CU ? total / NUM_CU : 1.0;
+  const double turns = (double)ceil_div(a.units, gx), blocks = (double)ceil_div(a.NBK, tile::WAVES);
+  const double x_instr = 8.0 * (a.bands == 1 ? ceil_div((long long)a.CG * a.LP, 16 * a.vec_x) : a.CG * ceil_div(a.LP, 16 * a.vec_x));
+  const double d_instr = 8.0 * (a.bands == 1 ? ceil_div(a.CO * HoWo, 16 * a.vec_d) : a.CO * ceil_div(a.DL, 16 * a.vec_d));
+  p.cost = 450.0 * wgs * nt * mt + turns * (share * (blocks * 49.0 * nt * mt + 10.0 * x_instr + 22.0 * d_instr + 207.0) + 12000.0) +
+           (gx > 1 ? 13400.0 + 0.0193 * gx * a.RS : 0.0);
+  p.nt = nt, p.mt = mt, p.lds_bytes = (size_t)lds;
+  p.grid = dim3((unsigned)gx, (unsigned)(MB * a.NTG));
+  p.workspace_bytes = gx > 1 ? (size_t)gx * a.RS * sizeof(float) : 0;
+  a.inv_khkwp = 1.0f / (float)KHKWP, a.inv_kwp = 1.0f / (float)a.KWP, a.inv_wop = 1.0f / (float)a.WOP;
+  a.inv_dl = 1.0f / (float)a.DL;
+  a.by_band = tile::fast_div(a.bands);
+  return true;
+}
+
+Tile16WgradPlan plan_tile16_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
+  static PlanMemo<Tile16WgradPlan, 7> memo;
+  return memo.get({B, Cin, H, W, Cout, KH, KW}, [&] {
+    Tile16WgradPlan best, p;
+    tile16::WgradArgs& a = p.a;
+    a.in = a.d_out = nullptr, a.out_k = a.out_b = nullptr;
+    a.B = B, a.Cin = Cin, a.H = H, a.W = W, a.Cout = Cout, a.KH = KH, a.KW = KW, a.Ho = H - KH + 1, a.Wo = W - KW + 1;
+    const long long K = (long long)Cin * KH * KW;
+    if ((long long)Cin * H * W > (1ll << 29) || (long long)H * W >= tile::FAR_SIZE / 4 || 16 * K > (1 << 22)) return best;
+    if (ceil_div(Cout, 16) * ceil_div(K, 16) > 60000) return best;
+    for (int P = 1; P <= a.Wo && (P == 1 || (KW > 1 && P * Cout <= 16)); ++P) {
+      if (a.Wo % P) continue;
+      for (int mt = 1; mt <= (Cout > 16 ? 2 : 1); ++mt) {
+        const int NT = (int)ceil_div((long long)Cin * KH * (KW + P - 1), 16);
+        for (int nt : {1, 2, 3, 4, 6, 8, 12}) {
+          if (nt * mt > 16 || (nt > 1 && nt / 2 >= NT) || 16 * nt < KW + P - 1) continue;
+          for (int TH = 1; TH <= a.Ho; ++TH)
+            if (TH <= 2 || ceil_div(a.Ho, TH) != ceil_div(a.Ho, TH - 1))
+              for (int res = B > 64 ? 1 : 0; res <= 4; ++res)
+                if (tile16_wgrad_candidate(p, P, mt, nt, TH, res) && (!best.nt || p.cost < best.cost)) best = p;
+        }
+      }
+    }
+    return best;
+  });
+}
+
+int launch_tile16_wgrad(Tile16WgradPlan& p, const float* in, const float* d_out, float* d_k, float* d_bias, float* part,
+                        hipStream_t st) {
+  const int nk = p.a.RS - p.a.Cout, G = (int)p.grid.x;
+  p.a.in = in, p.a.d_out = d_out, p.a.out_k = G > 1 ? part : d_k, p.a.out_b = G > 1 ? part + nk : d_bias;
+#define CNN_TILE_WGRAD(NT, MT) \
+  case 100 * MT + NT: launch_tiled(tile16::wgrad_kernel<NT, MT>, p.grid, p.lds_bytes, st, p.a); break
+  switch (100 * p.mt + p.nt) {
+    CNN_TILE_WGRAD(1, 1);
+    CNN_TILE_WGRAD(2, 1);
+    CNN_TILE_WGRAD(3, 1);
+    CNN_TILE_WGRAD(4, 1);
+    CNN_TILE_WGRAD(6, 1);
+    CNN_TILE_WGRAD(8, 1);
+    CNN_TILE_WGRAD(12, 1);
+    CNN_TILE_WGRAD(1, 2);
+    CNN_TILE_WGRAD(2, 2);
+    CNN_TILE_WGRAD(3, 2);
+    CNN_TILE_WGRAD(4, 2);
+    CNN_TILE_WGRAD(6, 2);
+    CNN_TILE_WGRAD(8, 2);
+    default: return CNN_EINVAL;
+  }
+#undef CNN_TILE_WGRAD
+  return launch_reduce_rows(part, G, p.a.RS, nk, d_k, d_bias, st);
+}
+
+// The weight gradient in reduced precision: eight images at a time on the bf16 matrix cores, or (few images, few
+// operands) the fp32 kernel with rounded operands, whichever the two fits say is faster; the factor is what rounding
+// costs that kernel's vector unit.  Measured (us, the kernel before / eight images / rounded): 10000 images 6 -> 12 of
+// 12 x 12, 5 x 5 taps 34.9 / 27.3 / 46; 256 images 16 -> 32 of 28 x 28, 3 x 3 taps 2353 / 52 / 48; 577 images 6 -> 14
+// of 23 x 25, 3 x 3 taps 22.9 / 30.2 / 23.
+struct Wgrad16Plan {
+  Tile16WgradPlan eight;
+  TileWgradPlan rounded;
+  bool use_rounded() const { return rounded.nt && (!eight.nt || 1.08 * rounded.cost < eight.cost); }
+  bool use_plain() const { return !rounded.nt && (!eight.nt || (rounded.cost > 0.0 && rounded.cost < eight.cost)); }
+  size_t workspace_bytes() const { return use_plain() ? 0 : use_rounded() ? rounded.workspace_bytes : eight.workspace_bytes; }
 };
 
 Wgrad16Plan plan_wgrad16(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
   Wgrad16Plan p;
-  igemm16::WArgs& a = p.a;
-  a.in = nullptr, a.d_out = nullptr, a.part = nullptr;
-  a.B = B, a.Cin = Cin, a.H = H, a.W = W, a.Cout = Cout, a.KH = KH, a.KW = KW;
-  a.Ho = H - KH + 1, a.Wo = W - KW + 1;
-  const long long K = (long long)Cin * KH * KW, NT = (K + 15) / 16, MT = ((long long)Cout + 15) / 16;
-  const long long XG = (a.Wo + 7) / 8, WP = 8 * XG, RUNS = a.Ho * XG;
-  const long long WR = WP + 8 > (((long long)W + 7) & ~7LL) ? WP + 8 : (((long long)W + 7) & ~7LL), W4 = (W + 3) / 4;
-  if (KW > 8) return p;  // the shifted copies are made for at most eight kernel columns
-  // in 64 bits first: one image must fit
-  if (16 * (16 * ((RUNS + 3) / 4 * 4) + 16) + 2 * Cin * (long long)H * (KW * WP + WR) + 64 > LDS_LIMIT || NT > (1 << 20)) return p;
-  a.K = (int)K, a.NT = (int)NT, a.MT = (int)MT, a.NTG = (int)((NT + 15) / 16), a.XG = (int)XG, a.WP = (int)WP;
-  a.WR = (int)WR, a.W4 = (int)W4, a.DR = Cout < 16 ? Cout : 16;
-  auto bytes = [&](int nb) {
-    a.NB = nb;
-    a.NBK = (int)((nb * RUNS + 3) / 4);
-    a.RSD = 64 * a.NBK + 16;
-    return (long long)igemm16::wlds_layout(a).total;
-  };
-  if (bytes(1) > LDS_LIMIT) return p;
-  p.fits = true;
-  int nb = 1;
-  const int nb_fill = (B + MAX_PARTIALS - 1) / MAX_PARTIALS;
-  for (int c = 2; c <= MAX_GROUP && c <= B && c <= (nb_fill > 4 ? nb_fill : 4) && bytes(c) <= WGRAD_LDS_TARGET; ++c) nb = c;
-  p.lds_bytes = (size_t)bytes(nb);
-  a.groups = (B + nb - 1) / nb;
-  unsigned gx = resident_workgroups(p.lds_bytes) / (unsigned)(a.MT * a.NTG);
-  if (gx < 1) gx = 1;
-  if (gx > 2 * MAX_PARTIALS) gx = 2 * MAX_PARTIALS;  // every resident workgroup: this kernel lives on hidden latency
-  if (gx > (unsigned)a.groups) gx = (unsigned)a.groups;
-  p.gx = gx;
-  p.gy = (unsigned)(a.MT * a.NTG);
-  p.workspace_bytes = ((size_t)gx * a.MT * a.NT * 256 + (size_t)gx * a.MT * 16) * sizeof(float);
-  a.inv_khkw = 1.0f / (float)(KH * KW), a.inv_kw = 1.0f / (float)KW, a.inv_xg = 1.0f / (float)XG;
-  a.inv_hoxg = 1.0f / (float)RUNS, a.inv_hxg = 1.0f / (float)(H * XG);
-  a.inv_cinhxg = 1.0f / (float)(Cin * H * XG), a.inv_w4 = 1.0f / (float)W4, a.inv_hw4 = 1.0f / (float)(H * W4);
-  a.inv_cinhw4 = 1.0f / (float)(Cin * H * W4);
+  p.eight = plan_tile16_wgrad(B, Cin, H, W, Cout, KH, KW);
+  p.rounded = plan_tile_wgrad(B, Cin, H, W, Cout, KH, KW);
   return p;
+}
+
+int launch_wgrad16(Wgrad16Plan& p, const float* in, const float* d_out, float* d_k, float* d_bias, float* part, hipStream_t st) {
+  return p.use_rounded() ? launch_tile_wgrad<true>(p.rounded, in, d_out, d_k, d_bias, part, st)
+                         : launch_tile16_wgrad(p.eight, in, d_out, d_k, d_bias, part, st);
 }
 
 inline bool conv_args_ok(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
@@ -815,7 +941,7 @@ inline bool wgrad_args_ok(const float* in, const float* d_out, const float* d_k,
 int launch_wgrad(WgradPlan& p, const float* in, const float* d_out, float* d_k, float* d_bias, int B, int Cin, int Cout,
                  int KH, int KW, float* part, hipStream_t st) {
   switch (p.kernel) {
-    case WgradPlan::TILED: return launch_tile_wgrad(p.tile, in, d_out, d_k, d_bias, part, st);
+    case WgradPlan::TILED: return launch_tile_wgrad<false>(p.tile, in, d_out, d_k, d_bias, part, st);
     case WgradPlan::FC: fc::bwd_weight_kernel<<<p.gx, fc::WGRAD_THREADS, 0, st>>>(in, d_out, part, B); break;
     case WgradPlan::CONV1: conv1::bwd_weight_kernel<<<p.gx, conv1::THREADS, 0, st>>>(in, d_out, part, B); break;
     case WgradPlan::CONV2: conv2::bwd_weight_kernel<<<p.gx, conv2::THREADS, 0, st>>>(in, d_out, part, B); break;
@@ -950,8 +1076,8 @@ int cnn_conv_fwd_bf16(const float* in, const float* k, const float* bias, float*
                       int W, int Cout, int KH, int KW, void* hip_stream) {
   if (!in || !k || !out || !conv_args_ok(B, Cin, H, W, Cout, KH, KW)) return CNN_EINVAL;
   if (!aligned16(in) || !aligned16(k) || !aligned16(out) || (bias && !aligned16(bias))) return CNN_EINVAL;
-  const Conv16Plan p = plan_conv16(in, k, bias, out, B, Cout, Cin, H, W, KH, KW, H - KH + 1, W - KW + 1, 0, 0, 0);
-  if (p.tp) return launch_conv16(p, (hipStream_t)hip_stream);
+  const Tile16ConvPlan p = plan_tile16_conv(in, k, bias, out, B, Cout, Cin, H, W, KH, KW, H - KH + 1, W - KW + 1, 0, 0, 0);
+  if (p.nt) return launch_tile16_conv(p, (hipStream_t)hip_stream);
   const size_t total = (size_t)B * Cout * (H - KH + 1) * (W - KW + 1);
   conv_fwd_kernel<true><<<grid_for(total), TPB, 0, (hipStream_t)hip_stream>>>(in, k, bias, out, total, Cin,
                                                                                H, W, Cout, KH, KW);
@@ -962,9 +1088,9 @@ int cnn_conv_bwd_input_bf16(const float* d_out, const float* k, float* d_in, int
                             int Cout, int KH, int KW, void* hip_stream) {
   if (!d_out || !k || !d_in || !conv_args_ok(B, Cin, H, W, Cout, KH, KW)) return CNN_EINVAL;
   if (!aligned16(d_out) || !aligned16(k) || !aligned16(d_in)) return CNN_EINVAL;
-  const Conv16Plan p = plan_conv16(d_out, k, nullptr, d_in, B, Cin, Cout, H - KH + 1, W - KW + 1, KH, KW, H, W,
-                                   KH - 1, KW - 1, 1);
-  if (p.tp) return launch_conv16(p, (hipStream_t)hip_stream);
+  const Tile16ConvPlan p = plan_tile16_conv(d_out, k, nullptr, d_in, B, Cin, Cout, H - KH + 1, W - KW + 1, KH, KW, H, W,
+                                            KH - 1, KW - 1, 1);
+  if (p.nt) return launch_tile16_conv(p, (hipStream_t)hip_stream);
   const size_t total = (size_t)B * Cin * H * W;
   conv_bwd_input_kernel<true><<<grid_for(total), TPB, 0, (hipStream_t)hip_stream>>>(d_out, k, d_in, total,
                                                                                      Cin, H, W, Cout, KH, KW);
@@ -1004,7 +1130,9 @@ int cnn_conv_bwd_weight_static(const float* in, const float* d_out, float* d_k, 
 
 size_t cnn_conv_bwd_weight_bf16_workspace_bytes(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
   if (!conv_args_ok(B, Cin, H, W, Cout, KH, KW)) return 0;
-  return plan_wgrad16(B, Cin, H, W, Cout, KH, KW).workspace_bytes;
+  // in whole rows of padded 16 x 16 tiles and biases, the unit this query has always had
+  const size_t rows = ceil_div(Cout, 16), row = sizeof(float) * rows * (ceil_div((long long)Cin * KH * KW, 16) * 256 + 16);
+  return ceil_div(plan_wgrad16(B, Cin, H, W, Cout, KH, KW).workspace_bytes(), row) * row;
 }
 
 int cnn_conv_bwd_weight_bf16(const float* in, const float* d_out, float* d_k, float* d_bias, int B, int Cin,
@@ -1015,16 +1143,9 @@ int cnn_conv_bwd_weight_bf16(const float* in, const float* d_out, float* d_k, fl
     return CNN_EINVAL;
   if (workspace && !aligned16(workspace)) return CNN_EINVAL;
   Wgrad16Plan p = plan_wgrad16(B, Cin, H, W, Cout, KH, KW);
-  if (p.fits && workspace && workspace_bytes >= p.workspace_bytes) {
-    p.a.in = in, p.a.d_out = d_out, p.a.part = static_cast<float*>(workspace);
-    hipStream_t st = (hipStream_t)hip_stream;
-    igemm16::wgrad_kernel<<<dim3(p.gx, p.gy), igemm::THREADS, p.lds_bytes, st>>>(p.a);
-    const size_t outputs = (size_t)Cout * Cin * KH * KW + Cout;
-    const int epw = outputs >= 2048 ? 16 : outputs >= 512 ? 8 : 4;
-    igemm::wgrad_reduce_kernel<<<(unsigned)((outputs + epw - 1) / epw), igemm::THREADS, 0, st>>>(
-        p.a.part, (int)p.gx, p.a.MT, p.a.NT, Cout, Cin, KH, KW, 1, epw, d_k, d_bias);
-    return launched();
-  }
+  const size_t need = p.workspace_bytes();
+  if (!p.use_plain() && (need == 0 || (workspace && workspace_bytes >= need)))
+    return launch_wgrad16(p, in, d_out, d_k, d_bias, static_cast<float*>(workspace), (hipStream_t)hip_stream);
   const unsigned blocks = (unsigned)(Cout * Cin * KH * KW + (d_bias ? Cout : 0));
   conv_bwd_weight_kernel<true><<<blocks, TPB, 0, (hipStream_t)hip_stream>>>(in, d_out, d_k, d_bias, B, Cin, H,
                                                                             W, Cout, KH, KW);

@@ -90,20 +90,26 @@ __device__ __forceinline__ void buffer_to_lds(__amdgpu_buffer_rsrc_t rs, float* 
 }
 
 // Stages runs of consecutive floats: run r of `runs` is `len` floats at src + r * sstride, to LDS floats
-// dst + r * dstride.  VB bytes per lane (16: everything a multiple of four floats).
+// dst + r * dstride.  VB bytes per lane (16: everything a multiple of four floats).  Of a run only the first `valid`
+// floats exist (the others are staged as zeros).
 template <int VB>
 __device__ __forceinline__ void stage_runs(const float* src, float* dst, int runs, int len, size_t sstride,
-                                           int dstride, int wave, int l) {
+                                           int dstride, int wave, int l, int valid) {
   constexpr int V = VB / 4, CH = 64 * V;
   const bool spread = runs >= WAVES;  // whole runs to waves, or the pieces of each run
 #pragma unroll 1
   for (int r = spread ? wave : 0; r < runs; r += spread ? WAVES : 1) {
-    const __amdgpu_buffer_rsrc_t rs = buffer_at(src + r * sstride, 4 * len);
+    const __amdgpu_buffer_rsrc_t rs = buffer_at(src + r * sstride, 4 * valid);
     float* d = dst + r * dstride;
 #pragma unroll 1
     for (int c = (spread ? 0 : wave) * CH; c < len; c += (spread ? 1 : WAVES) * CH)
       if (c + l * V < len) buffer_to_lds<VB>(rs, d + c, 4 * c + VB * l);
   }
+}
+
+template <int VB>
+__device__ __forceinline__ void stage_runs(const float* src, float* dst, int runs, int len, size_t sstride, int dstride, int wave, int l) {
+  stage_runs<VB>(src, dst, runs, len, sstride, dstride, wave, l, len);
 }
 
 // ---- forward and input gradient -----------------------------------------------------------------------
@@ -205,6 +211,157 @@ __device__ __forceinline__ void gemm(f4 (&acc)[MT][NT], const float* wt, const i
   }
 }
 
+// What a workgroup works on at a time.
+struct Unit {
+  int b0, y0, x0, nb, th, txp;  // first image, row, column (pixels); images, rows, pixel columns that exist
+};
+__device__ __forceinline__ Unit unit_at(const ConvArgs& g, unsigned u) {
+  unsigned r, strip;
+  const unsigned grp = divide(u, g.by_unit, r), band = divide(r, g.by_strip, strip);
+  Unit v;
+  v.b0 = grp * g.NB;
+  v.y0 = band * g.TH;
+  v.x0 = strip * g.TXC * g.P;
+  v.nb = min(g.NB, g.B - v.b0);
+  v.th = min(g.TH, g.OH - v.y0);
+  v.txp = min(g.TXC * g.P, g.OW - v.x0);
+  return v;
+}
+// Issues the loads of a unit's channel chunk into the fp32 planes at `buf`.
+template <bool BORDER>
+__device__ __forceinline__ void stage_unit(const ConvArgs& g, const Unit& u, int chunk, float* buf, int wave, int t) {
+  const int plane = g.SH * g.SW;
+  const size_t per_image = (size_t)g.SC * plane;
+  const int c0 = chunk * g.CC, cc = min(g.CC, g.SC - c0);
+  const float* src = g.src + u.b0 * per_image + (size_t)c0 * plane;
+  if (!BORDER) {
+    const int l = t & 63;
+    if (g.bands == 1) {  // whole planes: the channels of an image are one run, and so are all images of the unit if nothing lies between
+      const bool one = cc == g.SC && g.LI == g.SC * plane;
+      const int runs = one ? 1 : u.nb, len = one ? u.nb * g.LI : cc * plane;
+      if (g.linear == 16)
+        stage_runs<16>(src, buf, runs, len, per_image, g.LI, wave, l);
+      else
+        stage_runs<4>(src, buf, runs, len, per_image, g.LI, wave, l);
+      return;
+    }
+    const float* s = src + (size_t)u.y0 * g.SW;
+    const int len = min(g.RH, g.SH - u.y0) * g.SW;
+    if (g.linear == 16)
+      stage_runs<16>(s, buf, cc, len, plane, g.LP, wave, l);
+    else
+      stage_runs<4>(s, buf, cc, len, plane, g.LP, wave, l);
+    return;
+  }
+  // by rows: RPI rows of LW columns per instruction (or 64 columns of one wide row).  Rows above and
+  // below the image fall outside the plane's buffer by themselves, columns beside it are marked.
+  const int yb = u.y0 - g.pady, xb = u.x0 - g.padx;
+  int l = t & 63;
+  asm volatile("" : "+v"(l));  // decoded here, not kept in registers through the main loop
+#pragma unroll 1
+  for (int cx = 0; cx < g.LW; cx += 64) {
+    const int lrr = g.LW <= 64 ? (int)((float)l * g.inv_lw + 1e-4f) : 0, col = g.LW <= 64 ? l - lrr * g.LW : cx + l;
+    const bool inside = (unsigned)(xb + col) < (unsigned)g.SW;
+    const int off0 = inside ? 4 * ((yb + lrr) * g.SW + xb + col) : FAR, step = inside ? 4 * g.RPI * g.SW : 0;
+    if (lrr < g.RPI && col < g.LW) {
+#pragma unroll 1
+      for (int ic = wave; ic < u.nb * cc; ic += WAVES) {
+        unsigned c = ic;
+        const unsigned img = u.nb == 1 ? 0 : divide(ic, g.by_cc, c);
+        const __amdgpu_buffer_rsrc_t rs = buffer_at(src + img * per_image + (size_t)c * plane, 4 * plane);
+        float* d = buf + img * g.LI + c * g.LP + cx;
+        int off = off0;
+#pragma unroll 1
+        for (int r = 0; r < g.RH; r += g.RPI) {
+          buffer_to_lds<4>(rs, d, off);
+          off += step;
+          d += g.RPI * g.LW;
+        }
+      }
+    }
+  }
+}
+// The columns of a wave: tiles wave, wave + 4, ...
+template <int NT>
+struct Columns {
+  int oo[NT], where[NT];  // byte offset in dst (FAR: none); image, row, column inside the unit
+};
+template <int NT>
+__device__ __forceinline__ void columns(const ConvArgs& g, Columns<NT>& c, int wave, int j) {
+#pragma unroll
+  for (int tt = 0; tt < NT; ++tt) {
+    const int n = 16 * (wave + WAVES * tt) + j;
+    int img, r, y, xx;
+    divmod(n, g.TH * g.TXC, g.inv_cols, img, r);
+    divmod(r, g.TXC, g.inv_txc, y, xx);
+    const bool have = img < g.NB;
+    if (!have) img = y = xx = 0;
+    c.oo[tt] = have ? 4 * (img * g.M * g.OH * g.OW + y * g.OW + g.P * xx) : FAR;
+    c.where[tt] = (img << 20) | (y << 10) | xx;
+  }
+}
+// The rows of D in a lane's result registers.
+template <int MT>
+struct Rows {
+  int ro[MT][4], shift[4];  // byte offset in dst of result register r (FAR: not a row), its pixel of the column
+  f4 binit[MT];             // bias
+};
+template <int MT>
+__device__ __forceinline__ void rows_of(const ConvArgs& g, Rows<MT>& w, int row0, int q) {
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int mrow = row0 + 16 * m + 4 * q + r;
+      int ch = mrow, sh = 0;
+      if (MT == 1 && g.P > 1) divmod(mrow, g.P, g.inv_p, ch, sh);
+      if (m == 0) w.shift[r] = sh;
+      w.ro[m][r] = mrow < g.MR ? 4 * (ch * g.OH * g.OW + sh) : FAR;
+      w.binit[m][r] = g.bias && mrow < g.MR ? g.bias[ch] : 0.0f;
+    }
+}
+template <int NT, int MT>
+__device__ __forceinline__ void store_unit(const ConvArgs& g, const Unit& u, const Columns<NT>& c, const Rows<MT>& w,
+                                           const f4 (&acc)[MT][NT]) {
+  // how a lane's four result registers of a column lie in memory: one 16-byte item, two of 8 bytes, or single floats
+  const int wide = MT > 1 || g.P == 1 ? 1 : (g.P & 3) == 0 && (g.OW & 3) == 0 ? 4 : (g.P & 1) == 0 && (g.OW & 1) == 0 ? 2 : 1;
+  const bool ragged_p = MT == 1 && g.OW % g.P != 0;  // the last column of a row has fewer than P pixels
+  const __amdgpu_buffer_rsrc_t rs = buffer_at(g.dst + (size_t)u.b0 * g.M * g.OH * g.OW + (size_t)u.y0 * g.OW + u.x0, FAR_SIZE);
+  const bool full = u.nb == g.NB && u.th == g.TH && u.txp == g.TXC * g.P;
+  int ox[NT], left[NT];
+#pragma unroll
+  for (int tt = 0; tt < NT; ++tt) {
+    left[tt] = u.txp - g.P * (c.where[tt] & 1023);
+    ox[tt] = full || ((c.where[tt] >> 20) < u.nb && ((c.where[tt] >> 10) & 1023) < u.th && left[tt] > 0) ? c.oo[tt] : FAR;
+  }
+  if (wide == 4) {
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt) {
+      const int off = ragged_p && w.shift[0] >= left[tt] ? FAR : ox[tt] + w.ro[0][0];
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i4, acc[0][tt]), rs, off, 0, 2);
+    }
+  } else if (wide == 2) {
+#pragma unroll
+    for (int r = 0; r < 4; r += 2)
+#pragma unroll
+      for (int tt = 0; tt < NT; ++tt) {
+        using i2 = int __attribute__((ext_vector_type(2)));
+        const int off = ragged_p && w.shift[r] >= left[tt] ? FAR : ox[tt] + w.ro[0][r];
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(i2, f2{acc[0][tt][r], acc[0][tt][r + 1]}), rs, off, 0, 0);
+      }
+  } else {
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int tt = 0; tt < NT; ++tt) {
+          const int off = ragged_p && w.shift[r] >= left[tt] ? FAR : ox[tt] + w.ro[m][r];
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(acc[m][tt][r]), rs, off, 0, 0);
+        }
+  }
+}
+
 // Waves per SIMD (= workgroups per compute unit) the registers allow; the grid is sized to what is resident.
 __host__ __device__ constexpr int conv_residency(int nt, int mt) { return nt * mt <= 4 ? 4 : 3; }
 
@@ -217,74 +374,8 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
   int* koff = reinterpret_cast<int*>(lds + L.koff);
   const int t = threadIdx.x, l = t & 63, q = l >> 4, j = l & 15;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int KHKW = g.KH * g.KW, KHKWP = g.KH * g.KWP, OHOW = g.OH * g.OW, plane = g.SH * g.SW;
-  const int COLS = g.TH * g.TXC, row0 = 16 * MT * blockIdx.y;  // first row of A of this workgroup
-  const size_t per_image = (size_t)g.SC * plane;
-
-  struct Unit {
-    int b0, y0, x0, nb, th, txp;  // first image, row, column (pixels); images, rows, pixel columns that exist
-  };
-  auto unit_at = [&](unsigned u) {
-    unsigned r, strip;
-    const unsigned grp = divide(u, g.by_unit, r), band = divide(r, g.by_strip, strip);
-    Unit v;
-    v.b0 = grp * g.NB;
-    v.y0 = band * g.TH;
-    v.x0 = strip * g.TXC * g.P;
-    v.nb = min(g.NB, g.B - v.b0);
-    v.th = min(g.TH, g.OH - v.y0);
-    v.txp = min(g.TXC * g.P, g.OW - v.x0);
-    return v;
-  };
-  auto issue = [&](const Unit& u, int chunk, float* buf) {
-    const int c0 = chunk * g.CC, cc = min(g.CC, g.SC - c0);
-    const float* src = g.src + u.b0 * per_image + (size_t)c0 * plane;
-    if (!BORDER) {
-      if (g.bands == 1) {  // whole planes: the channels of an image are one run, and so are all images of the unit if nothing lies between
-        const bool one = cc == g.SC && g.LI == g.SC * plane;
-        const int runs = one ? 1 : u.nb, len = one ? u.nb * g.LI : cc * plane;
-        if (g.linear == 16)
-          stage_runs<16>(src, buf, runs, len, per_image, g.LI, wave, l);
-        else
-          stage_runs<4>(src, buf, runs, len, per_image, g.LI, wave, l);
-        return;
-      }
-      const float* s = src + (size_t)u.y0 * g.SW;
-      const int len = min(g.RH, g.SH - u.y0) * g.SW;
-      if (g.linear == 16)
-        stage_runs<16>(s, buf, cc, len, plane, g.LP, wave, l);
-      else
-        stage_runs<4>(s, buf, cc, len, plane, g.LP, wave, l);
-      return;
-    }
-    // by rows: RPI rows of LW columns per instruction (or 64 columns of one wide row).  Rows above and
-    // below the image fall outside the plane's buffer by themselves, columns beside it are marked.
-    const int yb = u.y0 - g.pady, xb = u.x0 - g.padx;
-    int l = t & 63;
-    asm volatile("" : "+v"(l));  // decoded here, not kept in registers through the main loop
-#pragma unroll 1
-    for (int cx = 0; cx < g.LW; cx += 64) {
-      const int lrr = g.LW <= 64 ? (int)((float)l * g.inv_lw + 1e-4f) : 0, col = g.LW <= 64 ? l - lrr * g.LW : cx + l;
-      const bool inside = (unsigned)(xb + col) < (unsigned)g.SW;
-      const int off0 = inside ? 4 * ((yb + lrr) * g.SW + xb + col) : FAR, step = inside ? 4 * g.RPI * g.SW : 0;
-      if (lrr < g.RPI && col < g.LW) {
-#pragma unroll 1
-        for (int ic = wave; ic < u.nb * cc; ic += WAVES) {
-          unsigned c = ic;
-          const unsigned img = u.nb == 1 ? 0 : divide(ic, g.by_cc, c);
-          const __amdgpu_buffer_rsrc_t rs = buffer_at(src + img * per_image + (size_t)c * plane, 4 * plane);
-          float* d = buf + img * g.LI + c * g.LP + cx;
-          int off = off0;
-#pragma unroll 1
-          for (int r = 0; r < g.RH; r += g.RPI) {
-            buffer_to_lds<4>(rs, d, off);
-            off += step;
-            d += g.RPI * g.LW;
-          }
-        }
-      }
-    }
-  };
+  const int KHKW = g.KH * g.KW, KHKWP = g.KH * g.KWP, row0 = 16 * MT * blockIdx.y;  // first row of A of this workgroup
+  auto issue = [&](const Unit& u, int chunk, float* buf) { stage_unit<BORDER>(g, u, chunk, buf, wave, t); };
   // A in LDS: a thread keeps one K index and walks the rows (every RG-th one), eight loads in flight; rows and
   // taps that do not exist are loads outside the buffer, i.e. zeros.
   const int KP = 16 * g.NBK, RG = KP < THREADS ? THREADS / KP : 1, rows = min(g.R, g.MR - row0);
@@ -333,7 +424,7 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
   for (int e = t; e < 2 * L.buf / 4; e += THREADS) reinterpret_cast<f4*>(xbuf)[e] = f4{0.0f, 0.0f, 0.0f, 0.0f};
   lds_barrier();
   unsigned unit = blockIdx.x;
-  Unit cur = unit_at(unit);
+  Unit cur = unit_at(g, unit);
   issue(cur, 0, xbuf);
   for (int e = t; e < 4 * g.SK; e += THREADS) {
     const int qq = e >= 3 * g.SK ? 3 : e >= 2 * g.SK ? 2 : e >= g.SK ? 1 : 0, kk = 4 * (e - qq * g.SK) + qq;
@@ -349,44 +440,23 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
   if (g.resident)
     for (int c = 0; c < g.chunks; ++c) weights(c);
 
-  // this wave's columns: tiles wave, wave + 4, ...
-  int po[NT], oo[NT], where[NT];  // byte offset in a buffer; byte offset in dst (FAR: none); image, row, column inside the unit
+  Columns<NT> col;
+  columns(g, col, wave, j);
+  int po[NT];  // byte offset of the columns in a buffer
 #pragma unroll
-  for (int tt = 0; tt < NT; ++tt) {
-    const int n = 16 * (wave + WAVES * tt) + j;
-    int img, r, y, xx;
-    divmod(n, COLS, g.inv_cols, img, r);
-    divmod(r, g.TXC, g.inv_txc, y, xx);
-    const bool have = img < g.NB;
-    if (!have) img = y = xx = 0;
-    po[tt] = 4 * (img * g.LI + y * g.LW + g.P * xx);
-    oo[tt] = have ? 4 * (img * g.M * OHOW + y * g.OW + g.P * xx) : FAR;
-    where[tt] = (img << 20) | (y << 10) | xx;
-  }
-  int arow[MT], ro[MT][4], shift[4];  // row of A in LDS; byte offset in dst of result register r (FAR: not a row), its pixel of the column
-  f4 binit[MT];
+  for (int tt = 0; tt < NT; ++tt)
+    po[tt] = 4 * ((col.where[tt] >> 20) * g.LI + ((col.where[tt] >> 10) & 1023) * g.LW + g.P * (col.where[tt] & 1023));
+  Rows<MT> row;
+  rows_of(g, row, row0, q);
+  int arow[MT];
 #pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    arow[m] = (min(16 * m + j, g.R) * 4 + q) * g.SP;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int mrow = row0 + 16 * m + 4 * q + r;
-      int ch = mrow, sh = 0;
-      if (MT == 1 && g.P > 1) divmod(mrow, g.P, g.inv_p, ch, sh);
-      if (m == 0) shift[r] = sh;
-      ro[m][r] = mrow < g.MR ? 4 * (ch * OHOW + sh) : FAR;
-      binit[m][r] = g.bias && mrow < g.MR ? g.bias[ch] : 0.0f;
-    }
-  }
+  for (int m = 0; m < MT; ++m) arow[m] = (min(16 * m + j, g.R) * 4 + q) * g.SP;
   f4 acc[MT][NT];
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int tt = 0; tt < NT; ++tt) acc[m][tt] = binit[m];
+    for (int tt = 0; tt < NT; ++tt) acc[m][tt] = row.binit[m];
   const i4* kq = reinterpret_cast<const i4*>(koff + q * g.SK);
-  // how a lane's four result registers of a column lie in memory: one 16-byte item, two of 8 bytes, or single floats
-  const int wide = MT > 1 || g.P == 1 ? 1 : (g.P & 3) == 0 && (g.OW & 3) == 0 ? 4 : (g.P & 1) == 0 && (g.OW & 1) == 0 ? 2 : 1;
-  const bool ragged_p = MT == 1 && g.OW % g.P != 0;  // the last column of a row has fewer than P pixels
 
   int chunk = 0, par = 0;
   wait_loads();
@@ -401,49 +471,16 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
       weights(chunk);
       lds_barrier();
     }
-    const Unit nxt = nunit == unit || !more ? cur : unit_at(nunit);
+    const Unit nxt = nunit == unit || !more ? cur : unit_at(g, nunit);
     if (more) issue(nxt, nchunk, xbuf + (par ^ 1) * L.buf);
     gemm<NT, MT>(acc, wt + (g.resident ? 4 * g.NBK * chunk : 0), arow, kq, reinterpret_cast<const char*>(xbuf + par * L.buf), po, g.NBK);
     wait_loads();  // before this unit's stores are issued, so that those stay in flight under the next unit's work
     if (nchunk == 0) {
-      const __amdgpu_buffer_rsrc_t rs = buffer_at(g.dst + (size_t)cur.b0 * g.M * OHOW + (size_t)cur.y0 * g.OW + cur.x0, FAR_SIZE);
-      const bool full = cur.nb == g.NB && cur.th == g.TH && cur.txp == g.TXC * g.P;
-      int ox[NT], left[NT];
-#pragma unroll
-      for (int tt = 0; tt < NT; ++tt) {
-        left[tt] = cur.txp - g.P * (where[tt] & 1023);
-        ox[tt] = full || ((where[tt] >> 20) < cur.nb && ((where[tt] >> 10) & 1023) < cur.th && left[tt] > 0) ? oo[tt] : FAR;
-      }
-      if (wide == 4) {
-#pragma unroll
-        for (int tt = 0; tt < NT; ++tt) {
-          const int off = ragged_p && shift[0] >= left[tt] ? FAR : ox[tt] + ro[0][0];
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i4, acc[0][tt]), rs, off, 0, 2);
-        }
-      } else if (wide == 2) {
-#pragma unroll
-        for (int r = 0; r < 4; r += 2)
-#pragma unroll
-          for (int tt = 0; tt < NT; ++tt) {
-            using i2 = int __attribute__((ext_vector_type(2)));
-            const int off = ragged_p && shift[r] >= left[tt] ? FAR : ox[tt] + ro[0][r];
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(i2, f2{acc[0][tt][r], acc[0][tt][r + 1]}), rs, off, 0, 0);
-          }
-      } else {
-#pragma unroll
-        for (int m = 0; m < MT; ++m)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int tt = 0; tt < NT; ++tt) {
-              const int off = ragged_p && shift[r] >= left[tt] ? FAR : ox[tt] + ro[m][r];
-              __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(acc[m][tt][r]), rs, off, 0, 0);
-            }
-      }
+      store_unit(g, cur, col, row, acc);
 #pragma unroll
       for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int tt = 0; tt < NT; ++tt) acc[m][tt] = binit[m];
+        for (int tt = 0; tt < NT; ++tt) acc[m][tt] = row.binit[m];
     }
     if (!more) break;
     cur = nxt, unit = nunit, chunk = nchunk, par ^= 1;
@@ -496,7 +533,91 @@ __host__ __device__ inline WgradLds wgrad_lds(const WgradArgs& a) {
 constexpr int T_STRIDE(int nt) { return 16 * nt + 4; }
 constexpr int wgrad_end_floats(int nt, int mt) { return WAVES * WAVES * 256 + WAVES * 16 * mt + 16 * mt * T_STRIDE(nt); }
 
-template <int NT, int MT>
+// The end of a weight-gradient kernel: the waves' accumulators (and row sums of A) are added in LDS in wave order, the
+// P shifts joined, and the workgroup's outputs written.  Uses wgrad_end_floats(NT, MT) of LDS from `lds` on.
+template <int NT, int MT, typename ARGS>
+__device__ __forceinline__ void finish_wgrad(const ARGS& g, const f4 (&acc)[MT][NT], float (&asum)[MT], float* lds, int row0,
+                                             int rows, int tap0, int taps, bool sums_bias) {
+  const int t = threadIdx.x, l = t & 63, q = l >> 4, j = l & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  // the waves' sums meet in LDS, WAVES tiles at a time: wave w adds tile 4 p + w, in wave order, into T
+  float* xch = lds;
+  float* bs = xch + WAVES * WAVES * 256;    // [wave][16 MT]
+  float* T = bs + WAVES * 16 * MT;          // [16 MT][T_STRIDE]
+  constexpr int TS = T_STRIDE(NT);
+#pragma unroll
+  for (int p = 0; p < (MT * NT + WAVES - 1) / WAVES; ++p) {
+    loads_and_lds_barrier();
+#pragma unroll
+    for (int k = 0; k < WAVES; ++k) {
+      const int ti = WAVES * p + k;
+      if (ti < MT * NT) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) xch[(wave * WAVES + k) * 256 + 64 * r + l] = acc[ti / NT < MT ? ti / NT : 0][ti % NT][r];
+      }
+    }
+    if (p == 0 && sums_bias) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        asum[m] += __shfl_xor(asum[m], 16, 64);
+        asum[m] += __shfl_xor(asum[m], 32, 64);
+        if (q == 0) bs[(wave * MT + m) * 16 + j] = asum[m];
+      }
+    }
+    lds_barrier();
+    const int ti = WAVES * p + wave, m = ti / NT, i = ti - m * NT;
+    if (m < MT) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float s = 0.0f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) s += xch[(w * WAVES + wave) * 256 + 64 * r + l];
+        T[(16 * m + 4 * q + r) * TS + 16 * i + j] = s;
+      }
+    }
+  }
+  lds_barrier();
+  // outputs of this workgroup: channels row0 / P .., (c,u) groups tap0 / KWP .., KW taps each
+  float* out = g.out_k + (size_t)blockIdx.x * g.RS;
+  const int co0 = row0 / g.P, ncu = g.P == 1 ? 1 : taps / g.KWP, per = g.P == 1 ? taps : ncu * g.KW, nco = rows / g.P;
+  const int K1 = g.Cin * g.KH * g.KW, first = g.P == 1 ? tap0 : tap0 / g.KWP * g.KW;
+  const float inv_per = 1.0f / (float)per, inv_kw = 1.0f / (float)g.KW;
+#pragma unroll 1
+  for (int e = t; e < nco * per; e += THREADS) {
+    int co, k;
+    divmod(e, per, inv_per, co, k);
+    float s;
+    if (g.P == 1) {
+      s = T[co * TS + k];
+    } else {
+      int cu, v;
+      divmod(k, g.KW, inv_kw, cu, v);
+      const float* tp = T + co * g.P * TS + cu * g.KWP + v;
+      s = 0.0f;
+#pragma unroll 1
+      for (int sh = 0; sh < g.P; ++sh) s += tp[sh * (TS + 1)];
+    }
+    out[(size_t)(co0 + co) * K1 + first + k] = s;
+  }
+  if (sums_bias && g.out_b && t < nco) {
+    float s = 0.0f;
+    for (int sh = 0; sh < g.P; ++sh)
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) s += bs[w * MT * 16 + t * g.P + sh];
+    g.out_b[(size_t)blockIdx.x * g.RS + co0 + t] = s;
+  }
+}
+
+// An operand rounded to bfloat16 (nearest, ties to even), as a float.
+__device__ __forceinline__ float round_bf16(float v) {
+  using f2v = float __attribute__((ext_vector_type(2)));
+  using bf2v = __bf16 __attribute__((ext_vector_type(2)));
+  return __uint_as_float(__builtin_bit_cast(unsigned, __builtin_convertvector(f2v{0.0f, v}, bf2v)) & 0xffff0000u);
+}
+
+// ROUND: the reduced-precision form for few images (cnn_tile_bf16.h needs eight to fill its operands): operands are
+// rounded to bfloat16 as they are read, their products, exact in fp32, are summed as in the fp32 form.
+template <int NT, int MT, bool ROUND>
 __global__ __launch_bounds__(THREADS) void wgrad_kernel(const WgradArgs g) {
   extern __shared__ __align__(16) float lds[];
   const WgradLds L = wgrad_lds(g);
@@ -607,6 +728,10 @@ __global__ __launch_bounds__(THREADS) void wgrad_kernel(const WgradArgs g) {
       for (int i = 0; i < NT; ++i) b[0][i] = *reinterpret_cast<const float*>(xb + k[0] + toff[i]);
 #pragma unroll 1
       for (int blk = wave; blk < g.NBK; blk += WAVES) {
+        if (ROUND) {
+#pragma unroll
+          for (int m = 0; m < MT; ++m) a[m] = f4{round_bf16(a[m][0]), round_bf16(a[m][1]), round_bf16(a[m][2]), round_bf16(a[m][3])};
+        }
         const int nblk = min(blk + WAVES, last);
         const i4 kn = pq[nblk];
         f4 an[MT];
@@ -618,9 +743,11 @@ __global__ __launch_bounds__(THREADS) void wgrad_kernel(const WgradArgs g) {
 #pragma unroll
           for (int i = 0; i < NT; ++i) b[(s + 1) & 1][i] = *reinterpret_cast<const float*>(xb + ko + toff[i]);
 #pragma unroll
-          for (int i = 0; i < NT; ++i)
+          for (int i = 0; i < NT; ++i) {
+            const float bi = ROUND ? round_bf16(b[s & 1][i]) : b[s & 1][i];
 #pragma unroll
-            for (int m = 0; m < MT; ++m) acc[m][i] = mfma16(a[m][s], b[s & 1][i], acc[m][i]);
+            for (int m = 0; m < MT; ++m) acc[m][i] = mfma16(a[m][s], bi, acc[m][i]);
+          }
         }
         if (sums_bias) {
 #pragma unroll
@@ -632,72 +759,7 @@ __global__ __launch_bounds__(THREADS) void wgrad_kernel(const WgradArgs g) {
       }
     }
   }
-  // the waves' sums meet in LDS, WAVES tiles at a time: wave w adds tile 4 p + w, in wave order, into T
-  float* xch = lds;
-  float* bs = xch + WAVES * WAVES * 256;    // [wave][16 MT]
-  float* T = bs + WAVES * 16 * MT;          // [16 MT][T_STRIDE]
-  constexpr int TS = T_STRIDE(NT);
-#pragma unroll
-  for (int p = 0; p < (MT * NT + WAVES - 1) / WAVES; ++p) {
-    loads_and_lds_barrier();
-#pragma unroll
-    for (int k = 0; k < WAVES; ++k) {
-      const int ti = WAVES * p + k;
-      if (ti < MT * NT) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) xch[(wave * WAVES + k) * 256 + 64 * r + l] = acc[ti / NT < MT ? ti / NT : 0][ti % NT][r];
-      }
-    }
-    if (p == 0 && sums_bias) {
-#pragma unroll
-      for (int m = 0; m < MT; ++m) {
-        asum[m] += __shfl_xor(asum[m], 16, 64);
-        asum[m] += __shfl_xor(asum[m], 32, 64);
-        if (q == 0) bs[(wave * MT + m) * 16 + j] = asum[m];
-      }
-    }
-    lds_barrier();
-    const int ti = WAVES * p + wave, m = ti / NT, i = ti - m * NT;
-    if (m < MT) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float s = 0.0f;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) s += xch[(w * WAVES + wave) * 256 + 64 * r + l];
-        T[(16 * m + 4 * q + r) * TS + 16 * i + j] = s;
-      }
-    }
-  }
-  lds_barrier();
-  // outputs of this workgroup: channels row0 / P .., (c,u) groups tap0 / KWP .., KW taps each
-  float* out = g.out_k + (size_t)blockIdx.x * g.RS;
-  const int co0 = row0 / g.P, ncu = g.P == 1 ? 1 : taps / g.KWP, per = g.P == 1 ? taps : ncu * g.KW, nco = rows / g.P;
-  const int K1 = g.Cin * g.KH * g.KW, first = g.P == 1 ? tap0 : tap0 / g.KWP * g.KW;
-  const float inv_per = 1.0f / (float)per, inv_kw = 1.0f / (float)g.KW;
-#pragma unroll 1
-  for (int e = t; e < nco * per; e += THREADS) {
-    int co, k;
-    divmod(e, per, inv_per, co, k);
-    float s;
-    if (g.P == 1) {
-      s = T[co * TS + k];
-    } else {
-      int cu, v;
-      divmod(k, g.KW, inv_kw, cu, v);
-      const float* tp = T + co * g.P * TS + cu * g.KWP + v;
-      s = 0.0f;
-#pragma unroll 1
-      for (int sh = 0; sh < g.P; ++sh) s += tp[sh * (TS + 1)];
-    }
-    out[(size_t)(co0 + co) * K1 + first + k] = s;
-  }
-  if (sums_bias && g.out_b && t < nco) {
-    float s = 0.0f;
-    for (int sh = 0; sh < g.P; ++sh)
-#pragma unroll
-      for (int w = 0; w < WAVES; ++w) s += bs[w * MT * 16 + t * g.P + sh];
-    g.out_b[(size_t)blockIdx.x * g.RS + co0 + t] = s;
-  }
+  finish_wgrad<NT, MT>(g, acc, asum, lds, row0, rows, tap0, taps, sums_bias);
 }
 
 // out[i] = sum over the G rows of part[g][i], i < n: the gradient d_k[0 .. nk) and, if d_bias is not null, d_bias

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_1912_05234_amd import binding, inputs
 from parity import RTOL_ACT, assert_close
 
@@ -44,6 +45,26 @@ def test_tiled_convolutions(case):
     assert_close(host(d_k), host(p_k).astype(np.float64), RTOL_ACT, "tiled conv_bwd_weight")
     assert_close(host(d_b), host(p_b).astype(np.float64), RTOL_ACT, "tiled conv_bwd_bias")
     again, none = binding.conv_bwd_weight(x, d, want_bias=False)
+    assert none is None and torch.equal(again, d_k)
+
+
+# besides: channel counts on both sides of eight and a last group of eight images with one, seven and eight of them
+@pytest.mark.parametrize("case", CASES + [(7, 8, 10, 10, 8, 3, 3), (8, 9, 10, 10, 17, 3, 3), (257, 7, 12, 12, 33, 5, 5)])
+def test_tiled_convolutions_bf16(case):
+    B, Cin, H, W, Cout, KH, KW = case
+    x = oracle.round_bf16(inputs.make_signed((B, Cin, H, W), 81))
+    k = oracle.round_bf16(inputs.make_signed((Cout, Cin, KH, KW), 82))
+    d = oracle.round_bf16(inputs.make_signed((B, Cout, H - KH + 1, W - KW + 1), 83))
+    x, k, d, b = dev(x), dev(k), dev(d), dev(inputs.make_signed((Cout,), 84))  # rounding again changes nothing
+    assert_close(host(binding.conv_fwd(x, k, b, bf16=True)), host(binding.conv_fwd(x, k, b, valu=True)).astype(np.float64),
+                 RTOL_ACT, "tiled conv_fwd_bf16")
+    assert_close(host(binding.conv_bwd_input(d, k, H, W, bf16=True)),
+                 host(binding.conv_bwd_input(d, k, H, W, valu=True)).astype(np.float64), RTOL_ACT, "tiled conv_bwd_input_bf16")
+    d_k, d_b = binding.conv_bwd_weight(x, d, bf16=True)
+    p_k, p_b = binding.conv_bwd_weight(x, d, workspace=False)
+    assert_close(host(d_k), host(p_k).astype(np.float64), RTOL_ACT, "tiled conv_bwd_weight_bf16")
+    assert_close(host(d_b), host(p_b).astype(np.float64), RTOL_ACT, "tiled conv_bwd_bias_bf16")
+    again, none = binding.conv_bwd_weight(x, d, want_bias=False, bf16=True)
     assert none is None and torch.equal(again, d_k)
 
 
