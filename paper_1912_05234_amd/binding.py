@@ -1,16 +1,20 @@
-"""ctypes binding over the C ABI in include/cnn.h (same names, argument marshalling only).
+"""Binding over the C ABI in include/cnn.h (same names, argument marshalling only).
 
 PyTorch supplies device memory (tensors) and the stream handle; every step of
 the computation runs inside the library's HIP kernels.  The built library must
 be present (python -m paper_1912_05234_amd.build): there is no fallback path.
+The calls that a program repeats go through the extension module built from
+csrc/torch_calls.cpp (5 us a call instead of 10), the others through ctypes.
 """
 import ctypes
+import importlib.util
 import os
 
 import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libcnn_mi355x.so")
+CALLS_PATH = os.path.join(_PKG, "_calls.so")
 
 NPARAM = 3898
 PARAM_SHAPES = (("k1", (6, 5, 5)), ("b1", (6,)), ("k2", (12, 6, 5, 5)), ("b2", (12,)),
@@ -58,6 +62,7 @@ SIGNATURES = {
 }
 
 _lib = None
+_calls = None
 
 
 class CnnError(RuntimeError):
@@ -80,6 +85,21 @@ def lib():
             fn.restype, fn.argtypes = res, args
         _lib = handle
     return _lib
+
+
+def _native():
+    """The extension module over the same library; raises if it has not been built."""
+    global _calls
+    if _calls is None:
+        lib()
+        if not os.path.exists(CALLS_PATH):
+            raise RuntimeError("%s is missing: build it with `python -m paper_1912_05234_amd.build`" % CALLS_PATH)
+        spec = importlib.util.spec_from_file_location("_calls", CALLS_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.raise_through(_check)
+        _calls = module
+    return _calls
 
 
 def _check(code, where):
@@ -108,6 +128,7 @@ class CNN:
 
     def __init__(self, weights, max_batch, device="cuda:0"):
         self.device = torch.device(device)
+        self._index = -1 if self.device.index is None else self.device.index  # -1: the current one
         self.max_batch = int(max_batch)
         L = lib()
         nbytes = L.cnn_workspace_bytes(self.max_batch)
@@ -148,12 +169,7 @@ class CNN:
         self._stream_obj.synchronize()
 
     def forward(self, images, yhat=None):
-        images = _dev(images)
-        B = images.shape[0]
-        if yhat is None:
-            yhat = torch.empty((B, 10), dtype=torch.float32, device=self.device)
-        _check(lib().cnn_forward(self._ctx, _ptr(images), B, _ptr(_dev(yhat))), "cnn_forward")
-        return yhat
+        return (_calls or _native()).forward(self._ctx.value, images, yhat, self._index)
 
     def forward_activations(self, images):
         images = _dev(images)
@@ -166,19 +182,10 @@ class CNN:
         return a
 
     def gradient(self, images, labels):
-        images, labels = _dev(images), _dev(labels, torch.int32)
-        B = images.shape[0]
-        grad = torch.empty(NPARAM, dtype=torch.float32, device=self.device)
-        loss = torch.empty(1, dtype=torch.float32, device=self.device)
-        _check(lib().cnn_gradient(self._ctx, _ptr(images), _ptr(labels), B, _ptr(grad), _ptr(loss)),
-               "cnn_gradient")
-        return grad, loss
+        return (_calls or _native()).gradient(self._ctx.value, images, labels, self._index)
 
     def train_batch(self, images, labels, lr, loss_sum=None):
-        images, labels = _dev(images), _dev(labels, torch.int32)
-        _check(lib().cnn_train_batch(self._ctx, _ptr(images), _ptr(labels), images.shape[0], float(lr),
-                                     _ptr(_dev(loss_sum))), "cnn_train_batch")
-        return loss_sum
+        return (_calls or _native()).train_batch(self._ctx.value, images, labels, lr, loss_sum)
 
     def train_epoch(self, images, labels, batch, lr, loss_sums=None):
         """One pass over `images` in consecutive batches of `batch` (the last may be shorter)."""
@@ -198,13 +205,7 @@ class CNN:
         return lib().cnn_epoch_status(self._ctx)
 
     def evaluate(self, images, labels):
-        images, labels = _dev(images), _dev(labels, torch.int32)
-        n_ok = torch.empty(1, dtype=torch.int64, device=self.device)
-        loss = torch.empty(1, dtype=torch.float32, device=self.device)
-        _check(lib().cnn_evaluate(self._ctx, _ptr(images), _ptr(labels), images.shape[0], _ptr(n_ok),
-                                  _ptr(loss)), "cnn_evaluate")
-        return n_ok, loss
-
+        return (_calls or _native()).evaluate(self._ctx.value, images, labels, self._index)
 
     def profile_begin(self, capacity):
         _check(lib().cnn_profile_begin(self._ctx, int(capacity)), "cnn_profile_begin")
@@ -220,47 +221,16 @@ class CNN:
 
 # ---- per-operation entry points -------------------------------------------------
 def conv_fwd(inp, k, bias=None, bf16=False, valu=False):
-    inp, k, bias = _dev(inp), _dev(k), _dev(bias)
-    B, Cin, H, W = inp.shape
-    Cout, _, KH, KW = k.shape
-    out = torch.empty((B, Cout, H - KH + 1, W - KW + 1), dtype=torch.float32, device=inp.device)
-    name = "cnn_conv_fwd_bf16" if bf16 else "cnn_conv_fwd_valu" if valu else "cnn_conv_fwd"
-    _check(getattr(lib(), name)(_ptr(inp), _ptr(k), _ptr(bias), _ptr(out), B, Cin, H, W, Cout, KH, KW,
-                                _stream()), name)
-    return out
+    return (_calls or _native()).conv_fwd(inp, k, bias, 1 if bf16 else 2 if valu else 0)
 
 
 def conv_bwd_input(d_out, k, H, W, bf16=False, valu=False):
-    d_out, k = _dev(d_out), _dev(k)
-    B = d_out.shape[0]
-    Cout, Cin, KH, KW = k.shape
-    d_in = torch.empty((B, Cin, H, W), dtype=torch.float32, device=d_out.device)
-    name = "cnn_conv_bwd_input_bf16" if bf16 else "cnn_conv_bwd_input_valu" if valu else "cnn_conv_bwd_input"
-    _check(getattr(lib(), name)(_ptr(d_out), _ptr(k), _ptr(d_in), B, Cin, H, W, Cout, KH, KW, _stream()), name)
-    return d_in
-
-
-def _workspace(nbytes, device, use):
-    if not use or nbytes == 0:
-        return None, 0
-    return torch.empty((nbytes,), dtype=torch.uint8, device=device), nbytes
+    return (_calls or _native()).conv_bwd_input(d_out, k, H, W, 1 if bf16 else 2 if valu else 0)
 
 
 def conv_bwd_weight(inp, d_out, want_bias=True, workspace=True, bf16=False):
     """workspace=False passes none, which selects the kernel that needs no partial sums."""
-    suffix = "_bf16" if bf16 else ""
-    inp, d_out = _dev(inp), _dev(d_out)
-    B, Cin, H, W = inp.shape
-    Cout, Ho, Wo = d_out.shape[1:]
-    KH, KW = H - Ho + 1, W - Wo + 1
-    d_k = torch.empty((Cout, Cin, KH, KW), dtype=torch.float32, device=inp.device)
-    d_b = torch.empty((Cout,), dtype=torch.float32, device=inp.device) if want_bias else None
-    query = getattr(lib(), "cnn_conv_bwd_weight%s_workspace_bytes" % suffix)
-    ws, nbytes = _workspace(query(B, Cin, H, W, Cout, KH, KW), inp.device, workspace)
-    name = "cnn_conv_bwd_weight" + suffix
-    _check(getattr(lib(), name)(_ptr(inp), _ptr(d_out), _ptr(d_k), _ptr(d_b), B, Cin, H, W, Cout, KH, KW,
-                                _ptr(ws), nbytes, _stream()), name)
-    return d_k, d_b
+    return (_calls or _native()).conv_bwd_weight(inp, d_out, bool(want_bias), bool(workspace), bool(bf16))
 
 
 def conv_bwd_weight_static(inp, d_out, d_k, d_b=None):
@@ -275,60 +245,28 @@ def conv_bwd_weight_static(inp, d_out, d_k, d_b=None):
 
 
 def avgpool_fwd(inp):
-    inp = _dev(inp)
-    B, C, H, W = inp.shape
-    out = torch.empty((B, C, H // 2, W // 2), dtype=torch.float32, device=inp.device)
-    _check(lib().cnn_avgpool_fwd(_ptr(inp), _ptr(out), B, C, H, W, _stream()), "cnn_avgpool_fwd")
-    return out
+    return (_calls or _native()).avgpool_fwd(inp)
 
 
 def avgpool_bwd(d_out):
-    d_out = _dev(d_out)
-    B, C, Ho, Wo = d_out.shape
-    d_in = torch.empty((B, C, 2 * Ho, 2 * Wo), dtype=torch.float32, device=d_out.device)
-    _check(lib().cnn_avgpool_bwd(_ptr(d_out), _ptr(d_in), B, C, Ho, Wo, _stream()), "cnn_avgpool_bwd")
-    return d_in
+    return (_calls or _native()).avgpool_bwd(d_out)
 
 
 def fc_fwd(inp, w, bias=None):
-    inp, w, bias = _dev(inp), _dev(w), _dev(bias)
-    B, I = inp.shape
-    O = w.shape[0]
-    out = torch.empty((B, O), dtype=torch.float32, device=inp.device)
-    _check(lib().cnn_fc_fwd(_ptr(inp), _ptr(w), _ptr(bias), _ptr(out), B, I, O, _stream()), "cnn_fc_fwd")
-    return out
+    return (_calls or _native()).fc_fwd(inp, w, bias)
 
 
 def fc_bwd_input(d_out, w):
-    d_out, w = _dev(d_out), _dev(w)
-    B, O = d_out.shape
-    I = w.shape[1]
-    d_in = torch.empty((B, I), dtype=torch.float32, device=d_out.device)
-    _check(lib().cnn_fc_bwd_input(_ptr(d_out), _ptr(w), _ptr(d_in), B, I, O, _stream()), "cnn_fc_bwd_input")
-    return d_in
+    return (_calls or _native()).fc_bwd_input(d_out, w)
 
 
 def fc_bwd_weight(inp, d_out, want_bias=True, workspace=True):
-    inp, d_out = _dev(inp), _dev(d_out)
-    B, I = inp.shape
-    O = d_out.shape[1]
-    d_w = torch.empty((O, I), dtype=torch.float32, device=inp.device)
-    d_b = torch.empty((O,), dtype=torch.float32, device=inp.device) if want_bias else None
-    ws, nbytes = _workspace(lib().cnn_fc_bwd_weight_workspace_bytes(B, I, O), inp.device, workspace)
-    _check(lib().cnn_fc_bwd_weight(_ptr(inp), _ptr(d_out), _ptr(d_w), _ptr(d_b), B, I, O, _ptr(ws), nbytes,
-                                   _stream()), "cnn_fc_bwd_weight")
-    return d_w, d_b
+    return (_calls or _native()).fc_bwd_weight(inp, d_out, bool(want_bias), bool(workspace))
 
 
 def logistic_fwd(x):
-    x = _dev(x)
-    y = torch.empty_like(x)
-    _check(lib().cnn_logistic_fwd(_ptr(x), _ptr(y), x.numel(), _stream()), "cnn_logistic_fwd")
-    return y
+    return (_calls or _native()).logistic_fwd(x)
 
 
 def logistic_bwd(y, d_y):
-    y, d_y = _dev(y), _dev(d_y)
-    d_x = torch.empty_like(y)
-    _check(lib().cnn_logistic_bwd(_ptr(y), _ptr(d_y), _ptr(d_x), y.numel(), _stream()), "cnn_logistic_bwd")
-    return d_x
+    return (_calls or _native()).logistic_bwd(y, d_y)
