@@ -29,10 +29,30 @@ constexpr int FWD_GCAP = 3072;  // most forward-only waves: three per SIMD
 // (more images in flight, no barriers).  Measured crossover: 21.7 against 27.9 us per step at batch
 // 512, 30.8 against 28.8 us at batch 768.
 constexpr int GROUP_MAX_BATCH = 640;
+// The same choice for the forward pass alone: 4.1 against 9.6 us for one image, 6.5 against 10.4 at 512, 13.4 against 14.8 at
+// 1536, 17.1 against 14.8 at 2048 (every 256 images, one more for each compute unit, cost the first form 1.8 us).
+constexpr int FWD_GROUP_MAX_BATCH = 1536;
 // Device-side epoch loop: one barrier flag per workgroup (a batch of at most EPOCH_MAX_BATCH images:
 // thread t of a 512-thread workgroup polls flag t), one flag nobody sets, the error word.
 constexpr int EPOCH_MAX_BATCH = 256;
 constexpr int SYNC_PHANTOM = EPOCH_MAX_BATCH, SYNC_ERROR = EPOCH_MAX_BATCH + 1, SYNC_WORDS = EPOCH_MAX_BATCH + 2;
+
+// Adds one image's prediction (right: 1) and half its squared error to the two sums.
+__device__ __forceinline__ void judge(const float (&y)[10], int label, float& n_ok, float& loss) {
+  int best = 0;
+  float bestv = y[0], lsum = 0.0f;
+#pragma unroll
+  for (int o = 0; o < NY; ++o) {
+    if (o > 0 && y[o] > bestv) {  // strict '>' keeps the lowest index on ties
+      bestv = y[o];
+      best = o;
+    }
+    const float e = y[o] - (o == label ? 1.0f : 0.0f);
+    lsum = fmaf(e, e, lsum);
+  }
+  n_ok += (best == label) ? 1.0f : 0.0f;
+  loss = fmaf(0.5f, lsum, loss);
+}
 
 // Forward-only: yhat[B,10], optional activation dump, optional (count, loss) per wave.
 // Wave gw = 4 * blockIdx.x + wave walks the images gw, gw + G, gw + 2G, ... (G = waves in the grid).
@@ -64,26 +84,34 @@ __global__ __launch_bounds__(64 * WAVES, 2) void forward_kernel(const float* __r
         if (l == o) yhat[n * NY + o] = y[o];
     }
     if (labels) {
-      const int label = labels[n];
-      int best = 0;
-      float bestv = y[0], lsum = 0.0f;
-#pragma unroll
-      for (int o = 0; o < NY; ++o) {
-        if (o > 0 && y[o] > bestv) {  // strict '>' keeps the lowest index on ties
-          bestv = y[o];
-          best = o;
-        }
-        const float e = y[o] - (o == label ? 1.0f : 0.0f);
-        lsum = fmaf(e, e, lsum);
-      }
-      n_ok += (best == label) ? 1.0f : 0.0f;
-      loss = fmaf(0.5f, lsum, loss);
+      judge(y, labels[n], n_ok, loss);
     }
     wave_sync();
   }
   if (eval_partial && l == 0) {
     eval_partial[2 * gw] = n_ok;  // exact: far fewer than 2^24 images per wave
     eval_partial[2 * gw + 1] = loss;
+  }
+}
+
+// The same for few images: eight waves share one (cnn_group.h), one workgroup per image.
+template <bool DUMP>
+__global__ __launch_bounds__(64 * GWAVES) void forward_group_kernel(const float* __restrict__ images,
+                                                                const int32_t* __restrict__ labels,
+                                                                const float* __restrict__ tabg, float* __restrict__ yhat,
+                                                                DumpPtrs dump, float* __restrict__ eval_partial) {
+  __shared__ GroupForwardLds s;
+  const size_t n = blockIdx.x;
+  group_forward<DUMP>(images + n * NI, tabg, yhat ? yhat + n * NY : nullptr, s, dump, n);
+  if (!eval_partial) return;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float y[10], n_ok = 0.0f, loss = 0.0f;
+#pragma unroll
+    for (int o = 0; o < NY; ++o) y[o] = s.y[o];
+    judge(y, labels[n], n_ok, loss);
+    eval_partial[2 * n] = n_ok;
+    eval_partial[2 * n + 1] = loss;
   }
 }
 
@@ -511,7 +539,7 @@ struct cnn_ctx {
   float* tabg;          // [TABG_FLOATS]: the operand table expanded from w, kept in step with it
   int32_t* dest;        // [PSTRIDE][TABLE_MAX_DEST]: slots of tabg that hold parameter p
   float* partial;       // [partial_rows_for(max_batch)][PSTRIDE]
-  float* eval_partial;  // [gcap][2]
+  float* eval_partial;  // [gcap_for(max_batch, FWD_GCAP)][2]: one pair per wave, or per image
   float* fc_hist;       // [max_batch][FC_HIST] when max_batch > GROUP_MAX_BATCH: per image, what the FC weight gradient needs
   unsigned* sync;       // [SYNC_WORDS]: barrier flags of the device-side epoch loop, then its error word
   int epoch_mode = 0;         // 1: cnn_train_epoch runs as one kernel where it can
@@ -592,14 +620,17 @@ inline int blocks_for(const cnn_ctx* ctx, int B, bool forward_only) {
 
 int run_forward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B, float* yhat, float* c1,
                 float* s1, float* c2, float* s2, bool eval) {
-  const int blocks = blocks_for(ctx, B, true);
   const DumpPtrs dump = {c1, s1, c2, s2};
-  if (c1 || s1 || c2 || s2)
-    forward_kernel<kForwardDump><<<blocks, 64 * WAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, yhat,
-                                                                          dump, nullptr);
-  else
-    forward_kernel<kForward><<<blocks, 64 * WAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, yhat, dump,
-                                                                      eval ? ctx->eval_partial : nullptr);
+  const bool dumps = c1 || s1 || c2 || s2;
+  float* pairs = eval ? ctx->eval_partial : nullptr;
+  if (B <= FWD_GROUP_MAX_BATCH) {
+    auto kernel = dumps ? forward_group_kernel<true> : forward_group_kernel<false>;
+    kernel<<<B, 64 * GWAVES, 0, ctx->stream>>>(images, labels, ctx->tabg, yhat, dump, pairs);
+    return hipGetLastError() == hipSuccess ? B : CNN_EHIP;
+  }
+  const int blocks = blocks_for(ctx, B, true);
+  auto kernel = dumps ? forward_kernel<kForwardDump> : forward_kernel<kForward>;
+  kernel<<<blocks, 64 * WAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, yhat, dump, pairs);
   if (hipGetLastError() != hipSuccess) return CNN_EHIP;
   return blocks * WAVES;
 }

@@ -44,24 +44,59 @@ struct GroupState {
 };
 
 // C1 forward + S1 for this wave's NT tiles T = wave + 8 k of the C1 GEMM (cnn_wave.h): returns the
-// activations in c1[k].  All MFMAs first (two independent chains at a time), then the sigmoids and
-// the pooling.
+// activations in c1[k].  `c1a` are the eight operand entries, `bias` the table's biases.  All MFMAs
+// first (two independent chains at a time), then the sigmoids and the pooling.
 template <int NT>
-__device__ __forceinline__ void group_c1_forward(TrainLds& s, const OperandTable<TAB_TRAIN_ENTRIES>& tab, int wave,
+__device__ __forceinline__ void group_c1_forward(const float* c1a, const float* bias, const float* img, float* s1, int wave,
                                                  const C1Lane& ln, f4 (&c1)[3]) {
   const int l = threadIdx.x & 63, q = l >> 4;
   float wa[C1F_KSTEPS];
 #pragma unroll
-  for (int ks = 0; ks < C1F_KSTEPS; ++ks) wa[ks] = tab.e[(TAB_C1A + ks) * 64 + l];
+  for (int ks = 0; ks < C1F_KSTEPS; ++ks) wa[ks] = c1a[ks * 64 + l];
   f4 binit = f4{0.0f, 0.0f, 0.0f, 0.0f};
   if (q < 3) {
-    const float2 bq = *reinterpret_cast<const float2*>(&tab.bias[TAB_BIAS_B1 + 2 * q]);
+    const float2 bq = *reinterpret_cast<const float2*>(&bias[TAB_BIAS_B1 + 2 * q]);
     binit = f4{bq.x, bq.x, bq.y, bq.y};
   }
-  c1f_gemm_pair(wa, ln, s.img + c1f_tile_img(wave), s.img + c1f_tile_img(wave + 8), binit, c1[0], c1[1]);
-  if (NT == 3) c1f_gemm_one(wa, ln, s.img + c1f_tile_img(wave + 16), binit, c1[2]);
+  c1f_gemm_pair(wa, ln, img + c1f_tile_img(wave), img + c1f_tile_img(wave + 8), binit, c1[0], c1[1]);
+  if (NT == 3) c1f_gemm_one(wa, ln, img + c1f_tile_img(wave + 16), binit, c1[2]);
 #pragma unroll
-  for (int k = 0; k < NT; ++k) c1f_finish(c1[k], ln, s.pool + P_S1 + c1f_tile_s1(wave + 8 * k));
+  for (int k = 0; k < NT; ++k) c1f_finish(c1[k], ln, s1 + c1f_tile_s1(wave + 8 * k));
+}
+
+// K steps FIRST .. FIRST + COUNT - 1 of the C2 forward GEMM (cnn_wave.h) for one pixel tile, added to acc;
+// `s1` is that tile's origin for this lane's pixel, `bf` the lane's column of the operand entries.
+template <int FIRST, int COUNT>
+__device__ __forceinline__ void group_c2_steps(const float* s1, const float* bf, f4& acc) {
+  const int q = (threadIdx.x & 63) >> 4;
+  const float *a12 = s1 + 12 * q, *a1 = s1 + q, *a144 = s1 + 144 * q;
+  // operands of step s + AHEAD are read while step s issues: an LDS read takes longer than three
+  // matrix instructions, and with eight waves per image there are registers to spare
+  constexpr int AHEAD = 6, SLOTS = 8;
+  float opa[SLOTS], opw[SLOTS];
+  auto load_step = [&](int k, float& oa, float& ow) {
+    const int sidx = FIRST + k;
+    const float* base = sidx < 30 ? a12 : sidx < 36 ? a1 : a144;
+    ow = bf[sidx * 64];
+    oa = base[fwd_imm(sidx)];
+  };
+#pragma unroll
+  for (int k = 0; k < AHEAD; ++k) load_step(k, opa[k], opw[k]);
+  // even and odd K steps in two sums: a matrix instruction waits for the previous one of its own
+  // chain only
+  f4 odd = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int k = 0; k < COUNT; ++k) {
+    if (k + AHEAD < COUNT) load_step(k + AHEAD, opa[(k + AHEAD) % SLOTS], opw[(k + AHEAD) % SLOTS]);
+    if (k & 1)
+      odd = mfma16(opa[k % SLOTS], opw[k % SLOTS], odd);
+    else
+      acc = mfma16(opa[k % SLOTS], opw[k % SLOTS], acc);
+    if (k + AHEAD < COUNT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) acc[r] += odd[r];
 }
 
 // C1 error of this wave's tiles into the staged d1[6][24][24]; the error at S1 is the sum of the two
@@ -169,9 +204,9 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
     // ---- C1 forward + S1 for this wave's tiles ---------------------------------------------------------
     f4 c1[3];
     if (wave < 2)
-      group_c1_forward<3>(s, tab, wave, ln, c1);
+      group_c1_forward<3>(tab.e + TAB_C1A * 64, tab.bias, s.img, s.pool + P_S1, wave, ln, c1);
     else
-      group_c1_forward<2>(s, tab, wave, ln, c1);
+      group_c1_forward<2>(tab.e + TAB_C1A * 64, tab.bias, s.img, s.pool + P_S1, wave, ln, c1);
     table.commit_rest(tab);
     CNN_GROUP_MARK(3);
     __syncthreads();  // (2) S1 and the operand table complete
@@ -179,35 +214,9 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
     // ---- C2 forward for pixel tile mt = wave, S2 (waves 0..3) -----------------------------------------
     f4 c2v = f4{st.bias2, st.bias2, st.bias2, st.bias2};
     if (wave < 4) {
-      const float* a12 = s.pool + P_S1 + pp + 12 * q + 24 * wave;
-      const float* a1 = s.pool + P_S1 + pp + q + 24 * wave;
-      const float* a144 = s.pool + P_S1 + pp + 144 * q + 24 * wave;
-      // operands of step s + AHEAD are read while step s issues: an LDS read takes longer than three
-      // matrix instructions, and with eight waves per image there are registers to spare
-      constexpr int AHEAD = 6, SLOTS = 8;
-      float opa[SLOTS], opw[SLOTS];
-      auto load_step = [&](int sidx, float& oa, float& ow) {
-        const float* base = sidx < 30 ? a12 : sidx < 36 ? a1 : a144;
-        ow = tl[(TAB_BF + sidx) * 64];
-        oa = base[fwd_imm(sidx)];
-      };
+      group_c2_steps<0, 38>(s.pool + P_S1 + pp + 24 * wave, tl + TAB_BF * 64, c2v);
 #pragma unroll
-      for (int sidx = 0; sidx < AHEAD; ++sidx) load_step(sidx, opa[sidx], opw[sidx]);
-      // even and odd K steps in two sums: a matrix instruction waits for the previous one of its own
-      // chain only
-      f4 odd = f4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int sidx = 0; sidx < 38; ++sidx) {
-        if (sidx + AHEAD < 38) load_step(sidx + AHEAD, opa[(sidx + AHEAD) % SLOTS], opw[(sidx + AHEAD) % SLOTS]);
-        if (sidx & 1)
-          odd = mfma16(opa[sidx % SLOTS], opw[sidx % SLOTS], odd);
-        else
-          c2v = mfma16(opa[sidx % SLOTS], opw[sidx % SLOTS], c2v);
-        if (sidx + AHEAD < 38) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) c2v[r] = logistic_of_scaled(c2v[r] + odd[r]);
+      for (int r = 0; r < 4; ++r) c2v[r] = logistic_of_scaled(c2v[r]);
       if (n16 < 12) s.pool[P_S2 + n16 * 16 + 4 * wave + q] = 0.25f * ((c2v[0] + c2v[1]) + (c2v[2] + c2v[3]));
     }
     CNN_GROUP_MARK(4);
@@ -462,6 +471,108 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
   }
   if (t == 0) put_row<COHERENT>(out + LOSS_SLOT, st.loss);
   CNN_GROUP_MARK(10);
+}
+
+// ---- forward pass alone: the same eight waves on one image -------------------------------------------------
+// Here the K steps of C2 are shared too: waves 4..7 take the second half of pixel tile wave - 4's and hand their sums
+// over through LDS (600 clocks of matrix instructions for one barrier).  The latency of one image bounds this kernel:
+// one memory round trip for the image and the operands, then five short phases.
+struct __align__(16) GroupForwardLds {
+  float c1a[C1F_KSTEPS * 64];  // operand entries TAB_C1A ..
+  float e[TAB_FWD_ENTRIES * 64];  // entries TAB_BF .., TAB_FCW ..
+  float bias[TAB_BIAS_FLOATS];
+  float img[NI];
+  float s1[NS1 + 288];  // maps 6, 7: what the padding rows of C1 leave, finite, read by the padded K steps of C2
+  float s2[NS2];
+  f4 half[4 * 64];
+  float y[16];
+};
+
+// yhat of the workgroup's image (`yhat`: its ten outputs in memory, or null) into s.y, complete for the caller after
+// a barrier.  DUMP: the activations of image n too.
+template <bool DUMP>
+__device__ __forceinline__ void group_forward(const float* __restrict__ image, const float* __restrict__ tabg,
+                                              float* __restrict__ yhat, GroupForwardLds& s, const DumpPtrs& dump, size_t n) {
+  const int t = threadIdx.x, wave = t >> 6, l = t & 63, q = l >> 4, n16 = l & 15;
+  const int pp = 12 * ((n16 & 3) >> 1) + 2 * (n16 >> 2) + (n16 & 1);
+  // one 16-byte piece per thread of what C1 needs (its operands, the biases, the image), then the other operands
+  constexpr int OPS = C1F_KSTEPS * 16, BIAS = TAB_BIAS_FLOATS / 4, FROM = 64 * GWAVES - NI / 4;
+  static_assert(OPS + BIAS <= FROM, "one piece per thread");
+  const f4* tg = reinterpret_cast<const f4*>(tabg);
+  const f4 first = *(t < OPS ? tg + TAB_C1A * 16 + t : t < OPS + BIAS ? tg + TABG_BIAS / 4 + (t - OPS)
+                             : t < FROM ? tg : reinterpret_cast<const f4*>(image) + (t - FROM));
+  constexpr int PIECES = TAB_FWD_ENTRIES * 16, ROUNDS = (PIECES + 64 * GWAVES - 1) / (64 * GWAVES);
+  f4 rest[ROUNDS];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) rest[r] = tg[t + 64 * GWAVES * r < PIECES ? t + 64 * GWAVES * r : 0];
+  const C1Lane ln = c1f_lane();
+  if (t < OPS)
+    reinterpret_cast<f4*>(s.c1a)[t] = first;
+  else if (t < OPS + BIAS)
+    reinterpret_cast<f4*>(s.bias)[t - OPS] = first;
+  else if (t >= FROM)
+    reinterpret_cast<f4*>(s.img)[t - FROM] = first;
+  __syncthreads();  // image, C1 operands, biases
+
+  f4 c1[3];
+  if (wave < 2)
+    group_c1_forward<3>(s.c1a, s.bias, s.img, s.s1, wave, ln, c1);
+  else
+    group_c1_forward<2>(s.c1a, s.bias, s.img, s.s1, wave, ln, c1);
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r)
+    if (t + 64 * GWAVES * r < PIECES) reinterpret_cast<f4*>(s.e)[t + 64 * GWAVES * r] = rest[r];
+  if (DUMP && dump.c1 && q < 3) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (wave + 8 * k < C1F_TILES) {
+        float* dst = dump.c1 + n * NC1 + ln.c1 + 2 * q * (576 - D1_MAP) + c1f_tile_c1(wave + 8 * k);
+        *reinterpret_cast<float2*>(dst) = float2{c1[k][0], c1[k][1]};
+        *reinterpret_cast<float2*>(dst + 576) = float2{c1[k][2], c1[k][3]};
+      }
+  }
+  __syncthreads();  // S1, the other operands
+  if (DUMP && dump.s1 && t < NS1 / 4) reinterpret_cast<f4*>(dump.s1 + n * NS1)[t] = reinterpret_cast<const f4*>(s.s1)[t];
+
+  const float bias2 = wave < 4 ? s.bias[n16] : 0.0f;
+  f4 c2v = f4{bias2, bias2, bias2, bias2};
+  const float* s1 = s.s1 + pp + 24 * (wave & 3);
+  if (wave < 4) {
+    group_c2_steps<0, 19>(s1, s.e + TAB_BF * 64 + l, c2v);
+  } else {
+    group_c2_steps<19, 19>(s1, s.e + TAB_BF * 64 + l, c2v);
+    s.half[t - 256] = c2v;
+  }
+  __syncthreads();  // the upper waves' sums
+  if (wave < 4) {
+    const f4 up = s.half[t];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) c2v[r] = logistic_of_scaled(c2v[r] + up[r]);
+    if (n16 < 12) s.s2[n16 * 16 + 4 * wave + q] = 0.25f * ((c2v[0] + c2v[1]) + (c2v[2] + c2v[3]));
+    if (DUMP && dump.c2 && n16 < 12) {  // register r: pixel (2 wave + r / 2, 2 q + r % 2)
+      float* dst = dump.c2 + n * NC2 + n16 * 64 + 16 * wave + 2 * q;
+      *reinterpret_cast<float2*>(dst) = float2{c2v[0], c2v[1]};
+      *reinterpret_cast<float2*>(dst + 8) = float2{c2v[2], c2v[3]};
+    }
+  }
+  __syncthreads();  // S2
+  if (DUMP && dump.s2 && t < NS2 / 4) reinterpret_cast<f4*>(dump.s2 + n * NS2)[t] = reinterpret_cast<const f4*>(s.s2)[t];
+  float sv[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) sv[k] = s.s2[l + 64 * k];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int o = wave + GWAVES * j;  // wave-uniform
+    if (o < NY) {
+      const float* w = s.e + (TAB_FCW + 3 * o) * 64 + l;
+      const float p = fmaf(w[128], sv[2], fmaf(w[64], sv[1], w[0] * sv[0]));
+      const float yo = logistic(wave_sum(p) + s.bias[TAB_BIAS_B + o]);
+      if (l == 0) {
+        s.y[o] = yo;
+        if (yhat) yhat[o] = yo;
+      }
+    }
+  }
 }
 
 }  // namespace cnn
