@@ -11,27 +11,32 @@
 // wave_image); only the index helpers are shared.
 #pragma once
 
-#include "cnn_wave.h"
+#include "cnn_conv_wave.h"
 
 namespace cnn {
 namespace col2im {
 
-constexpr int WAVES_PER_GROUP = 8;
 constexpr int ENTRIES = 18 + 12;   // plain tiles V(0..4), U4 of the maps 0..3; packed tiles PV(0..2), PU
 constexpr int ACC_FLOATS = NS1 + 304;  // d_in[6][12][12] and the second copy of the maps 4, 5 (with its reach)
+template <int WAVES>
 struct __align__(16) Lds {
   float tab[ENTRIES * 64];                    // A operands, [entry = tile * 3 + K step][lane]
-  float acc[WAVES_PER_GROUP][ACC_FLOATS];
+  float acc[WAVES][ACC_FLOATS];
 };
 constexpr int COUT = 12, CIN = 6, OUT_PIXELS = 64, IN_FLOATS = NS1, OUT_FLOATS = COUT * OUT_PIXELS;
 
-__global__ __launch_bounds__(64 * WAVES_PER_GROUP) void conv_bwd_input_kernel(const float* __restrict__ d_out,
-                                                                             const float* __restrict__ k,
-                                                                             float* __restrict__ d_in, int B) {
-  __shared__ Lds lds;
+// PARTS = 2: one wave takes the maps 0..3, its neighbour the maps 4 and 5.
+template <int WAVES, int PARTS>
+__global__ __launch_bounds__(64 * WAVES) void conv_bwd_input_kernel(const float* __restrict__ d_out,
+                                                                    const float* __restrict__ k,
+                                                                    float* __restrict__ d_in, int B) {
+  static_assert(PARTS <= 2, "parts are the plain and the packed maps");
+  __shared__ Lds<WAVES> lds;
+  const Share<WAVES, PARTS> mine;
   const int t = threadIdx.x, wave = t >> 6, l = t & 63, q = l >> 4, n16 = l & 15;
   // ---- A operands: lane (q, n16) of entry (tile, s) holds k[j = 4 s + q][c][tap] of tile row n16 ----
-  for (int i = t; i < ENTRIES * 64; i += 64 * WAVES_PER_GROUP) {
+#pragma unroll 4
+  for (int i = t; i < ENTRIES * 64; i += 64 * WAVES) {
     const int e = i >> 6, lane = i & 63, j = 4 * (e % 3) + (lane >> 4), row = lane & 15;
     int src;  // 25 c + tap, or -1
     if (e < 18) {
@@ -56,11 +61,10 @@ __global__ __launch_bounds__(64 * WAVES_PER_GROUP) void conv_bwd_input_kernel(co
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt) bd[s][nt] = src[4 * s * OUT_PIXELS + 16 * nt];
   };
-  const size_t G = (size_t)gridDim.x * WAVES_PER_GROUP, first = (size_t)blockIdx.x * WAVES_PER_GROUP + wave;
   float bd[3][4], next[3][4];
-  if (first < (size_t)B) load_image(first, bd);
-  for (size_t n = first; n < (size_t)B; n += G) {
-    if (n + G < (size_t)B) load_image(n + G, next);  // in flight during this image
+  if (mine.first < (size_t)B) load_image(mine.first, bd);
+  for (size_t n = mine.first; n < (size_t)B; n += mine.step) {
+    if (n + mine.step < (size_t)B) load_image(n + mine.step, next);  // in flight during this image
     for (int e = l; e < ACC_FLOATS / 4; e += 64) reinterpret_cast<f4*>(acc)[e] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     wave_sync();
     auto tiles = [&](int first_entry, f4 (&out)[4]) {
@@ -109,7 +113,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_GROUP) void conv_bwd_input_kernel(co
     };
     f4 tu[4];
     tiles(18 + kTilePU * 3, tu);
-    {  // maps 0..3: lane quarter q owns map q
+    if (PARTS == 1 || mine.part == 0) {  // maps 0..3: lane quarter q owns map q
       f4 t4[4], tv[4], tn[4];
       tiles(kTileU4 * 3, t4);
       float* tgt = acc + 144 * q + pp;
@@ -127,7 +131,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_GROUP) void conv_bwd_input_kernel(co
         }
       }
     }
-    {  // maps 4, 5: quarters 0, 1 for the tap columns 0..2 into d_in, quarters 2, 3 for 3, 4 into the copy
+    if (PARTS == 1 || mine.part == 1) {  // maps 4, 5: quarters 0, 1 for the tap columns 0..2 into d_in, quarters 2, 3 for 3, 4 into the copy
       float* tgt = q < 2 ? acc + 144 * (4 + q) + pp : copy + 144 * (q - 2) + pp + 3;
       f4 tv[4], tn[4];
       tiles(18 + kTilePV0 * 3, tv);
@@ -144,9 +148,10 @@ __global__ __launch_bounds__(64 * WAVES_PER_GROUP) void conv_bwd_input_kernel(co
         }
       }
     }
-    // ---- d_in of this image: 864 consecutive floats, the two halves of the maps 4, 5 joined ----
+    // ---- d_in of this image (or of this wave's maps): consecutive floats, the two halves of the maps 4, 5 joined ----
     float* dst = d_in + n * IN_FLOATS;
-    for (int e = l; e < IN_FLOATS; e += 64) {
+    const int begin = PARTS == 1 || mine.part == 0 ? 0 : 4 * 144, end = PARTS == 1 || mine.part == 1 ? IN_FLOATS : 4 * 144;
+    for (int e = begin + l; e < end; e += 64) {
       float v = acc[e];
       if (e >= 4 * 144) v += copy[e - 4 * 144];
       dst[e] = v;

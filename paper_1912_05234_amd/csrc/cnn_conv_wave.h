@@ -2,7 +2,11 @@
 // in the GEMM forms of the fused training step (arXiv 1912.05234, Section 3: listings conv / mconv,
 // backweights, backbias).  An image of these layers is small enough for one wave to hold in its LDS,
 // which saves the barriers and the staging for shared groups of images that the general kernels
-// (cnn_igemm.h) pay; eight waves per workgroup, two workgroups per compute unit.
+// (cnn_igemm.h) pay; eight waves per workgroup, two workgroups per compute unit.  A call on few images would be
+// bound by the chain of one image's matrix instructions in one wave (about 2 us; twice that with eight images in a
+// workgroup of two waves per SIMD), so there PARTS waves, each with its own copy of the image, share its pixels:
+// the forward passes by output tiles or bands (results bitwise the same), the weight gradients by the pixels they
+// sum over.  cnn_ops.hip chooses WAVES and PARTS by the number of images and holds what they measured.
 //
 // namespace conv2: six input and twelve output maps, 5 x 5 kernel, 12 x 12 input
 //   forward          M = 64 output pixels in four tiles, N = 12(16) maps, K = 150(152) taps: 152
@@ -10,7 +14,7 @@
 //                    wave's LDS, the weights sit in LDS as the instruction's B operand
 //   weight gradient  M = 12(16) maps, N = 150(160) taps in ten tiles, K = 64 pixels: 160 per image;
 //                    the output error is the A operand straight from global memory, the sums stay
-//                    in registers over all of a wave's images; the eight waves of a workgroup are
+//                    in registers over all of a wave's images; the waves of a workgroup are
 //                    added through LDS in a fixed order and the workgroup writes one set of partial
 //                    tiles in the layout of the general kernel, whose second kernel adds the
 //                    workgroups' partials
@@ -25,9 +29,24 @@
 #include "cnn_wave.h"
 
 namespace cnn {
+
+// PARTS waves share an image: which part this wave takes, its first image and the step to its next one.  The parts of an
+// image are neighbouring waves of one workgroup.
+template <int WAVES, int PARTS>
+struct Share {
+  static_assert(WAVES % PARTS == 0, "an image's parts are waves of one workgroup");
+  int part;
+  size_t first, step;
+  __device__ __forceinline__ Share() {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    part = PARTS == 1 ? 0 : wave % PARTS;
+    first = (size_t)blockIdx.x * (WAVES / PARTS) + wave / PARTS;
+    step = (size_t)gridDim.x * (WAVES / PARTS);
+  }
+};
+
 namespace conv2 {
 
-constexpr int WAVES_PER_GROUP = 8, THREADS = 64 * WAVES_PER_GROUP;
 constexpr int CIN = 6, COUT = 12, TAPS = CIN * 25, IN_FLOATS = NS1, OUT_FLOATS = COUT * 64;
 inline bool shape_fits(int Cin, int H, int W, int Cout, int KH, int KW) {
   return Cin == CIN && Cout == COUT && KH == 5 && KW == 5 && H == 12 && W == 12;
@@ -58,16 +77,23 @@ __device__ __forceinline__ void store_input(float* lds, const Input& x) {
 
 // ---- forward ---------------------------------------------------------------------------------------------
 constexpr int FWD_IN = IN_FLOATS + 288;  // the padded K steps read up to 1152 floats from the start (zero weights)
+template <int WAVES>
 struct __align__(16) FwdLds {
   float tab[38 * 64];  // B operand, [K step][lane]: k[j = lane % 16][fwd_tap(step, lane / 16)]
   float bias[16];
-  float in[WAVES_PER_GROUP][FWD_IN];
+  float in[WAVES][FWD_IN];
 };
-__global__ __launch_bounds__(THREADS) void forward_kernel(const float* __restrict__ in, const float* __restrict__ k,
-                                                          const float* __restrict__ bias, float* __restrict__ out,
-                                                          int B) {
-  __shared__ FwdLds lds;
+template <int WAVES, int PARTS>
+__global__ __launch_bounds__(64 * WAVES) void forward_kernel(const float* __restrict__ in, const float* __restrict__ k,
+                                                             const float* __restrict__ bias, float* __restrict__ out,
+                                                             int B) {
+  constexpr int THREADS = 64 * WAVES, TILES = 4 / PARTS;  // pixel tiles of a wave
+  __shared__ FwdLds<WAVES> lds;
+  const Share<WAVES, PARTS> mine;
+  Input cur;
+  if (mine.first < (size_t)B) cur = load_input(in, mine.first);
   const int t = threadIdx.x, wave = t >> 6, l = t & 63, q = l >> 4, n16 = l & 15;
+#pragma unroll 5
   for (int i = t; i < 38 * 64; i += THREADS) {
     const int lane = i & 63, tap = fwd_tap(i >> 6, lane >> 4), j = lane & 15;
     lds.tab[i] = j < COUT && tap >= 0 ? k[j * TAPS + tap] : 0.0f;
@@ -77,27 +103,24 @@ __global__ __launch_bounds__(THREADS) void forward_kernel(const float* __restric
   for (int e = IN_FLOATS + l; e < FWD_IN; e += 64) x[e] = 0.0f;  // finite filler behind the image
   __syncthreads();
   const float* tl = lds.tab + l;
-  const int pp = 12 * ((n16 & 3) >> 1) + 2 * (n16 >> 2) + (n16 & 1);
+  const int pp = 12 * ((n16 & 3) >> 1) + 2 * (n16 >> 2) + (n16 & 1) + 24 * TILES * mine.part;
   const float* a12 = x + pp + 12 * q;
   const float* a1 = x + pp + q;
   const float* a144 = x + pp + 144 * q;
   const float b2 = lds.bias[n16];
-  const size_t G = (size_t)gridDim.x * WAVES_PER_GROUP, first = (size_t)blockIdx.x * WAVES_PER_GROUP + wave;
-  Input cur;
-  if (first < (size_t)B) cur = load_input(in, first);
-  for (size_t n = first; n < (size_t)B; n += G) {
+  for (size_t n = mine.first; n < (size_t)B; n += mine.step) {
     store_input(x, cur);
     wave_sync();
-    if (n + G < (size_t)B) cur = load_input(in, n + G);  // in flight during this image
-    f4 acc[4];
+    if (n + mine.step < (size_t)B) cur = load_input(in, n + mine.step);  // in flight during this image
+    f4 acc[TILES];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) acc[mt] = f4{b2, b2, b2, b2};
-    float opa[3][4], opw[3];
-    auto load_step = [&](int s, float (&oa)[4], float& ow) {
+    for (int mt = 0; mt < TILES; ++mt) acc[mt] = f4{b2, b2, b2, b2};
+    float opa[3][TILES], opw[3];
+    auto load_step = [&](int s, float (&oa)[TILES], float& ow) {
       const float* base = s < 30 ? a12 : s < 36 ? a1 : a144;
       ow = tl[s * 64];
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) oa[mt] = base[fwd_imm(s) + 24 * mt];
+      for (int mt = 0; mt < TILES; ++mt) oa[mt] = base[fwd_imm(s) + 24 * mt];
     };
     load_step(0, opa[0], opw[0]);
     load_step(1, opa[1], opw[1]);
@@ -105,16 +128,16 @@ __global__ __launch_bounds__(THREADS) void forward_kernel(const float* __restric
     for (int s = 0; s < 38; ++s) {
       if (s + 2 < 38) load_step(s + 2, opa[(s + 2) % 3], opw[(s + 2) % 3]);
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) acc[mt] = mfma16(opa[s % 3][mt], opw[s % 3], acc[mt]);
-      if (s + 2 < 38) __builtin_amdgcn_sched_group_barrier(0x100, 5, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+      for (int mt = 0; mt < TILES; ++mt) acc[mt] = mfma16(opa[s % 3][mt], opw[s % 3], acc[mt]);
+      if (s + 2 < 38) __builtin_amdgcn_sched_group_barrier(0x100, TILES + 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, TILES, 0);
     }
     wave_sync();  // the reads of this image come before the next image's stores
     // register r of tile mt is pixel (y, x) = (2 mt + r / 2, 2 q + r % 2) of map n16: two 8-byte stores per tile
     if (n16 < COUT) {
-      float* dst = out + n * OUT_FLOATS + n16 * 64 + 2 * q;
+      float* dst = out + n * OUT_FLOATS + n16 * 64 + 2 * q + 16 * TILES * mine.part;
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
+      for (int mt = 0; mt < TILES; ++mt) {
         *reinterpret_cast<float2*>(dst + 16 * mt) = float2{acc[mt][0], acc[mt][1]};
         *reinterpret_cast<float2*>(dst + 16 * mt + 8) = float2{acc[mt][2], acc[mt][3]};
       }
@@ -124,18 +147,23 @@ __global__ __launch_bounds__(THREADS) void forward_kernel(const float* __restric
 
 // ---- weight and bias gradient -------------------------------------------------------------------------------
 constexpr int ACC_FLOATS = 10 * 4 * 64;  // a wave's sums: [tile nt][register r][lane]
+template <int WAVES>
 struct __align__(16) WgradLds {
   int k2b[10][64];                           // first s1 cell of tap 16 nt + lane % 16 for pixel quarter lane / 16
-  float x[WAVES_PER_GROUP][IN_FLOATS];
-  float comb[WAVES_PER_GROUP / 2][ACC_FLOATS];  // cross-wave sums
-  float bsum[WAVES_PER_GROUP][64];
+  float x[WAVES][IN_FLOATS];
+  float comb[WAVES / 2][ACC_FLOATS];  // cross-wave sums
+  float bsum[WAVES][64];
 };
 // part: [gridDim.x][10 tiles][16 rows j][16 columns] then the bias rows [gridDim.x][16] (the layout
 // igemm::wgrad_reduce_kernel reads with MT = 1, NT = 10, P = 1).
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4, 4))) void bwd_weight_kernel(const float* __restrict__ in,
+template <int WAVES, int PARTS>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 4))) void bwd_weight_kernel(const float* __restrict__ in,
                                                              const float* __restrict__ d_out,
                                                              float* __restrict__ part, int B) {
-  __shared__ WgradLds lds;
+  constexpr int THREADS = 64 * WAVES, QUARTERS = 4 / PARTS;  // groups of sixteen pixels that a wave sums over
+  static_assert((WAVES & (WAVES - 1)) == 0, "the waves' sums are added in halves");
+  __shared__ WgradLds<WAVES> lds;
+  const Share<WAVES, PARTS> mine;
   const int t = threadIdx.x, wave = t >> 6, l = t & 63, q = l >> 4, n16 = l & 15;
   for (int e = t; e < 640; e += THREADS) {
     const int nt = e >> 6, lane = e & 63, tap = 16 * nt + (lane & 15);
@@ -146,14 +174,14 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
   float* x = lds.x[wave];
   const float* bsrc[10];
 #pragma unroll
-  for (int nt = 0; nt < 10; ++nt) bsrc[nt] = x + lds.k2b[nt][l];
+  for (int nt = 0; nt < 10; ++nt) bsrc[nt] = x + lds.k2b[nt][l] + 24 * QUARTERS * mine.part;
   // A operand: lane (q, n16) holds d_out[map n16][pixel 16 S + 4 q + r] = (y, x) = (2 S + r / 2, 2 q + r % 2);
   // the lanes of the padding rows 12..15 read map 11 (their result rows are never stored)
-  const int lane_src = (n16 < COUT ? n16 : COUT - 1) * 64 + 2 * q;
-  auto load_error = [&](size_t n, f4 (&d)[4]) {
+  const int lane_src = (n16 < COUT ? n16 : COUT - 1) * 64 + 2 * q + 16 * QUARTERS * mine.part;
+  auto load_error = [&](size_t n, f4 (&d)[QUARTERS]) {
     const float* src = d_out + n * OUT_FLOATS + lane_src;
 #pragma unroll
-    for (int S = 0; S < 4; ++S) {
+    for (int S = 0; S < QUARTERS; ++S) {
       const float2 lo = *reinterpret_cast<const float2*>(src + 16 * S), hi = *reinterpret_cast<const float2*>(src + 16 * S + 8);
       d[S] = f4{lo.x, lo.y, hi.x, hi.y};
     }
@@ -162,22 +190,21 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 #pragma unroll
   for (int nt = 0; nt < 10; ++nt) acc[nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
   float g_b = 0.0f;
-  const size_t G = (size_t)gridDim.x * WAVES_PER_GROUP, first = (size_t)blockIdx.x * WAVES_PER_GROUP + wave;
   Input cur;
-  f4 d[4], dn[4];
-  if (first < (size_t)B) {
-    cur = load_input(in, first);
-    load_error(first, d);
+  f4 d[QUARTERS], dn[QUARTERS];
+  if (mine.first < (size_t)B) {
+    cur = load_input(in, mine.first);
+    load_error(mine.first, d);
   }
-  for (size_t n = first; n < (size_t)B; n += G) {
+  for (size_t n = mine.first; n < (size_t)B; n += mine.step) {
     store_input(x, cur);
     wave_sync();
-    if (n + G < (size_t)B) {  // in flight during this image
-      cur = load_input(in, n + G);
-      load_error(n + G, dn);
+    if (n + mine.step < (size_t)B) {  // in flight during this image
+      cur = load_input(in, n + mine.step);
+      load_error(n + mine.step, dn);
     }
 #pragma unroll
-    for (int S = 0; S < 4; ++S) g_b += (d[S][0] + d[S][1]) + (d[S][2] + d[S][3]);
+    for (int S = 0; S < QUARTERS; ++S) g_b += (d[S][0] + d[S][1]) + (d[S][2] + d[S][3]);
     float bv[2][10];
     auto load_step = [&](int step, float (&o)[10]) {
       const int S = step >> 2, r = step & 3, imm = 24 * S + 12 * (r >> 1) + (r & 1);
@@ -186,21 +213,21 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
     };
     load_step(0, bv[0]);
 #pragma unroll
-    for (int step = 0; step < 16; ++step) {
-      if (step < 15) load_step(step + 1, bv[(step + 1) & 1]);
+    for (int step = 0; step < 4 * QUARTERS; ++step) {
+      if (step + 1 < 4 * QUARTERS) load_step(step + 1, bv[(step + 1) & 1]);
 #pragma unroll
       for (int nt = 0; nt < 10; ++nt) acc[nt] = mfma16(d[step >> 2][step & 3], bv[step & 1][nt], acc[nt]);
-      if (step < 15) __builtin_amdgcn_sched_group_barrier(0x100, 10, 0);
+      if (step + 1 < 4 * QUARTERS) __builtin_amdgcn_sched_group_barrier(0x100, 10, 0);
       __builtin_amdgcn_sched_group_barrier(0x008, 10, 0);
     }
     wave_sync();  // the reads of this image come before the next image's stores
 #pragma unroll
-    for (int S = 0; S < 4; ++S) d[S] = dn[S];
+    for (int S = 0; S < QUARTERS; ++S) d[S] = dn[S];
   }
-  // ---- the eight waves' sums in a fixed order: (w, w + 4), then (w, w + 2), then (0, 1) ----
+  // ---- the waves' sums in a fixed order, the upper half to the lower: (w, w + 4), then (w, w + 2), then (0, 1) ----
   lds.bsum[wave][l] = g_b;
 #pragma unroll
-  for (int half = WAVES_PER_GROUP / 2; half >= 1; half >>= 1) {
+  for (int half = WAVES / 2; half >= 1; half >>= 1) {
     __syncthreads();
     if (wave >= half && wave < 2 * half) {
       float* dst = lds.comb[wave - half];
@@ -225,10 +252,10 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 #pragma unroll
       for (int r = 0; r < 4; ++r) tile[nt * 256 + (4 * q + r) * 16 + n16] = acc[nt][r];  // row j = 4 q + r, column n16
   } else if (wave == 1 && l < 16) {
-    // bias gradient of map l: the four lane quarters of the eight waves, in wave order
+    // bias gradient of map l: the four lane quarters of the waves, in wave order
     float s = 0.0f;
     if (l < COUT)
-      for (int w = 0; w < WAVES_PER_GROUP; ++w) s += (lds.bsum[w][l] + lds.bsum[w][l + 16]) + (lds.bsum[w][l + 32] + lds.bsum[w][l + 48]);
+      for (int w = 0; w < WAVES; ++w) s += (lds.bsum[w][l] + lds.bsum[w][l + 16]) + (lds.bsum[w][l + 32] + lds.bsum[w][l + 48]);
     part[(size_t)gridDim.x * 10 * 256 + (size_t)blockIdx.x * 16 + l] = s;
   }
 }
@@ -246,25 +273,31 @@ inline size_t bwd_weight_workspace_bytes(unsigned groups) { return sizeof(float)
 // last-level cache).
 namespace conv1 {
 
-constexpr int WAVES_PER_GROUP = 8, THREADS = 64 * WAVES_PER_GROUP;
 inline bool shape_fits(int Cin, int H, int W, int Cout, int KH, int KW) {
   return Cin == 1 && Cout == 6 && KH == 5 && KW == 5 && H == 28 && W == 28;
 }
 constexpr int BAND = 6 * 4 * 24;  // one band of the output: six maps, four rows
+template <int WAVES>
 struct __align__(16) FwdLds {
   float wa[C1F_KSTEPS * 64];  // A operand, [K step][lane]
   float bias[8];
-  float img[WAVES_PER_GROUP][NI];
-  float band[WAVES_PER_GROUP][BAND];
+  float img[WAVES][NI];
+  float band[WAVES][BAND];
 };
-__global__ __launch_bounds__(THREADS) void forward_kernel(const float* __restrict__ in, const float* __restrict__ k,
-                                                          const float* __restrict__ bias, float* __restrict__ out,
-                                                          int B) {
-  __shared__ FwdLds lds;
+template <int WAVES, int PARTS>
+__global__ __launch_bounds__(64 * WAVES) void forward_kernel(const float* __restrict__ in, const float* __restrict__ k,
+                                                             const float* __restrict__ bias, float* __restrict__ out,
+                                                             int B) {
+  constexpr int BANDS = 6 / PARTS;  // bands of a wave
+  __shared__ FwdLds<WAVES> lds;
+  const Share<WAVES, PARTS> mine;
+  Pixels px;
+  if (mine.first < (size_t)B) px = load_pixels(in + mine.first * NI);
   const int t = threadIdx.x, wave = t >> 6, l = t & 63, q = l >> 4, n16 = l & 15;
-  if (t < C1F_KSTEPS * 64) {
-    const int src = c1f_weight(t >> 6, t & 63);  // index into the flat parameter vector, k1 first
-    lds.wa[t] = src >= 0 ? k[src - OFF_K1] : 0.0f;
+#pragma unroll
+  for (int i = t; i < C1F_KSTEPS * 64; i += 64 * WAVES) {
+    const int src = c1f_weight(i >> 6, i & 63);  // index into the flat parameter vector, k1 first
+    lds.wa[i] = src >= 0 ? k[src - OFF_K1] : 0.0f;
   }
   if (t < 8) lds.bias[t] = bias && t < 6 ? bias[t] : 0.0f;
   __syncthreads();
@@ -278,16 +311,14 @@ __global__ __launch_bounds__(THREADS) void forward_kernel(const float* __restric
   const int lane_band = 2 * q * 96 + (((n16 >> 1) & 1) * 2 + (n16 & 1)) * 24 + 2 * (n16 >> 2);
   float* img = lds.img[wave];
   float* band = lds.band[wave];
-  const size_t G = (size_t)gridDim.x * WAVES_PER_GROUP, first = (size_t)blockIdx.x * WAVES_PER_GROUP + wave;
-  Pixels px;
-  if (first < (size_t)B) px = load_pixels(in + first * NI);
-  for (size_t n = first; n < (size_t)B; n += G) {
+  for (size_t n = mine.first; n < (size_t)B; n += mine.step) {
     store_pixels(img, px);
     wave_sync();
-    if (n + G < (size_t)B) px = load_pixels(in + (n + G) * NI);  // in flight during this image
+    if (n + mine.step < (size_t)B) px = load_pixels(in + (n + mine.step) * NI);  // in flight during this image
     float* dst = out + n * NC1;
 #pragma unroll
-    for (int ty = 0; ty < 6; ++ty) {
+    for (int i0 = 0; i0 < BANDS; ++i0) {
+      const int ty = BANDS * mine.part + i0;
       f4 d0, d1, d2;
       c1f_gemm_pair(wa, ln, img + c1f_tile_img(3 * ty), img + c1f_tile_img(3 * ty + 1), binit, d0, d1);
       c1f_gemm_one(wa, ln, img + c1f_tile_img(3 * ty + 2), binit, d2);
@@ -322,14 +353,15 @@ __global__ __launch_bounds__(THREADS) void forward_kernel(const float* __restric
 // instructions per image.  The output error (13.8 KB per image, the bulk of what the operation
 // reads) comes in three chunks of eight rows, d1c[6][8][24] with the maps D1C_MAP apart, the next
 // chunk in registers while the current one is multiplied.  The sums stay in registers over all of
-// a wave's images; the workgroup's eight waves are added in a fixed order and one set of partial
+// a wave's images; the workgroup's waves are added in a fixed order and one set of partial
 // tiles goes to the workspace in the general kernel's layout for P = 2 (rows 2 m + sh, columns
 // 6 u + v'; bias rows 2 m + sh), which its second kernel joins and adds.
 constexpr int CHUNK_PIECES = 6 * 8 * 24 / 4;  // 16-byte pieces of an error chunk
+template <int WAVES>
 struct __align__(16) WgradLds {
   float ones[C1G_ONES];
-  float img[WAVES_PER_GROUP][NI];
-  float d1c[WAVES_PER_GROUP][6 * D1C_MAP + 8];  // after the last image: the wave's sums, [8 registers][64 lanes]
+  float img[WAVES][NI];
+  float d1c[WAVES][6 * D1C_MAP + 8];  // after the last image: the wave's sums, [8 registers][64 lanes]
 };
 static_assert(6 * D1C_MAP + 8 >= 8 * 64, "a wave's chunk area holds its sums");
 struct Chunk {
@@ -353,53 +385,55 @@ __device__ __forceinline__ void store_chunk(float* d1c, const Chunk& c) {
     if (e < CHUNK_PIECES) *reinterpret_cast<f4*>(d1c + m * D1C_MAP + 4 * piece) = c.v[i];
   }
 }
-__global__ __launch_bounds__(THREADS) void bwd_weight_kernel(const float* __restrict__ in,
-                                                             const float* __restrict__ d_out,
-                                                             float* __restrict__ part, int B) {
-  __shared__ WgradLds lds;
+template <int WAVES, int PARTS>
+__global__ __launch_bounds__(64 * WAVES) void bwd_weight_kernel(const float* __restrict__ in,
+                                                                const float* __restrict__ d_out,
+                                                                float* __restrict__ part, int B) {
+  constexpr int THREADS = 64 * WAVES, CHUNKS = 3 / PARTS;  // error chunks of a wave
+  __shared__ WgradLds<WAVES> lds;
+  const Share<WAVES, PARTS> mine;
+  const int gp0 = CHUNKS * mine.part;
   const int t = threadIdx.x, wave = t >> 6, l = t & 63, q = l >> 4, n16 = l & 15;
   for (int e = t; e < C1G_ONES; e += THREADS) lds.ones[e] = 1.0f;
   __syncthreads();
   float* img = lds.img[wave];
   float* d1c = lds.d1c[wave];
   f4 acc[2] = {f4{0.0f, 0.0f, 0.0f, 0.0f}, f4{0.0f, 0.0f, 0.0f, 0.0f}};
-  const size_t G = (size_t)gridDim.x * WAVES_PER_GROUP, first = (size_t)blockIdx.x * WAVES_PER_GROUP + wave;
   Pixels px;
   Chunk ch;
-  if (first < (size_t)B) {
-    px = load_pixels(in + first * NI);
-    ch = load_chunk(d_out, first, 0);
+  if (mine.first < (size_t)B) {
+    px = load_pixels(in + mine.first * NI);
+    ch = load_chunk(d_out, mine.first, gp0);
   }
-  for (size_t n = first; n < (size_t)B; n += G) {
+  for (size_t n = mine.first; n < (size_t)B; n += mine.step) {
     store_pixels(img, px);
-    const bool more = n + G < (size_t)B;
-    if (more) px = load_pixels(in + (n + G) * NI);  // in flight during this image
+    const bool more = n + mine.step < (size_t)B;
+    if (more) px = load_pixels(in + (n + mine.step) * NI);  // in flight during this image
 #pragma unroll
-    for (int gp = 0; gp < 3; ++gp) {
+    for (int i = 0; i < CHUNKS; ++i) {
       store_chunk(d1c, ch);
       wave_sync();
       // the next chunk (of this image, or the first of the next image) is in flight during the GEMM
-      if (gp < 2)
-        ch = load_chunk(d_out, n, gp + 1);
+      if (i + 1 < CHUNKS)
+        ch = load_chunk(d_out, n, gp0 + i + 1);
       else if (more)
-        ch = load_chunk(d_out, n + G, 0);
-      c1g_accumulate<C1G_STEPS / 3, D1C_MAP>(acc, d1c, img + 8 * 28 * gp, l, lds.ones);
+        ch = load_chunk(d_out, n + mine.step, gp0);
+      c1g_accumulate<C1G_STEPS / 3, D1C_MAP>(acc, d1c, img + 8 * 28 * (gp0 + i), l, lds.ones);
       wave_sync();  // the reads of this chunk come before the next chunk's (and image's) stores
     }
   }
-  // ---- the eight waves' sums in wave order; T[row i = 4 q + r][column 16 nt + n16] ----
-  float* mine = lds.d1c[wave];
+  // ---- the waves' sums in wave order; T[row i = 4 q + r][column 16 nt + n16] ----
 #pragma unroll
   for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) mine[(4 * nt + r) * 64 + l] = acc[nt][r];
+    for (int r = 0; r < 4; ++r) d1c[(4 * nt + r) * 64 + l] = acc[nt][r];
   __syncthreads();
   if (wave < 2) {  // wave nt adds and stores tile nt
     float* tile = part + ((size_t)blockIdx.x * 2 + wave) * 256;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       float sum = 0.0f;
-      for (int w = 0; w < WAVES_PER_GROUP; ++w) sum += lds.d1c[w][(4 * wave + r) * 64 + l];
+      for (int w = 0; w < WAVES; ++w) sum += lds.d1c[w][(4 * wave + r) * 64 + l];
       tile[(4 * q + r) * 16 + n16] = sum;
       // column 30 (tile 1, n16 = 14) holds the sums of the error by (map, x parity): the bias rows
       if (wave == 1 && n16 == 14) part[(size_t)gridDim.x * 2 * 256 + (size_t)blockIdx.x * 16 + 4 * q + r] = sum;
@@ -421,6 +455,7 @@ inline size_t bwd_weight_workspace_bytes(unsigned groups) { return sizeof(float)
 // the 24 values: the zeros of the next row are the right border, so no column is tested; a row
 // above or below the map is replaced by one row of zeros (chosen per lane and kernel row when the
 // kernel starts).
+constexpr int WAVES_PER_GROUP = 8, THREADS = 64 * WAVES_PER_GROUP;
 constexpr int BI_STRIDE = 28, BI_MAP = 24 * BI_STRIDE, BI_ZERO = 6 * BI_MAP, BI_FLOATS = BI_ZERO + 32;
 constexpr int BI_KPAD = 28;                  // a map's 25 weights as seven 16-byte pieces
 constexpr int BI_PIECES = 6 * 24 * 24 / 4;  // 16-byte pieces of an image's error

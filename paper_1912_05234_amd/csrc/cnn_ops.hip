@@ -651,6 +651,74 @@ int launch_tile_wgrad(TileWgradPlan& p, const float* in, const float* d_out, flo
   return launch_reduce_rows(part, G, p.a.RS, nk, d_k, d_bias, st);
 }
 
+// ---- the network's own layers: how many waves share an image (cnn_conv_wave.h, cnn_col2im.h) -----------------
+// One wave per image leaves the machine idle while there are fewer images than SIMDs (1024): a call then takes as long as
+// one image does in one wave, next to seven others of its workgroup.  Up to SPLIT_IMAGES the image's pixels (input
+// gradient: its maps) are shared out among waves, in workgroups of fewer images, as long as all of them are
+// resident at once; beyond, the copies of the image and of the operand tables cost more than the shorter chain gives.
+// Kernel times, us, one wave per image -> as below (weight gradients: + 0 .. 2 us of the second kernel, which adds more rows):
+//   images            10              100             250             500             800             2000 (split, not taken)
+//   C1 forward        7.5 -> 3.9      8.5 -> 4.0      8.8 -> 4.2      8.9 -> 5.4      9.3 -> 7.0      10.2 -> 11.1
+//   C2 forward        7.4 -> 4.6      8.1 -> 4.7      8.3 -> 4.9      8.7 -> 5.4      8.9 -> 7.0      10.3 -> 10.6
+//   C2 input gr.      8.1 -> 6.4      8.4 -> 6.5      8.6 -> 6.6      8.8 -> 6.9      9.0 -> 8.0       9.7 -> 12.6
+//   C1 weight gr.     6.9 -> 3.7      8.0 -> 3.7      8.2 -> 3.8      9.1 -> 5.8      9.3 -> 6.4      10.2 + 5.8 -> 9.7 + 7.6
+//   C2 weight gr.     8.7 -> 4.9     10.6 -> 5.1     10.6 -> 5.4     11.0 -> 7.1     10.5 -> 8.2      11.6 + 5.8 -> 11.8 + 7.6
+// FEW_IMAGES: one workgroup per compute unit at one image each; above, the finest split of C1 forward has two (5.7 us
+// at 500 images where two waves per image take 5.4), and the second kernel of the weight gradients has as many
+// rows to add as there are workgroups (C2 at 500 images: 6.4 + 5.4 us with two waves per image, 7.1 + 3.9 with one).
+constexpr int FEW_IMAGES = NUM_CU, SPLIT_IMAGES = 4 * NUM_CU;
+
+// The grid of a kernel whose workgroups take `images` images per round: at most two workgroups per compute unit.
+inline unsigned image_groups(int B, int images) {
+  const long long g = ceil_div(B, images);
+  return (unsigned)(g < 2 * NUM_CU ? g : 2 * NUM_CU);
+}
+
+void launch_conv1_fwd(const float* in, const float* k, const float* bias, float* out, int B, hipStream_t st) {
+  if (B <= FEW_IMAGES)
+    conv1::forward_kernel<6, 6><<<image_groups(B, 1), 64 * 6, 0, st>>>(in, k, bias, out, B);
+  else if (B <= SPLIT_IMAGES)
+    conv1::forward_kernel<4, 2><<<image_groups(B, 2), 64 * 4, 0, st>>>(in, k, bias, out, B);
+  else
+    conv1::forward_kernel<8, 1><<<image_groups(B, 8), 64 * 8, 0, st>>>(in, k, bias, out, B);
+}
+
+void launch_conv2_fwd(const float* in, const float* k, const float* bias, float* out, int B, hipStream_t st) {
+  // (beyond: two workgroups per compute unit; one, three or four measured the same, the kernel is bound by its matrix instructions)
+  if (B <= SPLIT_IMAGES)
+    conv2::forward_kernel<8, 4><<<image_groups(B, 2), 64 * 8, 0, st>>>(in, k, bias, out, B);
+  else
+    conv2::forward_kernel<8, 1><<<image_groups(B, 8), 64 * 8, 0, st>>>(in, k, bias, out, B);
+}
+
+void launch_conv2_bwd_input(const float* d_out, const float* k, float* d_in, int B, hipStream_t st) {
+  // col2im form, 120 instead of 414 matrix instructions per image; beyond: 112 registers per lane, four waves per SIMD
+  if (B <= SPLIT_IMAGES)
+    col2im::conv_bwd_input_kernel<4, 2><<<image_groups(B, 2), 64 * 4, 0, st>>>(d_out, k, d_in, B);
+  else
+    col2im::conv_bwd_input_kernel<8, 1><<<image_groups(B, 8), 64 * 8, 0, st>>>(d_out, k, d_in, B);
+}
+
+// Images per round of a workgroup of the weight gradients launched below.
+inline int conv1_wgrad_images(int B) { return B <= FEW_IMAGES ? 1 : B <= SPLIT_IMAGES ? 4 : 8; }
+inline int conv2_wgrad_images(int B) { return B <= FEW_IMAGES ? 2 : B <= SPLIT_IMAGES ? 4 : 8; }
+
+void launch_conv1_wgrad(const float* in, const float* d_out, float* part, int B, unsigned gx, hipStream_t st) {
+  switch (conv1_wgrad_images(B)) {
+    case 1: conv1::bwd_weight_kernel<3, 3><<<gx, 64 * 3, 0, st>>>(in, d_out, part, B); break;
+    case 4: conv1::bwd_weight_kernel<4, 1><<<gx, 64 * 4, 0, st>>>(in, d_out, part, B); break;
+    default: conv1::bwd_weight_kernel<8, 1><<<gx, 64 * 8, 0, st>>>(in, d_out, part, B); break;
+  }
+}
+
+void launch_conv2_wgrad(const float* in, const float* d_out, float* part, int B, unsigned gx, hipStream_t st) {
+  switch (conv2_wgrad_images(B)) {
+    case 2: conv2::bwd_weight_kernel<4, 2><<<gx, 64 * 4, 0, st>>>(in, d_out, part, B); break;
+    case 4: conv2::bwd_weight_kernel<4, 1><<<gx, 64 * 4, 0, st>>>(in, d_out, part, B); break;
+    default: conv2::bwd_weight_kernel<8, 1><<<gx, 64 * 8, 0, st>>>(in, d_out, part, B); break;
+  }
+}
+
 struct WgradPlan {
   // which kernel: cnn_tile.h by the plan in `tile`, or one of the network's own layers (gx workgroups that leave partial
   // 16 x 16 tiles, MT x NT of them with P shifts, for igemm::wgrad_reduce_kernel)
@@ -658,37 +726,46 @@ struct WgradPlan {
   TileWgradPlan tile;
   int P = 1, MT = 1, NT = 0;
   unsigned gx = 0;
-  size_t workspace_bytes = 0;
+  size_t workspace_bytes = 0;  // what the plan uses
+  size_t least_bytes = 0;      // what it can run with
 };
 
 WgradPlan plan_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
   WgradPlan p;
-  auto groups = [&](int images) {  // workgroups that take `images` images per round, at most two per compute unit
-    const unsigned g = (unsigned)ceil_div(B, images);
-    return g < 2u * NUM_CU ? g : 2u * NUM_CU;
-  };
   if (conv1::shape_fits(Cin, H, W, Cout, KH, KW)) {
     p.kernel = WgradPlan::CONV1;
     p.P = 2, p.NT = 2;  // rows (map, x parity), columns the shifted taps: what the second kernel joins
-    p.gx = groups(conv1::WAVES_PER_GROUP);
+    p.gx = image_groups(B, conv1_wgrad_images(B));
     p.workspace_bytes = conv1::bwd_weight_workspace_bytes(p.gx);
+    p.least_bytes = conv1::bwd_weight_workspace_bytes(image_groups(B, 8));
   } else if (H == 1 && W == 1 && KH == 1 && KW == 1 && fc::shape_fits(Cin, Cout)) {
     p.kernel = WgradPlan::FC;
     p.NT = fc::NT;
-    p.gx = groups(4 * fc::AHEAD * fc::WGRAD_WAVES);  // a wave takes fc::AHEAD steps of four images per memory round trip
-    p.workspace_bytes = fc::bwd_weight_workspace_bytes(p.gx);
+    p.gx = image_groups(B, 4 * fc::AHEAD * fc::WGRAD_WAVES);  // a wave takes fc::AHEAD steps of four images per memory round trip
+    p.workspace_bytes = p.least_bytes = fc::bwd_weight_workspace_bytes(p.gx);
   } else if (conv2::shape_fits(Cin, H, W, Cout, KH, KW)) {
     p.kernel = WgradPlan::CONV2;
     p.NT = 10;
-    p.gx = groups(conv2::WAVES_PER_GROUP);
+    p.gx = image_groups(B, conv2_wgrad_images(B));
     p.workspace_bytes = conv2::bwd_weight_workspace_bytes(p.gx);
+    p.least_bytes = conv2::bwd_weight_workspace_bytes(image_groups(B, 8));
   } else {
     p.tile = plan_tile_wgrad(B, Cin, H, W, Cout, KH, KW);
     if (p.tile.nt) p.kernel = WgradPlan::TILED;
     p.workspace_bytes = p.tile.workspace_bytes;
     if (p.tile.nt && p.tile.interface_bytes > p.workspace_bytes) p.workspace_bytes = p.tile.interface_bytes;
+    p.least_bytes = p.workspace_bytes;
   }
   return p;
+}
+
+// Fits the plan to the caller's workspace; false: it cannot run in it.  (The network's own layers have asked for the
+// rows of workgroups of eight images before they were split; with a workspace of that size they run in as many workgroups
+// as it has rows for.)
+bool fit_wgrad(WgradPlan& p, size_t bytes) {
+  if (p.kernel == WgradPlan::PLAIN || bytes < p.least_bytes) return false;
+  if (bytes < p.workspace_bytes) p.gx = (unsigned)(bytes / (p.workspace_bytes / p.gx));
+  return true;
 }
 
 // ---- reduced precision: the image-tiled kernels with bf16 operands (cnn_tile_bf16.h) -----------------------
@@ -943,8 +1020,8 @@ int launch_wgrad(WgradPlan& p, const float* in, const float* d_out, float* d_k, 
   switch (p.kernel) {
     case WgradPlan::TILED: return launch_tile_wgrad<false>(p.tile, in, d_out, d_k, d_bias, part, st);
     case WgradPlan::FC: fc::bwd_weight_kernel<<<p.gx, fc::WGRAD_THREADS, 0, st>>>(in, d_out, part, B); break;
-    case WgradPlan::CONV1: conv1::bwd_weight_kernel<<<p.gx, conv1::THREADS, 0, st>>>(in, d_out, part, B); break;
-    case WgradPlan::CONV2: conv2::bwd_weight_kernel<<<p.gx, conv2::THREADS, 0, st>>>(in, d_out, part, B); break;
+    case WgradPlan::CONV1: launch_conv1_wgrad(in, d_out, part, B, p.gx, st); break;
+    case WgradPlan::CONV2: launch_conv2_wgrad(in, d_out, part, B, p.gx, st); break;
     default: return CNN_EINVAL;
   }
   const size_t outputs = (size_t)Cout * Cin * KH * KW + Cout;
@@ -1003,17 +1080,12 @@ int cnn_conv_fwd(const float* in, const float* k, const float* bias, float* out,
                  int W, int Cout, int KH, int KW, void* hip_stream) {
   if (!in || !k || !out || !conv_args_ok(B, Cin, H, W, Cout, KH, KW)) return CNN_EINVAL;
   if (!aligned16(in) || !aligned16(k) || !aligned16(out) || (bias && !aligned16(bias))) return CNN_EINVAL;
-  if (conv1::shape_fits(Cin, H, W, Cout, KH, KW)) {  // the network's first convolution: one wave per image
-    const int groups = (B + conv1::WAVES_PER_GROUP - 1) / conv1::WAVES_PER_GROUP, resident = 2 * NUM_CU;
-    conv1::forward_kernel<<<groups < resident ? groups : resident, conv1::THREADS, 0, (hipStream_t)hip_stream>>>(
-        in, k, bias, out, B);
+  if (conv1::shape_fits(Cin, H, W, Cout, KH, KW)) {  // the network's first convolution
+    launch_conv1_fwd(in, k, bias, out, B, (hipStream_t)hip_stream);
     return launched();
   }
-  if (conv2::shape_fits(Cin, H, W, Cout, KH, KW)) {  // the network's second convolution: one wave per image
-    // (two workgroups per compute unit; one, three or four measured the same: the kernel is bound by its matrix instructions)
-    const int groups = (B + conv2::WAVES_PER_GROUP - 1) / conv2::WAVES_PER_GROUP, resident = 2 * NUM_CU;
-    conv2::forward_kernel<<<groups < resident ? groups : resident, conv2::THREADS, 0, (hipStream_t)hip_stream>>>(
-        in, k, bias, out, B);
+  if (conv2::shape_fits(Cin, H, W, Cout, KH, KW)) {  // the network's second convolution
+    launch_conv2_fwd(in, k, bias, out, B, (hipStream_t)hip_stream);
     return launched();
   }
   const TileConvPlan p = plan_tile_conv(in, k, bias, out, B, Cout, Cin, H, W, KH, KW, H - KH + 1, W - KW + 1, 0, 0, 0);
@@ -1028,12 +1100,8 @@ int cnn_conv_bwd_input(const float* d_out, const float* k, float* d_in, int B, i
                        int Cout, int KH, int KW, void* hip_stream) {
   if (!d_out || !k || !d_in || !conv_args_ok(B, Cin, H, W, Cout, KH, KW)) return CNN_EINVAL;
   if (!aligned16(d_out) || !aligned16(k) || !aligned16(d_in)) return CNN_EINVAL;
-  if (col2im::shape_fits(Cin, H, W, Cout, KH, KW)) {
-    // the shape of the network's second convolution: col2im form, 120 instead of 414 matrix instructions per image
-    const int groups = (B + col2im::WAVES_PER_GROUP - 1) / col2im::WAVES_PER_GROUP;
-    const int resident = 2 * NUM_CU;  // 112 registers per lane: four waves per SIMD, two workgroups per compute unit
-    col2im::conv_bwd_input_kernel<<<groups < resident ? groups : resident, 64 * col2im::WAVES_PER_GROUP, 0,
-                                    (hipStream_t)hip_stream>>>(d_out, k, d_in, B);
+  if (col2im::shape_fits(Cin, H, W, Cout, KH, KW)) {  // the network's second convolution
+    launch_conv2_bwd_input(d_out, k, d_in, B, (hipStream_t)hip_stream);
     return launched();
   }
   if (conv1::shape_fits(Cin, H, W, Cout, KH, KW)) {
@@ -1108,7 +1176,7 @@ int cnn_conv_bwd_weight(const float* in, const float* d_out, float* d_k, float* 
   if (!wgrad_args_ok(in, d_out, d_k, d_bias, B, Cin, H, W, Cout, KH, KW)) return CNN_EINVAL;
   if (workspace && !aligned16(workspace)) return CNN_EINVAL;
   WgradPlan p = plan_wgrad(B, Cin, H, W, Cout, KH, KW);
-  if (p.kernel != WgradPlan::PLAIN && (p.workspace_bytes == 0 || (workspace && workspace_bytes >= p.workspace_bytes)))
+  if (fit_wgrad(p, workspace ? workspace_bytes : 0))
     return launch_wgrad(p, in, d_out, d_k, d_bias, B, Cin, Cout, KH, KW, static_cast<float*>(workspace), (hipStream_t)hip_stream);
   return launch_wgrad_plain(in, d_out, d_k, d_bias, B, Cin, H, W, Cout, KH, KW, (hipStream_t)hip_stream);
 }
@@ -1211,7 +1279,7 @@ int cnn_fc_bwd_weight(const float* in, const float* d_out, float* d_w, float* d_
     return CNN_EINVAL;
   if (workspace && !aligned16(workspace)) return CNN_EINVAL;
   WgradPlan p = plan_wgrad(B, I, 1, 1, O, 1, 1);
-  if (p.kernel != WgradPlan::PLAIN && (p.workspace_bytes == 0 || (workspace && workspace_bytes >= p.workspace_bytes)))
+  if (fit_wgrad(p, workspace ? workspace_bytes : 0))
     return launch_wgrad(p, in, d_out, d_w, d_bias, B, I, O, 1, 1, static_cast<float*>(workspace), (hipStream_t)hip_stream);
   const unsigned blocks = (unsigned)(O * I + (d_bias ? O : 0));
   fc_bwd_weight_kernel<<<blocks, TPB, 0, (hipStream_t)hip_stream>>>(in, d_out, d_w, d_bias, B, I, O);
