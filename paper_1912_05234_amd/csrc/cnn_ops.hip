@@ -332,15 +332,16 @@ int tile_columns(int units, int gy, int res) {
 void tile_constants(tile::ConvArgs& a) {
   a.inv_p = 1.0f / a.P, a.inv_khkwp = 1.0f / (float)(a.KH * a.KWP), a.inv_kwp = 1.0f / (float)a.KWP;
   a.inv_cols = 1.0f / (float)(a.TH * a.TXC), a.inv_txc = 1.0f / (float)a.TXC, a.inv_lw = 1.0f / (float)a.LW;
-  a.inv_kp = 1.0f / (float)(16 * a.NBK);
+  a.inv_khkw = 1.0f / (float)(a.KH * a.KW), a.inv_kw = 1.0f / (float)a.KW, a.inv_cc = 1.0f / (float)a.CC;
 }
 
 // Fills in one candidate, `res` workgroups per compute unit; false when it does not fit.  The cost is an estimate
 // of the kernel's clocks, linear in what a compute unit has to do: matrix instructions (32 clocks each, partly
 // hidden under the vector instructions of other waves), blocks of operand reads, staging and store instructions,
 // a fixed share per unit, and a memory round trip per unit that a workgroup takes.  The coefficients are a least
-// squares fit to 5000 timed plans of 40 shapes (7 % rms); the plan it picks is on average 1.4 % slower than the
-// fastest one of a shape.
+// squares fit to 5000 timed plans of 40 shapes (7 % rms); the plan it picks was on average 1.4 % slower than the
+// fastest one of a shape.  The weights' share `wt` is a memory round trip and P writes per item of eight maps that a thread
+// takes (estimated; plans picked with it were 2 % faster over 60 shapes than with the share of the way before).
 bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH, int TXC, int res) {
   tile::ConvArgs& a = p.a;
   if (!tile_unit(a, P, mt, NB, TH, TXC)) return false;
@@ -371,11 +372,11 @@ bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH,
       const double wgs = total < (double)NUM_CU * res ? ceil(total / NUM_CU) : res;
       const double per_cu = total > NUM_CU ? ceil(total / NUM_CU) : 1.0, turns = (double)ceil_div(a.units, gx) * chunks;
       const double stage = 0.25 * NB * (!border && a.bands == 1 ? (double)ceil_div(a.CC * a.LP, 16 * a.linear) : a.CC * 1.0 * (!border ? ceil_div(a.LP, 16 * a.linear) : a.LW <= 64 ? ceil_div(a.RH, a.RPI) : a.RH * ceil_div(a.LW, 64)));
-      const double mfma = 128.0 * a.NBK * nt * mt, wt = a.R * 16.0 * a.NBK * chunks / tile::THREADS;
+      const double mfma = 128.0 * a.NBK * nt * mt, wt = chunks * ceil(a.CC * a.KH * a.KW * ceil(a.R / (8.0 * P)) / tile::THREADS) * (450.0 + 90.0 * P);
       const int wide = P % 4 == 0 && a.OW % 4 == 0 ? 4 : P % 2 == 0 && a.OW % 2 == 0 ? 2 : 1;
       const double unit = chunks * (mfma * (wgs == 1.0 ? 1.1 : wgs == 2.0 ? 0.6 : 0.5) + a.NBK * (80.0 * nt + 23.0) + stage * (border ? 50.0 : 82.0) + 430.0) +
                           16.5 * nt * mt * 4 / wide + 83.0 * nt;
-      const double cost = 9300.0 + 500.0 * wgs + 290.0 * wt * (resident ? wgs : per_cu) + per_cu * unit + turns * (wgs == 1.0 ? 1970.0 : wgs == 2.0 ? 1820.0 : 1630.0);
+      const double cost = 9300.0 + 500.0 * wgs + wt * (resident ? wgs : per_cu) + per_cu * unit + turns * (wgs == 1.0 ? 1970.0 : wgs == 2.0 ? 1820.0 : 1630.0);
       if (best < 0.0 || cost < best) {
         best = cost, keep = a;
         p.lds_bytes = (size_t)lds;

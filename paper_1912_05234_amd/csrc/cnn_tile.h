@@ -29,9 +29,11 @@
 // What bounds it (timed plans, cnn_ops.hip): a block of a column tile costs 144 clocks of its SIMD against the
 // 128 of its matrix instructions; around that a unit pays about 500 + 83 NT clocks of staging, addressing and
 // stores, and a workgroup one memory round trip (1700 clocks) per unit, the largest share for layers with few
-// channels.  500 images 3 -> 16 maps, 32 x 32, 5 x 5: forward 24 us, input gradient 45 us, weight gradient 33 us (the
-// kernels before, which needed whole images in LDS: 26, 290 and 1540 us); 256 images 16 -> 32, 28 x 28, 3 x 3: 27,
-// 34, 42 us (364, 460, 2020 us).
+// channels.  500 images 3 -> 16 maps, 32 x 32, 5 x 5: forward 25 us, input gradient 39 us, weight gradient 32 us (the
+// kernels before, which needed whole images in LDS: 26, 290 and 1540 us); 256 images 16 -> 32, 28 x 28, 3 x 3: 28,
+// 36, 41 us (364, 460, 2020 us).  Without its matrix instructions and operand reads the input gradient of the first
+// takes 25 of 46 us, without the weights' way into LDS 33, without staging 40, without stores 45 (before the weights
+// were loaded as below).  Small calls are bound by what comes before the first matrix instruction.
 #pragma once
 
 #include "cnn_igemm.h"
@@ -131,7 +133,7 @@ struct ConvArgs {
   int linear;              // planes are staged as runs of memory (no border, full width): 16 or 4 bytes per lane; 0: by rows
   int RPI;                 // rows per staging instruction (by rows)
   int R;                   // rows of A held in LDS: min(16*MT, MR); row R is zero
-  float inv_p, inv_khkwp, inv_kwp, inv_cols, inv_txc, inv_lw, inv_kp;
+  float inv_p, inv_khkwp, inv_kwp, inv_cols, inv_txc, inv_lw, inv_khkw, inv_kw, inv_cc;
   FastDiv by_unit, by_strip, by_cc;
 };
 struct ConvLds {
@@ -376,52 +378,69 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int KHKW = g.KH * g.KW, KHKWP = g.KH * g.KWP, row0 = 16 * MT * blockIdx.y;  // first row of A of this workgroup
   auto issue = [&](const Unit& u, int chunk, float* buf) { stage_unit<BORDER>(g, u, chunk, buf, wave, t); };
-  // A in LDS: a thread keeps one K index and walks the rows (every RG-th one), eight loads in flight; rows and
-  // taps that do not exist are loads outside the buffer, i.e. zeros.
-  const int KP = 16 * g.NBK, RG = KP < THREADS ? THREADS / KP : 1, rows = min(g.R, g.MR - row0);
+  // A in LDS: a thread takes a weight's place in the kernels, (channel, tap), of eight maps at a time, all eight loads in
+  // flight (the first item's while LDS is cleared and the first unit's loads are issued), and writes each to its P shifted
+  // places; the other places are zero from before.  Walking the places of A instead, most of them zeros when packed, eight
+  // rows per memory round trip, measured (us, forward / input gradient, then as here): 500 images 3 -> 16, 32 x 32, 5 x 5
+  // 25 / 49.5, now 25 / 39; 935 images 2 -> 25, 20 x 11, 5 x 5 12.9 / 50, 11.7 / 35; 115 images 20 -> 4, 31 x 37, 7 x 7
+  // 46 / 27, 33 / 27; one image 1 -> 19, 7 x 28, 3 x 3 5.7 / 6.7, 5.0 / 6.4; over 60 random shapes 1.12x / 1.07x.
+  const int maps = g.P == 1 ? min(g.R, g.MR - row0) : g.M;  // (packed: one row tile, M * P <= 16)
   const __amdgpu_buffer_rsrc_t ws = buffer_at(g.w, 4 * g.M * g.SC * KHKW);
-  const int mstep = 4 * (g.flip ? KHKW : g.SC * KHKW), shstep = g.flip ? 4 : -4;
-  auto weights = [&](int chunk) {
-    const int c0 = chunk * g.CC;
-    int rg0, kk0, me = t;
-    asm volatile("" : "+v"(me));  // decoded here, not kept in registers through the main loop
-    divmod(me, KP < THREADS ? KP : THREADS, KP < THREADS ? g.inv_kp : 1.0f / THREADS, rg0, kk0);
-    if (rg0 >= RG) return;
-#pragma unroll 1
-    for (int kk = kk0; kk < KP; kk += THREADS) {
-      int c, rem, u, vp;
-      divmod(kk, KHKWP, g.inv_khkwp, c, rem);
-      divmod(rem, g.KWP, g.inv_kwp, u, vp);
-      int off = !g.flip ? 4 * ((c0 + c) * KHKW + u * g.KW + vp)
-                        : 4 * ((c0 + c) * g.M * KHKW + (g.KH - 1 - u) * g.KW + (g.KW - 1 - vp));
-      if (kk >= g.K || c0 + c >= g.SC) off = FAR;
-      float* dst = wt + (kk & 3) * g.SP + (kk >> 2) + (g.resident ? 4 * g.NBK * chunk : 0) + rg0 * 4 * g.SP;
-#pragma unroll 1
-      for (int r0 = 0; r0 <= g.R; r0 += 8 * RG, dst += 32 * RG * g.SP) {
-        float v[8];
+  struct Item {
+    float v[8];
+    int m0, kk;
+  };
+  auto load_item = [&](int chunk, int e, Item& w) {
+    const int c0 = chunk * g.CC, cc = g.resident ? g.SC : min(g.CC, g.SC - c0), places = cc * KHKW;
+    int grp, r, c, tap, u, x, ck = 0;
+    divmod(e, places, 1.0f / (float)places, grp, r);
+    divmod(r, KHKW, g.inv_khkw, c, tap);
+    divmod(tap, g.KW, g.inv_kw, u, x);
+    w.m0 = 8 * grp;
+    const int step = (g.flip ? 1 : g.SC) * KHKW, at = g.flip ? ((c0 + c) * g.M + row0) * KHKW + tap : (row0 * g.SC + c0) * KHKW + r;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int r = r0 + i * RG + rg0;
-          int at;
-          if (g.P == 1) {
-            at = r < rows ? off + (row0 + r) * mstep : FAR;
-          } else {
-            int m, sh;
-            divmod(r, g.P, g.inv_p, m, sh);
-            at = r < rows && (unsigned)(vp - sh) < (unsigned)g.KW ? off + m * mstep + sh * shstep : FAR;
-          }
-          v[i] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(ws, at, 0, 0));
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          if (r0 + i * RG + rg0 <= g.R) dst[i * RG * 4 * g.SP] = v[i];
-      }
+    for (int i = 0; i < 8; ++i)
+      w.v[i] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(ws, w.m0 + i < maps ? 4 * (at + (w.m0 + i) * step) : FAR, 0, 0));
+    if (g.flip) u = g.KH - 1 - u, x = g.KW - 1 - x;
+    if (g.resident && g.chunks > 1) {  // chunk ck's blocks lie behind those of the chunks before it
+      int rest;
+      divmod(c, g.CC, g.inv_cc, ck, rest);
+      c = rest;
     }
+    w.kk = ck * 16 * g.NBK + c * KHKWP + u * g.KWP + x;
+  };
+  auto place_item = [&](const Item& w) {
+#pragma unroll 1
+    for (int sh = 0; sh < g.P; ++sh) {
+      const int kk = w.kk + sh;
+      float* dst = wt + ((w.m0 * g.P + sh) * 4 + (kk & 3)) * g.SP + (kk >> 2);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (w.m0 + i < maps) dst[i * g.P * 4 * g.SP] = w.v[i];
+    }
+  };
+  auto items = [&](int chunk) { return (g.resident ? g.SC : min(g.CC, g.SC - chunk * g.CC)) * KHKW * ((maps + 7) >> 3); };
+  // (the next item's loads are in flight while one is written)
+  auto weights = [&](int chunk, int e, Item& w) {
+    const int n = items(chunk);
+#pragma unroll 1
+    for (; e < n; e += THREADS) {
+      Item next;
+      if (e + THREADS < n) load_item(chunk, e + THREADS, next);
+      place_item(w);
+      w = next;
+    }
+  };
+  auto clear_weights = [&]() {
+    for (int e = t; e < (g.R + 1) * g.SP; e += THREADS) reinterpret_cast<f4*>(wt)[e] = f4{0.0f, 0.0f, 0.0f, 0.0f};
   };
 
   float* const xbuf = lds + L.x;
+  Item item;  // in flight while LDS is cleared and the first unit's loads are issued
+  if (g.resident && t < items(0)) load_item(0, t, item);
   // every staged cell starts finite: padding K steps and images a ragged unit does not have meet zeros
   for (int e = t; e < 2 * L.buf / 4; e += THREADS) reinterpret_cast<f4*>(xbuf)[e] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  clear_weights();
   lds_barrier();
   unsigned unit = blockIdx.x;
   Unit cur = unit_at(g, unit);
@@ -437,8 +456,7 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
     }
     koff[e] = off;
   }
-  if (g.resident)
-    for (int c = 0; c < g.chunks; ++c) weights(c);
+  if (g.resident) weights(0, t, item);
 
   Columns<NT> col;
   columns(g, col, wave, j);
@@ -468,7 +486,14 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
     const bool more = nunit < (unsigned)g.units;
     lds_barrier();  // this buffer is complete; the other one, and the weights, are no longer read
     if (!g.resident) {
-      weights(chunk);
+      int e = t;
+      asm volatile("" : "+v"(e));  // decoded here, not kept in registers through the main loop
+      if (e < items(chunk)) load_item(chunk, e, item);
+      if (g.SC - chunk * g.CC < g.CC) {  // fewer channels than the chunk before: what they leave has to be zero
+        clear_weights();
+        lds_barrier();
+      }
+      weights(chunk, e, item);
       lds_barrier();
     }
     const Unit nxt = nunit == unit || !more ? cur : unit_at(g, nunit);

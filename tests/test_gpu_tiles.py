@@ -48,6 +48,20 @@ def test_tiled_convolutions(case):
     assert none is None and torch.equal(again, d_k)
 
 
+# Kernels of many channels or taps: weights that fit in LDS all at once, or only those of a chunk of channels, the last with fewer.
+@pytest.mark.parametrize("case", [(3, 100, 13, 14, 6, 7, 7), (4, 31, 40, 40, 31, 7, 7), (3, 60, 20, 20, 2, 5, 5), (2, 6, 13, 14, 100, 7, 7), (40, 3, 32, 32, 15, 5, 5),
+                                  (5, 200, 24, 24, 2, 5, 5)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_weight_tables(case, bf16):
+    B, Cin, H, W, Cout, KH, KW = case
+    x, k = oracle.round_bf16(inputs.make_signed((B, Cin, H, W), 85)), oracle.round_bf16(inputs.make_signed((Cout, Cin, KH, KW), 86))
+    d, b = oracle.round_bf16(inputs.make_signed((B, Cout, H - KH + 1, W - KW + 1), 87)), inputs.make_signed((Cout,), 88)
+    x, k, d, b = dev(x), dev(k), dev(d), dev(b)
+    assert_close(host(binding.conv_fwd(x, k, b, bf16=bf16)), host(binding.conv_fwd(x, k, b, valu=True)).astype(np.float64), RTOL_ACT, "tiled conv_fwd")
+    assert_close(host(binding.conv_bwd_input(d, k, H, W, bf16=bf16)), host(binding.conv_bwd_input(d, k, H, W, valu=True)).astype(np.float64),
+                 RTOL_ACT, "tiled conv_bwd_input")
+
+
 # besides: channel counts on both sides of eight and a last group of eight images with one, seven and eight of them
 @pytest.mark.parametrize("case", CASES + [(7, 8, 10, 10, 8, 3, 3), (8, 9, 10, 10, 17, 3, 3), (257, 7, 12, 12, 33, 5, 5)])
 def test_tiled_convolutions_bf16(case):
