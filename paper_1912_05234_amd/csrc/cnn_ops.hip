@@ -830,7 +830,8 @@ bool tile16_conv_candidate(Tile16ConvPlan& p, int P, int mt, int nt, int NB, int
   p.a = keep;
   p.cost = best, p.nt = nt, p.mt = mt;
   tile_constants(a);
-  p.a.inv_k8 = 1.0f / (float)(4 * a.NBK), p.a.inv_c8 = 1.0f / (float)p.a.C8, p.a.by_c8 = tile::fast_div(p.a.C8);
+  p.a.inv_eights = 1.0f / (float)(p.a.C8 * (a.resident ? a.chunks : 1)), p.a.inv_places = p.a.inv_eights / (float)(a.KH * a.KW);
+  p.a.inv_c8 = 1.0f / (float)p.a.C8, p.a.by_c8 = tile::fast_div(p.a.C8);
   p.a.inv_plane = 1.0f / (float)(p.a.RI * p.a.CI), p.a.inv_ci = 1.0f / (float)p.a.CI;
   return true;
 }

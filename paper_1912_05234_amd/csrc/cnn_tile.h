@@ -488,12 +488,13 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
     if (!g.resident) {
       int e = t;
       asm volatile("" : "+v"(e));  // decoded here, not kept in registers through the main loop
-      if (e < items(chunk)) load_item(chunk, e, item);
+      Item own;
+      if (e < items(chunk)) load_item(chunk, e, own);
       if (g.SC - chunk * g.CC < g.CC) {  // fewer channels than the chunk before: what they leave has to be zero
         clear_weights();
         lds_barrier();
       }
-      weights(chunk, e, item);
+      weights(chunk, e, own);
       lds_barrier();
     }
     const Unit nxt = nunit == unit || !more ? cur : unit_at(g, nunit);

@@ -16,8 +16,8 @@
 // instructions run.  LDS traffic bounds these kernels (16 bytes per lane and operand feed an instruction of 16
 // clocks), so a wave owns NT column tiles, or all tap tiles, per weight operand it reads.  Measured (forward / input
 // gradient / weight gradient, us; in brackets one workgroup per group of whole images, or one thread per element where
-// an image did not fit the LDS): 10000 images 6 -> 12 maps, 12 x 12, 5 x 5 taps 23 / 34 / 27 (32, 44, 35), of which a
-// copy of the same bytes takes 14; 500 images 3 -> 16, 32 x 32, 5 x 5: 18 / 19 / 31 (21, 29, 1840); 256 images 16 -> 32,
+// an image did not fit the LDS): 10000 images 6 -> 12 maps, 12 x 12, 5 x 5 taps 22 / 34 / 27 (32, 44, 35), of which a
+// copy of the same bytes takes 14; 500 images 3 -> 16, 32 x 32, 5 x 5: 17 / 17 / 31 (21, 29, 1840); 256 images 16 -> 32,
 // 28 x 28, 3 x 3: 16 / 22 / 48 (24, 870, 2353).
 #pragma once
 
@@ -108,7 +108,7 @@ struct ConvArgs {
   // stay zero from the start.  A band of a bordered image turns all its rows, a strip all its columns: `edges`, cells
   // outside the image are written as zeros.
   int RI, CI, r0, c0, edges;
-  float inv_k8, inv_c8;   // 1 / (4 NBK), for the eights of a weight row; 1 / C8
+  float inv_c8, inv_eights, inv_places;  // 1 / C8, 1 / the eights whose weights are in LDS, 1 / (KH KW those)
   float inv_plane, inv_ci;  // 1 / (RI CI), 1 / CI
   FastDiv by_c8;
 };
@@ -164,45 +164,65 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
   const int KHKW = g.KH * g.KW, OHOW = g.OH * g.OW, C8 = a16.C8;
   const int row0 = 16 * MT * blockIdx.y;
   auto issue = [&](const tile::Unit& u, int chunk) { stage_planes(g, u, chunk, x, wave, l); };
-  // A in LDS: a thread keeps one eight of K elements (a tap, eight channels) and walks the rows
-  const int K8 = 4 * g.NBK, RG = K8 < THREADS ? THREADS / K8 : 1, rows = min(g.R, g.MR - row0);
+  // A in LDS: a thread takes (tap, eight channels) of two maps at a time, sixteen loads in flight, the first of them while LDS
+  // is cleared and the first unit's loads are issued, and writes each eight to its P shifted places; the other places are
+  // zero from before (as in the fp32 kernel).  Against walking the places, three rows at a time:
+  // 18.8 -> 16.8 us for the input gradient of 500 images 3 -> 16, 32 x 32, 5 x 5, over 60 random shapes 1.06x forward and 1.08x
+  // input gradient (forward with seven by seven taps and twenty channels 0.95x: more trips).  A third map, or a second item in flight, costs registers that the NT = 4 forms spill (5 - 15 % slower forward).
+  const int K8 = 4 * g.NBK, maps = g.P == 1 ? min(g.R, g.MR - row0) : g.M;
   const __amdgpu_buffer_rsrc_t ws = buffer_at(g.w, 4 * g.M * g.SC * KHKW);
-  const int mstep = 4 * (g.flip ? KHKW : g.SC * KHKW), shstep = g.flip ? 4 : -4, cstep = 4 * (g.flip ? g.M * KHKW : KHKW);
-  auto weights = [&](int chunk) {
-    const int c0 = chunk * g.CC;
-    int rg0, k0, me = t;
-    asm volatile("" : "+v"(me));  // decoded here, not kept in registers through the main loop
-    divmod(me, K8 < THREADS ? K8 : THREADS, K8 < THREADS ? a16.inv_k8 : 1.0f / THREADS, rg0, k0);
-    if (rg0 >= RG) return;
+  const int mstep = 4 * (g.flip ? KHKW : g.SC * KHKW), cstep = 4 * (g.flip ? g.M * KHKW : KHKW);
+  const int eights = g.resident ? C8 * g.chunks : C8;  // of all chunks, or of one
+  const int n_items = KHKW * eights * ((maps + 1) / 2);
+  struct Item {
+    float v[2][8];
+    int m0, at;  // first map; byte offset of the unshifted place in a weight row
+  };
+  auto load_item = [&](int chunk, int e, Item& w) {
+    int grp, r, tap, c8, u, x0, ck = 0;
+    divmod(e, KHKW * eights, a16.inv_places, grp, r);
+    divmod(r, eights, a16.inv_eights, tap, c8);
+    divmod(tap, g.KW, g.inv_kw, u, x0);
+    w.m0 = 2 * grp;
+    if (g.resident && g.chunks > 1) {
+      int rest;
+      divmod(c8, C8, a16.inv_c8, ck, rest);
+      c8 = rest;
+    }
+    const int c0 = (chunk + ck) * g.CC, c = c0 + 8 * c8, have = min(8, min(g.SC, c0 + g.CC) - c);  // channels that exist
+    const int off = 4 * tap + c * cstep + (row0 + w.m0) * mstep;
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        w.v[n][i] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(ws, w.m0 + n < maps && i < have ? off + n * mstep + i * cstep : FAR, 0, 0));
+    if (g.flip) u = g.KH - 1 - u, x0 = g.KW - 1 - x0;
+    w.at = 64 * g.NBK * ck + 16 * ((u * g.KWP + x0) * C8 + c8);
+  };
+  auto place_item = [&](const Item& w) {
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      if (w.m0 + n < maps) {
+        const i4 eight = pack_item(w.v[n]);
+        char* dst = smem + L.wt + (w.m0 + n) * g.P * a16.RS + w.at;
 #pragma unroll 1
-    for (int k8 = k0; k8 < K8; k8 += THREADS) {
-      int tap, c8, u, vp;
-      divmod(k8, C8, a16.inv_c8, tap, c8);
-      divmod(tap, g.KWP, g.inv_kwp, u, vp);
-      const int c = c0 + 8 * c8, have = min(8, min(g.SC, c0 + g.CC) - c);  // channels that exist
-      const int off = (!g.flip ? 4 * (u * g.KW + vp) : 4 * ((g.KH - 1 - u) * g.KW + (g.KW - 1 - vp))) + c * cstep;
-#pragma unroll 1
-      for (int r0 = rg0; r0 <= g.R; r0 += 3 * RG) {  // three rows, 24 loads in flight
-        float v[3][8];
-#pragma unroll
-        for (int n = 0; n < 3; ++n) {
-          const int r = r0 + n * RG;
-          int m = row0 + r, sh = 0;
-          if (g.P > 1) divmod(r, g.P, g.inv_p, m, sh);
-          const bool real = u < g.KH && r < rows && (unsigned)(vp - sh) < (unsigned)g.KW;
-          const int at = off + m * mstep + sh * shstep;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) v[n][i] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(ws, real && i < have ? at + i * cstep : FAR, 0, 0));
-        }
-#pragma unroll
-        for (int n = 0; n < 3; ++n)
-          if (r0 + n * RG <= g.R)
-            *reinterpret_cast<i4*>(smem + L.wt + (r0 + n * RG) * a16.RS + (g.resident ? 64 * g.NBK * chunk : 0) + 16 * k8) =
-                i4{(int)pack_bf16(v[n][0], v[n][1]), (int)pack_bf16(v[n][2], v[n][3]), (int)pack_bf16(v[n][4], v[n][5]), (int)pack_bf16(v[n][6], v[n][7])};
+        for (int sh = 0; sh < g.P; ++sh, dst += a16.RS + 16 * C8) *reinterpret_cast<i4*>(dst) = eight;
       }
     }
   };
+  // (one item at a time: the registers of a second one would be spilled)
+  auto weights = [&](int chunk, int e, Item& w) {
+#pragma unroll 1
+    while (e < n_items) {
+      place_item(w);
+      e += THREADS;
+      if (e < n_items) load_item(chunk, e, w);
+    }
+  };
 
+  Item item;
+  if (g.resident && t < n_items) load_item(0, t, item);
+  for (int e = t; e < (g.R + 1) * a16.RS / 16; e += THREADS) reinterpret_cast<i4*>(smem + L.wt)[e] = i4{0, 0, 0, 0};
   // everything staged starts finite: padding K elements, and images a ragged unit does not have, meet zeros
   for (int e = t; e < (L.total - L.x) / 16; e += THREADS) reinterpret_cast<f4*>(smem + L.x)[e] = f4{0.0f, 0.0f, 0.0f, 0.0f};
   lds_barrier();
@@ -215,8 +235,7 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
     divmod(tap, g.KWP, g.inv_kwp, u, vp);
     koff[e] = u < g.KH ? 16 * (c8 * a16.LPIX + u * g.LW + vp) : 0;
   }
-  if (g.resident)
-    for (int c = 0; c < g.chunks; ++c) weights(c);
+  if (g.resident) weights(0, t, item);
 
   int po[NT];
   tile::Columns<NT> col;
@@ -246,7 +265,13 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
     if (nchunk == g.chunks) nchunk = 0, nunit = unit + gridDim.x;
     const bool more = nunit < (unsigned)g.units;
     lds_barrier();  // the fp32 planes are complete, the items and weights no longer read
-    if (!g.resident) weights(chunk);
+    if (!g.resident) {
+      int e = t;
+      asm volatile("" : "+v"(e));  // decoded here, not kept in registers through the main loop
+      Item own;
+      if (e < n_items) load_item(chunk, e, own);
+      weights(chunk, e, own);
+    }
     {
       const int cc = min(g.CC, g.SC - chunk * g.CC), per = a16.RI * a16.CI, yb = cur.y0 - g.pady, xb = cur.x0 - g.padx;
       const int ys = first_row(g, cur);
