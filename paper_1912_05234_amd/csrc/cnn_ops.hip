@@ -292,6 +292,7 @@ class PlanMemo {
 struct TileConvPlan {
   tile::ConvArgs a;
   int nt = 0, mt = 0;  // column and row tiles per wave; nt = 0: no unit fits in LDS
+  int run = 1;         // staged floats that a lane reads at once
   dim3 grid;
   size_t lds_bytes = 0;
   double cost = 0.0;
@@ -335,6 +336,10 @@ void tile_constants(tile::ConvArgs& a) {
   a.inv_khkw = 1.0f / (float)(a.KH * a.KW), a.inv_kw = 1.0f / (float)a.KW, a.inv_cc = 1.0f / (float)a.CC;
 }
 
+// Clocks per block of a column tile beside the matrix instructions, by the floats a lane reads at once (2 and 4: estimates
+// with which runs are taken where they fit).
+constexpr double RUN_CLOCKS[5] = {0.0, 80.0, 50.0, 0.0, 35.0};
+
 // Fills in one candidate, `res` workgroups per compute unit; false when it does not fit.  The cost is an estimate
 // of the kernel's clocks, linear in what a compute unit has to do: matrix instructions (32 clocks each, partly
 // hidden under the vector instructions of other waves), blocks of operand reads, staging and store instructions,
@@ -342,10 +347,20 @@ void tile_constants(tile::ConvArgs& a) {
 // squares fit to 5000 timed plans of 40 shapes (7 % rms); the plan it picks was on average 1.4 % slower than the
 // fastest one of a shape.  The weights' share `wt` is a memory round trip and P writes per item of eight maps that a thread
 // takes (estimated; plans picked with it were 2 % faster over 60 shapes than with the share of the way before).
-bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH, int TXC, int res) {
+bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH, int TXC, int res, int run) {
   tile::ConvArgs& a = p.a;
   if (!tile_unit(a, P, mt, NB, TH, TXC)) return false;
   const bool border = a.pady || a.padx || a.strips > 1;
+  if (run > 1) {
+    // whole runs of taps in a row (filled up with zero taps they cost more than the runs give: 362 images 22 -> 6, 19 x 36,
+    // 4 x 4, forward with 5 taps as 6 31.4 -> 39.0 us), staged rows and planes in whole runs
+    if (border) {
+      a.LW = (int)ceil_div(a.LW, run) * run;
+      a.RPI = a.LW <= 64 ? 64 / a.LW : 1;
+      a.LP = (int)ceil_div(a.RH, a.RPI) * a.RPI * a.LW;
+    }
+    if (P % run || a.KWP % run || a.LW % run || a.LP % run) return false;
+  }
   const int MB = (int)ceil_div(a.MR, 16 * mt);
   const double total = (double)a.units * MB;
   if (res > 1 && total <= NUM_CU * (res - 1.0)) return false;
@@ -374,7 +389,7 @@ bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH,
       const double stage = 0.25 * NB * (!border && a.bands == 1 ? (double)ceil_div(a.CC * a.LP, 16 * a.linear) : a.CC * 1.0 * (!border ? ceil_div(a.LP, 16 * a.linear) : a.LW <= 64 ? ceil_div(a.RH, a.RPI) : a.RH * ceil_div(a.LW, 64)));
       const double mfma = 128.0 * a.NBK * nt * mt, wt = chunks * ceil(a.CC * a.KH * a.KW * ceil(a.R / (8.0 * P)) / tile::THREADS) * (450.0 + 90.0 * P);
       const int wide = P % 4 == 0 && a.OW % 4 == 0 ? 4 : P % 2 == 0 && a.OW % 2 == 0 ? 2 : 1;
-      const double unit = chunks * (mfma * (wgs == 1.0 ? 1.1 : wgs == 2.0 ? 0.6 : 0.5) + a.NBK * (80.0 * nt + 23.0) + stage * (border ? 50.0 : 82.0) + 430.0) +
+      const double unit = chunks * (mfma * (wgs == 1.0 ? 1.1 : wgs == 2.0 ? 0.6 : 0.5) + a.NBK * (RUN_CLOCKS[run] * nt + 23.0) + stage * (border ? 50.0 : 82.0) + 430.0) +
                           16.5 * nt * mt * 4 / wide + 83.0 * nt;
       const double cost = 9300.0 + 500.0 * wgs + wt * (resident ? wgs : per_cu) + per_cu * unit + turns * (wgs == 1.0 ? 1970.0 : wgs == 2.0 ? 1820.0 : 1630.0);
       if (best < 0.0 || cost < best) {
@@ -387,7 +402,7 @@ bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH,
   if (best < 0.0) return false;
   a = keep;
   p.cost = best;
-  p.nt = nt, p.mt = mt;
+  p.nt = nt, p.mt = mt, p.run = run;
   tile_constants(a);
   return true;
 }
@@ -440,7 +455,8 @@ TileConvPlan plan_tile_conv(const float* src, const float* w, const float* bias,
     TileConvPlan best, c;
     if (!tile_args(c.a, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip)) return best;
     tile_units(c.a, [&](int P, int mt, int nt, int NB, int TH, int TXC, int res) {
-      if (tile_conv_candidate(c, P, mt, nt, NB, TH, TXC, res) && (!best.nt || c.cost < best.cost)) best = c;
+      for (int run = 1; run <= (mt == 1 ? 4 : 1); run <<= 1)
+        if (P % run == 0 && tile_conv_candidate(c, P, mt, nt, NB, TH, TXC, res, run) && (!best.nt || c.cost < best.cost)) best = c;
     });
     return best;
   });
@@ -456,15 +472,26 @@ void launch_tiled(void (*kernel)(const ARGS), dim3 grid, size_t lds_bytes, hipSt
   kernel<<<grid, tile::THREADS, lds_bytes, stream>>>(args);
 }
 
+template <bool BORDER, int RUN>
+void launch_tile_conv_as(const TileConvPlan& p, hipStream_t stream) {
+  switch (p.nt) {
+    case 1: launch_tiled(tile::conv_kernel<1, 1, BORDER, RUN>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 2: launch_tiled(tile::conv_kernel<2, 1, BORDER, RUN>, p.grid, p.lds_bytes, stream, p.a); break;
+    default: launch_tiled(tile::conv_kernel<4, 1, BORDER, RUN>, p.grid, p.lds_bytes, stream, p.a); break;
+  }
+}
+
 template <bool BORDER>
 void launch_tile_conv_as(const TileConvPlan& p, hipStream_t stream) {
-  switch (10 * p.mt + p.nt) {
-    case 11: launch_tiled(tile::conv_kernel<1, 1, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
-    case 12: launch_tiled(tile::conv_kernel<2, 1, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
-    case 14: launch_tiled(tile::conv_kernel<4, 1, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
-    case 21: launch_tiled(tile::conv_kernel<1, 2, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
-    case 22: launch_tiled(tile::conv_kernel<2, 2, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
-    default: launch_tiled(tile::conv_kernel<4, 2, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+  switch (10 * p.mt + p.run) {
+    case 11: return launch_tile_conv_as<BORDER, 1>(p, stream);
+    case 12: return launch_tile_conv_as<BORDER, 2>(p, stream);
+    case 14: return launch_tile_conv_as<BORDER, 4>(p, stream);
+  }
+  switch (p.nt) {  // two row tiles
+    case 1: launch_tiled(tile::conv_kernel<1, 2, BORDER, 1>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 2: launch_tiled(tile::conv_kernel<2, 2, BORDER, 1>, p.grid, p.lds_bytes, stream, p.a); break;
+    default: launch_tiled(tile::conv_kernel<4, 2, BORDER, 1>, p.grid, p.lds_bytes, stream, p.a); break;
   }
 }
 

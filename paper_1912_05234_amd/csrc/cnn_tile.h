@@ -122,7 +122,7 @@ struct ConvArgs {
   float* dst;         // [B][M][OH][OW]
   int B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx;
   int flip;                // 0: A[m][(c,u,v)] = w[m][c][u][v];  1: A[m][(c,u,v)] = w[c][m][KH-1-u][KW-1-v]
-  int P, MR, KWP;          // column packing: pixels per column, rows M*P, shifted taps KW+P-1
+  int P, MR, KWP;          // column packing: pixels per column, rows M*P, shifted taps KW+P-1 
   int NB, TH, TXC;         // a unit: images (1 unless TH covers the image), output rows, columns of P pixels per row
   int groups, bands, strips, units;
   int CC, chunks;          // channels per chunk (one chunk when NB > 1 and the planes have a border)
@@ -141,16 +141,28 @@ struct ConvLds {
 };
 __host__ __device__ inline ConvLds conv_lds(const ConvArgs& a) {
   ConvLds l;
-  l.wt = 0;                                // [R + 1 rows][4: q][SP]: A[row][4 s + q] at [s], chunk by chunk when resident
-  l.koff = l.wt + (a.R + 1) * 4 * a.SP;    // [4: q][SK] byte offset of K index 4 s + q
+  l.wt = 0;                                // [R + 1 rows][4: q][SP]: A[row][K index of step s in lane group q] at [s], chunk by chunk when resident
+  l.koff = l.wt + (a.R + 1) * 4 * a.SP;    // [4: q][SK] byte offset of that K index
   l.x = l.koff + 4 * a.SK;
   l.buf = round4(a.NB * a.LI + a.P + 4);   // (a padding column may read past the last row)
   l.total = l.x + 2 * l.buf;
   return l;
 }
 
+// The order of K inside a block of sixteen: index r of the block is step s of lane group q.  RUN neighbouring indices
+// (taps of one kernel row, i.e. neighbouring staged floats) belong to one lane, which reads them as one LDS item.
+template <int RUN>
+__device__ __forceinline__ void k_place(int r, int& q, int& s) {
+  q = RUN == 4 ? r >> 2 : RUN == 2 ? (r >> 1) & 3 : r & 3;
+  s = RUN == 4 ? r & 3 : RUN == 2 ? (r >> 3) * 2 + (r & 1) : r >> 2;
+}
+template <int RUN>
+__device__ __forceinline__ int k_index(int q, int s) {
+  return RUN == 4 ? 4 * q + s : RUN == 2 ? 8 * (s >> 1) + 2 * q + (s & 1) : 4 * s + q;
+}
+
 // Blocks of four K steps, the operands of block i + 1 read under the instructions of block i.
-template <int NT, int MT>
+template <int NT, int MT, int RUN>
 __device__ __forceinline__ void gemm(f4 (&acc)[MT][NT], const float* wt, const int (&arow)[MT], const i4* koff,
                                      const char* staged, const int (&off)[NT], int nbk) {
   f4 a0[MT], a1[MT];
@@ -165,9 +177,14 @@ __device__ __forceinline__ void gemm(f4 (&acc)[MT][NT], const float* wt, const i
   };
   auto gather = [&](float (&b)[4][NT], const i4& k) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
+    for (int s = 0; s < 4; s += RUN)
 #pragma unroll
-      for (int t = 0; t < NT; ++t) b[s][t] = *reinterpret_cast<const float*>(staged + k[s] + off[t]);
+      for (int t = 0; t < NT; ++t) {
+        using item = float __attribute__((ext_vector_type(RUN)));
+        const item v = *reinterpret_cast<const item*>(staged + k[s] + off[t]);
+#pragma unroll
+        for (int i = 0; i < RUN; ++i) b[s + i][t] = v[i];
+      }
   };
   auto multiply = [&](const f4 (&a)[MT], const float (&b)[4][NT]) {
 #pragma unroll
@@ -177,10 +194,10 @@ __device__ __forceinline__ void gemm(f4 (&acc)[MT][NT], const float* wt, const i
 #pragma unroll
         for (int m = 0; m < MT; ++m) acc[m][t] = mfma16(a[m][s], b[s][t], acc[m][t]);
   };
-  auto interleave = [&]() {  // one LDS read behind every MT matrix instructions
+  auto interleave = [&]() {  // one LDS read behind every MT (times RUN) matrix instructions
 #pragma unroll
-    for (int i = 0; i < 4 * NT; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, MT, 0);
+    for (int i = 0; i < 4 * NT / RUN; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, RUN * MT, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
     __builtin_amdgcn_sched_group_barrier(0x100, MT + 1, 0);
@@ -368,7 +385,11 @@ __device__ __forceinline__ void store_unit(const ConvArgs& g, const Unit& u, con
 __host__ __device__ constexpr int conv_residency(int nt, int mt) { return nt * mt <= 4 ? 4 : 3; }
 
 // BORDER: the staged planes have a border (or are strips of a wide image) and are staged by rows.
-template <int NT, int MT, bool BORDER>
+// RUN: floats of a staged row that a lane reads at once (k_place; KWP, P and the LDS strides are multiples of it): one LDS
+// read and one address for RUN matrix instructions.  Kernel times (us, one float at a time -> RUN): input gradient of 500
+// images 3 -> 16, 32 x 32, 5 x 5 38.5 -> 35.6 (4); 2585 images 2 -> 10, 22 x 18, 7 x 7 97 -> 94 (2); forward of 1376 images 3 ->
+// 3, 28 x 32, 5 x 5 23.6 -> 21.6 (4); the 23 of 120 calls on 60 random shapes that take runs 1.03x.
+template <int NT, int MT, bool BORDER, int RUN>
 __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(const ConvArgs g) {
   extern __shared__ __align__(16) float lds[];
   const ConvLds L = conv_lds(g);
@@ -413,7 +434,9 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
 #pragma unroll 1
     for (int sh = 0; sh < g.P; ++sh) {
       const int kk = w.kk + sh;
-      float* dst = wt + ((w.m0 * g.P + sh) * 4 + (kk & 3)) * g.SP + (kk >> 2);
+      int kq, ks;
+      k_place<RUN>(kk & 15, kq, ks);
+      float* dst = wt + ((w.m0 * g.P + sh) * 4 + kq) * g.SP + 4 * (kk >> 4) + ks;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         if (w.m0 + i < maps) dst[i * g.P * 4 * g.SP] = w.v[i];
@@ -446,7 +469,7 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
   Unit cur = unit_at(g, unit);
   issue(cur, 0, xbuf);
   for (int e = t; e < 4 * g.SK; e += THREADS) {
-    const int qq = e >= 3 * g.SK ? 3 : e >= 2 * g.SK ? 2 : e >= g.SK ? 1 : 0, kk = 4 * (e - qq * g.SK) + qq;
+    const int qq = e >= 3 * g.SK ? 3 : e >= 2 * g.SK ? 2 : e >= g.SK ? 1 : 0, at = e - qq * g.SK, kk = 16 * (at >> 2) + k_index<RUN>(qq, at & 3);
     int off = 0;
     if (kk < g.K) {
       int c, rem, u, vp;
@@ -499,7 +522,7 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
     }
     const Unit nxt = nunit == unit || !more ? cur : unit_at(g, nunit);
     if (more) issue(nxt, nchunk, xbuf + (par ^ 1) * L.buf);
-    gemm<NT, MT>(acc, wt + (g.resident ? 4 * g.NBK * chunk : 0), arow, kq, reinterpret_cast<const char*>(xbuf + par * L.buf), po, g.NBK);
+    gemm<NT, MT, RUN>(acc, wt + (g.resident ? 4 * g.NBK * chunk : 0), arow, kq, reinterpret_cast<const char*>(xbuf + par * L.buf), po, g.NBK);
     wait_loads();  // before this unit's stores are issued, so that those stay in flight under the next unit's work
     if (nchunk == 0) {
       store_unit(g, cur, col, row, acc);

@@ -48,6 +48,21 @@ def test_tiled_convolutions(case):
     assert none is None and torch.equal(again, d_k)
 
 
+# Packed columns whose taps lie in runs of two or four: with and without a border, ragged rows, bands and channel chunks,
+# whole images per unit, and (the last two) rows of odd length, which have no runs without a border.
+@pytest.mark.parametrize("case", [(33, 3, 28, 32, 3, 5, 5), (500, 3, 32, 32, 15, 5, 5), (130, 2, 20, 11, 25, 5, 5), (18, 5, 33, 33, 2, 3, 3),
+                                  (1100, 4, 17, 30, 2, 3, 3), (700, 2, 22, 18, 10, 7, 7), (723, 3, 21, 16, 1, 5, 5), (10, 1, 30, 36, 2, 3, 3),
+                                  (95, 3, 10, 40, 14, 5, 5), (60, 2, 13, 15, 3, 3, 5), (60, 5, 9, 35, 3, 5, 5)])
+def test_runs_of_taps(case):
+    B, Cin, H, W, Cout, KH, KW = case
+    x, k, b = inputs.make_signed((B, Cin, H, W), 91), inputs.make_signed((Cout, Cin, KH, KW), 92), inputs.make_signed((Cout,), 93)
+    d = inputs.make_signed((B, Cout, H - KH + 1, W - KW + 1), 94)
+    x, k, b, d = dev(x), dev(k), dev(b), dev(d)
+    assert_close(host(binding.conv_fwd(x, k, b)), host(binding.conv_fwd(x, k, b, valu=True)).astype(np.float64), RTOL_ACT, "tiled conv_fwd")
+    assert_close(host(binding.conv_bwd_input(d, k, H, W)), host(binding.conv_bwd_input(d, k, H, W, valu=True)).astype(np.float64),
+                 RTOL_ACT, "tiled conv_bwd_input")
+
+
 # Kernels of many channels or taps: weights that fit in LDS all at once, or only those of a chunk of channels, the last with fewer.
 @pytest.mark.parametrize("case", [(3, 100, 13, 14, 6, 7, 7), (4, 31, 40, 40, 31, 7, 7), (3, 60, 20, 20, 2, 5, 5), (2, 6, 13, 14, 100, 7, 7), (40, 3, 32, 32, 15, 5, 5),
                                   (5, 200, 24, 24, 2, 5, 5)])
