@@ -747,6 +747,10 @@ void launch_conv2_wgrad(const float* in, const float* d_out, float* part, int B,
   }
 }
 
+// A plan of one workgroup column leaves no partial sums, but asks for a workspace all the same: a call without one is the
+// plain kernel, which multiplies nothing by padding zeros and so keeps a NaN or an infinity to the weights that meet it.
+constexpr size_t NO_PARTIAL_SUMS_BYTES = 16;
+
 struct WgradPlan {
   // which kernel: cnn_tile.h by the plan in `tile`, or one of the network's own layers (gx workgroups that leave partial
   // 16 x 16 tiles, MT x NT of them with P shifts, for igemm::wgrad_reduce_kernel)
@@ -780,8 +784,7 @@ WgradPlan plan_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
   } else {
     p.tile = plan_tile_wgrad(B, Cin, H, W, Cout, KH, KW);
     if (p.tile.nt) p.kernel = WgradPlan::TILED;
-    p.workspace_bytes = p.tile.workspace_bytes;
-    if (p.tile.nt && p.tile.interface_bytes > p.workspace_bytes) p.workspace_bytes = p.tile.interface_bytes;
+    if (p.tile.nt) p.workspace_bytes = std::max({p.tile.workspace_bytes, p.tile.interface_bytes, NO_PARTIAL_SUMS_BYTES});
     p.least_bytes = p.workspace_bytes;
   }
   return p;
@@ -1016,7 +1019,7 @@ struct Wgrad16Plan {
   TileWgradPlan rounded;
   bool use_rounded() const { return rounded.nt && (!eight.nt || 1.08 * rounded.cost < eight.cost); }
   bool use_plain() const { return !rounded.nt && (!eight.nt || (rounded.cost > 0.0 && rounded.cost < eight.cost)); }
-  size_t workspace_bytes() const { return use_plain() ? 0 : use_rounded() ? rounded.workspace_bytes : eight.workspace_bytes; }
+  size_t workspace_bytes() const { return use_plain() ? 0 : std::max(use_rounded() ? rounded.workspace_bytes : eight.workspace_bytes, NO_PARTIAL_SUMS_BYTES); }
 };
 
 Wgrad16Plan plan_wgrad16(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
@@ -1240,8 +1243,7 @@ int cnn_conv_bwd_weight_bf16(const float* in, const float* d_out, float* d_k, fl
     return CNN_EINVAL;
   if (workspace && !aligned16(workspace)) return CNN_EINVAL;
   Wgrad16Plan p = plan_wgrad16(B, Cin, H, W, Cout, KH, KW);
-  const size_t need = p.workspace_bytes();
-  if (!p.use_plain() && (need == 0 || (workspace && workspace_bytes >= need)))
+  if (!p.use_plain() && workspace && workspace_bytes >= p.workspace_bytes())
     return launch_wgrad16(p, in, d_out, d_k, d_bias, static_cast<float*>(workspace), (hipStream_t)hip_stream);
   const unsigned blocks = (unsigned)(Cout * Cin * KH * KW + (d_bias ? Cout : 0));
   conv_bwd_weight_kernel<true><<<blocks, TPB, 0, (hipStream_t)hip_stream>>>(in, d_out, d_k, d_bias, B, Cin, H,

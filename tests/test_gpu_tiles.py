@@ -48,6 +48,29 @@ def test_tiled_convolutions(case):
     assert none is None and torch.equal(again, d_k)
 
 
+# Without a workspace the plain kernel runs, whatever the plan: an infinity reaches the weights that meet it and no others.
+# (One workgroup column each; the matrix-core kernel multiplies the rows' ends of the first by zero for other taps, and
+# cells of the others for padding steps.)
+@pytest.mark.parametrize("case,pixel", [((4, 16, 13, 40, 1, 3, 3), (3, 11, 7, 0)), ((2, 70, 17, 19, 70, 3, 3), (1, 5, 0, 0)),
+                                        ((6, 26, 16, 22, 1, 3, 3), (0, 25, 0, 0))])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_weight_gradient_without_workspace_keeps_infinities_local(case, pixel, bf16):
+    B, Cin, H, W, Cout, KH, KW = case
+    Ho, Wo = H - KH + 1, W - KW + 1
+    x, d = oracle.round_bf16(inputs.make_signed((B, Cin, H, W), 95)), oracle.round_bf16(inputs.make_signed((B, Cout, Ho, Wo), 96))
+    x[pixel] = np.inf
+    ref = np.zeros((Cout, Cin, KH, KW))
+    with np.errstate(invalid="raise"):  # one infinity and no zeros: every sum has a value
+        for u in range(KH):
+            for v in range(KW):
+                ref[:, :, u, v] = np.einsum("bchw,bohw->oc", x[:, :, u:u + Ho, v:v + Wo].astype(np.float64), d.astype(np.float64))
+    d_k, d_b = binding.conv_bwd_weight(dev(x), dev(d), workspace=False, bf16=bf16)
+    d_k, hit = host(d_k), np.isinf(ref)
+    assert 0 < hit.sum() < hit.size and np.array_equal(d_k[hit], ref[hit].astype(np.float32))
+    assert_close(d_k[~hit], ref[~hit], RTOL_ACT, "conv_bwd_weight beside an infinity")
+    assert_close(host(d_b), d.astype(np.float64).sum(axis=(0, 2, 3)), RTOL_ACT, "conv_bwd_bias beside an infinity")
+
+
 # Packed columns whose taps lie in runs of two or four: with and without a border, ragged rows, bands and channel chunks,
 # whole images per unit, and (the last two) rows of odd length, which have no runs without a border.
 @pytest.mark.parametrize("case", [(33, 3, 28, 32, 3, 5, 5), (500, 3, 32, 32, 15, 5, 5), (130, 2, 20, 11, 25, 5, 5), (18, 5, 33, 33, 2, 3, 3),
