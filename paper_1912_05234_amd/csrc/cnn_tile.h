@@ -75,14 +75,15 @@ __device__ __forceinline__ unsigned divide(unsigned n, FastDiv f, unsigned& rem)
 // Buffer accesses check every lane's byte offset against the buffer's size: a load past it (or before
 // the base: the offset is unsigned) delivers zero, a store is dropped.  That is how the zeros around
 // an image and the ragged ends of units are made, without branches.  FAR marks an offset as outside; two of
-// them, or one and any offset inside, still add up to an offset outside.
-constexpr int FAR = 0x40000000, FAR_SIZE = 0x3fffffff;
+// them, or one and any offset inside, still add up to an offset outside, and to one that an int holds.
+constexpr int FAR = 0x3ffffffc, FAR_SIZE = 0x3ffffffc;
+static_assert(FAR >= FAR_SIZE && FAR <= 0x7fffffff - FAR, "sums of offsets outside stay outside");
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const float* base, int bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, bytes, 0x00020000);
 }
 // Lane i's VB bytes at byte offset `off` of the buffer to LDS at dst + i VB bytes; dst is the same in every lane.
 template <int VB>
-__device__ __forceinline__ void buffer_to_lds(__amdgpu_buffer_rsrc_t rs, float* dst, int off) {
+__device__ __forceinline__ void buffer_to_lds(__amdgpu_buffer_rsrc_t rs, float* dst, unsigned off) {
   static_assert(VB == 16 || VB == 4, "item size");
   __attribute__((address_space(3))) void* to = (__attribute__((address_space(3))) void*)dst;
   if (VB == 16)
@@ -281,7 +282,8 @@ __device__ __forceinline__ void stage_unit(const ConvArgs& g, const Unit& u, int
   for (int cx = 0; cx < g.LW; cx += 64) {
     const int lrr = g.LW <= 64 ? (int)((float)l * g.inv_lw + 1e-4f) : 0, col = g.LW <= 64 ? l - lrr * g.LW : cx + l;
     const bool inside = (unsigned)(xb + col) < (unsigned)g.SW;
-    const int off0 = inside ? 4 * ((yb + lrr) * g.SW + xb + col) : FAR, step = inside ? 4 * g.RPI * g.SW : 0;
+    // (bytes as unsigned: rows above and below the image are off by up to three planes of almost FAR_SIZE bytes)
+    const unsigned off0 = inside ? 4u * (unsigned)((yb + lrr) * g.SW + xb + col) : FAR, step = inside ? 4u * g.RPI * g.SW : 0;
     if (lrr < g.RPI && col < g.LW) {
 #pragma unroll 1
       for (int ic = wave; ic < u.nb * cc; ic += WAVES) {
@@ -289,7 +291,7 @@ __device__ __forceinline__ void stage_unit(const ConvArgs& g, const Unit& u, int
         const unsigned img = u.nb == 1 ? 0 : divide(ic, g.by_cc, c);
         const __amdgpu_buffer_rsrc_t rs = buffer_at(src + img * per_image + (size_t)c * plane, 4 * plane);
         float* d = buf + img * g.LI + c * g.LP + cx;
-        int off = off0;
+        unsigned off = off0;
 #pragma unroll 1
         for (int r = 0; r < g.RH; r += g.RPI) {
           buffer_to_lds<4>(rs, d, off);
