@@ -257,32 +257,42 @@ constexpr int TILE_LDS_LIMIT = 79 * 1024;   // of an image-tiled kernel: two wor
 constexpr int NUM_CU = 256;
 
 // ---- image-tiled kernels (cnn_tile.h) ------------------------------------------------------------------
-// The last plans made, by shape: choosing one costs tens of microseconds of host time, which a call should
-// not pay twice.  A plan is a pure function of its key (it holds no caller's pointer).
+// Plans made before, by shape, so that a call does not choose one twice.  Choosing takes 2 to 3 us of host time in the
+// median over 1500 layers, 6 for the fp32 weight gradient, and 40 to 100 at most (every candidate evaluated, instead of
+// only those whose least cost is below the best one's: 6 to 8, 22, and 70 to 170).  A plan is a pure function of its key
+// (it holds no caller's pointer).  WAYS entries for each of SETS hash values, the oldest of a set is given up: a program
+// that goes round 40 batch sizes of a layer keeps them all.
 template <typename PLAN, int KEYS>
 class PlanMemo {
   struct Entry {
     int key[KEYS];
     PLAN plan;
   };
-  static constexpr int ENTRIES = 32;
-  Entry entry[ENTRIES];
-  int used = 0, next = 0;
+  static constexpr int SETS = 64, WAYS = 4;
+  Entry entry[SETS][WAYS];
+  unsigned char used[SETS] = {}, next[SETS] = {};
   std::mutex guard;
+
+  static unsigned set_of(const int (&key)[KEYS]) {
+    unsigned h = 0;
+    for (int k : key) h = (h ^ (unsigned)k) * 0x9e3779b1u, h ^= h >> 15;
+    return h % SETS;
+  }
 
  public:
   template <typename MAKE>
   PLAN get(const int (&key)[KEYS], MAKE make) {
+    const unsigned set = set_of(key);
     {
       std::lock_guard<std::mutex> lock(guard);
-      for (int i = 0; i < used; ++i)
-        if (std::equal(key, key + KEYS, entry[i].key)) return entry[i].plan;
+      for (int i = 0; i < used[set]; ++i)
+        if (std::equal(key, key + KEYS, entry[set][i].key)) return entry[set][i].plan;
     }
     const PLAN plan = make();
     std::lock_guard<std::mutex> lock(guard);
-    Entry& slot = entry[next];
-    next = (next + 1) % ENTRIES;
-    if (used < ENTRIES) ++used;
+    Entry& slot = entry[set][next[set]];
+    next[set] = (next[set] + 1) % WAYS;
+    if (used[set] < WAYS) ++used[set];
     std::copy(key, key + KEYS, slot.key);
     slot.plan = plan;
     return plan;
@@ -299,6 +309,7 @@ struct TileConvPlan {
 };
 
 inline long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
+inline int up(int a, int b) { return (a + b - 1) / b; }  // (for the planner's inner loops: a 64-bit division takes three times as long)
 
 // The unit's geometry in `a`; false when it cannot be.
 bool tile_unit(tile::ConvArgs& a, int P, int mt, int NB, int TH, int TXC) {
@@ -312,6 +323,7 @@ bool tile_unit(tile::ConvArgs& a, int P, int mt, int NB, int TH, int TXC) {
   a.RH = TH + a.KH - 1;
   const bool border = a.pady || a.padx || a.strips > 1;
   a.LW = border ? TXC * P + a.KW - 1 : a.SW;
+  if ((long long)a.RH * a.LW > TILE_LDS_LIMIT / 4) return false;
   a.RPI = a.LW <= 64 ? 64 / a.LW : 1;
   // (by rows, the last instruction of a plane may bring rows past RH)
   a.LP = border ? (int)ceil_div(a.RH, a.RPI) * a.RPI * a.LW : a.bands == 1 ? a.SH * a.SW : a.RH * a.LW;
@@ -327,7 +339,8 @@ int tile_linear(const tile::ConvArgs& a, bool border) {
 }
 // Workgroups in x for `res` per compute unit and `gy` in y (res = 0: one).
 int tile_columns(int units, int gy, int res) {
-  const int gx = NUM_CU * res / gy > 0 ? NUM_CU * res / gy : 1;
+  if (gy >= NUM_CU * res) return 1;
+  const int gx = gy == 1 ? NUM_CU * res : NUM_CU * res / gy;
   return gx < units ? gx : units;
 }
 void tile_constants(tile::ConvArgs& a) {
@@ -340,71 +353,74 @@ void tile_constants(tile::ConvArgs& a) {
 // with which runs are taken where they fit).
 constexpr double RUN_CLOCKS[5] = {0.0, 80.0, 50.0, 0.0, 35.0};
 
-// Fills in one candidate, `res` workgroups per compute unit; false when it does not fit.  The cost is an estimate
-// of the kernel's clocks, linear in what a compute unit has to do: matrix instructions (32 clocks each, partly
+// Keeps the best of one unit's candidates: runs, weights resident or not, 1 .. 4 workgroups per compute unit.  The cost is
+// an estimate of the kernel's clocks, linear in what a compute unit has to do: matrix instructions (32 clocks each, partly
 // hidden under the vector instructions of other waves), blocks of operand reads, staging and store instructions,
 // a fixed share per unit, and a memory round trip per unit that a workgroup takes.  The coefficients are a least
 // squares fit to 5000 timed plans of 40 shapes (7 % rms); the plan it picks was on average 1.4 % slower than the
 // fastest one of a shape.  The weights' share `wt` is a memory round trip and P writes per item of eight maps that a thread
 // takes (estimated; plans picked with it were 2 % faster over 60 shapes than with the share of the way before).
-bool tile_conv_candidate(TileConvPlan& p, int P, int mt, int nt, int NB, int TH, int TXC, int res, int run) {
+void tile_conv_candidates(TileConvPlan& best, TileConvPlan& p, int P, int mt, int nt, int NB, int TH, int TXC) {
   tile::ConvArgs& a = p.a;
-  if (!tile_unit(a, P, mt, NB, TH, TXC)) return false;
+  if (!tile_unit(a, P, mt, NB, TH, TXC)) return;
   const bool border = a.pady || a.padx || a.strips > 1;
-  if (run > 1) {
-    // whole runs of taps in a row (filled up with zero taps they cost more than the runs give: 362 images 22 -> 6, 19 x 36,
-    // 4 x 4, forward with 5 taps as 6 31.4 -> 39.0 us), staged rows and planes in whole runs
-    if (border) {
-      a.LW = (int)ceil_div(a.LW, run) * run;
-      a.RPI = a.LW <= 64 ? 64 / a.LW : 1;
-      a.LP = (int)ceil_div(a.RH, a.RPI) * a.RPI * a.LW;
-    }
-    if (P % run || a.KWP % run || a.LW % run || a.LP % run) return false;
-  }
-  const int MB = (int)ceil_div(a.MR, 16 * mt);
-  const double total = (double)a.units * MB;
-  if (res > 1 && total <= NUM_CU * (res - 1.0)) return false;
-  const int gx = tile_columns(a.units, MB, res);
-  // channels per chunk: the fewest equal shares that fit, with all the weights in LDS or with each chunk's own
-  double best = -1.0;
-  tile::ConvArgs keep = a;
-  for (int resident = 1; resident >= 0; --resident)
-    for (int chunks = resident ? 1 : 2; chunks <= a.SC && (chunks == 1 || NB == 1 || !border); ++chunks) {
-      a.CC = (int)ceil_div(a.SC, chunks);
-      if (ceil_div(a.SC, a.CC) != chunks) continue;
-      const long long K = (long long)a.CC * a.KH * a.KWP;
-      if (K > (1 << 16) || (long long)a.CC * a.LP * NB > TILE_LDS_LIMIT / 4) continue;
-      a.chunks = chunks, a.resident = resident, a.K = (int)K, a.NBK = (int)ceil_div(K, 16), a.LI = a.CC * a.LP;
-      // the sixteen columns of a tile are the same pixel of sixteen images when there are few pixels: images start in different banks
-      if (NB > 1 && a.TH * a.TXC < 16 && !border && a.LI % 8 == 0) a.LI += 4;
-      a.SP = igemm::row_stride(resident ? a.NBK * chunks : a.NBK), a.SK = igemm::row_stride(a.NBK);
-      const long long lds = (long long)tile::conv_lds(a).total * 4;
-      if (lds > TILE_LDS_LIMIT) continue;
-      a.linear = tile_linear(a, border);
-      const int by_lds = (int)(CU_LDS / (lds + 512)), by_regs = tile::conv_residency(nt, mt);
-      if (res > (by_lds < by_regs ? by_lds : by_regs)) break;
-      // workgroups of a compute unit, units it works off, units one workgroup takes in turn
-      const double wgs = total < (double)NUM_CU * res ? ceil(total / NUM_CU) : res;
-      const double per_cu = total > NUM_CU ? ceil(total / NUM_CU) : 1.0, turns = (double)ceil_div(a.units, gx) * chunks;
-      const double stage = 0.25 * NB * (!border && a.bands == 1 ? (double)ceil_div(a.CC * a.LP, 16 * a.linear) : a.CC * 1.0 * (!border ? ceil_div(a.LP, 16 * a.linear) : a.LW <= 64 ? ceil_div(a.RH, a.RPI) : a.RH * ceil_div(a.LW, 64)));
-      const double mfma = 128.0 * a.NBK * nt * mt, wt = chunks * ceil(a.CC * a.KH * a.KW * ceil(a.R / (8.0 * P)) / tile::THREADS) * (450.0 + 90.0 * P);
-      const int wide = P % 4 == 0 && a.OW % 4 == 0 ? 4 : P % 2 == 0 && a.OW % 2 == 0 ? 2 : 1;
-      const double unit = chunks * (mfma * (wgs == 1.0 ? 1.1 : wgs == 2.0 ? 0.6 : 0.5) + a.NBK * (RUN_CLOCKS[run] * nt + 23.0) + stage * (border ? 50.0 : 82.0) + 430.0) +
-                          16.5 * nt * mt * 4 / wide + 83.0 * nt;
-      const double cost = 9300.0 + 500.0 * wgs + wt * (resident ? wgs : per_cu) + per_cu * unit + turns * (wgs == 1.0 ? 1970.0 : wgs == 2.0 ? 1820.0 : 1630.0);
-      if (best < 0.0 || cost < best) {
-        best = cost, keep = a;
-        p.lds_bytes = (size_t)lds;
-        p.grid = dim3((unsigned)gx, (unsigned)MB);
+  const int MB = up(a.MR, 16 * mt), by_regs = tile::conv_residency(nt, mt);
+  const int wide = P % 4 == 0 && a.OW % 4 == 0 ? 4 : P % 2 == 0 && a.OW % 2 == 0 ? 2 : 1;
+  const long long total = (long long)a.units * MB, taps = (long long)a.KH * a.KWP;
+  const double per_cu = (double)ceil_div(total, NUM_CU), stores = 16.5 * nt * mt * 4 / wide + 83.0 * nt;
+  // what every candidate of the unit costs at least
+  const double read = RUN_CLOCKS[mt > 1 || P % 2 ? 1 : P % 4 ? 2 : 4] * nt + 23.0;
+  if (best.nt && 9800.0 + per_cu * ((double)ceil_div(a.SC * taps, 16) * (64.0 * nt * mt + read) + 430.0 + stores) +
+                     1630.0 * up(a.units, tile_columns(a.units, MB, 4)) >= best.cost)
+    return;
+  for (int run = 1; run <= (mt == 1 ? 4 : 1) && P % run == 0; run <<= 1) {
+    if (run > 1) {
+      // whole runs of taps in a row (filled up with zero taps they cost more than the runs give: 362 images 22 -> 6, 19 x 36,
+      // 4 x 4, forward with 5 taps as 6 31.4 -> 39.0 us), staged rows and planes in whole runs
+      if (border) {
+        a.LW = up(a.LW, run) * run;
+        a.RPI = a.LW <= 64 ? 64 / a.LW : 1;
+        a.LP = up(a.RH, a.RPI) * a.RPI * a.LW;
       }
-      break;
+      if (a.KWP % run || a.LW % run || a.LP % run) continue;
     }
-  if (best < 0.0) return false;
-  a = keep;
-  p.cost = best;
-  p.nt = nt, p.mt = mt, p.run = run;
-  tile_constants(a);
-  return true;
+    // channels per chunk: the fewest equal shares that fit, with all the weights in LDS or with each chunk's own
+    for (int resident = 1; resident >= 0; --resident) {
+      // (floats: `fixed` and `each` per channel at least)
+      const long long fixed = resident ? a.SC * taps * (a.R + 1) : 0, each = (resident ? taps : (a.R + 2) * taps) + 2LL * NB * a.LP;
+      const long long most = (TILE_LDS_LIMIT / 4 - fixed) / each;
+      if (fixed > TILE_LDS_LIMIT / 4 || most < 1) continue;
+      const int fewest = (int)ceil_div(a.SC, most);
+      for (int chunks = std::max(fewest, resident ? 1 : 2); chunks <= a.SC && (chunks == 1 || NB == 1 || !border); ++chunks) {
+        a.CC = up(a.SC, chunks);
+        if (up(a.SC, a.CC) != chunks) continue;
+        const long long K = a.CC * taps;
+        if (K > (1 << 16) || (long long)a.CC * a.LP * NB > TILE_LDS_LIMIT / 4) continue;
+        a.chunks = chunks, a.resident = resident, a.K = (int)K, a.NBK = up((int)K, 16), a.LI = a.CC * a.LP;
+        // the sixteen columns of a tile are the same pixel of sixteen images when there are few pixels: images start in different banks
+        if (NB > 1 && a.TH * a.TXC < 16 && !border && a.LI % 8 == 0) a.LI += 4;
+        a.SP = igemm::row_stride(resident ? a.NBK * chunks : a.NBK), a.SK = igemm::row_stride(a.NBK);
+        const long long lds = (long long)tile::conv_lds(a).total * 4;
+        if (lds > TILE_LDS_LIMIT) continue;
+        a.linear = tile_linear(a, border);
+        const int by_lds = CU_LDS / ((int)lds + 512);
+        const double stage = 0.25 * NB * (!border && a.bands == 1 ? up(a.CC * a.LP, 16 * a.linear) : a.CC * 1.0 * (!border ? up(a.LP, 16 * a.linear) : a.LW <= 64 ? up(a.RH, a.RPI) : a.RH * up(a.LW, 64)));
+        const double mfma = 128.0 * a.NBK * nt * mt, reads = a.NBK * (RUN_CLOCKS[run] * nt + 23.0) + stage * (border ? 50.0 : 82.0) + 430.0;
+        const double wt = chunks * (double)up(a.CC * a.KH * a.KW * up(a.R, 8 * P), tile::THREADS) * (450.0 + 90.0 * P);
+        for (int res = 1; res <= 4 && res <= by_lds && res <= by_regs && (res == 1 || total > NUM_CU * (res - 1)); ++res) {
+          // workgroups of a compute unit, units it works off, units one workgroup takes in turn
+          const int gx = tile_columns(a.units, MB, res), wgs = total < NUM_CU * res ? (int)ceil_div(total, NUM_CU) : res;
+          const double turns = (double)up(a.units, gx) * chunks, unit = chunks * (mfma * (wgs == 1 ? 1.1 : wgs == 2 ? 0.6 : 0.5) + reads) + stores;
+          const double cost = 9300.0 + 500.0 * wgs + wt * (resident ? wgs : per_cu) + per_cu * unit + turns * (wgs == 1 ? 1970.0 : wgs == 2 ? 1820.0 : 1630.0);
+          if (best.nt && cost >= best.cost) continue;
+          p.cost = cost, p.nt = nt, p.mt = mt, p.run = run, p.lds_bytes = (size_t)lds;
+          p.grid = dim3((unsigned)gx, (unsigned)MB);
+          best = p;
+        }
+        break;
+      }
+    }
+  }
 }
 
 // The problem in `a`; false where the kernels' 32-bit offsets end.
@@ -417,8 +433,7 @@ bool tile_args(tile::ConvArgs& a, int B, int M, int SC, int SH, int SW, int KH, 
   a.pady = pady, a.padx = padx, a.flip = flip;
   return true;
 }
-// Hands every unit worth considering to `consider`: packing, row and column tiles, images, rows and columns, workgroups
-// per compute unit.
+// Hands every unit worth considering to `consider`: packing, row and column tiles, images, rows and columns.
 template <typename CONSIDER>
 void tile_units(const tile::ConvArgs& a, CONSIDER consider) {
   const int M = a.M, OH = a.OH, OW = a.OW, B = a.B;
@@ -427,7 +442,7 @@ void tile_units(const tile::ConvArgs& a, CONSIDER consider) {
     for (int mt = 1; mt <= (M > 16 ? 2 : 1); ++mt)
       for (int nt = 1; nt <= 4; nt <<= 1) {
         auto sizes = [&](int NB, long long TH, long long TXC) {
-          for (int res = 1; res <= 4; ++res) consider(P, mt, nt, NB, (int)TH, (int)TXC, res);
+          consider(P, mt, nt, NB, (int)TH, (int)TXC);
         };
         const long long OWP = ceil_div(OW, P), most = 64 * nt;
         if (OWP > most) {
@@ -454,10 +469,8 @@ TileConvPlan plan_tile_conv(const float* src, const float* w, const float* bias,
   TileConvPlan p = memo.get({B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip}, [&] {
     TileConvPlan best, c;
     if (!tile_args(c.a, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip)) return best;
-    tile_units(c.a, [&](int P, int mt, int nt, int NB, int TH, int TXC, int res) {
-      for (int run = 1; run <= (mt == 1 ? 4 : 1); run <<= 1)
-        if (P % run == 0 && tile_conv_candidate(c, P, mt, nt, NB, TH, TXC, res, run) && (!best.nt || c.cost < best.cost)) best = c;
-    });
+    tile_units(c.a, [&](int P, int mt, int nt, int NB, int TH, int TXC) { tile_conv_candidates(best, c, P, mt, nt, NB, TH, TXC); });
+    if (best.nt) tile_constants(best.a);
     return best;
   });
   p.a.src = src, p.a.w = w, p.a.bias = bias, p.a.dst = dst;
@@ -511,52 +524,67 @@ struct TileWgradPlan {
   double cost = 0.0;
 };
 
-// As above for the weight gradient; res = 0: one workgroup column, which needs no second kernel.  (Fit: 12600 plans,
-// 10 % rms, 5 % lost on average.)
-bool tile_wgrad_candidate(TileWgradPlan& p, int P, int mt, int nt, int NB, int TH, int res) {
+// As above for the weight gradient.  A form is its packing and the row and tap tiles of a workgroup; false when there is no
+// such form, or none of its units can be better than `best`.
+bool tile_wgrad_form(TileWgradPlan& p, const TileWgradPlan& best, int P, int mt, int nt) {
   tile::WgradArgs& a = p.a;
-  const int plane = a.H * a.W;
-  a.P = P, a.MR = a.Cout * P, a.KWP = a.KW + P - 1, a.WOP = (int)ceil_div(a.Wo, P);
-  a.K = a.Cin * a.KH * a.KWP, a.MT = (int)ceil_div(a.MR, 16), a.NT = (int)ceil_div(a.K, 16);
-  const int KHKWP = a.KH * a.KWP;
+  a.P = P, a.MR = a.Cout * P, a.KWP = a.KW + P - 1, a.WOP = up(a.Wo, P);
+  a.K = a.Cin * a.KH * a.KWP, a.MT = up(a.MR, 16), a.NT = up(a.K, 16);
   // taps of a workgroup: all of its tiles, or (packed) whole groups of KWP
   a.TG = P == 1 ? 16 * nt : 16 * nt / a.KWP * a.KWP;
   if (a.TG < 1) return false;
   if (a.TG > a.K) a.TG = a.K;
-  a.NTG = (int)ceil_div(a.K, a.TG);
-  a.RS = a.Cout * a.Cin * a.KH * a.KW + a.Cout;
-  const int MB = (int)ceil_div(a.MT, mt);
-  a.NB = NB, a.TH = TH, a.groups = (int)ceil_div(a.B, NB), a.bands = (int)ceil_div(a.Ho, TH);
-  if ((long long)a.groups * a.bands > 0x3fffffff || (long long)NB * a.Cout * a.Ho * a.Wo >= tile::FAR_SIZE / 4) return false;
-  a.units = a.groups * a.bands;
-  // channels a group of 16 nt consecutive taps can touch
-  const long long cg = a.NTG == 1 ? a.Cin : (16LL * nt + KHKWP - 2) / KHKWP + 1;
-  a.CG = (int)(cg < a.Cin ? cg : a.Cin);
-  a.RH = a.bands == 1 ? a.H : TH + a.KH - 1;
-  if ((long long)NB * a.CG * a.RH * a.W > TILE_LDS_LIMIT / 4 || (long long)NB * TH * a.WOP > 4096) return false;
-  a.LP = a.RH * a.W, a.LI = a.CG * a.LP;
+  a.NTG = up(a.K, a.TG);
   a.R = a.MR < 16 * mt ? a.MR : 16 * mt;
-  a.N = NB * TH * a.WOP, a.NBK = (a.N + 15) / 16, a.NPS = 16 * a.NBK + 4;
+  a.RS = a.Cout * a.Cin * a.KH * a.KW + a.Cout;
+  // channels a group of 16 nt consecutive taps can touch
+  const long long KHKWP = (long long)a.KH * a.KWP, cg = a.NTG == 1 ? a.Cin : (16LL * nt + KHKWP - 2) / KHKWP + 1;
+  a.CG = (int)(cg < a.Cin ? cg : a.Cin);
+  p.nt = nt, p.mt = mt;
+  p.grid.y = (unsigned)(up(a.MT, mt) * a.NTG);
+  if (!best.nt) return true;
+  const double rounds = (double)a.B * a.Ho * a.WOP / 64.0 * p.grid.y / NUM_CU;
+  return 9500.0 + 256.0 * nt * mt + rounds * (69.0 * nt * mt + 320.0 + 33.0 * a.R) < best.cost;
+}
+
+// Keeps the best of one unit of p's form, `few` .. `most` workgroups per compute unit; 0: one workgroup column, which needs
+// no second kernel.  (Fit: 12600 plans, 10 % rms, 5 % lost on average.)
+void tile_wgrad_candidates(TileWgradPlan& best, TileWgradPlan& p, int NB, int TH, int few, int most) {
+  tile::WgradArgs& a = p.a;
+  const int plane = a.H * a.W, gy = (int)p.grid.y, nt = p.nt, mt = p.mt;
+  const long long groups = NB == 1 ? a.B : ceil_div(a.B, NB), units = TH == a.Ho ? groups : groups * up(a.Ho, TH);
+  if (units > 0x3fffffff || (long long)NB * a.Cout * a.Ho * a.Wo >= tile::FAR_SIZE / 4 || (long long)NB * TH * a.WOP > 4096) return;
+  a.NB = NB, a.TH = TH, a.groups = (int)groups, a.bands = TH == a.Ho ? 1 : up(a.Ho, TH), a.units = (int)units;
+  a.N = NB * TH * a.WOP, a.NBK = up(a.N, 16), a.NPS = 16 * a.NBK + 4;
+  const double blocks = up(a.NBK, tile::WAVES), mfma = 128.0 * blocks * nt * mt, d_instr = (double)a.R * up(a.NBK, 4);
+  const double per_block = blocks * (5.0 * nt + 320.0) + 33.0 * d_instr, work = (double)units * gy / NUM_CU;
+  auto second_kernel = [&](int gx) { return gx > 1 ? 6650.0 + 0.0097 * gx * a.RS + 2.4 * gx : 0.0; };
+  // what every candidate of the unit costs at least
+  if (best.nt && 9500.0 + 256.0 * nt * mt + (work > 1.0 ? work : 1.0) * (mfma * 0.5 + per_block) + 2000.0 * up(a.units, tile_columns(a.units, gy, 4)) +
+                     second_kernel(tile_columns(a.units, gy, few)) >= best.cost)
+    return;
+  a.RH = a.bands == 1 ? a.H : TH + a.KH - 1;
+  if ((long long)NB * a.CG * a.RH * a.W > TILE_LDS_LIMIT / 4) return;
+  a.LP = a.RH * a.W, a.LI = a.CG * a.LP;
   a.vec_x = plane % 4 == 0 && a.LP % 4 == 0 && (a.bands == 1 || TH * a.W % 4 == 0) ? 16 : 4;
   if (a.bands == 1 && a.NTG == 1 && (long long)a.Cin * plane % 4 == 0) a.vec_x = 16;  // (runs of whole images)
   const long long end = tile::wgrad_end_floats(nt, mt), all = tile::wgrad_lds(a).total, lds = 4 * (all > end ? all : end);
-  if (lds > TILE_LDS_LIMIT) return false;
+  if (lds > TILE_LDS_LIMIT) return;
   const int regs = 4 * nt * mt + 3 * nt + 60;  // registers a wave needs, roughly
-  if (res > CU_LDS / (lds + 512) || res > 512 / regs) return false;
-  if (res > 1 && (double)a.units * MB * a.NTG <= NUM_CU * (res - 1.0)) return false;
-  const int gx = tile_columns(a.units, MB * a.NTG, res);
-  const double total = (double)gx * MB * a.NTG, wgs = total > NUM_CU ? ceil(total / NUM_CU) : 1.0, share = total > NUM_CU ? total / NUM_CU : 1.0;
-  const double turns = (double)ceil_div(a.units, gx), blocks = (double)ceil_div(a.NBK, tile::WAVES), mfma = 128.0 * blocks * nt * mt;
-  const double x_instr = (double)NB * (a.bands == 1 ? ceil_div((long long)a.CG * a.LP, 16 * a.vec_x) : a.CG * ceil_div(a.LP, 16 * a.vec_x)), d_instr = (double)a.R * ceil_div(a.NBK, 4);
-  p.cost = 9500.0 + 256.0 * wgs * nt * mt +
-           turns * (share * (mfma * (wgs == 1.0 ? 2.0 : wgs == 2.0 ? 0.9 : 0.5) + blocks * (5.0 * nt + 320.0) + 19.0 * x_instr + 33.0 * d_instr) + 2000.0) +
-           (gx > 1 ? 6650.0 + 0.0097 * gx * a.RS + 2.4 * gx : 0.0);
-  p.nt = nt, p.mt = mt, p.lds_bytes = (size_t)lds;
-  p.grid = dim3((unsigned)gx, (unsigned)(MB * a.NTG));
-  p.workspace_bytes = gx > 1 ? (size_t)gx * a.RS * sizeof(float) : 0;
-  a.inv_khkwp = 1.0f / (float)KHKWP, a.inv_kwp = 1.0f / (float)a.KWP, a.inv_slots = 1.0f / (float)(TH * a.WOP), a.inv_wop = 1.0f / (float)a.WOP;
-  a.by_band = tile::fast_div(a.bands), a.by_p = tile::fast_div(P);
-  return true;
+  const int resident = std::min(CU_LDS / ((int)lds + 512), 512 / regs);
+  auto loads = [&](int floats) { return a.vec_x == 16 ? up(floats, 256) : up(floats, 64); };
+  const double x_instr = (double)NB * (a.bands == 1 ? loads(a.LI) : a.CG * loads(a.LP)), around = per_block + 19.0 * x_instr;
+  for (int res = few; res <= most && res <= resident && (res <= 1 || (long long)a.units * gy > NUM_CU * (res - 1)); ++res) {
+    const int gx = tile_columns(a.units, gy, res);
+    const long long total = (long long)gx * gy, wgs = total > NUM_CU ? ceil_div(total, NUM_CU) : 1;
+    const double share = total > NUM_CU ? (double)total / NUM_CU : 1.0, turns = up(a.units, gx);
+    const double cost = 9500.0 + 256.0 * wgs * nt * mt + turns * (share * (mfma * (wgs == 1 ? 2.0 : wgs == 2 ? 0.9 : 0.5) + around) + 2000.0) + second_kernel(gx);
+    if (best.nt && cost >= best.cost) continue;
+    p.cost = cost, p.lds_bytes = (size_t)lds;
+    p.grid.x = (unsigned)gx;
+    p.workspace_bytes = gx > 1 ? (size_t)gx * a.RS * sizeof(float) : 0;
+    best = p;
+  }
 }
 
 // The workspace that callers have been asked for, and the shapes that the built-in scratch has been documented to
@@ -616,19 +644,20 @@ TileWgradPlan search_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, 
   for (int P = 1; P <= a.Wo && (P == 1 || (KW > 1 && P * Cout <= 16)); ++P) {
     if ((P & (P - 1)) && P != 16 / Cout && a.Wo % P) continue;
     for (int mt = 1; mt <= (Cout > 16 ? 2 : 1); ++mt) {
-      const int NT = (int)ceil_div((long long)Cin * KH * (KW + P - 1), 16);
+      const int NT = up(Cin * KH * (KW + P - 1), 16);
       for (int nt : {1, 2, 3, 4, 6, 8, 12}) {
-        if (nt * mt > 16 || (nt > 1 && nt / 2 >= NT) || 16 * nt < KW + P - 1) continue;
-        auto consider = [&](int NB, int TH) {
-          for (int res = B > 64 ? 1 : 0; res <= (tiny ? 0 : 4); ++res)
-            if (tile_wgrad_candidate(p, P, mt, nt, NB, TH, res) && (!best.nt || p.cost < best.cost)) best = p;
-        };
-        const long long WOP = ceil_div(a.Wo, P);
-        for (int NB = 1; NB <= B && NB * a.Ho * WOP <= 1536; NB = NB < 4 ? NB + 1 : 2 * NB) consider(NB, a.Ho);
-        for (int TH = 1; TH < a.Ho && TH * WOP <= 1536; ++TH)
-          if (TH <= 4 || ceil_div(a.Ho, TH) != ceil_div(a.Ho, TH - 1)) consider(1, TH);
+        if (nt * mt > 16 || (nt > 1 && nt / 2 >= NT) || 16 * nt < KW + P - 1 || !tile_wgrad_form(p, best, P, mt, nt)) continue;
+        auto consider = [&](int NB, int TH) { tile_wgrad_candidates(best, p, NB, TH, B > 64 ? 1 : 0, tiny ? 0 : 4); };
+        for (long long NB = 1; NB <= B && NB * a.Ho * a.WOP <= 1536; NB = NB < 4 ? NB + 1 : 2 * NB) consider((int)NB, a.Ho);
+        for (int TH = 1; TH < a.Ho && (long long)TH * a.WOP <= 1536; ++TH)
+          if (TH <= 4 || up(a.Ho, TH) != up(a.Ho, TH - 1)) consider(1, TH);
       }
     }
+  }
+  if (best.nt) {
+    tile::WgradArgs& b = best.a;
+    b.inv_khkwp = 1.0f / (float)(KH * b.KWP), b.inv_kwp = 1.0f / (float)b.KWP, b.inv_slots = 1.0f / (float)(b.TH * b.WOP), b.inv_wop = 1.0f / (float)b.WOP;
+    b.by_band = tile::fast_div(b.bands), b.by_p = tile::fast_div(b.P);
   }
   if (tiny && best.cost > plain) best.nt = 0, best.cost = plain;
   return best;
@@ -808,62 +837,57 @@ struct Tile16ConvPlan {
   double cost = 0.0;
 };
 
-bool tile16_conv_candidate(Tile16ConvPlan& p, int P, int mt, int nt, int NB, int TH, int TXC, int res) {
+void tile16_conv_candidates(Tile16ConvPlan& best, Tile16ConvPlan& p, int P, int mt, int nt, int NB, int TH, int TXC) {
   tile::ConvArgs& a = p.a.t;
-  if (!tile_unit(a, P, mt, NB, TH, TXC)) return false;
+  if (!tile_unit(a, P, mt, NB, TH, TXC)) return;
   const bool border = a.pady || a.padx || a.strips > 1;
-  const int MB = (int)ceil_div(a.MR, 16 * mt), eights = (int)ceil_div(a.SC, 8);
-  const double total = (double)a.units * MB;
-  if (res > 1 && total <= NUM_CU * (res - 1.0)) return false;
-  const int plane = a.SH * a.SW, gx = tile_columns(a.units, MB, res);
+  const int MB = up(a.MR, 16 * mt), eights = up(a.SC, 8), plane = a.SH * a.SW, by_regs = tile16::conv_residency(nt, mt);
+  const long long total = (long long)a.units * MB, taps = (long long)a.KH * a.KWP;
+  const int wide = P % 4 == 0 && a.OW % 4 == 0 ? 4 : P % 2 == 0 && a.OW % 2 == 0 ? 2 : 1;
+  const double per_cu = (double)ceil_div(total, NUM_CU), stores = 16.0 * nt * mt * 4 / wide + 76.0 * nt, block = 15.0 * nt + 1.5 * nt * mt + 18.0;
+  // what every candidate of the unit costs at least
+  if (best.nt && 12115.0 + per_cu * (block * (double)ceil_div(taps * eights, 4) + stores) + 3600.0 * up(a.units, tile_columns(a.units, MB, 4)) >= best.cost) return;
   // planes are staged without their border, which lies around them in the items
   // (rows an odd number of items apart when the columns of a tile are an even number apart: they start in different banks)
-  a.LW = border ? TXC * P + a.KW - 1 : a.SW;
   if (border && P % 2 == 0) a.LW |= 1;
   a.LP = a.bands == 1 ? plane : (a.RH < a.SH ? a.RH : a.SH) * a.SW;
   p.a.LPIX = a.RH * a.LW;
   p.a.RI = a.bands == 1 ? a.SH : a.RH, p.a.r0 = a.bands == 1 ? a.pady : 0;
   p.a.CI = a.strips == 1 ? a.SW : TXC * P + a.KW - 1, p.a.c0 = a.strips == 1 ? a.padx : 0;
   p.a.edges = (a.bands > 1 && a.pady) || a.strips > 1 || (a.bands > 1 && a.OH % TH) ? 1 : 0;
-  double best = -1.0;
-  tile16::ConvArgs keep = p.a;
-  for (int resident = 1; resident >= 0; --resident)
-    for (int chunks = resident ? 1 : 2; chunks <= eights; ++chunks) {
-      p.a.C8 = (int)ceil_div(eights, chunks);
-      if (ceil_div(eights, p.a.C8) != chunks) continue;
+  for (int resident = 1; resident >= 0; --resident) {
+    // the fewest chunks whose weights and items can fit (bytes: `fixed`, and `each` per eight channels at least)
+    const long long fixed = resident ? 16 * taps * eights * (a.R + 1) : 0, each = (resident ? 0 : 16 * taps * (a.R + 1)) + 16LL * NB * p.a.LPIX;
+    const long long most = (TILE_LDS_LIMIT - fixed) / each;
+    if (fixed > TILE_LDS_LIMIT || most < 1) continue;
+    for (int chunks = std::max((int)ceil_div(eights, most), resident ? 1 : 2); chunks <= eights; ++chunks) {
+      p.a.C8 = up(eights, chunks);
+      if (up(eights, p.a.C8) != chunks) continue;
       a.CC = chunks == 1 ? a.SC : 8 * p.a.C8;
-      const long long K8 = (long long)a.KH * a.KWP * p.a.C8;
+      const long long K8 = taps * p.a.C8;
       if (K8 > (1 << 14) || (long long)a.CC * a.LP * NB > TILE_LDS_LIMIT / 4) continue;
-      a.chunks = chunks, a.resident = resident, a.K = (int)(8 * K8), a.NBK = (int)ceil_div(K8, 4), a.LI = a.CC * a.LP;
+      a.chunks = chunks, a.resident = resident, a.K = (int)(8 * K8), a.NBK = up((int)K8, 4), a.LI = a.CC * a.LP;
       p.a.RS = 64 * a.NBK * (resident ? chunks : 1) + 16;
       const long long lds = tile16::conv_lds(p.a).total;
       if (lds > TILE_LDS_LIMIT) continue;
       a.linear = (a.bands == 1 ? (long long)a.SC * plane % 4 == 0 && (long long)a.CC * plane % 4 == 0
                                : plane % 4 == 0 && (a.SW % 4 == 0 || (!a.pady && a.LP % 4 == 0 && TH * a.SW % 4 == 0))) ? 16 : 4;
-      const int by_lds = (int)(CU_LDS / (lds + 512)), by_regs = tile16::conv_residency(nt, mt);
-      if (res > (by_lds < by_regs ? by_lds : by_regs)) break;
-      const double wgs = total < (double)NUM_CU * res ? ceil(total / NUM_CU) : res;
-      const double per_cu = total > NUM_CU ? ceil(total / NUM_CU) : 1.0, turns = (double)ceil_div(a.units, gx) * chunks;
-      const double stage = 0.25 * (a.bands == 1 ? (double)NB * ceil_div(a.CC * a.LP, 16 * a.linear) : (double)a.CC * ceil_div(a.LP, 16 * a.linear));
-      const double turned = (double)ceil_div((long long)NB * p.a.C8 * p.a.RI * p.a.CI, tile::THREADS), wt = (a.R + 1.0) * a.NBK * 4 * chunks / tile::THREADS;
-      const int wide = P % 4 == 0 && a.OW % 4 == 0 ? 4 : P % 2 == 0 && a.OW % 2 == 0 ? 2 : 1;
-      const double unit = chunks * (a.NBK * (15.0 * nt + 1.5 * nt * mt + 18.0) + turned * 340.0 + stage * 40.0) + 16.0 * nt * mt * 4 / wide + 76.0 * nt;
-      const double cost = 11600.0 + 515.0 * wt * (resident ? wgs : per_cu) + per_cu * unit + turns * (wgs == 1.0 ? 4900.0 : wgs == 2.0 ? 4200.0 : 3600.0);
-      if (best < 0.0 || cost < best) {
-        best = cost, keep = p.a;
-        p.lds_bytes = (size_t)lds;
+      const int by_lds = CU_LDS / ((int)lds + 512);
+      const double stage = 0.25 * (a.bands == 1 ? (double)NB * up(a.CC * a.LP, 16 * a.linear) : (double)a.CC * up(a.LP, 16 * a.linear));
+      const double turned = up(NB * p.a.C8 * p.a.RI * p.a.CI, tile::THREADS), wt = (a.R + 1.0) * a.NBK * 4 * chunks / tile::THREADS;
+      const double unit = chunks * (a.NBK * block + turned * 340.0 + stage * 40.0) + stores;
+      for (int res = 1; res <= 4 && res <= by_lds && res <= by_regs && (res == 1 || total > NUM_CU * (res - 1)); ++res) {
+        const int gx = tile_columns(a.units, MB, res), wgs = total < NUM_CU * res ? (int)ceil_div(total, NUM_CU) : res;
+        const double turns = (double)up(a.units, gx) * chunks;
+        const double cost = 11600.0 + 515.0 * wt * (resident ? wgs : per_cu) + per_cu * unit + turns * (wgs == 1 ? 4900.0 : wgs == 2 ? 4200.0 : 3600.0);
+        if (best.nt && cost >= best.cost) continue;
+        p.cost = cost, p.nt = nt, p.mt = mt, p.lds_bytes = (size_t)lds;
         p.grid = dim3((unsigned)gx, (unsigned)MB);
+        best = p;
       }
       break;
     }
-  if (best < 0.0) return false;
-  p.a = keep;
-  p.cost = best, p.nt = nt, p.mt = mt;
-  tile_constants(a);
-  p.a.inv_eights = 1.0f / (float)(p.a.C8 * (a.resident ? a.chunks : 1)), p.a.inv_places = p.a.inv_eights / (float)(a.KH * a.KW);
-  p.a.inv_c8 = 1.0f / (float)p.a.C8, p.a.by_c8 = tile::fast_div(p.a.C8);
-  p.a.inv_plane = 1.0f / (float)(p.a.RI * p.a.CI), p.a.inv_ci = 1.0f / (float)p.a.CI;
-  return true;
+  }
 }
 
 Tile16ConvPlan plan_tile16_conv(const float* src, const float* w, const float* bias, float* dst, int B, int M, int SC,
@@ -872,9 +896,14 @@ Tile16ConvPlan plan_tile16_conv(const float* src, const float* w, const float* b
   Tile16ConvPlan p = memo.get({B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip}, [&] {
     Tile16ConvPlan best, c;
     if (!tile_args(c.a.t, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip)) return best;
-    tile_units(c.a.t, [&](int P, int mt, int nt, int NB, int TH, int TXC, int res) {
-      if (tile16_conv_candidate(c, P, mt, nt, NB, TH, TXC, res) && (!best.nt || c.cost < best.cost)) best = c;
-    });
+    tile_units(c.a.t, [&](int P, int mt, int nt, int NB, int TH, int TXC) { tile16_conv_candidates(best, c, P, mt, nt, NB, TH, TXC); });
+    if (best.nt) {
+      tile16::ConvArgs& a = best.a;
+      tile_constants(a.t);
+      a.inv_eights = 1.0f / (float)(a.C8 * (a.t.resident ? a.t.chunks : 1)), a.inv_places = a.inv_eights / (float)(KH * KW);
+      a.inv_c8 = 1.0f / (float)a.C8, a.by_c8 = tile::fast_div(a.C8);
+      a.inv_plane = 1.0f / (float)(a.RI * a.CI), a.inv_ci = 1.0f / (float)a.CI;
+    }
     return best;
   });
   p.a.t.src = src, p.a.t.w = w, p.a.t.bias = bias, p.a.t.dst = dst;
@@ -907,53 +936,63 @@ struct Tile16WgradPlan {
   double cost = 0.0;
 };
 
-bool tile16_wgrad_candidate(Tile16WgradPlan& p, int P, int mt, int nt, int TH, int res) {
+bool tile16_wgrad_form(Tile16WgradPlan& p, const Tile16WgradPlan& best, int P, int mt, int nt) {
   tile16::WgradArgs& a = p.a;
-  const int plane = a.H * a.W;
   a.P = P, a.MR = a.Cout * P, a.KWP = a.KW + P - 1, a.WOP = a.Wo / P;
-  a.K = a.Cin * a.KH * a.KWP, a.MT = (int)ceil_div(a.MR, 16), a.NT = (int)ceil_div(a.K, 16);
-  const int KHKWP = a.KH * a.KWP, MB = (int)ceil_div(a.MT, mt);
+  a.K = a.Cin * a.KH * a.KWP, a.MT = up(a.MR, 16), a.NT = up(a.K, 16);
   a.TG = P == 1 ? 16 * nt : 16 * nt / a.KWP * a.KWP;
   if (a.TG < 1) return false;
   if (a.TG > a.K) a.TG = a.K;
-  a.NTG = (int)ceil_div(a.K, a.TG);
+  a.NTG = up(a.K, a.TG);
+  a.groups = (int)ceil_div(a.B, 8);
+  p.nt = nt, p.mt = mt;
+  const double rounds = (double)a.groups * a.Ho * a.WOP / 16.0 * up(a.MT, mt) * a.NTG / NUM_CU;
+  return !best.nt || 450.0 * nt * mt + rounds * 49.0 * nt * mt + 12000.0 < best.cost;
+}
+
+void tile16_wgrad_candidates(Tile16WgradPlan& best, Tile16WgradPlan& p, int TH, int few) {
+  tile16::WgradArgs& a = p.a;
+  const int plane = a.H * a.W, KHKWP = a.KH * a.KWP, MB = up(a.MT, p.mt), nt = p.nt, mt = p.mt;
+  a.TH = TH, a.bands = up(a.Ho, TH);
+  const long long units = (long long)a.groups * a.bands;
+  if (units > 0x3fffffff) return;
+  a.units = (int)units;
+  const double blocks = (double)ceil_div((long long)TH * a.WOP, 4 * tile::WAVES), work = (double)units * MB * a.NTG / NUM_CU;
+  if (best.nt && 450.0 * nt * mt + (work > 1.0 ? work : 1.0) * (blocks * 49.0 * nt * mt + 207.0) + 12000.0 * up(a.units, tile_columns(a.units, MB * a.NTG, 4)) >= best.cost)
+    return;
   a.RS = a.Cout * a.Cin * a.KH * a.KW + a.Cout;
-  a.TH = TH, a.groups = (int)ceil_div(a.B, 8), a.bands = (int)ceil_div(a.Ho, TH);
-  if ((long long)a.groups * a.bands > 0x3fffffff) return false;
-  a.units = a.groups * a.bands;
   const long long cg = a.NTG == 1 ? a.Cin : (a.TG + KHKWP - 2LL) / KHKWP + 1;
   a.CG = (int)(cg < a.Cin ? cg : a.Cin);
   const int R = a.MR < 16 * mt ? a.MR : 16 * mt;
-  a.CO = R / P;
+  a.CO = R / a.P;
   a.RH = a.bands == 1 ? a.H : TH + a.KH - 1;
-  if ((long long)a.CG * a.RH * a.W > TILE_LDS_LIMIT / 32 || (long long)a.CO * TH * a.Wo > TILE_LDS_LIMIT / 32) return false;
+  if ((long long)a.CG * a.RH * a.W > TILE_LDS_LIMIT / 32 || (long long)a.CO * TH * a.Wo > TILE_LDS_LIMIT / 32) return;
   a.LP = a.RH * a.W, a.LI = a.CG * a.LP;
   a.DL = TH * a.Wo, a.DI = a.CO * a.DL, a.DP = a.DL | 1;
-  a.N = TH * a.WOP, a.NBK = (a.N + 3) / 4;
+  a.N = TH * a.WOP, a.NBK = up(a.N, 4);
   a.vec_x = plane % 4 == 0 && a.LP % 4 == 0 && (a.bands == 1 || TH * a.W % 4 == 0) ? 16 : 4;
   if (a.bands == 1 && a.NTG == 1 && (long long)a.Cin * plane % 4 == 0) a.vec_x = 16;  // (runs of whole images)
-  const long long HoWo = (long long)a.Ho * a.Wo;
-  a.vec_d = a.bands == 1 ? (a.Cout * HoWo % 4 == 0 && a.CO * HoWo % 4 == 0 && 16 * mt / P * HoWo % 4 == 0 ? 16 : 4) : (HoWo % 4 == 0 && a.DL % 4 == 0 ? 16 : 4);
+  const int HoWo = a.Ho * a.Wo;
+  a.vec_d = a.bands == 1 ? ((long long)a.Cout * HoWo % 4 == 0 && a.CO * HoWo % 4 == 0 && 16 * mt / a.P * HoWo % 4 == 0 ? 16 : 4) : (HoWo % 4 == 0 && a.DL % 4 == 0 ? 16 : 4);
   if (a.MT > mt && a.bands == 1 && a.Cout % a.CO * HoWo % 4) a.vec_d = 4;
   const long long end = 4ll * tile::wgrad_end_floats(nt, mt), all = tile16::wgrad_lds(a).total, lds = all > end ? all : end;
-  if (lds > TILE_LDS_LIMIT) return false;
+  if (lds > TILE_LDS_LIMIT) return;
   const int regs = 4 * nt * mt + 9 * nt + 8 * mt + 50;
-  if (res > CU_LDS / (lds + 512) || res > 512 / regs) return false;
-  if (res > 1 && (double)a.units * MB * a.NTG <= NUM_CU * (res - 1.0)) return false;
-  const int gx = tile_columns(a.units, MB * a.NTG, res);
-  const double total = (double)gx * MB * a.NTG, wgs = total > NUM_CU ? ceil(total / NUM_CU) : 1.0, share = total > NUM_CU ? total / NUM_CU : 1.0;
-  const double turns = (double)ceil_div(a.units, gx), blocks = (double)ceil_div(a.NBK, tile::WAVES);
-  const double x_instr = 8.0 * (a.bands == 1 ? ceil_div((long long)a.CG * a.LP, 16 * a.vec_x) : a.CG * ceil_div(a.LP, 16 * a.vec_x));
-  const double d_instr = 8.0 * (a.bands == 1 ? ceil_div(a.CO * HoWo, 16 * a.vec_d) : a.CO * ceil_div(a.DL, 16 * a.vec_d));
-  p.cost = 450.0 * wgs * nt * mt + turns * (share * (blocks * 49.0 * nt * mt + 10.0 * x_instr + 22.0 * d_instr + 207.0) + 12000.0) +
-           (gx > 1 ? 13400.0 + 0.0193 * gx * a.RS : 0.0);
-  p.nt = nt, p.mt = mt, p.lds_bytes = (size_t)lds;
-  p.grid = dim3((unsigned)gx, (unsigned)(MB * a.NTG));
-  p.workspace_bytes = gx > 1 ? (size_t)gx * a.RS * sizeof(float) : 0;
-  a.inv_khkwp = 1.0f / (float)KHKWP, a.inv_kwp = 1.0f / (float)a.KWP, a.inv_wop = 1.0f / (float)a.WOP;
-  a.inv_dl = 1.0f / (float)a.DL;
-  a.by_band = tile::fast_div(a.bands);
-  return true;
+  const int resident = std::min(CU_LDS / ((int)lds + 512), 512 / regs);
+  const double x_instr = 8.0 * (a.bands == 1 ? up(a.CG * a.LP, 16 * a.vec_x) : a.CG * up(a.LP, 16 * a.vec_x));
+  const double d_instr = 8.0 * (a.bands == 1 ? up(a.CO * HoWo, 16 * a.vec_d) : a.CO * up(a.DL, 16 * a.vec_d));
+  for (int res = few; res <= 4 && res <= resident && (res <= 1 || (double)a.units * MB * a.NTG > NUM_CU * (res - 1.0)); ++res) {
+    const int gx = tile_columns(a.units, MB * a.NTG, res);
+    const long long total = (long long)gx * MB * a.NTG, wgs = total > NUM_CU ? ceil_div(total, NUM_CU) : 1;
+    const double share = total > NUM_CU ? (double)total / NUM_CU : 1.0, turns = up(a.units, gx);
+    const double cost = 450.0 * wgs * nt * mt + turns * (share * (blocks * 49.0 * nt * mt + 10.0 * x_instr + 22.0 * d_instr + 207.0) + 12000.0) +
+                        (gx > 1 ? 13400.0 + 0.0193 * gx * a.RS : 0.0);
+    if (best.nt && cost >= best.cost) continue;
+    p.cost = cost, p.lds_bytes = (size_t)lds;
+    p.grid = dim3((unsigned)gx, (unsigned)(MB * a.NTG));
+    p.workspace_bytes = gx > 1 ? (size_t)gx * a.RS * sizeof(float) : 0;
+    best = p;
+  }
 }
 
 Tile16WgradPlan plan_tile16_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
@@ -969,15 +1008,19 @@ Tile16WgradPlan plan_tile16_wgrad(int B, int Cin, int H, int W, int Cout, int KH
     for (int P = 1; P <= a.Wo && (P == 1 || (KW > 1 && P * Cout <= 16)); ++P) {
       if (a.Wo % P) continue;
       for (int mt = 1; mt <= (Cout > 16 ? 2 : 1); ++mt) {
-        const int NT = (int)ceil_div((long long)Cin * KH * (KW + P - 1), 16);
+        const int NT = up(Cin * KH * (KW + P - 1), 16);
         for (int nt : {1, 2, 3, 4, 6, 8, 12}) {
-          if (nt * mt > 16 || (nt > 1 && nt / 2 >= NT) || 16 * nt < KW + P - 1) continue;
+          if (nt * mt > 16 || (nt > 1 && nt / 2 >= NT) || 16 * nt < KW + P - 1 || !tile16_wgrad_form(p, best, P, mt, nt)) continue;
           for (int TH = 1; TH <= a.Ho; ++TH)
-            if (TH <= 2 || ceil_div(a.Ho, TH) != ceil_div(a.Ho, TH - 1))
-              for (int res = B > 64 ? 1 : 0; res <= 4; ++res)
-                if (tile16_wgrad_candidate(p, P, mt, nt, TH, res) && (!best.nt || p.cost < best.cost)) best = p;
+            if (TH <= 2 || up(a.Ho, TH) != up(a.Ho, TH - 1)) tile16_wgrad_candidates(best, p, TH, B > 64 ? 1 : 0);
         }
       }
+    }
+    if (best.nt) {
+      tile16::WgradArgs& b = best.a;
+      b.inv_khkwp = 1.0f / (float)(KH * b.KWP), b.inv_kwp = 1.0f / (float)b.KWP, b.inv_wop = 1.0f / (float)b.WOP;
+      b.inv_dl = 1.0f / (float)b.DL;
+      b.by_band = tile::fast_div(b.bands);
     }
     return best;
   });
