@@ -434,10 +434,14 @@ bool tile_args(tile::ConvArgs& a, int B, int M, int SC, int SH, int SW, int KH, 
   return true;
 }
 // Hands every unit worth considering to `consider`: packing, row and column tiles, images, rows and columns.
+// (Layers of one tap are packed too: as many matrix instructions, but P times fewer columns to address, and stores P times as
+// wide.  3000 images 2 -> 2, 24 x 24: forward 34.6 -> 10.7 us, input gradient 34.6 -> 10.5, bf16 36.2 -> 15.3; 500 images
+// 8 -> 8, 20 x 20: 9.5 -> 8.4.  In the weight gradient packing multiplies rows and taps alike: 22 -> 28 us at 700 images
+// 12 -> 7, 19 x 33.)
 template <typename CONSIDER>
 void tile_units(const tile::ConvArgs& a, CONSIDER consider) {
   const int M = a.M, OH = a.OH, OW = a.OW, B = a.B;
-  for (int P = 1; P <= OW && (P == 1 || (a.KW > 1 && P * M <= 16)); ++P) {
+  for (int P = 1; P <= OW && (P == 1 || P * M <= 16); ++P) {
     if ((P & (P - 1)) && P != 16 / M && OW % P) continue;  // powers of two (wide stores), divisors of the row, the one that fills the tile best
     for (int mt = 1; mt <= (M > 16 ? 2 : 1); ++mt)
       for (int nt = 1; nt <= 4; nt <<= 1) {

@@ -86,6 +86,22 @@ def test_runs_of_taps(case):
                  RTOL_ACT, "tiled conv_bwd_input")
 
 
+# One tap, columns packed: rows of whole and of ragged columns, several images or bands per unit, more than one chunk of
+# channels, one row of pixels, and maps that fill a row tile by themselves.
+@pytest.mark.parametrize("case", [(300, 2, 24, 24, 2), (78, 16, 27, 19, 2), (50, 32, 33, 10, 3), (1, 1, 5, 17, 1), (40, 1, 39, 37, 5), (90, 8, 21, 23, 4),
+                                  (200, 3, 1, 33, 7), (25, 40, 36, 36, 2), (33, 4, 14, 14, 16)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_packed_columns_of_one_tap(case, bf16):
+    B, Cin, H, W, Cout = case
+    x, k = oracle.round_bf16(inputs.make_signed((B, Cin, H, W), 97)), oracle.round_bf16(inputs.make_signed((Cout, Cin, 1, 1), 98))
+    d, b = oracle.round_bf16(inputs.make_signed((B, Cout, H, W), 99)), inputs.make_signed((Cout,), 100)
+    x64, k64, d64 = x.astype(np.float64), k[:, :, 0, 0].astype(np.float64), d.astype(np.float64)
+    out = np.tensordot(k64, x64, axes=(1, 1)).transpose(1, 0, 2, 3) + b[:, None, None]
+    d_in = np.tensordot(k64, d64, axes=(0, 1)).transpose(1, 0, 2, 3)
+    assert_close(host(binding.conv_fwd(dev(x), dev(k), dev(b), bf16=bf16)), out, RTOL_ACT, "tiled conv_fwd of one tap")
+    assert_close(host(binding.conv_bwd_input(dev(d), dev(k), H, W, bf16=bf16)), d_in, RTOL_ACT, "tiled conv_bwd_input of one tap")
+
+
 # Kernels of many channels or taps: weights that fit in LDS all at once, or only those of a chunk of channels, the last with fewer.
 @pytest.mark.parametrize("case", [(3, 100, 13, 14, 6, 7, 7), (4, 31, 40, 40, 31, 7, 7), (3, 60, 20, 20, 2, 5, 5), (2, 6, 13, 14, 100, 7, 7), (40, 3, 32, 32, 15, 5, 5),
                                   (5, 200, 24, 24, 2, 5, 5)])
