@@ -47,6 +47,17 @@ __device__ __forceinline__ float logistic_of_scaled(float z) {
   return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z));
 }
 
+// An operand rounded to bfloat16 (nearest, ties to even), as a float.
+__device__ __forceinline__ float round_bf16(float v) {
+  using f2v = float __attribute__((ext_vector_type(2)));
+  using bf2v = __bf16 __attribute__((ext_vector_type(2)));
+  return __uint_as_float(__builtin_bit_cast(unsigned, __builtin_convertvector(f2v{0.0f, v}, bf2v)) & 0xffff0000u);
+}
+template <bool ROUND>
+__device__ __forceinline__ float operand(float v) {
+  return ROUND ? round_bf16(v) : v;
+}
+
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 }  // namespace cnn

@@ -277,6 +277,10 @@ inline bool shape_fits(int Cin, int H, int W, int Cout, int KH, int KW) {
   return Cin == 1 && Cout == 6 && KH == 5 && KW == 5 && H == 28 && W == 28;
 }
 constexpr int BAND = 6 * 4 * 24;  // one band of the output: six maps, four rows
+template <bool ROUND>
+__device__ __forceinline__ f4 operands(f4 v) {
+  return f4{operand<ROUND>(v[0]), operand<ROUND>(v[1]), operand<ROUND>(v[2]), operand<ROUND>(v[3])};
+}
 template <int WAVES>
 struct __align__(16) FwdLds {
   float wa[C1F_KSTEPS * 64];  // A operand, [K step][lane]
@@ -284,7 +288,9 @@ struct __align__(16) FwdLds {
   float img[WAVES][NI];
   float band[WAVES][BAND];
 };
-template <int WAVES, int PARTS>
+// ROUND: the reduced-precision call.  One input channel leaves seven of the eight values of a bf16 item empty (cnn_tile_bf16.h),
+// so this kernel serves it too, the operands rounded on their way into LDS: 94 -> 37 us at 10000 images, 17 -> 7.5 at 1000.
+template <int WAVES, int PARTS, bool ROUND>
 __global__ __launch_bounds__(64 * WAVES) void forward_kernel(const float* __restrict__ in, const float* __restrict__ k,
                                                              const float* __restrict__ bias, float* __restrict__ out,
                                                              int B) {
@@ -297,7 +303,7 @@ __global__ __launch_bounds__(64 * WAVES) void forward_kernel(const float* __rest
 #pragma unroll
   for (int i = t; i < C1F_KSTEPS * 64; i += 64 * WAVES) {
     const int src = c1f_weight(i >> 6, i & 63);  // index into the flat parameter vector, k1 first
-    lds.wa[i] = src >= 0 ? k[src - OFF_K1] : 0.0f;
+    lds.wa[i] = src >= 0 ? operand<ROUND>(k[src - OFF_K1]) : 0.0f;
   }
   if (t < 8) lds.bias[t] = bias && t < 6 ? bias[t] : 0.0f;
   __syncthreads();
@@ -312,7 +318,7 @@ __global__ __launch_bounds__(64 * WAVES) void forward_kernel(const float* __rest
   float* img = lds.img[wave];
   float* band = lds.band[wave];
   for (size_t n = mine.first; n < (size_t)B; n += mine.step) {
-    store_pixels(img, px);
+    store_pixels(img, ROUND ? Pixels{operands<ROUND>(px.a), operands<ROUND>(px.b), operands<ROUND>(px.c), operands<ROUND>(px.d)} : px);
     wave_sync();
     if (n + mine.step < (size_t)B) px = load_pixels(in + (n + mine.step) * NI);  // in flight during this image
     float* dst = out + n * NC1;
@@ -464,6 +470,8 @@ struct __align__(16) BwdInputLds {
   float k[6 * BI_KPAD];
   float d[WAVES_PER_GROUP][BI_FLOATS];
 };
+// (ROUND: as in the forward kernel.)
+template <bool ROUND>
 __global__ __launch_bounds__(THREADS) void bwd_input_kernel(const float* __restrict__ d_out,
                                                             const float* __restrict__ k, float* __restrict__ d_in,
                                                             int B) {
@@ -471,7 +479,7 @@ __global__ __launch_bounds__(THREADS) void bwd_input_kernel(const float* __restr
   const int t = threadIdx.x, wave = t >> 6, l = t & 63;
   for (int e = t; e < 6 * BI_KPAD; e += THREADS) {
     const int m = e / BI_KPAD, tap = e - BI_KPAD * m;
-    lds.k[e] = tap < 25 ? k[m * 25 + tap] : 0.0f;
+    lds.k[e] = tap < 25 ? operand<ROUND>(k[m * 25 + tap]) : 0.0f;
   }
   float* d = lds.d[wave];
   for (int e = l; e < BI_FLOATS; e += 64) d[e] = 0.0f;  // the borders stay zero, the values are replaced per image
@@ -506,7 +514,7 @@ __global__ __launch_bounds__(THREADS) void bwd_input_kernel(const float* __restr
   for (size_t n = first; n < (size_t)B; n += G) {
 #pragma unroll
     for (int j = 0; j < BI_ROUNDS; ++j)
-      if (l + 64 * j < BI_PIECES) *reinterpret_cast<f4*>(d + put[j]) = cur[j];  // 16-byte aligned: rows of 28 floats
+      if (l + 64 * j < BI_PIECES) *reinterpret_cast<f4*>(d + put[j]) = operands<ROUND>(cur[j]);  // 16-byte aligned: rows of 28 floats
     wave_sync();
     if (n + G < (size_t)B) load_error(n + G, cur);  // in flight during this image
     float acc[14];

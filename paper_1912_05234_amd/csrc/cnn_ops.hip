@@ -41,12 +41,6 @@ inline unsigned grid_stream(size_t n) {
 typedef float vec2 __attribute__((ext_vector_type(2)));
 typedef float vec4 __attribute__((ext_vector_type(4)));
 
-// An operand as the arithmetic sees it: itself, or rounded to bfloat16 (nearest even).
-template <bool BF16>
-__device__ __forceinline__ float operand(float v) {
-  return BF16 ? __uint_as_float((unsigned)tile16::to_bf16(v) << 16) : v;
-}
-
 // out[b,co,y,x] = bias[co] + sum_{ci,u,v} in[b,ci,y+u,x+v] * k[co,ci,u,v]
 template <bool BF16>
 __global__ __launch_bounds__(TPB) void conv_fwd_kernel(const float* __restrict__ in,
@@ -489,34 +483,44 @@ void launch_tiled(void (*kernel)(const ARGS), dim3 grid, size_t lds_bytes, hipSt
   kernel<<<grid, tile::THREADS, lds_bytes, stream>>>(args);
 }
 
-template <bool BORDER, int RUN>
+template <bool BORDER, int RUN, bool ROUND>
 void launch_tile_conv_as(const TileConvPlan& p, hipStream_t stream) {
   switch (p.nt) {
-    case 1: launch_tiled(tile::conv_kernel<1, 1, BORDER, RUN>, p.grid, p.lds_bytes, stream, p.a); break;
-    case 2: launch_tiled(tile::conv_kernel<2, 1, BORDER, RUN>, p.grid, p.lds_bytes, stream, p.a); break;
-    default: launch_tiled(tile::conv_kernel<4, 1, BORDER, RUN>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 1: launch_tiled(tile::conv_kernel<1, 1, BORDER, RUN, ROUND>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 2: launch_tiled(tile::conv_kernel<2, 1, BORDER, RUN, ROUND>, p.grid, p.lds_bytes, stream, p.a); break;
+    default: launch_tiled(tile::conv_kernel<4, 1, BORDER, RUN, ROUND>, p.grid, p.lds_bytes, stream, p.a); break;
+  }
+}
+
+template <bool BORDER, bool ROUND>
+void launch_tile_conv_as(const TileConvPlan& p, hipStream_t stream) {
+  switch (p.run) {
+    case 2: return launch_tile_conv_as<BORDER, 2, ROUND>(p, stream);
+    case 4: return launch_tile_conv_as<BORDER, 4, ROUND>(p, stream);
+    default: return launch_tile_conv_as<BORDER, 1, ROUND>(p, stream);
   }
 }
 
 template <bool BORDER>
-void launch_tile_conv_as(const TileConvPlan& p, hipStream_t stream) {
-  switch (10 * p.mt + p.run) {
-    case 11: return launch_tile_conv_as<BORDER, 1>(p, stream);
-    case 12: return launch_tile_conv_as<BORDER, 2>(p, stream);
-    case 14: return launch_tile_conv_as<BORDER, 4>(p, stream);
-  }
-  switch (p.nt) {  // two row tiles
-    case 1: launch_tiled(tile::conv_kernel<1, 2, BORDER, 1>, p.grid, p.lds_bytes, stream, p.a); break;
-    case 2: launch_tiled(tile::conv_kernel<2, 2, BORDER, 1>, p.grid, p.lds_bytes, stream, p.a); break;
-    default: launch_tiled(tile::conv_kernel<4, 2, BORDER, 1>, p.grid, p.lds_bytes, stream, p.a); break;
+void launch_two_row_tiles(const TileConvPlan& p, hipStream_t stream) {
+  switch (p.nt) {
+    case 1: launch_tiled(tile::conv_kernel<1, 2, BORDER, 1, false>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 2: launch_tiled(tile::conv_kernel<2, 2, BORDER, 1, false>, p.grid, p.lds_bytes, stream, p.a); break;
+    default: launch_tiled(tile::conv_kernel<4, 2, BORDER, 1, false>, p.grid, p.lds_bytes, stream, p.a); break;
   }
 }
 
 int launch_tile_conv(const TileConvPlan& p, hipStream_t stream) {
-  if (p.a.linear)
-    launch_tile_conv_as<false>(p, stream);
+  if (p.mt == 2)
+    p.a.linear ? launch_two_row_tiles<false>(p, stream) : launch_two_row_tiles<true>(p, stream);
   else
-    launch_tile_conv_as<true>(p, stream);
+    p.a.linear ? launch_tile_conv_as<false, false>(p, stream) : launch_tile_conv_as<true, false>(p, stream);
+  return launched();
+}
+
+// With operands rounded to bfloat16 (one row tile).
+int launch_tile_conv_rounded(const TileConvPlan& p, hipStream_t stream) {
+  p.a.linear ? launch_tile_conv_as<false, true>(p, stream) : launch_tile_conv_as<true, true>(p, stream);
   return launched();
 }
 
@@ -735,13 +739,23 @@ inline unsigned image_groups(int B, int images) {
   return (unsigned)(g < 2 * NUM_CU ? g : 2 * NUM_CU);
 }
 
-void launch_conv1_fwd(const float* in, const float* k, const float* bias, float* out, int B, hipStream_t st) {
+template <bool ROUND>
+int launch_conv1_fwd(const float* in, const float* k, const float* bias, float* out, int B, hipStream_t st) {
   if (B <= FEW_IMAGES)
-    conv1::forward_kernel<6, 6><<<image_groups(B, 1), 64 * 6, 0, st>>>(in, k, bias, out, B);
+    conv1::forward_kernel<6, 6, ROUND><<<image_groups(B, 1), 64 * 6, 0, st>>>(in, k, bias, out, B);
   else if (B <= SPLIT_IMAGES)
-    conv1::forward_kernel<4, 2><<<image_groups(B, 2), 64 * 4, 0, st>>>(in, k, bias, out, B);
+    conv1::forward_kernel<4, 2, ROUND><<<image_groups(B, 2), 64 * 4, 0, st>>>(in, k, bias, out, B);
   else
-    conv1::forward_kernel<8, 1><<<image_groups(B, 8), 64 * 8, 0, st>>>(in, k, bias, out, B);
+    conv1::forward_kernel<8, 1, ROUND><<<image_groups(B, 8), 64 * 8, 0, st>>>(in, k, bias, out, B);
+  return launched();
+}
+
+// One output map: nothing for a matrix tile to share.
+template <bool ROUND>
+int launch_conv1_bwd_input(const float* d_out, const float* k, float* d_in, int B, hipStream_t st) {
+  const int groups = (B + conv1::WAVES_PER_GROUP - 1) / conv1::WAVES_PER_GROUP;
+  conv1::bwd_input_kernel<ROUND><<<groups < NUM_CU ? groups : NUM_CU, conv1::THREADS, 0, st>>>(d_out, k, d_in, B);  // 128 KB of LDS: one workgroup per compute unit
+  return launched();
 }
 
 void launch_conv2_fwd(const float* in, const float* k, const float* bias, float* out, int B, hipStream_t st) {
@@ -930,6 +944,38 @@ int launch_tile16_conv_as(const Tile16ConvPlan& p, hipStream_t stream) {
 int launch_tile16_conv(const Tile16ConvPlan& p, hipStream_t stream) {
   const bool border = p.a.t.pady || p.a.t.padx || p.a.t.strips > 1;
   return border ? launch_tile16_conv_as<true>(p, stream) : launch_tile16_conv_as<false>(p, stream);
+}
+
+// Forward and input gradient in reduced precision: items of eight channels on the bf16 matrix cores, or the fp32 kernel
+// with its operands rounded in LDS, whichever the two fits say is faster.  With few channels most of an item is zeros, and a
+// small call is over before its items are made.  ROUND_CLOCKS per 1024 floats of a unit's staged planes and ROUND_UNIT_CLOCKS for
+// the barrier behind them were fitted to 224 timed calls; the margin keeps calls where the fits err with the items (4 of the 85
+// calls that change are more than 3 % slower, 5 % at most).  Measured, us, items / rounded: 680 images 2 -> 2 of 29 x 22, 3 x 3
+// 12.4 / 8.2; 1000 images 1 -> 1 of 40 x 40, 7 x 7 20.6 / 15.0; 3 images 6 -> 5 of 6 x 18, one tap 5.3 / 4.8; 1500 images 7 -> 9 of
+// 20 x 20, 3 x 3 17.8 / 26.2.
+struct Conv16Plan {
+  Tile16ConvPlan items;
+  TileConvPlan rounded;
+  bool use_rounded() const {
+    constexpr double ROUND_CLOCKS = 190.0, ROUND_UNIT_CLOCKS = 140.0, MARGIN = 1.1;
+    if (rounded.mt != 1) return false;
+    if (!items.nt) return true;
+    const double per_cu = (double)ceil_div((long long)rounded.a.units * rounded.grid.y, NUM_CU) * rounded.a.chunks;
+    const double rounding = per_cu * (ROUND_CLOCKS * up(tile::conv_lds(rounded.a).buf, 1024) + ROUND_UNIT_CLOCKS);
+    return MARGIN * (rounded.cost + rounding) < items.cost;
+  }
+};
+
+Conv16Plan plan_conv16(const float* src, const float* w, const float* bias, float* dst, int B, int M, int SC,
+                       int SH, int SW, int KH, int KW, int OH, int OW, int pady, int padx, int flip) {
+  Conv16Plan p;
+  p.items = plan_tile16_conv(src, w, bias, dst, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip);
+  p.rounded = plan_tile_conv(src, w, bias, dst, B, M, SC, SH, SW, KH, KW, OH, OW, pady, padx, flip);
+  return p;
+}
+
+int launch_conv16(const Conv16Plan& p, hipStream_t stream) {
+  return p.use_rounded() ? launch_tile_conv_rounded(p.rounded, stream) : launch_tile16_conv(p.items, stream);
 }
 
 struct Tile16WgradPlan {
@@ -1159,10 +1205,8 @@ int cnn_conv_fwd(const float* in, const float* k, const float* bias, float* out,
                  int W, int Cout, int KH, int KW, void* hip_stream) {
   if (!in || !k || !out || !conv_args_ok(B, Cin, H, W, Cout, KH, KW)) return CNN_EINVAL;
   if (!aligned16(in) || !aligned16(k) || !aligned16(out) || (bias && !aligned16(bias))) return CNN_EINVAL;
-  if (conv1::shape_fits(Cin, H, W, Cout, KH, KW)) {  // the network's first convolution
-    launch_conv1_fwd(in, k, bias, out, B, (hipStream_t)hip_stream);
-    return launched();
-  }
+  if (conv1::shape_fits(Cin, H, W, Cout, KH, KW))  // the network's first convolution
+    return launch_conv1_fwd<false>(in, k, bias, out, B, (hipStream_t)hip_stream);
   if (conv2::shape_fits(Cin, H, W, Cout, KH, KW)) {  // the network's second convolution
     launch_conv2_fwd(in, k, bias, out, B, (hipStream_t)hip_stream);
     return launched();
@@ -1183,13 +1227,7 @@ int cnn_conv_bwd_input(const float* d_out, const float* k, float* d_in, int B, i
     launch_conv2_bwd_input(d_out, k, d_in, B, (hipStream_t)hip_stream);
     return launched();
   }
-  if (conv1::shape_fits(Cin, H, W, Cout, KH, KW)) {
-    // the shape of the network's first convolution: one output map, nothing for a matrix tile to share
-    const int groups = (B + conv1::WAVES_PER_GROUP - 1) / conv1::WAVES_PER_GROUP;
-    conv1::bwd_input_kernel<<<groups < NUM_CU ? groups : NUM_CU, conv1::THREADS, 0, (hipStream_t)hip_stream>>>(
-        d_out, k, d_in, B);  // 128 KB of LDS: one workgroup per compute unit
-    return launched();
-  }
+  if (conv1::shape_fits(Cin, H, W, Cout, KH, KW)) return launch_conv1_bwd_input<false>(d_out, k, d_in, B, (hipStream_t)hip_stream);
   const TileConvPlan p = plan_tile_conv(d_out, k, nullptr, d_in, B, Cin, Cout, H - KH + 1, W - KW + 1, KH, KW, H, W,
                                         KH - 1, KW - 1, 1);
   if (p.nt) return launch_tile_conv(p, (hipStream_t)hip_stream);
@@ -1223,8 +1261,9 @@ int cnn_conv_fwd_bf16(const float* in, const float* k, const float* bias, float*
                       int W, int Cout, int KH, int KW, void* hip_stream) {
   if (!in || !k || !out || !conv_args_ok(B, Cin, H, W, Cout, KH, KW)) return CNN_EINVAL;
   if (!aligned16(in) || !aligned16(k) || !aligned16(out) || (bias && !aligned16(bias))) return CNN_EINVAL;
-  const Tile16ConvPlan p = plan_tile16_conv(in, k, bias, out, B, Cout, Cin, H, W, KH, KW, H - KH + 1, W - KW + 1, 0, 0, 0);
-  if (p.nt) return launch_tile16_conv(p, (hipStream_t)hip_stream);
+  if (conv1::shape_fits(Cin, H, W, Cout, KH, KW)) return launch_conv1_fwd<true>(in, k, bias, out, B, (hipStream_t)hip_stream);
+  const Conv16Plan p = plan_conv16(in, k, bias, out, B, Cout, Cin, H, W, KH, KW, H - KH + 1, W - KW + 1, 0, 0, 0);
+  if (p.use_rounded() || p.items.nt) return launch_conv16(p, (hipStream_t)hip_stream);
   const size_t total = (size_t)B * Cout * (H - KH + 1) * (W - KW + 1);
   conv_fwd_kernel<true><<<grid_for(total), TPB, 0, (hipStream_t)hip_stream>>>(in, k, bias, out, total, Cin,
                                                                                H, W, Cout, KH, KW);
@@ -1235,9 +1274,12 @@ int cnn_conv_bwd_input_bf16(const float* d_out, const float* k, float* d_in, int
                             int Cout, int KH, int KW, void* hip_stream) {
   if (!d_out || !k || !d_in || !conv_args_ok(B, Cin, H, W, Cout, KH, KW)) return CNN_EINVAL;
   if (!aligned16(d_out) || !aligned16(k) || !aligned16(d_in)) return CNN_EINVAL;
-  const Tile16ConvPlan p = plan_tile16_conv(d_out, k, nullptr, d_in, B, Cin, Cout, H - KH + 1, W - KW + 1, KH, KW, H, W,
-                                            KH - 1, KW - 1, 1);
-  if (p.nt) return launch_tile16_conv(p, (hipStream_t)hip_stream);
+  // (one wave per image: 85 -> 55 us at 10000 images, as fast as the other forms at 1000, 7.8 -> 12 us at 64)
+  if (B > SPLIT_IMAGES && conv1::shape_fits(Cin, H, W, Cout, KH, KW))
+    return launch_conv1_bwd_input<true>(d_out, k, d_in, B, (hipStream_t)hip_stream);
+  const Conv16Plan p = plan_conv16(d_out, k, nullptr, d_in, B, Cin, Cout, H - KH + 1, W - KW + 1, KH, KW, H, W,
+                                   KH - 1, KW - 1, 1);
+  if (p.use_rounded() || p.items.nt) return launch_conv16(p, (hipStream_t)hip_stream);
   const size_t total = (size_t)B * Cin * H * W;
   conv_bwd_input_kernel<true><<<grid_for(total), TPB, 0, (hipStream_t)hip_stream>>>(d_out, k, d_in, total,
                                                                                      Cin, H, W, Cout, KH, KW);

@@ -391,7 +391,10 @@ __host__ __device__ constexpr int conv_residency(int nt, int mt) { return nt * m
 // read and one address for RUN matrix instructions.  Kernel times (us, one float at a time -> RUN): input gradient of 500
 // images 3 -> 16, 32 x 32, 5 x 5 38.5 -> 35.6 (4); 2585 images 2 -> 10, 22 x 18, 7 x 7 97 -> 94 (2); forward of 1376 images 3 ->
 // 3, 28 x 32, 5 x 5 23.6 -> 21.6 (4); the 23 of 120 calls on 60 random shapes that take runs 1.03x.
-template <int NT, int MT, bool BORDER, int RUN>
+// ROUND: the reduced-precision form for few channels or little work (cnn_ops.hip): operands are rounded to bfloat16 in LDS,
+// their products, exact in fp32, are summed as in the fp32 form.  (As a flag of the launch instead of a kernel of its own it
+// cost the small fp32 calls 0.3 us of 5.)
+template <int NT, int MT, bool BORDER, int RUN, bool ROUND>
 __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(const ConvArgs g) {
   extern __shared__ __align__(16) float lds[];
   const ConvLds L = conv_lds(g);
@@ -441,7 +444,7 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
       float* dst = wt + ((w.m0 * g.P + sh) * 4 + kq) * g.SP + 4 * (kk >> 4) + ks;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        if (w.m0 + i < maps) dst[i * g.P * 4 * g.SP] = w.v[i];
+        if (w.m0 + i < maps) dst[i * g.P * 4 * g.SP] = operand<ROUND>(w.v[i]);
     }
   };
   auto items = [&](int chunk) { return (g.resident ? g.SC : min(g.CC, g.SC - chunk * g.CC)) * KHKW * ((maps + 7) >> 3); };
@@ -520,6 +523,15 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
         lds_barrier();
       }
       weights(chunk, e, own);
+      lds_barrier();
+    }
+    if (ROUND) {
+      f4* x = reinterpret_cast<f4*>(xbuf + par * L.buf);
+#pragma unroll 1
+      for (int e = t; e < L.buf / 4; e += THREADS) {
+        const f4 v = x[e];
+        x[e] = f4{round_bf16(v[0]), round_bf16(v[1]), round_bf16(v[2]), round_bf16(v[3])};
+      }
       lds_barrier();
     }
     const Unit nxt = nunit == unit || !more ? cur : unit_at(g, nunit);
@@ -657,13 +669,6 @@ __device__ __forceinline__ void finish_wgrad(const ARGS& g, const f4 (&acc)[MT][
       for (int w = 0; w < WAVES; ++w) s += bs[w * MT * 16 + t * g.P + sh];
     g.out_b[(size_t)blockIdx.x * g.RS + co0 + t] = s;
   }
-}
-
-// An operand rounded to bfloat16 (nearest, ties to even), as a float.
-__device__ __forceinline__ float round_bf16(float v) {
-  using f2v = float __attribute__((ext_vector_type(2)));
-  using bf2v = __bf16 __attribute__((ext_vector_type(2)));
-  return __uint_as_float(__builtin_bit_cast(unsigned, __builtin_convertvector(f2v{0.0f, v}, bf2v)) & 0xffff0000u);
 }
 
 // ROUND: the reduced-precision form for few images (cnn_tile_bf16.h needs eight to fill its operands): operands are

@@ -43,16 +43,7 @@ using tile::wait_loads;
 using tile::WAVES;
 using bf8 = __bf16 __attribute__((ext_vector_type(8)));
 
-// fp32 -> bf16 bits, round to nearest even; a NaN stays a (quiet) NaN instead of having its
-// mantissa carried into the exponent
-__device__ __forceinline__ unsigned short to_bf16(float f) {
-  unsigned u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (unsigned short)(u >> 16);
-}
-// two at once: lo in bits 0..15, hi in bits 16..31 (the conversion of a float pair is one
-// instruction on gfx950, same rounding)
+// fp32 -> bf16 bits (nearest, ties to even), two at once: lo in bits 0..15, hi in bits 16..31
 __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
   using f2v = float __attribute__((ext_vector_type(2)));
   using bf2v = __bf16 __attribute__((ext_vector_type(2)));

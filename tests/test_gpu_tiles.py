@@ -116,6 +116,23 @@ def test_weight_tables(case, bf16):
                  RTOL_ACT, "tiled conv_bwd_input")
 
 
+# Reduced-precision calls that run an fp32 kernel with rounded operands (few channels, small calls, the network's first
+# layer in its three splits), on operands that rounding changes.
+@pytest.mark.parametrize("case", [(1, 1, 28, 28, 6, 5, 5), (700, 1, 28, 28, 6, 5, 5), (1500, 1, 28, 28, 6, 5, 5), (680, 2, 29, 22, 2, 3, 3), (100, 1, 40, 40, 1, 7, 7),
+                                  (3, 6, 6, 18, 5, 1, 1), (10, 1, 30, 36, 2, 3, 3), (600, 8, 14, 15, 8, 1, 1), (2, 40, 9, 11, 3, 3, 3), (5, 2, 4, 300, 2, 3, 5)])
+def test_rounded_operands(case):
+    B, Cin, H, W, Cout, KH, KW = case
+    x, k, b = inputs.make_signed((B, Cin, H, W), 101), inputs.make_signed((Cout, Cin, KH, KW), 102), dev(inputs.make_signed((Cout,), 103))
+    d = inputs.make_signed((B, Cout, H - KH + 1, W - KW + 1), 104)
+    xr, kr, dr = dev(oracle.round_bf16(x)), dev(oracle.round_bf16(k)), dev(oracle.round_bf16(d))
+    out, want = host(binding.conv_fwd(dev(x), dev(k), b, bf16=True)), host(binding.conv_fwd(xr, kr, b, valu=True)).astype(np.float64)
+    assert_close(out, want, RTOL_ACT, "rounded conv_fwd")
+    assert np.abs(host(binding.conv_fwd(dev(x), dev(k), b)) - want).max() > 20 * np.abs(out - want).max()
+    d_in, want = host(binding.conv_bwd_input(dev(d), dev(k), H, W, bf16=True)), host(binding.conv_bwd_input(dr, kr, H, W, valu=True)).astype(np.float64)
+    assert_close(d_in, want, RTOL_ACT, "rounded conv_bwd_input")
+    assert np.abs(host(binding.conv_bwd_input(dev(d), dev(k), H, W)) - want).max() > 20 * np.abs(d_in - want).max()
+
+
 # besides: channel counts on both sides of eight and a last group of eight images with one, seven and eight of them
 @pytest.mark.parametrize("case", CASES + [(7, 8, 10, 10, 8, 3, 3), (8, 9, 10, 10, 17, 3, 3), (257, 7, 12, 12, 33, 5, 5)])
 def test_tiled_convolutions_bf16(case):
