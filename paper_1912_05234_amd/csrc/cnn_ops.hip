@@ -532,6 +532,18 @@ struct TileWgradPlan {
   double cost = 0.0;
 };
 
+// Clocks of the weight gradient's parts beside its matrix instructions: per tap tile of a block and per block, per load of
+// x and of d_out with 16 and with 4 bytes per lane, per unit that a workgroup takes.  Unpacked plans: fit to 1924 timed plans of
+// 122 layers, 10 % rms; packed ones, whose loads of d_out are scattered: 12600 plans of the kernels before, and a factor that
+// brings the two together.  The plan picked is 4.3 % slower on average than the fastest of the sixteen or so that were timed
+// of a layer, 15 % in the worst twentieth.
+struct WgradClocks {
+  double tile, block, x16, x4, d16, d4, turn, scale;
+};
+inline WgradClocks wgrad_clocks(int P) {
+  return P == 1 ? WgradClocks{45.0, 135.0, 55.0, 25.0, 32.0, 17.5, 900.0, 1.0} : WgradClocks{5.0, 320.0, 19.0, 19.0, 33.0, 33.0, 2000.0, 1.05};
+}
+
 // As above for the weight gradient.  A form is its packing and the row and tap tiles of a workgroup; false when there is no
 // such form, or none of its units can be better than `best`.
 bool tile_wgrad_form(TileWgradPlan& p, const TileWgradPlan& best, int P, int mt, int nt) {
@@ -552,24 +564,27 @@ bool tile_wgrad_form(TileWgradPlan& p, const TileWgradPlan& best, int P, int mt,
   p.grid.y = (unsigned)(up(a.MT, mt) * a.NTG);
   if (!best.nt) return true;
   const double rounds = (double)a.B * a.Ho * a.WOP / 64.0 * p.grid.y / NUM_CU;
-  return 9500.0 + 256.0 * nt * mt + rounds * (69.0 * nt * mt + 320.0 + 33.0 * a.R) < best.cost;
+  const WgradClocks k = wgrad_clocks(P);
+  return k.scale * (9500.0 + 256.0 * nt * mt + rounds * (64.0 * nt * mt + k.tile * nt + k.block + (P == 1 ? k.d16 / 4.0 : k.d4) * a.R)) < best.cost;
 }
 
 // Keeps the best of one unit of p's form, `few` .. `most` workgroups per compute unit; 0: one workgroup column, which needs
-// no second kernel.  (Fit: 12600 plans, 10 % rms, 5 % lost on average.)
+// no second kernel.
 void tile_wgrad_candidates(TileWgradPlan& best, TileWgradPlan& p, int NB, int TH, int few, int most) {
   tile::WgradArgs& a = p.a;
   const int plane = a.H * a.W, gy = (int)p.grid.y, nt = p.nt, mt = p.mt;
+  const WgradClocks k = wgrad_clocks(a.P);
   const long long groups = NB == 1 ? a.B : ceil_div(a.B, NB), units = TH == a.Ho ? groups : groups * up(a.Ho, TH);
   if (units > 0x3fffffff || (long long)NB * a.Cout * a.Ho * a.Wo >= tile::FAR_SIZE / 4 || (long long)NB * TH * a.WOP > 4096) return;
   a.NB = NB, a.TH = TH, a.groups = (int)groups, a.bands = TH == a.Ho ? 1 : up(a.Ho, TH), a.units = (int)units;
   a.N = NB * TH * a.WOP, a.NBK = up(a.N, 16), a.NPS = 16 * a.NBK + 4;
-  const double blocks = up(a.NBK, tile::WAVES), mfma = 128.0 * blocks * nt * mt, d_instr = (double)a.R * up(a.NBK, 4);
-  const double per_block = blocks * (5.0 * nt + 320.0) + 33.0 * d_instr, work = (double)units * gy / NUM_CU;
+  a.vec_d = a.P == 1 && a.Ho * a.Wo % 4 == 0 && TH * a.Wo % 4 == 0 ? 16 : 4;
+  const double blocks = up(a.NBK, tile::WAVES), mfma = 128.0 * blocks * nt * mt, d_loads = a.R * (a.vec_d == 16 ? k.d16 * up(a.NBK, 16) : k.d4 * up(a.NBK, 4));
+  const double per_unit = blocks * (k.tile * nt + k.block) + d_loads, work = (double)units * gy / NUM_CU;
   auto second_kernel = [&](int gx) { return gx > 1 ? 6650.0 + 0.0097 * gx * a.RS + 2.4 * gx : 0.0; };
   // what every candidate of the unit costs at least
-  if (best.nt && 9500.0 + 256.0 * nt * mt + (work > 1.0 ? work : 1.0) * (mfma * 0.5 + per_block) + 2000.0 * up(a.units, tile_columns(a.units, gy, 4)) +
-                     second_kernel(tile_columns(a.units, gy, few)) >= best.cost)
+  if (best.nt && k.scale * (9500.0 + 256.0 * nt * mt + (work > 1.0 ? work : 1.0) * (mfma * 0.5 + per_unit) + k.turn * up(a.units, tile_columns(a.units, gy, 4)) +
+                            second_kernel(tile_columns(a.units, gy, few))) >= best.cost)
     return;
   a.RH = a.bands == 1 ? a.H : TH + a.KH - 1;
   if ((long long)NB * a.CG * a.RH * a.W > TILE_LDS_LIMIT / 4) return;
@@ -580,13 +595,13 @@ void tile_wgrad_candidates(TileWgradPlan& best, TileWgradPlan& p, int NB, int TH
   if (lds > TILE_LDS_LIMIT) return;
   const int regs = 4 * nt * mt + 3 * nt + 60;  // registers a wave needs, roughly
   const int resident = std::min(CU_LDS / ((int)lds + 512), 512 / regs);
-  auto loads = [&](int floats) { return a.vec_x == 16 ? up(floats, 256) : up(floats, 64); };
-  const double x_instr = (double)NB * (a.bands == 1 ? loads(a.LI) : a.CG * loads(a.LP)), around = per_block + 19.0 * x_instr;
+  auto loads = [&](int floats) { return a.vec_x == 16 ? k.x16 * up(floats, 256) : k.x4 * up(floats, 64); };
+  const double around = per_unit + NB * (a.bands == 1 ? loads(a.LI) : a.CG * loads(a.LP));
   for (int res = few; res <= most && res <= resident && (res <= 1 || (long long)a.units * gy > NUM_CU * (res - 1)); ++res) {
     const int gx = tile_columns(a.units, gy, res);
     const long long total = (long long)gx * gy, wgs = total > NUM_CU ? ceil_div(total, NUM_CU) : 1;
     const double share = total > NUM_CU ? (double)total / NUM_CU : 1.0, turns = up(a.units, gx);
-    const double cost = 9500.0 + 256.0 * wgs * nt * mt + turns * (share * (mfma * (wgs == 1 ? 2.0 : wgs == 2 ? 0.9 : 0.5) + around) + 2000.0) + second_kernel(gx);
+    const double cost = k.scale * (9500.0 + 256.0 * wgs * nt * mt + turns * (share * (mfma * (wgs == 1 ? 2.0 : wgs == 2 ? 0.9 : 0.5) + around) + k.turn) + second_kernel(gx));
     if (best.nt && cost >= best.cost) continue;
     p.cost = cost, p.lds_bytes = (size_t)lds;
     p.grid.x = (unsigned)gx;
@@ -694,22 +709,29 @@ int launch_tile_wgrad(TileWgradPlan& p, const float* in, const float* d_out, flo
                       hipStream_t st) {
   const int nk = p.a.RS - p.a.Cout, G = (int)p.grid.x;
   p.a.in = in, p.a.d_out = d_out, p.a.out_k = G > 1 ? part : d_k, p.a.out_b = G > 1 ? part + nk : d_bias;
-#define CNN_TILE_WGRAD(NT, MT) \
-  case 100 * MT + NT: launch_tiled(tile::wgrad_kernel<NT, MT, ROUND>, p.grid, p.lds_bytes, st, p.a); break
-  switch (100 * p.mt + p.nt) {
-    CNN_TILE_WGRAD(1, 1);
-    CNN_TILE_WGRAD(2, 1);
-    CNN_TILE_WGRAD(3, 1);
-    CNN_TILE_WGRAD(4, 1);
-    CNN_TILE_WGRAD(6, 1);
-    CNN_TILE_WGRAD(8, 1);
-    CNN_TILE_WGRAD(12, 1);
-    CNN_TILE_WGRAD(1, 2);
-    CNN_TILE_WGRAD(2, 2);
-    CNN_TILE_WGRAD(3, 2);
-    CNN_TILE_WGRAD(4, 2);
-    CNN_TILE_WGRAD(6, 2);
-    CNN_TILE_WGRAD(8, 2);
+#define CNN_TILE_WGRAD(KIND, NT, MT, PACKED) \
+  case 1000 * KIND + NT: launch_tiled(tile::wgrad_kernel<NT, MT, ROUND, PACKED>, p.grid, p.lds_bytes, st, p.a); break
+  switch (1000 * (p.mt == 2 ? 2 : p.a.P > 1 ? 1 : 0) + p.nt) {  // (two row tiles are never packed)
+    CNN_TILE_WGRAD(0, 1, 1, false);
+    CNN_TILE_WGRAD(0, 2, 1, false);
+    CNN_TILE_WGRAD(0, 3, 1, false);
+    CNN_TILE_WGRAD(0, 4, 1, false);
+    CNN_TILE_WGRAD(0, 6, 1, false);
+    CNN_TILE_WGRAD(0, 8, 1, false);
+    CNN_TILE_WGRAD(0, 12, 1, false);
+    CNN_TILE_WGRAD(1, 1, 1, true);
+    CNN_TILE_WGRAD(1, 2, 1, true);
+    CNN_TILE_WGRAD(1, 3, 1, true);
+    CNN_TILE_WGRAD(1, 4, 1, true);
+    CNN_TILE_WGRAD(1, 6, 1, true);
+    CNN_TILE_WGRAD(1, 8, 1, true);
+    CNN_TILE_WGRAD(1, 12, 1, true);
+    CNN_TILE_WGRAD(2, 1, 2, false);
+    CNN_TILE_WGRAD(2, 2, 2, false);
+    CNN_TILE_WGRAD(2, 3, 2, false);
+    CNN_TILE_WGRAD(2, 4, 2, false);
+    CNN_TILE_WGRAD(2, 6, 2, false);
+    CNN_TILE_WGRAD(2, 8, 2, false);
     default: return CNN_EINVAL;
   }
 #undef CNN_TILE_WGRAD
@@ -1104,9 +1126,9 @@ int launch_tile16_wgrad(Tile16WgradPlan& p, const float* in, const float* d_out,
 
 // The weight gradient in reduced precision: eight images at a time on the bf16 matrix cores, or (few images, few
 // operands) the fp32 kernel with rounded operands, whichever the two fits say is faster; the factor is what rounding
-// costs that kernel's vector unit.  Measured (us, the kernel before / eight images / rounded): 10000 images 6 -> 12 of
-// 12 x 12, 5 x 5 taps 34.9 / 27.3 / 46; 256 images 16 -> 32 of 28 x 28, 3 x 3 taps 2353 / 52 / 48; 577 images 6 -> 14
-// of 23 x 25, 3 x 3 taps 22.9 / 30.2 / 23.
+// costs that kernel's vector unit.  Measured (us, eight images / rounded): 10000 images 6 -> 12 of 12 x 12, 5 x 5 taps
+// 28.8 / 67; 256 images 16 -> 32 of 28 x 28, 3 x 3 taps 59 / 45; 900 images 4 -> 30 of 31 x 18, 3 x 3 taps 47 / 33; 172 layers
+// with this rule 1.4 % slower than with the faster of the two for each.
 struct Wgrad16Plan {
   Tile16WgradPlan eight;
   TileWgradPlan rounded;

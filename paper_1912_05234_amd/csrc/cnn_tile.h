@@ -81,15 +81,16 @@ static_assert(FAR >= FAR_SIZE && FAR <= 0x7fffffff - FAR, "sums of offsets outsi
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const float* base, int bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, bytes, 0x00020000);
 }
-// Lane i's VB bytes at byte offset `off` of the buffer to LDS at dst + i VB bytes; dst is the same in every lane.
+// Lane i's VB bytes at byte offset `off` (and `at`, the same in every lane) of the buffer to LDS at dst + i VB bytes; dst is
+// the same in every lane.
 template <int VB>
-__device__ __forceinline__ void buffer_to_lds(__amdgpu_buffer_rsrc_t rs, float* dst, unsigned off) {
+__device__ __forceinline__ void buffer_to_lds(__amdgpu_buffer_rsrc_t rs, float* dst, unsigned off, int at = 0) {
   static_assert(VB == 16 || VB == 4, "item size");
   __attribute__((address_space(3))) void* to = (__attribute__((address_space(3))) void*)dst;
   if (VB == 16)
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, to, 16, off, 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, to, 16, off, at, 0, 0);
   else
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, to, 4, off, 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, to, 4, off, at, 0, 0);
 }
 
 // Stages runs of consecutive floats: run r of `runs` is `len` floats at src + r * sstride, to LDS floats
@@ -575,7 +576,7 @@ struct WgradArgs {
   int RH, LP, LI;        // staged rows; LDS strides (floats) of a plane and an image
   int R;                 // rows of d_out held: min(16*MT of the workgroup, MR); row R is zero
   int N, NBK, NPS;       // slots of a unit, blocks of 16, row stride of the staged d_out
-  int vec_x;             // bytes per lane of the image loads: 16 or 4
+  int vec_x, vec_d;      // bytes per lane of the loads of images and of d_out: 16 or 4
   float inv_khkwp, inv_kwp, inv_slots, inv_wop;
   FastDiv by_band, by_p;
 };
@@ -671,9 +672,37 @@ __device__ __forceinline__ void finish_wgrad(const ARGS& g, const f4 (&acc)[MT][
   }
 }
 
+// The staged rows of d_out (its base is the first of them in the unit's first image): the first `have` slots exist, the
+// others are zeros.  An item of vec_d bytes is of one image: planes are whole items where there are several.
+__device__ __forceinline__ void stage_slots(const WgradArgs& g, const float* d, float* buf, int rows, int have, int wave, int l) {
+  const int HoWo = g.Ho * g.Wo, V = g.vec_d >> 2, all = 16 * g.NBK;
+  const bool by_piece = all > 64 * V * (WAVES - 1);  // waves share out the pieces of a row, or the rows
+  const __amdgpu_buffer_rsrc_t rs = buffer_at(d, FAR_SIZE);
+#pragma unroll 1
+  for (int c = by_piece ? 64 * V * wave : 0; c < all; c += by_piece ? 64 * V * WAVES : 64 * V) {
+    const int n = c + V * l;
+    int img, r;
+    divmod(n, g.TH * g.WOP, g.inv_slots, img, r);
+    const int off = n < have ? 4 * (img * g.Cout * HoWo + r) : FAR;
+    if (n < all) {
+#pragma unroll 1
+      for (int row = by_piece ? 0 : wave; row < rows; row += by_piece ? 1 : WAVES) {
+        if (V == 4)
+          buffer_to_lds<16>(rs, buf + row * g.NPS + c, off, 4 * row * HoWo);
+        else
+          buffer_to_lds<4>(rs, buf + row * g.NPS + c, off, 4 * row * HoWo);
+      }
+    }
+  }
+}
+
 // ROUND: the reduced-precision form for few images (cnn_tile_bf16.h needs eight to fill its operands): operands are
 // rounded to bfloat16 as they are read, their products, exact in fp32, are summed as in the fp32 form.
-template <int NT, int MT, bool ROUND>
+// PACKED: P > 1, a row of d_out is every P-th pixel and is staged float by float.  Otherwise the slots of an image are its
+// pixels in order, and come 16 bytes per lane where rows of slots and planes are whole fours (stage_slots).  Kernel times,
+// us, float by float -> 16 bytes: 1000 images 1 -> 32, 28 x 28, 3 x 3 47 -> 38; 500 images 3 -> 64, 32 x 32, 3 x 3 68 -> 52;
+// 2000 images 4 -> 16, 14 x 14, one tap 22.4 -> 17.6.
+template <int NT, int MT, bool ROUND, bool PACKED>
 __global__ __launch_bounds__(THREADS) void wgrad_kernel(const WgradArgs g) {
   extern __shared__ __align__(16) float lds[];
   const WgradLds L = wgrad_lds(g);
@@ -720,8 +749,12 @@ __global__ __launch_bounds__(THREADS) void wgrad_kernel(const WgradArgs g) {
       stage_runs<16>(x, buf + L.x, runs, rlen, sstride, dstride, wave, l);
     else
       stage_runs<4>(x, buf + L.x, runs, rlen, sstride, dstride, wave, l);
-    // d_out: one slot per lane; slots that do not exist (and, packed, pixels past the row's end) read as zero
+    // d_out: slots that do not exist (and, packed, pixels past the row's end) read as zero
     const int have = g.NB > 1 ? nb * SPB : th * g.WOP;
+    if (!PACKED) {
+      stage_slots(g, d + (size_t)row0 * HoWo, buf, rows, have, wave, l);
+      return;
+    }
 #pragma unroll 1
     for (int c = by_chunk ? wave : 0; c < chunks; c += by_chunk ? WAVES : 1) {
       const int n = 64 * c + l;

@@ -71,6 +71,22 @@ def test_weight_gradient_without_workspace_keeps_infinities_local(case, pixel, b
     assert_close(host(d_b), d.astype(np.float64).sum(axis=(0, 2, 3)), RTOL_ACT, "conv_bwd_bias beside an infinity")
 
 
+# Weight gradients whose columns are not packed: planes of d_out in whole fours (16 bytes per lane) or not, several images per
+# unit with a ragged last group, bands with a ragged last one, row blocks of one and of many maps, one map of many pixels.
+@pytest.mark.parametrize("case", [(301, 3, 6, 6, 12, 3, 3), (70, 3, 30, 30, 20, 3, 3), (50, 2, 9, 8, 17, 2, 3), (65, 2, 9, 9, 16, 3, 3), (7, 4, 40, 40, 9, 5, 5),
+                                  (90, 1, 28, 30, 33, 3, 3), (1001, 4, 14, 14, 16, 1, 1), (130, 5, 11, 13, 40, 3, 2), (257, 2, 5, 5, 9, 4, 4),
+                                  (66, 3, 20, 300, 12, 1, 3), (5, 30, 12, 14, 64, 3, 3), (200, 1, 28, 28, 1, 1, 1), (80, 3, 41, 21, 1, 1, 1)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_unpacked_weight_gradients(case, bf16):
+    B, Cin, H, W, Cout, KH, KW = case
+    x, d = inputs.make_signed((B, Cin, H, W), 105), inputs.make_signed((B, Cout, H - KH + 1, W - KW + 1), 106)
+    x, d = dev(oracle.round_bf16(x) if bf16 else x), dev(oracle.round_bf16(d) if bf16 else d)
+    d_k, d_b = binding.conv_bwd_weight(x, d, bf16=bf16)
+    p_k, p_b = binding.conv_bwd_weight(x, d, workspace=False)
+    assert_close(host(d_k), host(p_k).astype(np.float64), RTOL_ACT, "unpacked conv_bwd_weight")
+    assert_close(host(d_b), host(p_b).astype(np.float64), RTOL_ACT, "unpacked conv_bwd_bias")
+
+
 # Packed columns whose taps lie in runs of two or four: with and without a border, ragged rows, bands and channel chunks,
 # whole images per unit, and (the last two) rows of odd length, which have no runs without a border.
 @pytest.mark.parametrize("case", [(33, 3, 28, 32, 3, 5, 5), (500, 3, 32, 32, 15, 5, 5), (130, 2, 20, 11, 25, 5, 5), (18, 5, 33, 33, 2, 3, 3),
