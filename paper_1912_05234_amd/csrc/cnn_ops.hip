@@ -427,7 +427,10 @@ bool tile_args(tile::ConvArgs& a, int B, int M, int SC, int SH, int SW, int KH, 
   a.pady = pady, a.padx = padx, a.flip = flip;
   return true;
 }
-// Hands every unit worth considering to `consider`: packing, row and column tiles, images, rows and columns.
+// Hands every unit worth considering to `consider`: packing, row and column tiles, images, rows and columns.  Six
+// column tiles per wave only for whole images of 257 to 384 columns without a border, which four would cut into bands: 2000
+// images 2 -> 16, 20 x 20, 3 x 3 25.4 -> 20.6 us, bf16 22.2 -> 16.6; 700 images 12 -> 7, 19 x 33, one tap 17.1 -> 14.3 and 18.9 -> 14.6.
+// With a border, or elsewhere, they were 5 to 20 % slower as often as faster (two or three workgroups per compute unit).
 // (Layers of one tap are packed too: as many matrix instructions, but P times fewer columns to address, and stores P times as
 // wide.  3000 images 2 -> 2, 24 x 24: forward 34.6 -> 10.7 us, input gradient 34.6 -> 10.5, bf16 36.2 -> 15.3; 500 images
 // 8 -> 8, 20 x 20: 9.5 -> 8.4.  In the weight gradient packing multiplies rows and taps alike: 22 -> 28 us at 700 images
@@ -458,6 +461,8 @@ void tile_units(const tile::ConvArgs& a, CONSIDER consider) {
           for (int f = 1; f <= 4; f <<= 1) sizes(1, ceil_div(OH, bands * f), OWP);
         }
       }
+    const long long image = OH * ceil_div(OW, P);
+    if (!a.pady && !a.padx && B >= 2 * NUM_CU && image > 256 && image <= 384) consider(P, 1, 6, 1, OH, (int)ceil_div(OW, P));
   }
 }
 
@@ -488,7 +493,9 @@ void launch_tile_conv_as(const TileConvPlan& p, hipStream_t stream) {
   switch (p.nt) {
     case 1: launch_tiled(tile::conv_kernel<1, 1, BORDER, RUN, ROUND>, p.grid, p.lds_bytes, stream, p.a); break;
     case 2: launch_tiled(tile::conv_kernel<2, 1, BORDER, RUN, ROUND>, p.grid, p.lds_bytes, stream, p.a); break;
-    default: launch_tiled(tile::conv_kernel<4, 1, BORDER, RUN, ROUND>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 4: launch_tiled(tile::conv_kernel<4, 1, BORDER, RUN, ROUND>, p.grid, p.lds_bytes, stream, p.a); break;
+    default:
+      if constexpr (!BORDER) launch_tiled(tile::conv_kernel<6, 1, false, RUN, ROUND>, p.grid, p.lds_bytes, stream, p.a);
   }
 }
 
@@ -956,6 +963,9 @@ int launch_tile16_conv_as(const Tile16ConvPlan& p, hipStream_t stream) {
     case 11: launch_tiled(tile16::conv_kernel<1, 1, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
     case 12: launch_tiled(tile16::conv_kernel<2, 1, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
     case 14: launch_tiled(tile16::conv_kernel<4, 1, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
+    case 16:
+      if constexpr (!BORDER) launch_tiled(tile16::conv_kernel<6, 1, false>, p.grid, p.lds_bytes, stream, p.a);
+      break;
     case 21: launch_tiled(tile16::conv_kernel<1, 2, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
     case 22: launch_tiled(tile16::conv_kernel<2, 2, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;
     default: launch_tiled(tile16::conv_kernel<4, 2, BORDER>, p.grid, p.lds_bytes, stream, p.a); break;

@@ -118,6 +118,19 @@ def test_packed_columns_of_one_tap(case, bf16):
     assert_close(host(binding.conv_bwd_input(dev(d), dev(k), H, W, bf16=bf16)), d_in, RTOL_ACT, "tiled conv_bwd_input of one tap")
 
 
+# Whole images of 257 to 384 columns (six column tiles per wave): unpacked, packed with ragged rows, with runs of taps, three
+# row blocks, one tap.
+@pytest.mark.parametrize("case", [(600, 2, 20, 20, 16, 3), (700, 12, 19, 33, 7, 1), (520, 2, 32, 42, 4, 3), (520, 1, 34, 44, 3, 5), (513, 9, 21, 21, 33, 4),
+                                  (800, 4, 30, 46, 2, 1)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_six_column_tiles(case, bf16):
+    B, Cin, H, W, Cout, K = case
+    x, k = oracle.round_bf16(inputs.make_signed((B, Cin, H, W), 107)), oracle.round_bf16(inputs.make_signed((Cout, Cin, K, K), 108))
+    x, k, b = dev(x), dev(k), dev(inputs.make_signed((Cout,), 109))
+    assert_close(host(binding.conv_fwd(x, k, b, bf16=bf16)), host(binding.conv_fwd(x, k, b, valu=True)).astype(np.float64), RTOL_ACT,
+                 "tiled conv_fwd of six column tiles")
+
+
 # Kernels of many channels or taps: weights that fit in LDS all at once, or only those of a chunk of channels, the last with fewer.
 @pytest.mark.parametrize("case", [(3, 100, 13, 14, 6, 7, 7), (4, 31, 40, 40, 31, 7, 7), (3, 60, 20, 20, 2, 5, 5), (2, 6, 13, 14, 100, 7, 7), (40, 3, 32, 32, 15, 5, 5),
                                   (5, 200, 24, 24, 2, 5, 5)])
