@@ -947,7 +947,7 @@ Tile16ConvPlan plan_tile16_conv(const float* src, const float* w, const float* b
     if (best.nt) {
       tile16::ConvArgs& a = best.a;
       tile_constants(a.t);
-      a.inv_eights = 1.0f / (float)(a.C8 * (a.t.resident ? a.t.chunks : 1)), a.inv_places = a.inv_eights / (float)(KH * KW);
+      a.inv_places = 1.0f / (float)(a.C8 * (a.t.resident ? a.t.chunks : 1) * KH * KW);
       a.inv_c8 = 1.0f / (float)a.C8, a.by_c8 = tile::fast_div(a.C8);
       a.inv_plane = 1.0f / (float)(a.RI * a.CI), a.inv_ci = 1.0f / (float)a.CI;
     }

@@ -99,7 +99,7 @@ struct ConvArgs {
   // stay zero from the start.  A band of a bordered image turns all its rows, a strip all its columns: `edges`, cells
   // outside the image are written as zeros.
   int RI, CI, r0, c0, edges;
-  float inv_c8, inv_eights, inv_places;  // 1 / C8, 1 / the eights whose weights are in LDS, 1 / (KH KW those)
+  float inv_c8, inv_places;  // 1 / C8, 1 / (KH KW eights whose weights are in LDS)
   float inv_plane, inv_ci;  // 1 / (RI CI), 1 / CI
   FastDiv by_c8;
 };
@@ -157,9 +157,11 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
   auto issue = [&](const tile::Unit& u, int chunk) { stage_planes(g, u, chunk, x, wave, l); };
   // A in LDS: a thread takes (tap, eight channels) of two maps at a time, sixteen loads in flight, the first of them while LDS
   // is cleared and the first unit's loads are issued, and writes each eight to its P shifted places; the other places are
-  // zero from before (as in the fp32 kernel).  Against walking the places, three rows at a time:
-  // 18.8 -> 16.8 us for the input gradient of 500 images 3 -> 16, 32 x 32, 5 x 5, over 60 random shapes 1.06x forward and 1.08x
-  // input gradient (forward with seven by seven taps and twenty channels 0.95x: more trips).  A third map, or a second item in flight, costs registers that the NT = 4 forms spill (5 - 15 % slower forward).
+  // zero from before (as in the fp32 kernel).  Neighbouring lanes take neighbouring taps, which are neighbours in memory: with
+  // the eights of a tap side by side, the order of A, every load met three runs, and forward with seven by seven taps and
+  // twenty channels was slower than walking the places of A three rows at a time (115 images, 31 x 37: 23.2 / 27.0 / now 23.2 us;
+  // input gradient 35.2 / 37.8 / 34.4).  Against that walk over 60 random shapes 1.06x forward and 1.08x input gradient.  A
+  // third map, or a second item in flight, costs registers that the NT = 4 forms spill (5 - 15 % slower forward).
   const int K8 = 4 * g.NBK, maps = g.P == 1 ? min(g.R, g.MR - row0) : g.M;
   const __amdgpu_buffer_rsrc_t ws = buffer_at(g.w, 4 * g.M * g.SC * KHKW);
   const int mstep = 4 * (g.flip ? KHKW : g.SC * KHKW), cstep = 4 * (g.flip ? g.M * KHKW : KHKW);
@@ -172,7 +174,7 @@ __global__ __launch_bounds__(THREADS, conv_residency(NT, MT)) void conv_kernel(c
   auto load_item = [&](int chunk, int e, Item& w) {
     int grp, r, tap, c8, u, x0, ck = 0;
     divmod(e, KHKW * eights, a16.inv_places, grp, r);
-    divmod(r, eights, a16.inv_eights, tap, c8);
+    divmod(r, KHKW, g.inv_khkw, c8, tap);
     divmod(tap, g.KW, g.inv_kw, u, x0);
     w.m0 = 2 * grp;
     if (g.resident && g.chunks > 1) {
