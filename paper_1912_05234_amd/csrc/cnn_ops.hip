@@ -343,9 +343,9 @@ void tile_constants(tile::ConvArgs& a) {
   a.inv_khkw = 1.0f / (float)(a.KH * a.KW), a.inv_kw = 1.0f / (float)a.KW, a.inv_cc = 1.0f / (float)a.CC;
 }
 
-// Clocks per block of a column tile beside the matrix instructions, by the floats a lane reads at once (2 and 4: estimates
-// with which runs are taken where they fit).
-constexpr double RUN_CLOCKS[5] = {0.0, 80.0, 50.0, 0.0, 35.0};
+// Clocks per block of a column tile beside the matrix instructions, by the floats a lane reads at once: 12 and 23 fewer
+// for 2 and 4 in 61 and 7 pairs of timed plans that differ in nothing else (1.04x and 1.08x in time).
+constexpr double RUN_CLOCKS[5] = {0.0, 80.0, 68.0, 0.0, 57.0};
 
 // Keeps the best of one unit's candidates: runs, weights resident or not, 1 .. 4 workgroups per compute unit.  The cost is
 // an estimate of the kernel's clocks, linear in what a compute unit has to do: matrix instructions (32 clocks each, partly
