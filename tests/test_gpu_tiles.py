@@ -1,6 +1,7 @@
 """The image-tiled convolution kernels where their cutting can go wrong: ragged bands, strips of very wide images,
 channel chunks, several row blocks, packed columns that do not divide a row, one workgroup column, images beyond
-64 KB.  Against the plain kernels, which test_gpu_ops.py pins to the oracle."""
+64 KB.  Forward and input gradient against the plain kernels, which test_gpu_ops.py pins to the oracle; the weight gradient,
+of which small calls run the plain kernel themselves, against a double-precision sum on the host."""
 import numpy as np
 import pytest
 import torch
@@ -12,12 +13,17 @@ from parity import RTOL_ACT, assert_close
 pytestmark = pytest.mark.gpu
 
 # (B, Cin, H, W, Cout, KH, KW)
-CASES = [(2, 3, 9, 700, 5, 3, 3), (1, 1, 3, 2500, 1, 3, 3),            # strips (the second: no weight-gradient plan)
-         (2, 70, 17, 19, 70, 3, 3), (1, 300, 9, 9, 5, 3, 3),            # chunks, several row blocks and tap groups
+CASES = [(2, 3, 9, 700, 5, 3, 3), (1, 1, 3, 2500, 1, 3, 3),            # strips (weight gradient: the plain kernel)
+         (70, 3, 9, 700, 5, 3, 3), (66, 1, 4, 1000, 3, 3, 3),           # wide rows, bands of one of them
+         (2, 70, 17, 19, 70, 3, 3), (1, 300, 9, 9, 5, 3, 3),            # chunks, several row blocks and tap groups (the second's
+                                                                        # weight gradient: the plain kernel)
          (33, 3, 32, 32, 16, 5, 5), (70, 16, 28, 28, 32, 3, 3),         # bands with a ragged last one, two row tiles
          (40, 2, 11, 7, 3, 2, 3), (5, 1, 13, 27, 2, 7, 7), (9, 2, 14, 7, 1, 5, 5),  # packed, ragged rows
          (301, 4, 30, 13, 4, 3, 3), (1100, 5, 6, 9, 7, 1, 1),           # several images per unit, a ragged last group
-         (1, 18, 27, 34, 2, 5, 5), (6, 26, 16, 22, 1, 3, 3),            # one workgroup column (no second kernel)
+         (1, 18, 27, 34, 2, 5, 5), (6, 26, 16, 22, 1, 3, 3),            # few images, few maps (weight gradient: the plain kernel)
+         (4, 16, 13, 40, 1, 3, 3), (5, 30, 12, 14, 64, 3, 3),           # weight gradients of one workgroup column (no second kernel;
+                                                                        # and 2 images 70 -> 70 above)
+         (70, 300, 9, 9, 5, 3, 3),                                      # many tap groups
          (3, 12, 70, 60, 9, 4, 6)]
 
 
@@ -30,20 +36,33 @@ def host(t):
     return t.cpu().numpy()
 
 
+def weight_gradient(x, d, KH, KW):
+    """`backweights` and `backbias` summed over the batch, in double precision on the host."""
+    x, d = x.astype(np.float64), d.astype(np.float64)
+    Ho, Wo = d.shape[2:]
+    k = np.empty((d.shape[1], x.shape[1], KH, KW))
+    for u in range(KH):
+        for v in range(KW):
+            k[:, :, u, v] = np.tensordot(d, x[:, :, u:u + Ho, v:v + Wo], axes=((0, 2, 3), (0, 2, 3)))
+    return k, d.sum(axis=(0, 2, 3))
+
+
 @pytest.mark.parametrize("case", CASES)
 def test_tiled_convolutions(case):
     B, Cin, H, W, Cout, KH, KW = case
-    x = dev(inputs.make_signed((B, Cin, H, W), 71))
+    x, d = inputs.make_signed((B, Cin, H, W), 71), inputs.make_signed((B, Cout, H - KH + 1, W - KW + 1), 74)
+    p_k, p_b = weight_gradient(x, d, KH, KW)
+    x, d = dev(x), dev(d)
     k = dev(inputs.make_signed((Cout, Cin, KH, KW), 72))
     b = dev(inputs.make_signed((Cout,), 73))
-    d = dev(inputs.make_signed((B, Cout, H - KH + 1, W - KW + 1), 74))
     assert_close(host(binding.conv_fwd(x, k, b)), host(binding.conv_fwd(x, k, b, valu=True)).astype(np.float64), RTOL_ACT, "tiled conv_fwd")
     assert_close(host(binding.conv_bwd_input(d, k, H, W)), host(binding.conv_bwd_input(d, k, H, W, valu=True)).astype(np.float64),
                  RTOL_ACT, "tiled conv_bwd_input")
-    d_k, d_b = binding.conv_bwd_weight(x, d)
-    p_k, p_b = binding.conv_bwd_weight(x, d, workspace=False)
-    assert_close(host(d_k), host(p_k).astype(np.float64), RTOL_ACT, "tiled conv_bwd_weight")
-    assert_close(host(d_b), host(p_b).astype(np.float64), RTOL_ACT, "tiled conv_bwd_bias")
+    for workspace in (True, False):
+        d_k, d_b = binding.conv_bwd_weight(x, d, workspace=workspace)
+        assert_close(host(d_k), p_k, RTOL_ACT, "tiled conv_bwd_weight")
+        assert_close(host(d_b), p_b, RTOL_ACT, "tiled conv_bwd_bias")
+    d_k, _ = binding.conv_bwd_weight(x, d)
     again, none = binding.conv_bwd_weight(x, d, want_bias=False)
     assert none is None and torch.equal(again, d_k)
 
@@ -59,16 +78,13 @@ def test_weight_gradient_without_workspace_keeps_infinities_local(case, pixel, b
     Ho, Wo = H - KH + 1, W - KW + 1
     x, d = oracle.round_bf16(inputs.make_signed((B, Cin, H, W), 95)), oracle.round_bf16(inputs.make_signed((B, Cout, Ho, Wo), 96))
     x[pixel] = np.inf
-    ref = np.zeros((Cout, Cin, KH, KW))
-    with np.errstate(invalid="raise"):  # one infinity and no zeros: every sum has a value
-        for u in range(KH):
-            for v in range(KW):
-                ref[:, :, u, v] = np.einsum("bchw,bohw->oc", x[:, :, u:u + Ho, v:v + Wo].astype(np.float64), d.astype(np.float64))
+    ref, ref_b = weight_gradient(x, d, KH, KW)
+    assert not np.isnan(ref).any()  # one infinity and no zeros: every sum has a value
     d_k, d_b = binding.conv_bwd_weight(dev(x), dev(d), workspace=False, bf16=bf16)
     d_k, hit = host(d_k), np.isinf(ref)
     assert 0 < hit.sum() < hit.size and np.array_equal(d_k[hit], ref[hit].astype(np.float32))
     assert_close(d_k[~hit], ref[~hit], RTOL_ACT, "conv_bwd_weight beside an infinity")
-    assert_close(host(d_b), d.astype(np.float64).sum(axis=(0, 2, 3)), RTOL_ACT, "conv_bwd_bias beside an infinity")
+    assert_close(host(d_b), ref_b, RTOL_ACT, "conv_bwd_bias beside an infinity")
 
 
 # Weight gradients whose columns are not packed: planes of d_out in whole fours (16 bytes per lane) or not, several images per
@@ -80,11 +96,10 @@ def test_weight_gradient_without_workspace_keeps_infinities_local(case, pixel, b
 def test_unpacked_weight_gradients(case, bf16):
     B, Cin, H, W, Cout, KH, KW = case
     x, d = inputs.make_signed((B, Cin, H, W), 105), inputs.make_signed((B, Cout, H - KH + 1, W - KW + 1), 106)
-    x, d = dev(oracle.round_bf16(x) if bf16 else x), dev(oracle.round_bf16(d) if bf16 else d)
-    d_k, d_b = binding.conv_bwd_weight(x, d, bf16=bf16)
-    p_k, p_b = binding.conv_bwd_weight(x, d, workspace=False)
-    assert_close(host(d_k), host(p_k).astype(np.float64), RTOL_ACT, "unpacked conv_bwd_weight")
-    assert_close(host(d_b), host(p_b).astype(np.float64), RTOL_ACT, "unpacked conv_bwd_bias")
+    p_k, p_b = weight_gradient(oracle.round_bf16(x) if bf16 else x, oracle.round_bf16(d) if bf16 else d, KH, KW)
+    d_k, d_b = binding.conv_bwd_weight(dev(x), dev(d), bf16=bf16)
+    assert_close(host(d_k), p_k, RTOL_ACT, "unpacked conv_bwd_weight")
+    assert_close(host(d_b), p_b, RTOL_ACT, "unpacked conv_bwd_bias")
 
 
 # Packed columns whose taps lie in runs of two or four: with and without a border, ragged rows, bands and channel chunks,
@@ -169,15 +184,15 @@ def test_tiled_convolutions_bf16(case):
     x = oracle.round_bf16(inputs.make_signed((B, Cin, H, W), 81))
     k = oracle.round_bf16(inputs.make_signed((Cout, Cin, KH, KW), 82))
     d = oracle.round_bf16(inputs.make_signed((B, Cout, H - KH + 1, W - KW + 1), 83))
+    p_k, p_b = weight_gradient(x, d, KH, KW)
     x, k, d, b = dev(x), dev(k), dev(d), dev(inputs.make_signed((Cout,), 84))  # rounding again changes nothing
     assert_close(host(binding.conv_fwd(x, k, b, bf16=True)), host(binding.conv_fwd(x, k, b, valu=True)).astype(np.float64),
                  RTOL_ACT, "tiled conv_fwd_bf16")
     assert_close(host(binding.conv_bwd_input(d, k, H, W, bf16=True)),
                  host(binding.conv_bwd_input(d, k, H, W, valu=True)).astype(np.float64), RTOL_ACT, "tiled conv_bwd_input_bf16")
     d_k, d_b = binding.conv_bwd_weight(x, d, bf16=True)
-    p_k, p_b = binding.conv_bwd_weight(x, d, workspace=False)
-    assert_close(host(d_k), host(p_k).astype(np.float64), RTOL_ACT, "tiled conv_bwd_weight_bf16")
-    assert_close(host(d_b), host(p_b).astype(np.float64), RTOL_ACT, "tiled conv_bwd_bias_bf16")
+    assert_close(host(d_k), p_k, RTOL_ACT, "tiled conv_bwd_weight_bf16")
+    assert_close(host(d_b), p_b, RTOL_ACT, "tiled conv_bwd_bias_bf16")
     again, none = binding.conv_bwd_weight(x, d, want_bias=False, bf16=True)
     assert none is None and torch.equal(again, d_k)
 
