@@ -127,7 +127,7 @@ def main():
         "vs_baseline": None,
         "dtype": "f32",
         "data": "synthetic",
-        "config": {"workload": "configs[1]: 1 epoch over 60000 synthetic 28x28 fp32 images, batch %d, "
+        "config": {"workload": "1 epoch over 60000 synthetic 28x28 fp32 images, batch %d, "
                                "SGD lr 0.05 (steps cycle over the epoch's batches)" % args.batch,
                    "batch": args.batch, "images_resident": N_TRAIN, "lr": LR},
         "roofline": {

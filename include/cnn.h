@@ -139,9 +139,10 @@ int cnn_profile_begin(cnn_ctx* ctx, int capacity);
 int cnn_profile_read(cnn_ctx* ctx, float* ms, int capacity, int* n_recorded);
 
 /* ---- Stateless per-operation entry points (batch axis first, NCHW). ----------
- * No context, no device state: results depend on the arguments alone.  (The host keeps one small
- * cache of launch parameters per tensor shape -- an LDS row stride chosen by a bank-conflict
- * model, a pure function of the shape -- guarded by a mutex; calls from several threads are fine.)
+ * No context, no device state: results depend on the arguments alone.  (For convolution and fully
+ * connected calls the host remembers launch plans by shape, batch included: four tables of 256 plans,
+ * each guarded by a mutex, a plan being a pure function of the shape.  Choosing one takes a few
+ * microseconds.  Calls from several threads are fine.)
  * conv = valid cross-correlation, no kernel flip (listing `conv`), over all Cin
  * input maps per output map plus bias (listing `mconv`), no activation:
  *   out[b,co,y,x] = bias[co] + sum_{ci,u,v} in[b,ci,y+u,x+v] * k[co,ci,u,v]
@@ -164,17 +165,20 @@ int cnn_conv_bwd_input(const float* d_out, const float* k, float* d_in, int B, i
  * comparison leg of the per-layer measurement (is the implicit-GEMM form on the matrix cores
  * faster than the vector unit?), and the form to call when the data may hold NaN or infinity:
  * it multiplies nothing by padding zeros.  Same arguments and results to rounding; any shape.
- * (For the weight gradient the same role is played by cnn_conv_bwd_weight with a NULL workspace.) */
+ * (For the weight gradient the same role is played by cnn_conv_bwd_weight with a NULL workspace, whatever
+ * its size query says.) */
 int cnn_conv_fwd_valu(const float* in, const float* k, const float* bias, float* out, int B, int Cin,
                       int H, int W, int Cout, int KH, int KW, void* hip_stream);
 int cnn_conv_bwd_input_valu(const float* d_out, const float* k, float* d_in, int B, int Cin, int H,
                             int W, int Cout, int KH, int KW, void* hip_stream);
 /* Reduced-precision forms of cnn_conv_fwd and cnn_conv_bwd_input, same arguments, same fp32 tensors: every operand
- * (input or output error, and kernel) is rounded to bfloat16 (nearest, ties to even) as it is read,
- * products are summed in fp32 on the bf16 matrix cores, bias and result stay fp32.  The paper
- * computes in `float` (Section 3, listings `conv` and `backin`); these trade its 1e-5 agreement for
- * matrix-core throughput: the result is the plain definition applied to the rounded operands, to
- * fp32 summation accuracy.  Shapes that do not fit in LDS run a plain kernel with the same rounding. */
+ * (input or output error, and kernel) is rounded to bfloat16 (nearest, ties to even) on its way into LDS, the
+ * products, exact in fp32, are summed in fp32, bias and result stay fp32.  The paper computes in `float`
+ * (Section 3, listings `conv` and `backin`); these trade its 1e-5 agreement for matrix-core throughput: the
+ * result is the plain definition applied to the rounded operands, to fp32 summation accuracy.  They run on the
+ * bf16 matrix cores, eight input channels to an operand; where channels are few or the call is small, on the
+ * fp32 ones, which are then no slower (the network's first layer takes as long as in fp32).  Shapes whose rows
+ * fit no LDS tile run a plain kernel with the same rounding. */
 int cnn_conv_fwd_bf16(const float* in, const float* k, const float* bias, float* out, int B, int Cin,
                       int H, int W, int Cout, int KH, int KW, void* hip_stream);
 int cnn_conv_bwd_input_bf16(const float* d_out, const float* k, float* d_in, int B, int Cin, int H,
@@ -182,10 +186,13 @@ int cnn_conv_bwd_input_bf16(const float* d_out, const float* k, float* d_in, int
 /* `backweights` and `backbias`, summed over the batch:
  *   d_k[co,ci,u,v] = sum_{b,y,x} in[b,ci,y+u,x+v] * d_out[b,co,y,x];  d_bias[co] = sum d_out[:,co].
  * d_bias may be NULL.  `workspace` is device memory (16-byte aligned) for partial sums that the call
- * may overwrite; with at least cnn_conv_bwd_weight_workspace_bytes() bytes the matrix-core kernel
- * runs, with NULL or fewer bytes a slower kernel that needs none.  The summation order is fixed in
- * either case (the two orders differ).  The size query returns 0 for invalid arguments and for
- * shapes only the slower kernel serves. */
+ * may overwrite; with at least cnn_conv_bwd_weight_workspace_bytes() bytes a matrix-core kernel
+ * runs, with NULL always the plain kernel, which is slower (except for some calls on few images) and
+ * needs none.  With fewer bytes it is the plain kernel too; only the network's two convolutions also
+ * run in a smaller one, down to ceil(min(B, 4096) / 8) rows of 2112 bytes (first) or 10304 bytes
+ * (second), with as many workgroups as it has rows for.  The summation order is fixed in each case
+ * (the orders differ).  The size query returns 0 for invalid arguments
+ * and for shapes that only the plain kernel serves. */
 size_t cnn_conv_bwd_weight_workspace_bytes(int B, int Cin, int H, int W, int Cout, int KH, int KW);
 int cnn_conv_bwd_weight(const float* in, const float* d_out, float* d_k, float* d_bias, int B,
                         int Cin, int H, int W, int Cout, int KH, int KW, void* workspace,
@@ -197,8 +204,8 @@ int cnn_conv_bwd_weight(const float* in, const float* d_out, float* d_k, float* 
  * therefore bitwise the same d_k / d_bias as cnn_conv_bwd_weight with a sufficient workspace.  The
  * call allocates and frees nothing.  Returns CNN_ESCRATCH, with nothing enqueued, when the shape
  * would need more partial sums than the buffer holds (cnn_conv_bwd_weight_workspace_bytes() tells:
- * the network's layers need 2 MiB (C1) and 10.1 MiB (C2) at any batch size); shapes that only the
- * slower kernel serves need no scratch and are accepted.  All calls on one GPU share that GPU's
+ * the network's layers need at most 1.1 MB (C1) and 5.3 MB (C2) at any batch size); shapes that only the
+ * plain kernel serves need no scratch and are accepted.  All calls on one GPU share that GPU's
  * buffer: two calls whose kernels may overlap on one GPU (different streams, different threads)
  * race, so serialise them.  The buffer's address on a device is looked up at the first call on
  * that device (no allocation either). */
@@ -206,8 +213,9 @@ int cnn_conv_bwd_weight(const float* in, const float* d_out, float* d_k, float* 
 int cnn_conv_bwd_weight_static(const float* in, const float* d_out, float* d_k, float* d_bias, int B,
                                int Cin, int H, int W, int Cout, int KH, int KW, void* hip_stream);
 /* Reduced-precision form of cnn_conv_bwd_weight, same arguments and workspace rules (its own size
- * query): `in` and `d_out` are rounded to bfloat16 as they are read, products are summed in fp32 on
- * the bf16 matrix cores; d_bias is the fp32 sum of the rounded d_out. */
+ * query; NULL: the plain kernel with the same rounding): `in` and `d_out` are rounded to bfloat16 as they
+ * are read, products are summed in fp32 on the bf16 matrix cores (eight images to an operand) or, for few
+ * images and few operands, the fp32 ones; d_bias is the fp32 sum of the rounded d_out. */
 size_t cnn_conv_bwd_weight_bf16_workspace_bytes(int B, int Cin, int H, int W, int Cout, int KH, int KW);
 int cnn_conv_bwd_weight_bf16(const float* in, const float* d_out, float* d_k, float* d_bias, int B,
                              int Cin, int H, int W, int Cout, int KH, int KW, void* workspace,

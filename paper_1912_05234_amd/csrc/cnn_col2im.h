@@ -4,7 +4,7 @@
 //   T[(c,u,v), p] = sum_j k[j,c,u,v] * d_out[j,p],      d_in[c, y(p)+u, x(p)+v] += T[(c,u,v), p]
 // one wave per image.  The 150 rows of T fill ten 16-row tiles of v_mfma_f32_16x16x4_f32 (K = 12
 // output maps in three steps, four tiles of sixteen pixels): 120 matrix instructions per image, where
-// the general kernel (cnn_igemm.h: a forward convolution over the bordered error) needs 414.  T is
+// a forward convolution over the bordered error (cnn_tile.h) needs 414.  T is
 // added into an LDS copy of d_in in rounds of read-add-write whose targets cannot collide; the
 // tiling of the taps, the two halves of the maps 4 and 5 and the rounds are those of the fused
 // training step and are described there (cnn_wave.h: bwd_tap, bwd_packed_source, phase 6 of

@@ -1,8 +1,8 @@
 // Convolution calls for the shapes of the network's own two convolution layers, ONE WAVE PER IMAGE,
 // in the GEMM forms of the fused training step (arXiv 1912.05234, Section 3: listings conv / mconv,
 // backweights, backbias).  An image of these layers is small enough for one wave to hold in its LDS,
-// which saves the barriers and the staging for shared groups of images that the general kernels
-// (cnn_igemm.h) pay; eight waves per workgroup, two workgroups per compute unit.  A call on few images would be
+// which saves the barriers and the staging for shared groups of images that the image-tiled kernels
+// (cnn_tile.h) pay; eight waves per workgroup, two workgroups per compute unit.  A call on few images would be
 // bound by the chain of one image's matrix instructions in one wave (about 2 us; twice that with eight images in a
 // workgroup of two waves per SIMD), so there PARTS waves, each with its own copy of the image, share its pixels:
 // the forward passes by output tiles or bands (results bitwise the same), the weight gradients by the pixels they
@@ -16,8 +16,7 @@
 //                    the output error is the A operand straight from global memory, the sums stay
 //                    in registers over all of a wave's images; the waves of a workgroup are
 //                    added through LDS in a fixed order and the workgroup writes one set of partial
-//                    tiles in the layout of the general kernel, whose second kernel adds the
-//                    workgroups' partials
+//                    tiles, which igemm::wgrad_reduce_kernel adds up
 //   (the input gradient of this shape is cnn_col2im.h)
 // namespace conv1: one input and six output maps, 5 x 5 kernel, 28 x 28 input: forward and weight
 //   gradient as GEMMs over pixel pairs, 144 per image each, and the input gradient on the vector
@@ -269,7 +268,7 @@ inline size_t bwd_weight_workspace_bytes(unsigned groups) { return sizeof(float)
 // operation moves 3.1 KB in and 13.8 KB out per image and is bound by those stores: the three tiles of
 // a band of four pixel rows are collected in LDS as out[6][4][24] and leave as six runs of 384
 // consecutive bytes in 16-byte items with the non-temporal hint (8-byte stores straight from the
-// result registers were 8 % slower than the general kernel once the output no longer fits the
+// result registers were 8 % slower than a kernel of four waves per group of images once the output no longer fits the
 // last-level cache).
 namespace conv1 {
 
@@ -360,8 +359,8 @@ __global__ __launch_bounds__(64 * WAVES) void forward_kernel(const float* __rest
 // reads) comes in three chunks of eight rows, d1c[6][8][24] with the maps D1C_MAP apart, the next
 // chunk in registers while the current one is multiplied.  The sums stay in registers over all of
 // a wave's images; the workgroup's waves are added in a fixed order and one set of partial
-// tiles goes to the workspace in the general kernel's layout for P = 2 (rows 2 m + sh, columns
-// 6 u + v'; bias rows 2 m + sh), which its second kernel joins and adds.
+// tiles goes to the workspace in the layout that igemm::wgrad_reduce_kernel joins and adds for P = 2 (rows
+// 2 m + sh, columns 6 u + v'; bias rows 2 m + sh).
 constexpr int CHUNK_PIECES = 6 * 8 * 24 / 4;  // 16-byte pieces of an error chunk
 template <int WAVES>
 struct __align__(16) WgradLds {

@@ -2,7 +2,7 @@
 // wave working straight from global memory (arXiv 1912.05234, Section 3: the layer is `mconv` with a
 // kernel as large as its input; its backward forms are backin, backweights and backbias).  A row of
 // this layer is 768 bytes in and 40 bytes out, so the calls are bound by memory and by their own
-// set-up; the general kernels (cnn_igemm.h) stage groups of images in LDS for four waves that share
+// set-up; the image-tiled kernels (cnn_tile.h) stage groups of images in LDS for four waves that share
 // them, which costs barriers and staging time that rows this small do not need.  Here the operands
 // of v_mfma_f32_16x16x4_f32 are loaded in the instruction's own layout, the K index permuted so that a
 // lane's four K elements are 16 consecutive bytes:
@@ -14,8 +14,8 @@
 //                    K = images four per step; column n16 of tile nt is input 64 (nt / 4) + 4 n16 + nt % 4,
 //                    so that a lane reads three 16-byte pieces per image; the sums stay in registers
 //                    over a wave's steps, the eight waves of a workgroup are added through LDS in a
-//                    fixed order and the workgroup writes one set of partial tiles in the layout of
-//                    the general kernel, whose second kernel adds the workgroups' partials.
+//                    fixed order and the workgroup writes one set of partial tiles, which
+//                    igemm::wgrad_reduce_kernel adds up.
 #pragma once
 
 #include "cnn_wave.h"

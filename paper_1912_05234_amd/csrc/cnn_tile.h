@@ -29,9 +29,9 @@
 // What bounds it (timed plans, cnn_ops.hip): a block of a column tile costs 144 clocks of its SIMD against the
 // 128 of its matrix instructions; around that a unit pays about 500 + 83 NT clocks of staging, addressing and
 // stores, and a workgroup one memory round trip (1700 clocks) per unit, the largest share for layers with few
-// channels.  500 images 3 -> 16 maps, 32 x 32, 5 x 5: forward 25 us, input gradient 36 us, weight gradient 32 us (the
+// channels.  500 images 3 -> 16 maps, 32 x 32, 5 x 5: forward 25 us, input gradient 36 us, weight gradient 24.5 + 4.6 us (the
 // kernels before, which needed whole images in LDS: 26, 290 and 1540 us); 256 images 16 -> 32, 28 x 28, 3 x 3: 28,
-// 36, 41 us (364, 460, 2020 us).  Without its matrix instructions and operand reads the input gradient of the first
+// 35, 38 + 5 us (364, 460, 2020 us).  Without its matrix instructions and operand reads the input gradient of the first
 // takes 25 of 46 us, without the weights' way into LDS 33, without staging 40, without stores 45 (before the weights
 // were loaded as below).  Small calls are bound by what comes before the first matrix instruction.
 #pragma once

@@ -16,9 +16,10 @@
 // instructions run.  LDS traffic bounds these kernels (16 bytes per lane and operand feed an instruction of 16
 // clocks), so a wave owns NT column tiles, or all tap tiles, per weight operand it reads.  Measured (forward / input
 // gradient / weight gradient, us; in brackets one workgroup per group of whole images, or one thread per element where
-// an image did not fit the LDS): 10000 images 6 -> 12 maps, 12 x 12, 5 x 5 taps 22 / 34 / 27 (32, 44, 35), of which a
-// copy of the same bytes takes 14; 500 images 3 -> 16, 32 x 32, 5 x 5: 17 / 17 / 31 (21, 29, 1840); 256 images 16 -> 32,
-// 28 x 28, 3 x 3: 16 / 22 / 48 (24, 870, 2353).
+// an image did not fit the LDS): 10000 images 6 -> 12 maps, 12 x 12, 5 x 5 taps 21 / 33 / 24.5 + 5 (32, 44, 36), of which a
+// copy of the same bytes takes 10.5; 500 images 3 -> 16, 32 x 32, 5 x 5: 17 / 16 / 32 (21, 29, 1840); 256 images 16 -> 32,
+// 28 x 28, 3 x 3: 15 / 22 / 45 (24, 870, 2353), the last two weight gradients the fp32 kernel with rounded operands, like forward
+// and input gradient where channels are few.
 #pragma once
 
 #include "cnn_tile.h"
