@@ -18,6 +18,9 @@
  *  - Return value: CNN_OK (0) or a negative CNN_E* code; nothing is enqueued
  *    when an argument check fails.  cnn_strerror names a code.
  *  - Labels must lie in 0..9; this is a precondition, not checked on the device.
+ *  - Images, weights and other inputs must be finite, unless an entry point says otherwise: matrix-core
+ *    kernels multiply padding by zero, so a NaN or an infinity can reach results that do not depend on it
+ *    (and, in kernels that work on groups of images, those of its neighbours).  Not checked on the device.
  *  - Parameter layout is the paper's: k1[i][u][v], k2[j][c][u][v],
  *    fc[o][c][y][x] (flat input index c*16 + y*4 + x), biases one per map.
  */
