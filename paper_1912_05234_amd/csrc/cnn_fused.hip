@@ -16,22 +16,21 @@
 
 #include "cnn_wave.h"
 #include "cnn_group.h"
+#include "cnn_split.h"
 
 namespace {
 
 using namespace cnn;
 
-constexpr int GCAP = 1024;      // waves of a full machine at one per SIMD (256 compute units)
 constexpr int TRAIN_BLOCKS = 256;  // most workgroups (= gradient partials) of the large-batch training kernel: one per compute unit
-constexpr int FWD_GCAP = 3072;  // most forward-only waves: three per SIMD
 // Batches up to this size give each image to a workgroup of eight waves (lower latency per image;
 // up to two such workgroups share a compute unit); larger ones give each image to a single wave
 // (more images in flight, no barriers).  Measured crossover: 21.7 against 27.9 us per step at batch
 // 512, 30.8 against 28.8 us at batch 768.
 constexpr int GROUP_MAX_BATCH = 640;
-// The same choice for the forward pass alone: 4.1 against 9.6 us for one image, 6.5 against 10.4 at 512, 13.4 against 14.8 at
-// 1536, 17.1 against 14.8 at 2048 (every 256 images, one more for each compute unit, cost the first form 1.8 us).
-constexpr int FWD_GROUP_MAX_BATCH = 1536;
+// The same choice for the forward pass alone: 4.6 us for up to 256 images, 1.8 more for every 256 beyond (8.0 at 768, 9.8 at
+// 1024, 11.7 at 1280) with eight waves per image, 11.1 for any number up to 2048 with one.
+constexpr int FWD_GROUP_MAX_BATCH = 1024;
 // Device-side epoch loop: one barrier flag per workgroup (a batch of at most EPOCH_MAX_BATCH images:
 // thread t of a 512-thread workgroup polls flag t), one flag nobody sets, the error word.
 constexpr int EPOCH_MAX_BATCH = 256;
@@ -54,41 +53,147 @@ __device__ __forceinline__ void judge(const float (&y)[10], int label, float& n_
   loss = fmaf(0.5f, lsum, loss);
 }
 
-// Forward-only: yhat[B,10], optional activation dump, optional (count, loss) per wave.
-// Wave gw = 4 * blockIdx.x + wave walks the images gw, gw + G, gw + 2G, ... (G = waves in the grid).
-template <int MODE>
-__global__ __launch_bounds__(64 * WAVES, 2) void forward_kernel(const float* __restrict__ images,
-                                                            const int32_t* __restrict__ labels, int B,
-                                                            const float* __restrict__ tabg,
-                                                            float* __restrict__ yhat, DumpPtrs dump,
-                                                            float* __restrict__ eval_partial) {
-  __shared__ OperandTable<TAB_FWD_ENTRIES> tab;
-  __shared__ FwdLds lds[WAVES];
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
-  FwdLds& s = lds[wave];
-  WaveState<MODE> st;
-  const size_t gw = (size_t)blockIdx.x * WAVES + wave, G = (size_t)gridDim.x * WAVES;
-  Pixels px = load_pixels(images + (gw < (size_t)B ? gw : 0) * NI);  // in flight during the set-up
-  load_tables<TAB_FWD_ENTRIES, 64 * WAVES>(tab, tabg);
-  wave_init(st, s);
-  __syncthreads();  // the only workgroup-wide barrier: the operand table is complete
-  st.bias2 = tab.bias[l & 15];
-  float n_ok = 0.0f, loss = 0.0f;
-  for (size_t n = gw; n < (size_t)B; n += G) {
-    float y[10];
-    const size_t nn = n + G;
-    wave_image<MODE>(st, s, tab, px, nn < (size_t)B ? images + nn * NI : nullptr, 0, y, dump, n);
-    if (yhat) {
+// The same for a wave that holds the outputs one per lane (out_of_lane); the sums are the same in every lane.
+__device__ __forceinline__ void judge_lanes(float y, bool out_lane, int label, float& n_ok, float& loss) {
+  const int l = threadIdx.x & 63;
+  const float e = out_lane ? y - (out_of_lane(l) == label ? 1.0f : 0.0f) : 0.0f;
+  float sq = e * e, top = out_lane ? y : 0.0f;  // (every output is at least 0)
+  sq += quad_xor1(sq);
+  sq += quad_xor2(sq);
+  top = fmaxf(top, quad_xor1(top));
+  top = fmaxf(top, quad_xor2(top));
+  auto from = [](float v, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+  };
+  top = fmaxf(fmaxf(from(top, 0), from(top, 16)), from(top, 32));
+  const unsigned long long best = __ballot(out_lane && y == top);  // the lowest lane is the lowest index
+  n_ok += best != 0 && __builtin_ctzll(best) == 16 * (label >> 2) + (label & 3) ? 1.0f : 0.0f;
+  loss = fmaf(0.5f, (from(sq, 0) + from(sq, 16)) + from(sq, 32), loss);
+}
+
+// Forward-only: yhat[B,10], optional activation dump, optional (count, loss) per wave.  One wave per image, FWAVES
+// waves per workgroup (they share the operands), one workgroup per compute unit; wave w of workgroup b takes the images
+// b + blocks * (w + FWAVES k).
+// What bounds it: a SIMD's issue.  264 matrix instructions at 6 ns (7.6 alone; a vector instruction hides under half of
+// one), about 570 vector instructions at 1.25 and 140 exponentials and reciprocals at 3.45 are 2.8 us of the 3.8 us that
+// an image takes a SIMD with two waves; three waves (with fewer registers each) take the same.  In fp32 (152 matrix, 2134
+// vector instructions) it was 6.3 us: evaluation of 10000 images 68 -> 45.7 us, of 60000 373 -> 228 us.
+constexpr int FWAVES = 8;
+struct __align__(16) SplitForwardLds {  // of one wave
+  unsigned img[3 * SPLIT_IMG_PLANE];
+  unsigned s1[SPLIT_S1_WORDS];
+  float s2[NS2];
+};
+template <bool DUMP>
+__global__ __launch_bounds__(64 * FWAVES) void forward_kernel(const float* __restrict__ images,
+                                                             const int32_t* __restrict__ labels, int B,
+                                                             const float* __restrict__ w, const float* __restrict__ tabg,
+                                                             float* __restrict__ yhat, DumpPtrs dump,
+                                                             float* __restrict__ eval_partial) {
+  __shared__ u4v items[SPLIT_ITEMS];
+  __shared__ __align__(16) float fc[30 * 64];
+  __shared__ SplitForwardLds lds[FWAVES];
+  const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, q = l >> 4, n16 = l & 15;
+  SplitForwardLds& s = lds[wave];
+  const size_t first = (size_t)blockIdx.x + (size_t)gridDim.x * wave, step = (size_t)gridDim.x * FWAVES;
+  Pixels px = load_pixels(images + (first < (size_t)B ? first : 0) * NI);  // in flight during the set-up
+  SplitLoad<64 * FWAVES> weights;
+  weights.fetch(w);
+  for (int i = t; i < 30 * 16; i += 64 * FWAVES)
+    reinterpret_cast<f4*>(fc)[i] = reinterpret_cast<const f4*>(tabg + TAB_FCW * 64)[i];
+  if (l < 4) s.s1[3 * SPLIT_S1_PLANE + l] = 0;  // read by the last items, meets zero weights
+  const float* bias = tabg + TABG_BIAS;
+  const float bias2 = bias[n16];
+  f4 bias1a, bias1b = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int o = 0; o < NY; ++o)
-        if (l == o) yhat[n * NY + o] = y[o];
+  for (int i = 0; i < 4; ++i) bias1a[i] = NEG_LOG2E * bias[TAB_BIAS_B1 + i];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) bias1b[i] = NEG_LOG2E * bias[TAB_BIAS_B1 + 4 + i];
+  const float bias3 = bias[TAB_BIAS_B + out_of_lane(l)];
+  const bool out_lane = (OUT_LANES >> l) & 1;
+  weights.commit(items);
+  __syncthreads();  // the operands are complete; from here on the waves go their own ways
+  C1SWeights w1;
+  c1s_load_weights(w1, items);
+  const C1SLane ln = c1s_lane(s.img, l);
+  const int es = c1s_lane_s1(l), eh = es + 4 - 2 * (n16 & 1);
+  const C2SLane ln2 = c2s_lane(s.s1, items);
+  unsigned short* s1 = reinterpret_cast<unsigned short*>(s.s1);
+  float n_ok = 0.0f, loss = 0.0f;
+  for (size_t n = first; n < (size_t)B; n += step) {
+    split_store_pixels(s.img, l, px.a);
+    split_store_pixels(s.img, l + 64, px.b);
+    split_store_pixels(s.img, l + 128, px.c);
+    if (l < 4) split_store_pixels(s.img, l + 192, px.d);
+    wave_sync();
+    if (n + step < (size_t)B) px = load_pixels(images + (n + step) * NI);
+    // C1 and S1, column tiles in pairs (the last alone)
+#pragma unroll
+    for (int T = 0; T < 9; T += 2) {
+      float low[2], high[2] = {0.0f, 0.0f};
+      const int count = T < 8 ? 2 : 1;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        if (k >= count) continue;
+        C1SItems it;
+        c1s_load(it, ln, T + k);
+        f4 d0 = bias1a, d1 = bias1b;
+        c1s_gemm(w1, it, d0, d1);
+        float c[6];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) c[i] = logistic_of_scaled(i < 4 ? d0[i & 3] : d1[i & 3]);
+        if (DUMP && dump.c1) {
+          const int y = 8 * ((T + k) / 3) + (n16 & 7), x = 8 * ((T + k) % 3) + 4 * (n16 >> 3) + q;
+#pragma unroll
+          for (int i = 0; i < 6; ++i) dump.c1[n * NC1 + i * 576 + y * 24 + x] = c[i];
+        }
+        c1s_pool(c, low[k], high[k]);
+      }
+      const float both = c1s_pool_rows(high[0], count == 2 ? high[1] : high[0]);
+      if (count == 2) {
+        split_store_s1(s1, es + c1s_tile_s1(T), low[0], es + c1s_tile_s1(T + 1), low[1]);
+        const int e = eh + ((n16 & 1) ? c1s_tile_s1(T + 1) : c1s_tile_s1(T));
+        split_store_s1_one(s1, e, both);
+      } else {
+        split_store_s1(s1, es + c1s_tile_s1(T), low[0], eh + c1s_tile_s1(T), both);
+      }
     }
-    if (labels) {
-      judge(y, labels[n], n_ok, loss);
+    wave_sync();
+    if (DUMP && dump.s1)
+      for (int e = l; e < NS1; e += 64) dump.s1[n * NS1 + e] = split_s1_value(s1, e);
+    // C2 and S2
+    f4 c2[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) c2[mt] = f4{bias2, bias2, bias2, bias2};
+    c2s_gemm(c2, ln2);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) c2[mt][r] = logistic_of_scaled(c2[mt][r]);
+      if (n16 < 12) s.s2[n16 * 16 + 4 * mt + q] = 0.25f * ((c2[mt][0] + c2[mt][1]) + (c2[mt][2] + c2[mt][3]));
+      if (DUMP && dump.c2 && n16 < 12)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dump.c2[n * NC2 + n16 * 64 + (2 * mt + (r >> 1)) * 8 + 2 * q + (r & 1)] = c2[mt][r];
     }
+    wave_sync();
+    if (DUMP && dump.s2)
+      for (int e = l; e < NS2; e += 64) dump.s2[n * NS2 + e] = s.s2[e];
+    // output layer: the lane owns the inputs lane, lane + 64, lane + 128
+    float sv[3], p[NY];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) sv[k] = s.s2[l + 64 * k];
+#pragma unroll
+    for (int o = 0; o < NY; ++o) {
+      const float* f = fc + 3 * o * 64 + l;
+      p[o] = fmaf(f[128], sv[2], fmaf(f[64], sv[1], f[0] * sv[0]));
+    }
+    const float y = logistic(wave_sum10(p) + bias3);
+    if (yhat && out_lane) yhat[n * NY + out_of_lane(l)] = y;
+    if (labels) judge_lanes(y, out_lane, labels[n], n_ok, loss);
     wave_sync();
   }
   if (eval_partial && l == 0) {
+    const size_t gw = (size_t)blockIdx.x * FWAVES + wave;
     eval_partial[2 * gw] = n_ok;  // exact: far fewer than 2^24 images per wave
     eval_partial[2 * gw + 1] = loss;
   }
@@ -533,13 +638,11 @@ __global__ __launch_bounds__(64 * GWAVES) void train_epoch_kernel(const float* _
 struct cnn_ctx {
   hipStream_t stream;
   int max_batch;
-  int gcap;      // cap on training waves
-  int fwd_gcap;  // cap on forward-only waves
   float* w;             // [PSTRIDE]
   float* tabg;          // [TABG_FLOATS]: the operand table expanded from w, kept in step with it
   int32_t* dest;        // [PSTRIDE][TABLE_MAX_DEST]: slots of tabg that hold parameter p
   float* partial;       // [partial_rows_for(max_batch)][PSTRIDE]
-  float* eval_partial;  // [gcap_for(max_batch, FWD_GCAP)][2]: one pair per wave, or per image
+  float* eval_partial;  // [eval_pairs(max_batch)][2]: one pair per wave, or per image
   float* fc_hist;       // [max_batch][FC_HIST] when max_batch > GROUP_MAX_BATCH: per image, what the FC weight gradient needs
   unsigned* sync;       // [SYNC_WORDS]: barrier flags of the device-side epoch loop, then its error word
   int epoch_mode = 0;         // 1: cnn_train_epoch runs as one kernel where it can
@@ -555,10 +658,14 @@ namespace {
 
 constexpr size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Cap on waves, rounded up to whole workgroups.
-inline int gcap_for(int max_batch, int cap = GCAP) {
-  const int g = max_batch < cap ? max_batch : cap;
-  return (g + WAVES - 1) / WAVES * WAVES;
+// Waves of the forward-only kernel for B images: whole workgroups, at most one of FWAVES waves per compute unit.
+inline int forward_blocks(int B) { return B < FWAVES * TRAIN_BLOCKS ? (B + FWAVES - 1) / FWAVES : TRAIN_BLOCKS; }
+
+// (count, loss) pairs an evaluation can write: one per image (eight waves share one) or one per wave.
+inline int eval_pairs(int max_batch) {
+  const int by_group = max_batch < FWD_GROUP_MAX_BATCH ? max_batch : FWD_GROUP_MAX_BATCH;
+  const int by_wave = forward_blocks(max_batch) * FWAVES;
+  return by_wave > by_group ? by_wave : by_group;
 }
 
 struct Layout {
@@ -581,7 +688,7 @@ inline Layout layout_for(int max_batch) {
   l.dest = align_up(l.tabg + sizeof(float) * TABG_FLOATS, 256);
   l.partial = align_up(l.dest + sizeof(int32_t) * TABLE_MAX_DEST * PSTRIDE, 256);
   l.eval_partial = align_up(l.partial + sizeof(float) * PSTRIDE * g, 256);
-  l.fc_hist = align_up(l.eval_partial + sizeof(float) * 2 * (size_t)gcap_for(max_batch, FWD_GCAP), 256);
+  l.fc_hist = align_up(l.eval_partial + sizeof(float) * 2 * (size_t)eval_pairs(max_batch), 256);
   // only the large-batch kernel keeps sums in global memory; it never launches more workgroups than images
   const size_t hist_rows = max_batch > GROUP_MAX_BATCH ? (size_t)max_batch : 0;
   l.sync = align_up(l.fc_hist + sizeof(float) * FC_HIST * hist_rows, 256);
@@ -594,30 +701,6 @@ const int kParamLen[6] = {150, 6, 1800, 12, 1920, 10};
 
 inline bool batch_ok(const cnn_ctx* ctx, int B) { return ctx && B >= 1 && B <= ctx->max_batch; }
 
-// Workgroups to launch for B images: one wave per image up to the cap on waves.  The forward-only
-// kernel may keep one, two or three waves per SIMD resident; the grid is the multiple of a full
-// machine (1024 SIMDs) that gives the busiest SIMD the least work.  A SIMD's throughput with w
-// resident waves was measured as 120 : 141 : 145 (w = 1, 2, 3), so its time is proportional to
-// w * ceil(B / (1024 w)) / rate(w); e.g. 10000 images take 10 image slots per SIMD with two waves
-// against 12 with three.
-inline int blocks_for(const cnn_ctx* ctx, int B, bool forward_only) {
-  const int cap = forward_only ? ctx->fwd_gcap : ctx->gcap;
-  int waves = B < cap ? B : cap;
-  if (forward_only && B > GCAP) {
-    static const float kRate[3] = {120.0f, 141.0f, 145.0f};
-    float best = 0.0f;
-    for (int w = 1; w <= 3 && GCAP * w <= cap; ++w) {
-      const int g = GCAP * w, per_wave = (B + g - 1) / g;
-      const float t = (float)(w * per_wave) / kRate[w - 1];
-      if (w == 1 || t < best) {
-        best = t;
-        waves = g;
-      }
-    }
-  }
-  return (waves + WAVES - 1) / WAVES;
-}
-
 int run_forward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B, float* yhat, float* c1,
                 float* s1, float* c2, float* s2, bool eval) {
   const DumpPtrs dump = {c1, s1, c2, s2};
@@ -628,11 +711,11 @@ int run_forward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B,
     kernel<<<B, 64 * GWAVES, 0, ctx->stream>>>(images, labels, ctx->tabg, yhat, dump, pairs);
     return hipGetLastError() == hipSuccess ? B : CNN_EHIP;
   }
-  const int blocks = blocks_for(ctx, B, true);
-  auto kernel = dumps ? forward_kernel<kForwardDump> : forward_kernel<kForward>;
-  kernel<<<blocks, 64 * WAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, yhat, dump, pairs);
+  const int blocks = forward_blocks(B);
+  auto kernel = dumps ? forward_kernel<true> : forward_kernel<false>;
+  kernel<<<blocks, 64 * FWAVES, 0, ctx->stream>>>(images, labels, B, ctx->w, ctx->tabg, yhat, dump, pairs);
   if (hipGetLastError() != hipSuccess) return CNN_EHIP;
-  return blocks * WAVES;
+  return blocks * FWAVES;
 }
 
 int run_backward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B, float scale,
@@ -711,8 +794,6 @@ int cnn_init(cnn_ctx** out, void* workspace, size_t workspace_bytes, int max_bat
   char* base = static_cast<char*>(workspace);
   ctx->stream = (hipStream_t)hip_stream;
   ctx->max_batch = max_batch;
-  ctx->gcap = gcap_for(max_batch);
-  ctx->fwd_gcap = gcap_for(max_batch, FWD_GCAP);
   ctx->w = reinterpret_cast<float*>(base + l.w);
   ctx->tabg = reinterpret_cast<float*>(base + l.tabg);
   ctx->dest = reinterpret_cast<int32_t*>(base + l.dest);

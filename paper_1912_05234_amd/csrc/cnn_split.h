@@ -1,0 +1,296 @@
+// The two convolutions of the forward pass on the bfloat16 matrix instruction, in fp32 accuracy.  A float is cut into
+// three bfloat16 pieces, x = h + m + l: eight significant bits each, so nothing of its twenty-four is lost, and the range of a
+// bfloat16 is a float's.  A product of two floats is then the six products of pieces whose sizes are at least 2^-16 of
+// the whole (h h, h m, m h, m m, h l, l h; the others are below a float's last bit), each exact, summed in fp32.  Why: a
+// v_mfma_f32_16x16x32_bf16 takes 7.6 ns of a SIMD for 8192 multiply-adds, a v_mfma_f32_16x16x4_f32 14.6 ns for 1024, so
+// six of the former replace eight of the latter in 46 instead of 117 ns, and they run beside the vector instructions of the
+// SIMD's other waves, which the fp32 ones do not.  Error against sums in 64 bits, uniform operands: 0.7 (160 products)
+// to 0.35 (32) times that of the fp32 instructions, because a step of 32 products is rounded once.
+//
+// Layouts (64 lanes, q = lane / 16, n16 = lane % 16): A[i = n16][k = 8 q ..  8 q + 7], B[k = 8 q .. 8 q + 7][j = n16],
+// D[i = 4 q + r][j = n16] in register r.  An "item" is what a lane supplies to one instruction: eight bfloat16, 16 bytes.
+#pragma once
+
+#include "cnn_wave.h"
+
+namespace cnn {
+
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef unsigned u4v __attribute__((ext_vector_type(4)));
+typedef unsigned u2v __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ f4 mfma_bf16(bf8 a, bf8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+
+// The pieces of x (low half of each word) and y (high half).  h is cut off, not rounded, so that no finite float
+// becomes an infinity; m and l are rounded to nearest, so that what is left out has either sign.
+struct Split2 {
+  unsigned h, m, l;
+};
+__device__ __forceinline__ unsigned pack_bf16(float x, float y) {
+  using f2v = float __attribute__((ext_vector_type(2)));
+  using bf2v = __bf16 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{x, y}, bf2v));
+}
+__device__ __forceinline__ Split2 split2(float x, float y) {
+  const unsigned xi = __float_as_uint(x), yi = __float_as_uint(y);
+  Split2 s;
+  s.h = __builtin_amdgcn_perm(yi, xi, 0x07060302u);
+  const float rx = x - __uint_as_float(xi & 0xffff0000u), ry = y - __uint_as_float(yi & 0xffff0000u);
+  s.m = pack_bf16(rx, ry);
+  s.l = pack_bf16(rx - __uint_as_float(s.m << 16), ry - __uint_as_float(s.m & 0xffff0000u));
+  return s;
+}
+
+// ---- operand items in LDS, shared by the waves of a workgroup -----------------------------------------------------
+// C1: item (piece, u, m, sh) holds kernel row u of map m shifted by sh: slot v' = k1[m][u][v' - sh], zero elsewhere.
+// C2: item (u, piece, q, j) holds slots kk = 8 q .. 8 q + 7 of kernel row u of map j, kk = 6 v + c, two zeros at the end.
+// Both carry -log2(e), like the float operands (logistic_of_scaled); C2's also the 1/4 of the average pooling below it (S1 is
+// kept as the sums of four).  A kernel cuts the flat weights itself when it starts: ready-made items, kept in step by the
+// update kernel like the float operands, cost every training step 0.28 us.
+constexpr int SPLIT_C1_ITEMS = 3 * 5 * 6 * 4, SPLIT_C2_ITEMS = 5 * 3 * 4 * 12;
+constexpr int SPLIT_ITEMS = SPLIT_C1_ITEMS + SPLIT_C2_ITEMS;
+__host__ __device__ constexpr int split_c1_item(int piece, int u, int m, int sh) { return ((piece * 5 + u) * 6 + m) * 4 + sh; }
+__host__ __device__ constexpr int split_c2_item(int u, int piece, int q, int j) { return SPLIT_C1_ITEMS + ((u * 3 + piece) * 4 + q) * 12 + j; }
+template <int THREADS>
+struct SplitLoad {
+  static constexpr int ROUNDS = (OFF_B2 + THREADS - 1) / THREADS;
+  float v[ROUNDS];
+  __device__ __forceinline__ void fetch(const float* __restrict__ w) {
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const int p = threadIdx.x + THREADS * r;
+      v[r] = w[p < OFF_B2 ? p : 0];
+    }
+  }
+  // Contains a workgroup barrier; the caller's follows.
+  __device__ __forceinline__ void commit(u4v* items) const {
+    for (int i = threadIdx.x; i < SPLIT_ITEMS; i += THREADS) items[i] = u4v{0, 0, 0, 0};
+    __syncthreads();
+    unsigned short* e = reinterpret_cast<unsigned short*>(items);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const int p = threadIdx.x + THREADS * r;
+      const Split2 s = split2((p < OFF_K2 ? NEG_LOG2E : 0.25f * NEG_LOG2E) * v[r], 0.0f);
+      const unsigned short piece[3] = {(unsigned short)s.h, (unsigned short)s.m, (unsigned short)s.l};
+      if (p < OFF_B1) {
+        const int m = p / 25, u = (p % 25) / 5, x = p % 5;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+          for (int sh = 0; sh < 4; ++sh) e[8 * split_c1_item(k, u, m, sh) + x + sh] = piece[k];
+      } else if (p >= OFF_K2 && p < OFF_B2) {
+        const int j = (p - OFF_K2) / 150, tap = (p - OFF_K2) % 150, c = tap / 25, u = (tap % 25) / 5, kk = 6 * (tap % 5) + c;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) e[8 * split_c2_item(u, k, kk >> 3, j) + (kk & 7)] = piece[k];
+      }
+    }
+  }
+};
+
+// ---- the image in LDS: three planes of pieces, [28][28] each ---------------------------------------------------
+constexpr int SPLIT_IMG_PLANE = NI / 2;  // words
+__device__ __forceinline__ void split_store_pixels(unsigned* img, int at, f4 v) {  // four pixels from pixel 4 at on
+  const Split2 a = split2(v[0], v[1]), b = split2(v[2], v[3]);
+  reinterpret_cast<u2v*>(img)[at] = u2v{a.h, b.h};
+  reinterpret_cast<u2v*>(img + SPLIT_IMG_PLANE)[at] = u2v{a.m, b.m};
+  reinterpret_cast<u2v*>(img + 2 * SPLIT_IMG_PLANE)[at] = u2v{a.l, b.l};
+}
+
+// ---- C1 forward ---------------------------------------------------------------------------------------------------
+// Output pixels are taken four at a time, x = 4 X + sh.  With v' = v + sh < 8 the image factor img[y+u][4X+v'] does not
+// depend on sh, and its eight values are one item of the image:
+//   pre[(sh,m)][(y,X)] = sum_{u < 5, v' < 8} W[(sh,m)][(u,v')] * img[y+u][4X+v'],  W = k1[m][u][v'-sh].
+// Rows i = 4 sh + m % 4, so that lane (q, n16) of the result holds the maps of ONE pixel, x = 4 X + q: tile 0 the maps 0..3,
+// tile 1 the maps 4, 5 (its other rows repeat them and are not used).  Columns: nine tiles T = 3 ty + tx of sixteen (y, X),
+// y = 8 ty + 2 a + dy, X = 2 tx + bx, n16 = dy + 2 a + 8 bx.  K: an instruction takes four (u, product) pairs, one per lane
+// quarter: quarter q takes row u = q in six instructions, one per product, and row u = 4's six products are two
+// instructions more (two quarters of the last are zero): 16 instructions per column tile, 144 per image.
+struct C1SWeights {
+  bf8 row[2][3];    // pieces of row u = q
+  bf8 mixed[2][2];  // row u = 4, piece by quarter
+};
+__device__ __forceinline__ void c1s_load_weights(C1SWeights& w, const u4v* items) {
+  const int l = threadIdx.x & 63, q = l >> 4, n16 = l & 15, sh = n16 >> 2;
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt) {
+    const int m = mt == 0 ? n16 & 3 : 4 + (n16 & 1);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w.row[mt][k] = __builtin_bit_cast(bf8, items[split_c1_item(k, q, m, sh)]);
+    // image pieces l, h, m, m | h, h, -, - (c1s_lane) meet weight pieces h, l, m, h | m, h, 0, 0
+    w.mixed[mt][0] = __builtin_bit_cast(bf8, items[split_c1_item(q == 1 ? 2 : q == 2 ? 1 : 0, 4, m, sh)]);
+    u4v last = items[split_c1_item(q == 0 ? 1 : 0, 4, m, sh)];
+    if (q >= 2) last = u4v{0, 0, 0, 0};
+    w.mixed[mt][1] = __builtin_bit_cast(bf8, last);
+  }
+}
+struct C1SLane {
+  const unsigned *row, *mixed0, *mixed1;  // the lane's items of column tile 0
+};
+__device__ __forceinline__ C1SLane c1s_lane(const unsigned* img, int l) {
+  const int q = l >> 4, n16 = l & 15, y = n16 & 7, bx = n16 >> 3;  // y = 2 a + dy
+  const unsigned* at = img + 14 * y + 2 * bx;
+  C1SLane o;
+  o.row = at + 14 * q;
+  o.mixed0 = at + 14 * 4 + SPLIT_IMG_PLANE * (q == 0 ? 2 : q == 1 ? 0 : 1);
+  o.mixed1 = at + 14 * 4;
+  return o;
+}
+__host__ __device__ constexpr int c1s_tile_img(int T) { return (T / 3) * 112 + (T % 3) * 4; }  // words
+// Sixteen bytes from an 8-byte (4-byte) aligned LDS address.
+__device__ __forceinline__ bf8 item8(const unsigned* p) {
+  const u2v a = *reinterpret_cast<const u2v*>(p), b = *reinterpret_cast<const u2v*>(p + 2);
+  return __builtin_bit_cast(bf8, u4v{a.x, a.y, b.x, b.y});
+}
+typedef const unsigned __attribute__((address_space(3)))* LdsWords;
+__device__ __forceinline__ bf8 item4(LdsWords p) { return __builtin_bit_cast(bf8, u4v{p[0], p[1], p[2], p[3]}); }
+
+struct C1SItems {
+  bf8 row[3], mixed[2];
+};
+__device__ __forceinline__ void c1s_load(C1SItems& it, const C1SLane& ln, int T) {
+  const int o = c1s_tile_img(T);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) it.row[k] = item8(ln.row + o + k * SPLIT_IMG_PLANE);
+  it.mixed[0] = item8(ln.mixed0 + o);
+  it.mixed[1] = item8(ln.mixed1 + o);
+}
+// Both row tiles of one column tile, the small products first; d0, d1 enter with the biases.
+__device__ __forceinline__ void c1s_gemm(const C1SWeights& w, const C1SItems& it, f4& d0, f4& d1) {
+  constexpr int PX[6] = {2, 0, 1, 1, 0, 0}, PW[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    d0 = mfma_bf16(w.mixed[0][k], it.mixed[k], d0);
+    d1 = mfma_bf16(w.mixed[1][k], it.mixed[k], d1);
+  }
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    d0 = mfma_bf16(w.row[0][PW[k]], it.row[PX[k]], d0);
+    d1 = mfma_bf16(w.row[1][PW[k]], it.row[PX[k]], d1);
+  }
+}
+
+// ---- S1 in LDS: three planes of pieces, channels last, [12][12][6] each ------------------------------------------
+constexpr int SPLIT_S1_PLANE = NS1 / 2;                       // words
+constexpr int SPLIT_S1_WORDS = 3 * SPLIT_S1_PLANE + 4;        // the last items reach 4 bytes past the planes (zero weights)
+// Lanes xor 16 of two registers at once: returns a's (even quarters) and b's (odd quarters) sum over the lane pair.
+__device__ __forceinline__ float pair16_sum(float a, float b) {
+  const u2v r = __builtin_bit_cast(u2v, __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false));
+  return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+// Average pooling of one column tile: a window is the lanes (q, q ^ 1) x (n16, n16 ^ 1).  Sums of the maps 0..3, one per
+// lane: map (q & 1) + 2 (n16 & 1); and of the maps 4, 5 over q alone: map 4 + (q & 1).
+__device__ __forceinline__ void c1s_pool(const float (&c)[6], float& low, float& high) {
+  const bool dy = threadIdx.x & 1;
+  const float s01 = pair16_sum(c[0], c[1]), s23 = pair16_sum(c[2], c[3]);
+  low = (dy ? s23 : s01) + quad_xor1(dy ? s01 : s23);
+  high = pair16_sum(c[4], c[5]);
+}
+__device__ __forceinline__ float c1s_pool_rows(float ha, float hb) {  // lanes n16 even: tile a, odd: tile b
+  const bool dy = threadIdx.x & 1;
+  return (dy ? hb : ha) + quad_xor1(dy ? ha : hb);
+}
+__host__ __device__ constexpr int c1s_tile_s1(int T) { return ((T / 3) * 48 + (T % 3) * 4) * 6; }  // elements
+// The lane's element of S1 for the sum `low` of tile 0 (`high`: element + 4 - 2 (n16 & 1)).
+__device__ __forceinline__ int c1s_lane_s1(int l) {
+  const int q = l >> 4, n16 = l & 15, a = (n16 >> 1) & 3, bx = n16 >> 3;
+  return (a * 12 + 2 * bx + (q >> 1)) * 6 + (q & 1) + 2 * (n16 & 1);
+}
+// Pieces of two values to two elements.
+__device__ __forceinline__ void split_store_s1(unsigned short* s1, int e0, float v0, int e1, float v1) {
+  const Split2 s = split2(v0, v1);
+  const unsigned p[3] = {s.h, s.m, s.l};
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    s1[e0 + k * NS1] = (unsigned short)p[k];
+    s1[e1 + k * NS1] = (unsigned short)(p[k] >> 16);
+  }
+}
+
+// The same for one value.
+__device__ __forceinline__ void split_store_s1_one(unsigned short* s1, int e, float v) {
+  const Split2 s = split2(v, 0.0f);
+  s1[e] = (unsigned short)s.h;
+  s1[e + NS1] = (unsigned short)s.m;
+  s1[e + 2 * NS1] = (unsigned short)s.l;
+}
+// S1 itself at index e of [6][12][12]: a quarter of the sum of its pieces, which is exactly the value that was cut.
+__device__ __forceinline__ float split_s1_value(const unsigned short* s1, int e) {
+  const int c = e / 144, at = 6 * (e - 144 * c) + c;
+  float p[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) p[k] = __uint_as_float((unsigned)s1[at + k * NS1] << 16);
+  return 0.25f * (p[0] + (p[1] + p[2]));
+}
+
+// ---- C2 forward ---------------------------------------------------------------------------------------------------
+// M = 64 pixels in four tiles (cnn_wave.h: a result lane's registers are one pooling window), N = 12(16) maps, K = one
+// kernel row u at a time: the patch row s1[y+u][x .. x+4][0..5] is thirty neighbouring elements, with two more (the next
+// pixel's, zero weights) one K step of 32.  Five steps of six products, 120 instructions.
+// Tile mt's row u is row u + 2 mt of the image plane: eleven rows of items, each read once.
+struct C2SLane {
+  LdsWords low[3], high[3];  // the lane's item of row 0 and of row 6, by piece (an LDS instruction reaches 1 KB)
+  const u4v* w;
+};
+__device__ __forceinline__ C2SLane c2s_lane(const unsigned* s1, const u4v* items) {
+  const int l = threadIdx.x & 63, q = l >> 4, n16 = l & 15;
+  const int pp = 12 * ((n16 & 3) >> 1) + 2 * (n16 >> 2) + (n16 & 1);
+  C2SLane o;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    o.low[k] = (LdsWords)s1 + 3 * pp + 4 * q + k * SPLIT_S1_PLANE;
+    o.high[k] = o.low[k] + 36 * 6;
+    asm volatile("" : "+v"(o.low[k]), "+v"(o.high[k]));  // addresses of their own, not one with offsets to be added
+  }
+  o.w = items + split_c2_item(0, 0, q, n16 < 12 ? n16 : n16 - 12);
+  return o;
+}
+__device__ __forceinline__ void c2s_gemm(f4 (&d)[4], const C2SLane& ln) {
+  constexpr int PX[6] = {2, 0, 1, 1, 0, 0}, PW[6] = {0, 2, 1, 0, 1, 0};
+  bf8 x[11][3];
+  auto load_row = [&](int row) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) x[row][k] = item4(row < 6 ? ln.low[k] + 36 * row : ln.high[k] + 36 * (row - 6));
+  };
+#pragma unroll
+  for (int row = 0; row < 7; ++row) load_row(row);
+#pragma unroll
+  for (int u = 0; u < 5; ++u) {
+    bf8 b[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) b[k] = __builtin_bit_cast(bf8, ln.w[(u * 3 + k) * 48]);
+    if (u < 4) load_row(u + 7);
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) d[mt] = mfma_bf16(x[u + 2 * mt][PX[k]], b[PW[k]], d[mt]);
+  }
+}
+
+// ---- output layer -------------------------------------------------------------------------------------------------
+// Sums over the wave of ten values per lane, several at a time: a step of the tree adds two values' lanes in one register.
+// Lane l holds the sum of value out_of_lane(l); the lanes 0..3, 16..19, 32 and 33 hold the ten in order.
+__device__ __forceinline__ float pair32_sum(float a, float b) {  // lanes below 32: a's sum over the lane pair, others: b's
+  const u2v r = __builtin_bit_cast(u2v, __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false));
+  return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ int out_of_lane(int l) { return l < 32 ? 4 * (l >> 4) + (l & 3) : 8 + (l & 1); }
+constexpr unsigned long long OUT_LANES = 0x3000F000Full;
+__device__ __forceinline__ float wave_sum10(const float (&p)[NY]) {
+  const bool odd = threadIdx.x & 1, hi = threadIdx.x & 2;
+  float a[5];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) a[k] = (odd ? p[2 * k + 1] : p[2 * k]) + quad_xor1(odd ? p[2 * k] : p[2 * k + 1]);
+  float b[3];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) b[k] = (hi ? a[2 * k + 1] : a[2 * k]) + quad_xor2(hi ? a[2 * k] : a[2 * k + 1]);
+  b[2] = a[4] + quad_xor2(a[4]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) b[k] = dpp_add<0x128>(dpp_add<0x124>(b[k]));  // the four quads of a row: rotations by 4 and 8
+  return pair32_sum(pair16_sum(b[0], b[1]), pair16_sum(b[2], b[2]));
+}
+
+}  // namespace cnn

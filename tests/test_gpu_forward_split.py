@@ -1,0 +1,46 @@
+"""The forward pass of more than 1024 images (one wave per image, convolutions as products of bfloat16 pieces) against
+the fp32 matrix instructions that smaller calls run on: sizes around a whole number of images per wave and workgroup, and
+operands far from 1, where the pieces have to keep a float's range."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1912_05234_amd import binding, inputs
+from parity import RTOL_ACT, assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,pixel,gain", [(1025, 1.0, 1.0), (2048, 1e-3, 40.0), (2049, 1.0, 4.0), (4101, 3e4, 1e-3),
+                                          (1031, 1e-30, 1e20), (1033, 1e30, 1e-30)])
+def test_against_the_fp32_instructions(B, pixel, gain):
+    images, labels = inputs.make_batch(B, 17)
+    images = images * np.float32(pixel)
+    w = inputs.make_random_biases(inputs.make_weights(), 18)
+    for name in ("k1", "k2", "fc"):
+        w[name] = (w[name] * np.float32(gain if name == "k1" else min(gain, 4.0))).astype(np.float32)
+    net = binding.CNN(w, max_batch=B)
+    x = torch.from_numpy(images).to("cuda:0")
+    got = net.forward_activations(x)
+    parts = [net.forward_activations(x[i:i + 1000]) for i in range(0, B, 1000)]
+    for name in ("c1", "s1", "c2", "s2", "y"):
+        want = torch.cat([p[name] for p in parts]).cpu().numpy().astype(np.float64)
+        assert_close(got[name].cpu().numpy(), want, RTOL_ACT, "split " + name)
+    y = net.forward(x)
+    n_ok, loss = net.evaluate(x, torch.from_numpy(labels).to("cuda:0"))
+    assert torch.equal(y, got["y"])
+    y64 = y.cpu().numpy().astype(np.float64)
+    assert int(n_ok[0]) == int((y64.argmax(axis=1) == labels).sum())
+    want = 0.5 * float(((y64 - np.eye(10)[labels]) ** 2).sum())
+    assert abs(float(loss[0]) - want) <= 1e-5 * want
+
+
+def test_updated_weights_reach_the_pieces():
+    """After a training step the pieces are those of the new weights."""
+    images, labels = inputs.make_batch(1100, 19)
+    net = binding.CNN(inputs.make_weights(), max_batch=1100)
+    x, lab = torch.from_numpy(images).to("cuda:0"), torch.from_numpy(labels).to("cuda:0")
+    for n in (100, 1100):
+        net.train_batch(x[:n].contiguous(), lab[:n].contiguous(), 2.0)
+    fresh = binding.CNN(net.get_weights(), max_batch=1100)
+    assert torch.equal(net.forward(x), fresh.forward(x))
