@@ -4,19 +4,20 @@
 // backin, backavgpool) and Section 2 (batch gradient descent,
 // w := w - eta * sum_i grad F_i).
 //
-// One wavefront owns one image at a time (cnn_wave.h): the pixels, every
+// Large batches: one wavefront owns one image at a time (cnn_train.h, cnn_split.h): the pixels, every
 // activation and every error array stay in that wave's LDS and registers; the
-// only HBM traffic per image is its 3136-byte pixel block and its label.  A
-// workgroup is a single wave, walks the images n = g, g+G, g+2G, ... and keeps
-// its 3898 gradient sums in registers, so no atomics touch memory shared between
+// only HBM traffic per image is its 3136-byte pixel block and its label.  Each wave
+// keeps its 3898 gradient sums in registers, so no atomics touch memory shared between
 // waves and a partial's value does not depend on scheduling.  A second kernel
-// adds the G partials in a fixed order and applies the update.
+// adds the partials in a fixed order and applies the update.  Small batches: eight waves
+// share an image (cnn_group.h).
 #include <new>
 #include <vector>
 
 #include "cnn_wave.h"
 #include "cnn_group.h"
 #include "cnn_split.h"
+#include "cnn_train.h"
 
 namespace {
 
@@ -82,7 +83,7 @@ constexpr int FWAVES = 8;
 struct __align__(16) SplitForwardLds {  // of one wave
   unsigned img[3 * SPLIT_IMG_PLANE];
   unsigned s1[SPLIT_S1_WORDS];
-  float s2[NS2];
+  float s2[S2_WORDS];
 };
 template <bool DUMP>
 __global__ __launch_bounds__(64 * FWAVES) void forward_kernel(const float* __restrict__ images,
@@ -97,11 +98,12 @@ __global__ __launch_bounds__(64 * FWAVES) void forward_kernel(const float* __res
   SplitForwardLds& s = lds[wave];
   const size_t first = (size_t)blockIdx.x + (size_t)gridDim.x * wave, step = (size_t)gridDim.x * FWAVES;
   Pixels px = load_pixels(images + (first < (size_t)B ? first : 0) * NI);  // in flight during the set-up
-  SplitLoad<64 * FWAVES> weights;
+  SplitLoad<64 * FWAVES, false> weights;
   weights.fetch(w);
   for (int i = t; i < 30 * 16; i += 64 * FWAVES)
     reinterpret_cast<f4*>(fc)[i] = reinterpret_cast<const f4*>(tabg + TAB_FCW * 64)[i];
-  if (l < 4) s.s1[3 * SPLIT_S1_PLANE + l] = 0;  // read by the last items, meets zero weights
+  // read by the last items, meets zero weights
+  if (l < 4) s.s1[3 * SPLIT_S1_PLANE + l] = s.s1[SPLIT_S1B + 3 * SPLIT_S1_PLANE + l] = 0;
   const float* bias = tabg + TABG_BIAS;
   const float bias2 = bias[n16];
   f4 bias1a, bias1b = f4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -114,10 +116,10 @@ __global__ __launch_bounds__(64 * FWAVES) void forward_kernel(const float* __res
   weights.commit(items);
   __syncthreads();  // the operands are complete; from here on the waves go their own ways
   C1SWeights w1;
-  c1s_load_weights(w1, items);
+  c1s_load_weights(w1, items, l);
   const C1SLane ln = c1s_lane(s.img, l);
   const int es = c1s_lane_s1(l), eh = es + 4 - 2 * (n16 & 1);
-  const C2SLane ln2 = c2s_lane(s.s1, items);
+  const C2SLane ln2 = c2s_lane(s.s1, items, l);
   unsigned short* s1 = reinterpret_cast<unsigned short*>(s.s1);
   float n_ok = 0.0f, loss = 0.0f;
   for (size_t n = first; n < (size_t)B; n += step) {
@@ -128,6 +130,8 @@ __global__ __launch_bounds__(64 * FWAVES) void forward_kernel(const float* __res
     wave_sync();
     if (n + step < (size_t)B) px = load_pixels(images + (n + step) * NI);
     // C1 and S1, column tiles in pairs (the last alone)
+    C1SItems it[2];
+    c1s_load(it[0], ln, 0);
 #pragma unroll
     for (int T = 0; T < 9; T += 2) {
       float low[2], high[2] = {0.0f, 0.0f};
@@ -135,10 +139,9 @@ __global__ __launch_bounds__(64 * FWAVES) void forward_kernel(const float* __res
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         if (k >= count) continue;
-        C1SItems it;
-        c1s_load(it, ln, T + k);
+        if (T + k < 8) c1s_load(it[(k + 1) & 1], ln, T + k + 1);
         f4 d0 = bias1a, d1 = bias1b;
-        c1s_gemm(w1, it, d0, d1);
+        c1s_gemm(w1, it[k], d0, d1);
         float c[6];
 #pragma unroll
         for (int i = 0; i < 6; ++i) c[i] = logistic_of_scaled(i < 4 ? d0[i & 3] : d1[i & 3]);
@@ -151,11 +154,11 @@ __global__ __launch_bounds__(64 * FWAVES) void forward_kernel(const float* __res
       }
       const float both = c1s_pool_rows(high[0], count == 2 ? high[1] : high[0]);
       if (count == 2) {
-        split_store_s1(s1, es + c1s_tile_s1(T), low[0], es + c1s_tile_s1(T + 1), low[1]);
+        split_store_s1<true>(s1, es + c1s_tile_s1(T), low[0], es + c1s_tile_s1(T + 1), low[1]);
         const int e = eh + ((n16 & 1) ? c1s_tile_s1(T + 1) : c1s_tile_s1(T));
-        split_store_s1_one(s1, e, both);
+        split_store_s1_one<true>(s1, e, both);
       } else {
-        split_store_s1(s1, es + c1s_tile_s1(T), low[0], eh + c1s_tile_s1(T), both);
+        split_store_s1<true>(s1, es + c1s_tile_s1(T), low[0], eh + c1s_tile_s1(T), both);
       }
     }
     wave_sync();
@@ -170,18 +173,18 @@ __global__ __launch_bounds__(64 * FWAVES) void forward_kernel(const float* __res
     for (int mt = 0; mt < 4; ++mt) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) c2[mt][r] = logistic_of_scaled(c2[mt][r]);
-      if (n16 < 12) s.s2[n16 * 16 + 4 * mt + q] = 0.25f * ((c2[mt][0] + c2[mt][1]) + (c2[mt][2] + c2[mt][3]));
+      if (n16 < 12) s.s2[n16 * S2_MAP + 4 * mt + q] = 0.25f * ((c2[mt][0] + c2[mt][1]) + (c2[mt][2] + c2[mt][3]));
       if (DUMP && dump.c2 && n16 < 12)
 #pragma unroll
         for (int r = 0; r < 4; ++r) dump.c2[n * NC2 + n16 * 64 + (2 * mt + (r >> 1)) * 8 + 2 * q + (r & 1)] = c2[mt][r];
     }
     wave_sync();
     if (DUMP && dump.s2)
-      for (int e = l; e < NS2; e += 64) dump.s2[n * NS2 + e] = s.s2[e];
+      for (int e = l; e < NS2; e += 64) dump.s2[n * NS2 + e] = s.s2[s2_at(e)];
     // output layer: the lane owns the inputs lane, lane + 64, lane + 128
     float sv[3], p[NY];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) sv[k] = s.s2[l + 64 * k];
+    for (int k = 0; k < 3; ++k) sv[k] = s.s2[s2_at(l + 64 * k)];
 #pragma unroll
     for (int o = 0; o < NY; ++o) {
       const float* f = fc + 3 * o * 64 + l;
@@ -323,57 +326,42 @@ struct WaveShare {
   }
 };
 __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void train_kernel(
-    const float* __restrict__ images, const int32_t* __restrict__ labels, int B, const float* __restrict__ tabg,
-    float* __restrict__ partial, float* fc_hist) {
-  __shared__ OperandTable<TAB_WAVE_ENTRIES> tab;
+    const float* __restrict__ images, const int32_t* __restrict__ labels, int B, const float* __restrict__ w,
+    const float* __restrict__ tabg, float* __restrict__ partial, float* fc_hist) {
+  __shared__ TrainOperands ops;
   __shared__ WaveTrainLds lds[TWAVES];
-  __shared__ WindowTable wt;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // in a scalar register: addresses built on it are wave-uniform
   WaveTrainLds& s = lds[wave];
-  WaveState<kTrain> st;
-  CNN_KERNEL_MARK(0);
+  WaveState st;
   const int K = B > (int)blockIdx.x ? (B - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x : 0;
   WaveShare mine(K, wave);
   const bool has_images = mine.left > 0;
+  const float sign = wave & 1 ? -1.0f : 1.0f;  // see wave_image
   auto image_index = [&](int k) { return (size_t)blockIdx.x + (size_t)gridDim.x * (size_t)k; };
-  Pixels px = load_pixels(images + (has_images ? image_index(mine.k()) : 0) * NI);  // in flight during the set-up
-  // every load of the set-up is issued before anything waits for one: the table proper (BF, FCW, AB,
-  // k1t, biases) in 16-byte pieces, and the packed entries, gathered one float at a time
-  TableLoad<TAB_WAVE_ENTRIES, 64 * TWAVES, false, TAB_PK> table;
-  table.fetch(tabg);
-  constexpr int PK_ROUNDS = (TAB_PK_COUNT * 64 + 64 * TWAVES - 1) / (64 * TWAVES);
-  float pk[PK_ROUNDS];
-#pragma unroll
-  for (int r = 0; r < PK_ROUNDS; ++r) {
-    const int e = r * TWAVES + wave;  // a wave gathers one entry per round (wave-uniform: scalar arithmetic)
-    const int slot = e < TAB_PK_COUNT ? packed_table_slot(e, threadIdx.x & 63) : -1;
-    pk[r] = tabg[slot >= 0 ? slot : 0];
-    if (slot < 0) pk[r] = 0.0f;
-  }
-  window_table_init<64 * TWAVES>(wt);
+  // every load of the set-up is issued before anything waits for one
+  const Pixels px = load_pixels(images + (has_images ? image_index(mine.k()) : 0) * NI);
+  SplitLoad<64 * TWAVES, true> weights;
+  weights.fetch(w);
+  constexpr int FC_PIECES = 30 * 16;
+  static_assert(FC_PIECES <= 64 * TWAVES, "one piece per thread");
+  const int t = threadIdx.x;
+  const f4 fc = reinterpret_cast<const f4*>(tabg)[TAB_FCW * 16 + (t < FC_PIECES ? t : 0)];
+  const float bias = tabg[TABG_BIAS + (t < TAB_BIAS_FLOATS ? t : 0)];
   // waves without images skip their set-up and their row
-  if (has_images) {
-    wave_init(st, s);
-    store_pixels(s.img, px);
-  }
-  table.commit(tab);
-#pragma unroll
-  for (int r = 0; r < PK_ROUNDS; ++r) {
-    const int i = r * 64 * TWAVES + threadIdx.x;
-    if (i < TAB_PK_COUNT * 64) tab.e[TAB_PK * 64 + i] = pk[r];
-  }
-  __syncthreads();  // the operand and window tables are complete
-  st.bias2 = tab.bias[threadIdx.x & 15];
-  const DumpPtrs none = {nullptr, nullptr, nullptr, nullptr};
-  CNN_KERNEL_MARK(1);
+  if (has_images) wave_init(st);
+  if (t < C1G_ONES) ops.ones[t] = 1.0f;
+  if (t < FC_PIECES) reinterpret_cast<f4*>(ops.fc)[t] = fc;
+  if (t < TAB_BIAS_FLOATS) ops.bias[t] = bias;
+  weights.commit(ops.items, ops.bwd);
+  if (has_images) place_image(s, px);
+  __syncthreads();  // the operands are complete
+  st.bias2 = ops.bias[threadIdx.x & 15];
   while (mine.left > 0) {
-    float y[10];
     const size_t n = image_index(mine.k());
     mine.advance();
     const size_t nn = mine.left > 0 ? image_index(mine.k()) : n;
-    wave_image<kTrain>(st, s, tab, px, images + nn * NI, labels[n], y, none, n, &wt, fc_hist + n * FC_HIST);
+    wave_image(st, s, ops, images + nn * NI, labels[n], sign, fc_hist + n * FC_HIST);
   }
-  CNN_KERNEL_MARK(2);
   // FC weight gradient: a second walk over this wave's images, four per K step (the history rows
   // have left the L2 cache by now; a wave that is done early does this while the others still work)
   f4 g_fc[12];
@@ -416,8 +404,9 @@ __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 
     if (again.left > 0) steps(std::integral_constant<int, 1>());
     if (again.left > 0) steps(std::integral_constant<int, 1>());
   }
-  __syncthreads();  // every wave is done with the operand table: its storage parks the C1 GEMM results
-  if (has_images) wave_flush(st, g_fc, reinterpret_cast<float*>(&s), tab.e + wave * C1G_PARK);
+  __syncthreads();  // every wave is done with the operands: their storage parks the C1 GEMM results
+  static_assert(TWAVES * C1G_PARK * sizeof(float) <= sizeof(ops.items), "the parked results fit");
+  if (has_images) wave_flush(st, sign, g_fc, reinterpret_cast<float*>(&s), reinterpret_cast<float*>(ops.items) + wave * C1G_PARK);
   __syncthreads();
   {
     // rows of the waves that had images in a fixed tree; an idle wave's row counts as zeros (the
@@ -433,8 +422,6 @@ __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 
       dst[i] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     }
   }
-  CNN_KERNEL_MARK(3);
-  CNN_PHASE_FLUSH;
 }
 
 // Small batches: eight waves share one image (cnn_group.h); one partial row per workgroup.
@@ -729,7 +716,7 @@ int run_backward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B
   if (grouped)
     train_group_kernel<<<blocks, 64 * GWAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, ctx->partial);
   else
-    train_kernel<<<blocks, 64 * TWAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, ctx->partial, ctx->fc_hist);
+    train_kernel<<<blocks, 64 * TWAVES, 0, ctx->stream>>>(images, labels, B, ctx->w, ctx->tabg, ctx->partial, ctx->fc_hist);
   if (hipGetLastError() != hipSuccess) return CNN_EHIP;
   if (timed) {
     CNN_HIP_TRY(hipEventRecord(ctx->ev[2 * ctx->ev_used + 1], ctx->stream));

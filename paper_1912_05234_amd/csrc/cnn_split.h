@@ -41,6 +41,18 @@ __device__ __forceinline__ Split2 split2(float x, float y) {
   return s;
 }
 
+// The same with h rounded to nearest too, for values that are far from the largest floats: m has either sign, so that the
+// products left out (m l, l m) do not add up over many values that meet one weight.  With h cut off, the C1 weight
+// gradient of 40000 images was off by 5.8e-8 where this gives 4.5e-8 and fp32 instructions 4.6e-8.
+__device__ __forceinline__ Split2 split2_nearest(float x, float y) {
+  Split2 s;
+  s.h = pack_bf16(x, y);
+  const float rx = x - __uint_as_float(s.h << 16), ry = y - __uint_as_float(s.h & 0xffff0000u);
+  s.m = pack_bf16(rx, ry);
+  s.l = pack_bf16(rx - __uint_as_float(s.m << 16), ry - __uint_as_float(s.m & 0xffff0000u));
+  return s;
+}
+
 // ---- operand items in LDS, shared by the waves of a workgroup -----------------------------------------------------
 // C1: item (piece, u, m, sh) holds kernel row u of map m shifted by sh: slot v' = k1[m][u][v' - sh], zero elsewhere.
 // C2: item (u, piece, q, j) holds slots kk = 8 q .. 8 q + 7 of kernel row u of map j, kk = 6 v + c, two zeros at the end.
@@ -51,7 +63,49 @@ constexpr int SPLIT_C1_ITEMS = 3 * 5 * 6 * 4, SPLIT_C2_ITEMS = 5 * 3 * 4 * 12;
 constexpr int SPLIT_ITEMS = SPLIT_C1_ITEMS + SPLIT_C2_ITEMS;
 __host__ __device__ constexpr int split_c1_item(int piece, int u, int m, int sh) { return ((piece * 5 + u) * 6 + m) * 4 + sh; }
 __host__ __device__ constexpr int split_c2_item(int u, int piece, int q, int j) { return SPLIT_C1_ITEMS + ((u * 3 + piece) * 4 + q) * 12 + j; }
-template <int THREADS>
+// Input error of C2 (training): T[row][pixel] = sum_j W[row][j] * d_c2[j][pixel] over twelve maps, rows as in cnn_wave.h (tiles
+// V(0..4), U4 of the maps 0..3, then the packed PV(0..2), PU), W = k2[j] / 4.  Twelve K elements would leave most of a step
+// of 32 empty, so the six products lie side by side: 72 slots, two steps of 32 and a quarter of a third.  A row is a
+// record [h 12][m 12][l 12][4 unused], and so is a pixel of d_c2; slot group g < 18 (four slots) is part g % 3 of product g / 3.
+constexpr int BWD_TILES = 10, BWD_REC = 40, BWD_PV = 6, BWD_PU = 9;
+__host__ __device__ constexpr int bwd_row(int c, int u, int v) {  // row of tap (c, u, v), 16 to a tile
+  if (c < 4) return u < 4 ? 16 * v + 4 * c + u : v < 4 ? 16 * 5 + 4 * c + v : 16 * BWD_PU + 4 * c + 3;
+  const int e = 4 * (c - 4) + (v < 3 ? 0 : 8), s = v < 3 ? v : v - 3;
+  return u < 4 ? 16 * (BWD_PV + s) + e + u : 16 * BWD_PU + e + s;
+}
+// Every other row holds the negative of its weights, and its terms are subtracted: the instruction cuts what it aligns towards
+// minus infinity (the mean of T comes out 7e-9 of its mean magnitude too low, a tenth of its rms error), which the sums of
+// the C1 gradients over all pixels and images, where most of T cancels, would show (8e-7 instead of 5e-8 at 700 images).
+__host__ __device__ constexpr bool bwd_negative(int c, int u, int v) { return (u + (c < 4 || v < 3 ? v : v - 3)) & 1; }
+// Rows without a tap: the upper eight of PV(2), two of PU.
+constexpr int BWD_ZERO_ROWS = 10;
+__host__ __device__ constexpr int bwd_zero_row(int k) { return k < 8 ? 16 * (BWD_PV + 2) + 8 + k : 16 * BWD_PU + 10 + 4 * (k - 8); }
+__host__ __device__ constexpr int bwd_group(int g, bool a) {  // offset of slot group g in a record, in fours
+  constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+  return 3 * (a ? PA[g / 3] : PB[g / 3]) + g % 3;
+}
+// The group that quarter q supplies as half i of the items (steps of two halves; the third step's two are quarter 0's
+// alone): quarters 0 and 1, and 2 and 3, differ by an odd number in both offsets, so that the sixteen records of both (an
+// odd multiple of four words apart) lie on different banks.
+constexpr int BWD_GROUPS[6][4] = {{0, 1, 2, 6}, {3, 4, 5, 8}, {9, 10, 12, 13}, {11, 14, 7, 16}, {15, 15, 15, 15}, {17, 17, 17, 17}};
+constexpr bool bwd_groups_ok() {
+  int seen = 0;
+  for (int i = 0; i < 4; ++i)
+    for (int q = 0; q < 4; q += 2)
+      for (int a = 0; a < 2; ++a)
+        if ((bwd_group(BWD_GROUPS[i][q], a) + bwd_group(BWD_GROUPS[i][q + 1], a)) % 2 == 0) return false;
+  for (int i = 0; i < 6; ++i)
+    for (int q = 0; q < (i < 4 ? 4 : 1); ++q) seen |= 1 << BWD_GROUPS[i][q];
+  return seen == (1 << 18) - 1;
+}
+static_assert(bwd_groups_ok(), "every group once, neighbours on different banks");
+__host__ __device__ constexpr unsigned bwd_groups(int q, bool a) {  // four bits each
+  unsigned w = 0;
+  for (int i = 0; i < 6; ++i) w |= (unsigned)bwd_group(BWD_GROUPS[i][q], a) << (4 * i);
+  return w;
+}
+// BWD: the records of the input error too.
+template <int THREADS, bool BWD>
 struct SplitLoad {
   static constexpr int ROUNDS = (OFF_B2 + THREADS - 1) / THREADS;
   float v[ROUNDS];
@@ -62,28 +116,43 @@ struct SplitLoad {
       v[r] = w[p < OFF_B2 ? p : 0];
     }
   }
-  // Contains a workgroup barrier; the caller's follows.
-  __device__ __forceinline__ void commit(u4v* items) const {
-    for (int i = threadIdx.x; i < SPLIT_ITEMS; i += THREADS) items[i] = u4v{0, 0, 0, 0};
-    __syncthreads();
+  // Every slot of every item is written by one thread: the zeros of a shifted row by the threads of its first three taps.
+  __device__ __forceinline__ void commit(u4v* items, unsigned short* bwd = nullptr) const {
     unsigned short* e = reinterpret_cast<unsigned short*>(items);
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
       const int p = threadIdx.x + THREADS * r;
       const Split2 s = split2((p < OFF_K2 ? NEG_LOG2E : 0.25f * NEG_LOG2E) * v[r], 0.0f);
       const unsigned short piece[3] = {(unsigned short)s.h, (unsigned short)s.m, (unsigned short)s.l};
-      if (p < OFF_B1) {
+      if (THREADS * r < OFF_B1 && p < OFF_B1) {
         const int m = p / 25, u = (p % 25) / 5, x = p % 5;
+        unsigned short* to = e + 8 * split_c1_item(0, u, m, 0);
 #pragma unroll
         for (int k = 0; k < 3; ++k)
 #pragma unroll
-          for (int sh = 0; sh < 4; ++sh) e[8 * split_c1_item(k, u, m, sh) + x + sh] = piece[k];
+          for (int sh = 0; sh < 4; ++sh) {
+            to[8 * split_c1_item(k, 0, 0, sh) + x + sh] = piece[k];
+            if (x < 3) to[8 * split_c1_item(k, 0, 0, sh) + (x < sh ? x : x + 5)] = 0;
+          }
       } else if (p >= OFF_K2 && p < OFF_B2) {
         const int j = (p - OFF_K2) / 150, tap = (p - OFF_K2) % 150, c = tap / 25, u = (tap % 25) / 5, kk = 6 * (tap % 5) + c;
+        unsigned short* to = e + 8 * split_c2_item(u, 0, kk >> 3, j) + (kk & 7);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) e[8 * split_c2_item(u, k, kk >> 3, j) + (kk & 7)] = piece[k];
+        for (int k = 0; k < 3; ++k) {
+          to[8 * 48 * k] = piece[k];
+          if (kk >= 28) to[8 * 48 * k + 2] = 0;  // slots 30 and 31
+        }
+        if (BWD) {
+          const Split2 b = split2((bwd_negative(c, u, tap % 5) ? -0.25f : 0.25f) * v[r], 0.0f);
+          unsigned short* rec = bwd + BWD_REC * bwd_row(c, u, tap % 5) + j;
+          rec[0] = (unsigned short)b.h;
+          rec[12] = (unsigned short)b.m;
+          rec[24] = (unsigned short)b.l;
+        }
       }
     }
+    if (BWD && threadIdx.x < BWD_ZERO_ROWS * BWD_REC / 2)
+      reinterpret_cast<unsigned*>(bwd + BWD_REC * bwd_zero_row(threadIdx.x / (BWD_REC / 2)))[threadIdx.x % (BWD_REC / 2)] = 0;
   }
 };
 
@@ -109,8 +178,8 @@ struct C1SWeights {
   bf8 row[2][3];    // pieces of row u = q
   bf8 mixed[2][2];  // row u = 4, piece by quarter
 };
-__device__ __forceinline__ void c1s_load_weights(C1SWeights& w, const u4v* items) {
-  const int l = threadIdx.x & 63, q = l >> 4, n16 = l & 15, sh = n16 >> 2;
+__device__ __forceinline__ void c1s_load_weights(C1SWeights& w, const u4v* items, int l) {
+  const int q = l >> 4, n16 = l & 15, sh = n16 >> 2;
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt) {
     const int m = mt == 0 ? n16 & 3 : 4 + (n16 & 1);
@@ -136,13 +205,14 @@ __device__ __forceinline__ C1SLane c1s_lane(const unsigned* img, int l) {
   return o;
 }
 __host__ __device__ constexpr int c1s_tile_img(int T) { return (T / 3) * 112 + (T % 3) * 4; }  // words
-// Sixteen bytes from an 8-byte (4-byte) aligned LDS address.
+// Sixteen bytes from an 8-byte aligned LDS address, as two loads that must not become one ds_read2_b64: that takes the LDS 16
+// cycles where two ds_read_b64 take 2 each.  (The compiler keeps such loads in the order they are written: what is to
+// be read ahead is written ahead.)
 __device__ __forceinline__ bf8 item8(const unsigned* p) {
-  const u2v a = *reinterpret_cast<const u2v*>(p), b = *reinterpret_cast<const u2v*>(p + 2);
+  typedef const volatile u2v __attribute__((address_space(3)))* LdsPair;
+  const u2v a = *(LdsPair)p, b = *(LdsPair)(p + 2);
   return __builtin_bit_cast(bf8, u4v{a.x, a.y, b.x, b.y});
 }
-typedef const unsigned __attribute__((address_space(3)))* LdsWords;
-__device__ __forceinline__ bf8 item4(LdsWords p) { return __builtin_bit_cast(bf8, u4v{p[0], p[1], p[2], p[3]}); }
 
 struct C1SItems {
   bf8 row[3], mixed[2];
@@ -170,8 +240,14 @@ __device__ __forceinline__ void c1s_gemm(const C1SWeights& w, const C1SItems& it
 }
 
 // ---- S1 in LDS: three planes of pieces, channels last, [12][12][6] each ------------------------------------------
+// Twice: a pixel is twelve bytes, and in the second copy, SPLIT_S1B words further, the odd pixels are eight-byte aligned.
+// Its place puts the four pixels of a transposing read (two rows of 36 words, odd pixels in the second copy) on different
+// banks: ranges of 14 words for two quarters at 0, 36 and 14 further.
 constexpr int SPLIT_S1_PLANE = NS1 / 2;                       // words
-constexpr int SPLIT_S1_WORDS = 3 * SPLIT_S1_PLANE + 4;        // the last items reach 4 bytes past the planes (zero weights)
+constexpr int SPLIT_S1_COPY = 3 * SPLIT_S1_PLANE + 4;         // the last items reach 4 bytes past the planes (zero weights)
+constexpr int SPLIT_S1B = SPLIT_S1_COPY + 55;
+constexpr int SPLIT_S1_WORDS = SPLIT_S1B + SPLIT_S1_COPY + 1;
+static_assert(SPLIT_S1B % 2 == 1 && (SPLIT_S1B + 3) % 64 == 14 && SPLIT_S1_WORDS % 4 == 0, "alignment and banks");
 // Lanes xor 16 of two registers at once: returns a's (even quarters) and b's (odd quarters) sum over the lane pair.
 __device__ __forceinline__ float pair16_sum(float a, float b) {
   const u2v r = __builtin_bit_cast(u2v, __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false));
@@ -195,23 +271,30 @@ __device__ __forceinline__ int c1s_lane_s1(int l) {
   const int q = l >> 4, n16 = l & 15, a = (n16 >> 1) & 3, bx = n16 >> 3;
   return (a * 12 + 2 * bx + (q >> 1)) * 6 + (q & 1) + 2 * (n16 & 1);
 }
-// Pieces of two values to two elements.
+// Pieces of two values to two elements; BOTH: of both copies.
+template <bool BOTH>
 __device__ __forceinline__ void split_store_s1(unsigned short* s1, int e0, float v0, int e1, float v1) {
-  const Split2 s = split2(v0, v1);
+  const Split2 s = split2_nearest(v0, v1);
   const unsigned p[3] = {s.h, s.m, s.l};
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    s1[e0 + k * NS1] = (unsigned short)p[k];
-    s1[e1 + k * NS1] = (unsigned short)(p[k] >> 16);
+#pragma unroll
+    for (int copy = 0; copy < (BOTH ? 2 : 1); ++copy) {
+      s1[e0 + k * NS1 + copy * 2 * SPLIT_S1B] = (unsigned short)p[k];
+      s1[e1 + k * NS1 + copy * 2 * SPLIT_S1B] = (unsigned short)(p[k] >> 16);
+    }
   }
 }
 
 // The same for one value.
+template <bool BOTH>
 __device__ __forceinline__ void split_store_s1_one(unsigned short* s1, int e, float v) {
-  const Split2 s = split2(v, 0.0f);
-  s1[e] = (unsigned short)s.h;
-  s1[e + NS1] = (unsigned short)s.m;
-  s1[e + 2 * NS1] = (unsigned short)s.l;
+  const Split2 s = split2_nearest(v, 0.0f);
+  const unsigned p[3] = {s.h, s.m, s.l};
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int copy = 0; copy < (BOTH ? 2 : 1); ++copy) s1[e + k * NS1 + copy * 2 * SPLIT_S1B] = (unsigned short)p[k];
 }
 // S1 itself at index e of [6][12][12]: a quarter of the sum of its pieces, which is exactly the value that was cut.
 __device__ __forceinline__ float split_s1_value(const unsigned short* s1, int e) {
@@ -228,43 +311,43 @@ __device__ __forceinline__ float split_s1_value(const unsigned short* s1, int e)
 // pixel's, zero weights) one K step of 32.  Five steps of six products, 120 instructions.
 // Tile mt's row u is row u + 2 mt of the image plane: eleven rows of items, each read once.
 struct C2SLane {
-  LdsWords low[3], high[3];  // the lane's item of row 0 and of row 6, by piece (an LDS instruction reaches 1 KB)
+  const unsigned* s1;  // the lane's item of row 0
   const u4v* w;
 };
-__device__ __forceinline__ C2SLane c2s_lane(const unsigned* s1, const u4v* items) {
-  const int l = threadIdx.x & 63, q = l >> 4, n16 = l & 15;
+__device__ __forceinline__ C2SLane c2s_lane(const unsigned* s1, const u4v* items, int l) {
+  const int q = l >> 4, n16 = l & 15;
   const int pp = 12 * ((n16 & 3) >> 1) + 2 * (n16 >> 2) + (n16 & 1);
-  C2SLane o;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    o.low[k] = (LdsWords)s1 + 3 * pp + 4 * q + k * SPLIT_S1_PLANE;
-    o.high[k] = o.low[k] + 36 * 6;
-    asm volatile("" : "+v"(o.low[k]), "+v"(o.high[k]));  // addresses of their own, not one with offsets to be added
-  }
-  o.w = items + split_c2_item(0, 0, q, n16 < 12 ? n16 : n16 - 12);
-  return o;
+  return C2SLane{s1 + ((n16 & 1) ? SPLIT_S1B : 0) + 3 * pp + 4 * q, items + split_c2_item(0, 0, q, n16 < 12 ? n16 : n16 - 12)};
 }
+// One piece of the image after the other (l, m, h), so that seven rows of items are in registers and not all of them; a step's
+// new row, and the next piece's first rows, are read a step ahead.
 __device__ __forceinline__ void c2s_gemm(f4 (&d)[4], const C2SLane& ln) {
-  constexpr int PX[6] = {2, 0, 1, 1, 0, 0}, PW[6] = {0, 2, 1, 0, 1, 0};
-  bf8 x[11][3];
-  auto load_row = [&](int row) {
+  bf8 x[2][11];
+  auto load_row = [&](int k, int row) { x[k & 1][row] = item8(ln.s1 + 36 * row + k * SPLIT_S1_PLANE); };
 #pragma unroll
-    for (int k = 0; k < 3; ++k) x[row][k] = item4(row < 6 ? ln.low[k] + 36 * row : ln.high[k] + 36 * (row - 6));
-  };
+  for (int row = 0; row < 7; ++row) load_row(2, row);
 #pragma unroll
-  for (int row = 0; row < 7; ++row) load_row(row);
+  for (int k = 2; k >= 0; --k)  // piece l meets h; m meets m, h; h meets l, m, h
 #pragma unroll
-  for (int u = 0; u < 5; ++u) {
-    bf8 b[3];
+    for (int u = 0; u < 5; ++u) {
+      if (u < 4) load_row(k, u + 7);
+      if (k > 0 && u >= 1) {
+        load_row(k - 1, 2 * u - 2);
+        if (u < 4) load_row(k - 1, 2 * u - 1);
+      }
 #pragma unroll
-    for (int k = 0; k < 3; ++k) b[k] = __builtin_bit_cast(bf8, ln.w[(u * 3 + k) * 48]);
-    if (u < 4) load_row(u + 7);
+      for (int j = 2 - k; j >= 0; --j) {
+        const bf8 b = __builtin_bit_cast(bf8, ln.w[(u * 3 + j) * 48]);
 #pragma unroll
-    for (int k = 0; k < 6; ++k)
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) d[mt] = mfma_bf16(x[u + 2 * mt][PX[k]], b[PW[k]], d[mt]);
-  }
+        for (int mt = 0; mt < 4; ++mt) d[mt] = mfma_bf16(x[k & 1][u + 2 * mt], b, d[mt]);
+      }
+    }
 }
+
+// ---- S2 and its error in LDS: sixteen to a map, seventeen apart (a store or load of a whole tile has lanes 16 apart) ----
+constexpr int S2_MAP = 17;
+__device__ __forceinline__ int s2_at(int i) { return i + (i >> 4); }
+constexpr int S2_WORDS = 12 * S2_MAP;
 
 // ---- output layer -------------------------------------------------------------------------------------------------
 // Sums over the wave of ten values per lane, several at a time: a step of the tree adds two values' lanes in one register.
