@@ -11,6 +11,8 @@
 // D[i = 4 q + r][j = n16] in register r.  An "item" is what a lane supplies to one instruction: eight bfloat16, 16 bytes.
 #pragma once
 
+#include <type_traits>
+
 #include "cnn_wave.h"
 
 namespace cnn {
@@ -22,7 +24,8 @@ typedef unsigned u2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ f4 mfma_bf16(bf8 a, bf8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 
 // The pieces of x (low half of each word) and y (high half).  h is cut off, not rounded, so that no finite float
-// becomes an infinity; m and l are rounded to nearest, so that what is left out has either sign.
+// becomes an infinity; m and l are rounded to nearest, so that what is left out has either sign.  Below 2^-109 (1.5e-33) the
+// last bits of l leave bfloat16's range: an operand is then kept to 2^-134 in place of 24 bits.
 struct Split2 {
   unsigned h, m, l;
 };
@@ -342,6 +345,226 @@ __device__ __forceinline__ void c2s_gemm(f4 (&d)[4], const C2SLane& ln) {
         for (int mt = 0; mt < 4; ++mt) d[mt] = mfma_bf16(x[k & 1][u + 2 * mt], b, d[mt]);
       }
     }
+}
+
+// ---- C2 weight gradient --------------------------------------------------------------------------------------------
+// C2 backweights: G[j, (c,u,v)] += sum_p d_c2[j, p] * s1[c, y(p)+u, x(p)+v].  K is the pixels: a step takes the windows 4 q + r
+// of the tiles 2 S and 2 S + 1, slots in the order of the result registers of d_c2, which so are the A operand as they
+// stand.  The columns of kernel row u are the thirty elements s1[y+u][x .. x+4][0..5], two tiles; a transposing
+// read brings four pixels (rows, twelve bytes apart) of sixteen columns: lane 4 r + i of a quarter gives the address of
+// pixel r's columns 4 i .. 4 i + 3 and receives column n16 of all four.
+__device__ __forceinline__ void k2_gradient(f4 (&acc)[10], const u4v (&d2)[2][3], const unsigned* s1, int l) {
+  typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
+  typedef bf4 __attribute__((address_space(3)))* LdsQuad;
+  const int q = l >> 4, n16 = l & 15, r = n16 >> 2, dx = r & 1;
+  LdsQuad at = (LdsQuad)(reinterpret_cast<const unsigned short*>(s1 + (dx ? SPLIT_S1B : 0)) + 6 * (12 * (r >> 1) + 2 * q + dx) + 4 * (n16 & 3));
+  bf8 a[2][3];
+#pragma unroll
+  for (int S = 0; S < 2; ++S)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) a[S][k] = __builtin_bit_cast(bf8, d2[S][k]);
+  // Rows R = u + 4 S and R + 2 of the image plane make an operand.  Every one is read afresh (two operands may share a row, but
+  // not in the same half of their registers), the next one's under an operand's products.  The image's sums are made on
+  // their own and then added: steps onto the sums over all images would be rounded, and cut, at their size.
+  bf8 x[2][2][3];
+  auto load = [&](int n) {
+    const int R = (n >> 1) + 4 * (n & 1);
+    LdsQuad from = at;
+    asm volatile("" : "+v"(from));
+#pragma unroll
+    for (int k = 2; k >= 0; --k)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const u2v lo = __builtin_bit_cast(u2v, __builtin_amdgcn_ds_read_tr16_b64_v4bf16(from + (R * 72 + 16 * t + k * NS1) / 4));
+        const u2v hi = __builtin_bit_cast(u2v, __builtin_amdgcn_ds_read_tr16_b64_v4bf16(from + ((R + 2) * 72 + 16 * t + k * NS1) / 4));
+        x[n & 1][t][k] = __builtin_bit_cast(bf8, u4v{lo.x, lo.y, hi.x, hi.y});
+      }
+  };
+  constexpr int PX[6] = {2, 0, 1, 1, 0, 0}, PA[6] = {0, 2, 1, 0, 1, 0};
+  load(0);
+  f4 sum[2];
+#pragma unroll
+  for (int n = 0; n < 10; ++n) {  // u = n / 2, S = n % 2
+    if (n < 9) load(n + 1);
+    if (!(n & 1)) sum[0] = sum[1] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) sum[t] = mfma_bf16(a[n & 1][PA[k]], x[n & 1][t][PX[k]], sum[t]);
+    if (n & 1)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[(n & ~1) + t][r] += sum[t][r];
+        asm volatile("" : "+v"(acc[(n & ~1) + t]));  // now: the compiler would keep the sums and the old `acc` until the end of the image
+      }
+  }
+}
+
+// ---- C2 input error -------------------------------------------------------------------------------------------------
+// d_in [6][12][16 of which 12], eight words more between maps: the lanes of two quarters (two maps, two rows of eight
+// neighbours in each) then lie on 32 different banks.
+constexpr int DS1_ROW = 16, DS1_MAP = 12 * DS1_ROW + 8;
+// Records of an image's d from its pieces d2[S][piece] (result layout: register r of tile 2 S + mt % 2 is pixel
+// (2 mt + r / 2, 2 q + r % 2)).  Record 16 mt + 2 x + y % 2 is pixel (y, x): the two rows of a tile alternate, see col2im_split.
+__device__ __forceinline__ void store_records(unsigned short* recs, const u4v (&d2)[2][3], int l) {
+  const int q = l >> 4, n16 = l & 15;
+  unsigned short* rec = recs + 4 * q * BWD_REC + n16;
+  if (n16 < 12) {
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const unsigned p = d2[mt >> 1][k][2 * (mt & 1) + h];
+          rec[(16 * mt + h) * BWD_REC + 12 * k] = (unsigned short)p;
+          rec[(16 * mt + 2 + h) * BWD_REC + 12 * k] = (unsigned short)(p >> 16);
+        }
+  }
+}
+template <int CTRL>  // row_shl:n 0x100 + n, row_shr:n 0x110 + n: lanes that nothing reaches get 0
+__device__ __forceinline__ float dpp(float v) {
+  return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), CTRL, 15, 15, true));
+}
+template <int CTRL, int ROWS>  // only the quarters ROWS, the others keep old
+__device__ __forceinline__ float dpp(float old, float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(old), __float_as_uint(v), CTRL, ROWS, 15, true));
+}
+// A sum over tap columns v of values shifted right by v: columns 0..7 of two rows in a quarter's sixteen lanes (lane 2 x + row),
+// columns 8..11 in the first lanes of a second register.
+template <int V>
+__device__ __forceinline__ void add_column(float& lo, float& hi, float e) {
+  if constexpr (V == 0) {
+    lo = e;
+    hi = 0.0f;
+  } else {
+    const float a = dpp<0x110 + 2 * V>(e), b = dpp<0x100 + 16 - 2 * V>(e);
+    lo = V & 1 ? lo - a : lo + a;  // (bwd_negative)
+    hi = V & 1 ? hi - b : hi + b;
+  }
+}
+// C2 backin summed over the twelve maps, col2im form:
+//      T[(c,u,v), p] = sum_j k2[j,c,u,v] * d[j,p];   d_in[c, y(p)+u, x(p)+v] += T[(c,u,v), p].
+// All in registers: with level = 2 nt + u (nt = pixel tile = row pair of p), terms of equal level and v are the same cells of
+// the same lanes, and an odd level shares its rows half and half with the two even ones beside it.  What is added over levels
+// is shifted by v within the quarter (one map) and added over v.  With the sums in
+// LDS, in sixteen dependent rounds of reads, additions and writes (its clearing, a second copy of the maps 4 and 5), an image
+// kept the LDS busy for 1000 clocks, eight waves 8000 of 13000; training on 60000 images took 588 us instead of 572, the
+// input gradient alone of as many 160 us instead of 137.  The input maps 0..3 and 4, 5 are taken one after the other: half the registers.
+// d_in may lie over the records; its columns 12..15 get zeros.  `sign`: what d was taken with.
+__device__ __forceinline__ void col2im_split(const unsigned short* bwd, const unsigned short* rec, float* d_in, float sign, int l) {
+  const int q = l >> 4, n16 = l & 15;
+  // this quarter's slot groups of a row record and of a pixel record
+  const unsigned ga = q == 0 ? bwd_groups(0, true) : q == 1 ? bwd_groups(1, true) : q == 2 ? bwd_groups(2, true) : bwd_groups(3, true);
+  const unsigned gb = q == 0 ? bwd_groups(0, false) : q == 1 ? bwd_groups(1, false) : q == 2 ? bwd_groups(2, false) : bwd_groups(3, false);
+  const u2v* arow[6];
+  u2v bd[4][6];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    arow[i] = reinterpret_cast<const u2v*>(bwd + BWD_REC * n16) + ((ga >> (4 * i)) & 15);
+    const u2v* b = reinterpret_cast<const u2v*>(rec) + n16 * (BWD_REC / 4) + ((gb >> (4 * i)) & 15);
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+      bd[nt][i] = b[16 * nt * (BWD_REC / 4)];
+      if (i >= 4 && q >= 1) bd[nt][i] = u2v{0, 0};
+    }
+  }
+  wave_sync();
+  float lo[6], hi[6];  // rows 2m and 2m + 1
+  // The tiles tv of tap column V; `u4` is the u = 4 term per pixel tile.  Level 2m has rows 2m and 2m + 1 in the even and
+  // the odd lanes, level 2m + 1, with the other sign (bwd_negative), rows 2m + 1 and 2m + 2.
+  auto column = [&](auto vc, const f4 (&tv)[4], const float (&u4)[4]) {
+    constexpr int V = decltype(vc)::value;
+    __builtin_amdgcn_sched_barrier(0);  // two columns' tiles at a time do not fit the registers of the training kernel
+    float odd[5];  // levels 2m + 1: (nt = m, u = 1) + (m-1, 3)
+#pragma unroll
+    for (int m = 0; m < 5; ++m) {
+      odd[m] = 0.0f;
+      if (m < 4) odd[m] = tv[m < 4 ? m : 0][1];
+      if (m >= 1) odd[m] += tv[m >= 1 ? m - 1 : 0][3];
+    }
+#pragma unroll
+    for (int m = 0; m < 6; ++m) {
+      // level 2m: (nt = m, u = 0) + (m-1, 2) + (m-2, 4)
+      float e = 0.0f;
+      if (m < 4) e = tv[m < 4 ? m : 0][0];
+      if (m >= 1 && m <= 4) e += tv[m >= 1 ? m - 1 : 0][2];
+      if (m >= 2) e += u4[m >= 2 ? m - 2 : 0];
+      const float z = n16 & 1 ? (m > 0 ? odd[m > 0 ? m - 1 : 0] : 0.0f) : (m < 5 ? odd[m < 5 ? m : 0] : 0.0f);
+      add_column<V>(lo[m], hi[m], e - dpp<0xb1>(z));  // quad_perm [1, 0, 3, 2]
+    }
+  };
+  // the four pixel tiles of one M tile
+  auto tiles = [&](int tile, f4 (&out)[4]) {
+    u2v a[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) a[i] = arow[i][16 * tile * (BWD_REC / 4)];
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+      f4 d = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        d = mfma_bf16(__builtin_bit_cast(bf8, u4v{a[2 * k].x, a[2 * k].y, a[2 * k + 1].x, a[2 * k + 1].y}),
+                      __builtin_bit_cast(bf8, u4v{bd[nt][2 * k].x, bd[nt][2 * k].y, bd[nt][2 * k + 1].x, bd[nt][2 * k + 1].y}), d);
+      out[nt] = d;
+    }
+  };
+  float* cell = d_in + DS1_ROW * (n16 & 1) + (n16 >> 1);  // of row 0 or 1, columns 0..7
+  f4 tu[4];
+  tiles(BWD_PU, tu);
+  // ---- input maps 4, 5, packed: lane quarters 0, 1 have them for tap columns 0..2 and quarters 2, 3 for columns 3, 4, in
+  //      round s column s or 3 + s (quarters 2, 3 have nothing in round 2: their tile rows are zero).  tu: the u = 4 term of
+  //      round s in register s ----
+  {
+    auto round = [&](auto sc) {
+      constexpr int S = decltype(sc)::value;
+      f4 tv[4];
+      tiles(BWD_PV + S, tv);
+      float u4[4];
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) u4[nt] = tu[nt][S];
+      column(sc, tv, u4);
+    };
+    round(std::integral_constant<int, 0>{});
+    round(std::integral_constant<int, 1>{});
+    round(std::integral_constant<int, 2>{});
+    float* to = cell + DS1_MAP * (4 + (q & 1)) + (q < 2 ? 0 : 8);
+#pragma unroll
+    for (int m = 0; m < 6; ++m) {
+      // quarters 2, 3: three columns further
+      const float h = dpp<0x116, 12>(hi[m], hi[m]) + dpp<0x10a, 12>(0.0f, lo[m]), a = dpp<0x116, 12>(lo[m], lo[m]);
+      // the sums over both halves: columns 0..7 in quarters 0, 1 and columns 8..11 in quarters 2, 3
+      const u2v s = __builtin_bit_cast(u2v, __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(h), false, false));
+      const float v = sign * (__uint_as_float(s.x) + __uint_as_float(s.y));
+      to[2 * DS1_ROW * m] = v;
+    }
+  }
+  // ---- input maps 0..3: lane quarter q owns map q; tiles V(0..4) and U4; tap (4, 4) rides in
+  //      register 3 of the packed tile PU of the maps 4, 5 above ----
+  {
+    f4 t4[4];  // taps (4, v), v < 4, in register v
+    tiles(kTileU4, t4);
+    auto round = [&](auto vc) {
+      constexpr int V = decltype(vc)::value;
+      f4 tv[4];  // taps (u, v), u < 4, in register u
+      tiles(kTileV0 + V, tv);
+      float u4[4];
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) u4[nt] = V < 4 ? t4[nt][V < 4 ? V : 0] : tu[nt][3];
+      column(vc, tv, u4);
+    };
+    round(std::integral_constant<int, 0>{});
+    round(std::integral_constant<int, 1>{});
+    round(std::integral_constant<int, 2>{});
+    round(std::integral_constant<int, 3>{});
+    round(std::integral_constant<int, 4>{});
+    float* to = cell + DS1_MAP * q;
+#pragma unroll
+    for (int m = 0; m < 6; ++m) to[2 * DS1_ROW * m] = sign * lo[m];
+#pragma unroll
+    for (int m = 0; m < 6; ++m) to[2 * DS1_ROW * m + 8] = sign * hi[m];
+  }
 }
 
 // ---- S2 and its error in LDS: sixteen to a map, seventeen apart (a store or load of a whole tile has lanes 16 apart) ----

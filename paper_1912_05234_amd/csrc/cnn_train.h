@@ -38,23 +38,18 @@ struct __align__(16) TrainOperands {
 // Per wave: the image, and 3120 words that the phases use in turn, exactly one partial row together.
 //   C1 forward          S1's pieces (first copy) at 0, the image's pieces behind them
 //   C2 forward, FC      both copies of S1, s2, d_s2
-//   C2 gradients        both copies of S1; then d_s1, the records of d_c2 with the second copy of d_s1's maps 4, 5 over them
-//   C1 weight gradient  d_s1 and that copy, and the C1 error of two column tiles
+//   C2 gradients        both copies of S1; then d_s1 and the records of d_c2
+//   C1 weight gradient  d_s1, and the C1 error of two column tiles
 constexpr int W_S1 = 0;
 constexpr int W_PIECES = SPLIT_S1_COPY;                // no longer needed when the second copy takes their place
 constexpr int W_S2 = SPLIT_S1_WORDS;                   // s2 as S2_MAP says
 constexpr int W_DS2 = W_S2 + S2_WORDS;
-// d_s1 [6][12][16 of which 12], eight words more between maps: the lanes of two quarters (two maps, two rows of eight
-// neighbours in each) then lie on 32 different banks.
-constexpr int DS1_ROW = 16, DS1_MAP = 12 * DS1_ROW + 8;
 constexpr int W_DS1 = 0, W_D2 = 6 * DS1_MAP;
-constexpr int W_DS1_COPY = 2 * DS1_MAP;
-constexpr int W_D1 = W_D2 + W_DS1_COPY;
+constexpr int W_D1 = W_D2;
 constexpr int D1T_HALF = 34, D1T_MAP = 2 * D1T_HALF, D1T_WORDS = 6 * D1T_MAP;
 constexpr int W_WORDS = PSTRIDE - NI;
 static_assert(W_PIECES % 4 == 0 && W_S2 % 4 == 0 && W_D2 % 4 == 0 && W_D1 % 4 == 0, "alignment");
 static_assert(W_PIECES + 3 * SPLIT_IMG_PLANE <= W_WORDS && W_DS2 + S2_WORDS <= W_WORDS && W_D1 + 2 * D1T_WORDS <= W_WORDS && W_D2 + 64 * BWD_REC / 2 <= W_WORDS, "the arrays fit");
-static_assert(W_DS1_COPY % 4 == 0, "alignment");
 struct __align__(16) WaveTrainLds {
   float img[NI];
   float pool[W_WORDS];
@@ -124,57 +119,6 @@ __device__ __forceinline__ void s1_second_copy(float* pool) {
 #pragma unroll
   for (int k = 0; k < WHOLE; ++k) to[64 * k] = v[k];
   if (l < REST) to[64 * WHOLE] = v[WHOLE];
-}
-
-// C2 backweights: G[j, (c,u,v)] += sum_p d_c2[j, p] * s1[c, y(p)+u, x(p)+v].  K is the pixels: a step takes the windows 4 q + r
-// of the tiles 2 S and 2 S + 1, slots in the order of the result registers of d_c2, which so are the A operand as they
-// stand.  The columns of kernel row u are the thirty elements s1[y+u][x .. x+4][0..5], two tiles; a transposing
-// read brings four pixels (rows, twelve bytes apart) of sixteen columns: lane 4 r + i of a quarter gives the address of
-// pixel r's columns 4 i .. 4 i + 3 and receives column n16 of all four.
-__device__ __forceinline__ void k2_gradient(f4 (&acc)[10], const u4v (&d2)[2][3], const float* pool, int l) {
-  typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
-  typedef bf4 __attribute__((address_space(3)))* LdsQuad;
-  const int q = l >> 4, n16 = l & 15, r = n16 >> 2, dx = r & 1;
-  LdsQuad at = (LdsQuad)(reinterpret_cast<const unsigned short*>(pool + W_S1 + (dx ? SPLIT_S1B : 0)) + 6 * (12 * (r >> 1) + 2 * q + dx) + 4 * (n16 & 3));
-  bf8 a[2][3];
-#pragma unroll
-  for (int S = 0; S < 2; ++S)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) a[S][k] = __builtin_bit_cast(bf8, d2[S][k]);
-  // Rows R = u + 4 S and R + 2 of the image plane make an operand.  Every one is read afresh (two operands may share a row, but
-  // not in the same half of their registers), the next one's under an operand's products.  The image's sums are made on
-  // their own and then added: steps onto the sums over all images would be rounded, and cut, at their size.
-  bf8 x[2][2][3];
-  auto load = [&](int n) {
-    const int R = (n >> 1) + 4 * (n & 1);
-    LdsQuad from = at;
-    asm volatile("" : "+v"(from));
-#pragma unroll
-    for (int k = 2; k >= 0; --k)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const u2v lo = __builtin_bit_cast(u2v, __builtin_amdgcn_ds_read_tr16_b64_v4bf16(from + (R * 72 + 16 * t + k * NS1) / 4));
-        const u2v hi = __builtin_bit_cast(u2v, __builtin_amdgcn_ds_read_tr16_b64_v4bf16(from + ((R + 2) * 72 + 16 * t + k * NS1) / 4));
-        x[n & 1][t][k] = __builtin_bit_cast(bf8, u4v{lo.x, lo.y, hi.x, hi.y});
-      }
-  };
-  constexpr int PX[6] = {2, 0, 1, 1, 0, 0}, PA[6] = {0, 2, 1, 0, 1, 0};
-  load(0);
-  f4 sum[2];
-#pragma unroll
-  for (int n = 0; n < 10; ++n) {  // u = n / 2, S = n % 2
-    if (n < 9) load(n + 1);
-    if (!(n & 1)) sum[0] = sum[1] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int k = 0; k < 6; ++k)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) sum[t] = mfma_bf16(a[n & 1][PA[k]], x[n & 1][t][PX[k]], sum[t]);
-    if (n & 1)
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[(n & ~1) + t][r] += sum[t][r];
-  }
 }
 
 // One image through forward and backward.  The image is in s (place_image) on entry and `next_image` (any valid image when
@@ -296,147 +240,15 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
         d2[mt >> 1][2][2 * (mt & 1) + h] = p.l;
       }
     }
-    k2_gradient(st.acc_k2, d2, s.pool, l);
+    k2_gradient(st.acc_k2, d2, reinterpret_cast<const unsigned*>(s.pool + W_S1), l);
   }
   wave_sync();
-  // S1 is dead: d_c2 as records of its pixels, and the col2im target cleared
-  {
-    const int l = phase_lane(), q = l >> 4, n16 = l & 15;
-    unsigned short* rec = reinterpret_cast<unsigned short*>(s.pool + W_D2) + 4 * q * BWD_REC + n16;
-    if (n16 < 12) {
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            const unsigned p = d2[mt >> 1][k][2 * (mt & 1) + h];
-            rec[(16 * mt + 2 * h) * BWD_REC + 12 * k] = (unsigned short)p;
-            rec[(16 * mt + 2 * h + 1) * BWD_REC + 12 * k] = (unsigned short)(p >> 16);
-          }
-    }
-    for (int e = l; e < 6 * DS1_MAP / 4; e += 64) reinterpret_cast<f4*>(s.pool + W_DS1)[e] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
+  // S1 is dead: d_c2 as records of its pixels
+  store_records(reinterpret_cast<unsigned short*>(s.pool + W_D2), d2, phase_lane());
   wave_sync();
 
-    // ---- C2 backin summed over the twelve maps, col2im form:
-    //        T[(c,u,v), p] = sum_j k2[j,c,u,v] * d_c2[j,p];   d_s1[c, y(p)+u, x(p)+v] += T[(c,u,v), p].
-    //      With level = 2 nt + u (nt = pixel tile = row pair of p), two terms of one map touch the
-    //      same cells only if their levels differ by at most 1; equal level and equal v means the very
-    //      same cells.  So for each v: terms of equal level are added in registers, then all even
-    //      levels go to LDS in one round of read-add-write, then all odd levels.  Within a round no two
-    //      lanes share an address (maps are DS1_MAP floats apart, levels two rows, pixels of a tile distinct).
-    //      The two groups of four input maps (cg) are taken one after the other: half the registers.
-    {
-      const int l = phase_lane(), q = l >> 4, n16 = l & 15;
-      const int pp = DS1_ROW * ((n16 & 3) >> 1) + 2 * (n16 >> 2) + (n16 & 1);
-      // this quarter's slot groups of a row record and of a pixel record
-      const unsigned ga = q == 0 ? bwd_groups(0, true) : q == 1 ? bwd_groups(1, true) : q == 2 ? bwd_groups(2, true) : bwd_groups(3, true);
-      const unsigned gb = q == 0 ? bwd_groups(0, false) : q == 1 ? bwd_groups(1, false) : q == 2 ? bwd_groups(2, false) : bwd_groups(3, false);
-      const u2v* arow[6];
-      u2v bd[4][6];
-#pragma unroll
-      for (int i = 0; i < 6; ++i) {
-        arow[i] = reinterpret_cast<const u2v*>(ops.bwd + BWD_REC * n16) + ((ga >> (4 * i)) & 15);
-        const u2v* b = reinterpret_cast<const u2v*>(s.pool + W_D2) + n16 * (BWD_REC / 4) + ((gb >> (4 * i)) & 15);
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-          bd[nt][i] = b[16 * nt * (BWD_REC / 4)];
-          if (i >= 4 && q >= 1) bd[nt][i] = u2v{0, 0};
-        }
-      }
-      // the second copy of maps 4 and 5 (see bwd_packed_tap) lies over d2, which is in registers now
-      float* copy = s.pool + W_D2;
-      wave_sync();
-      for (int e = l; e < W_DS1_COPY / 4; e += 64) reinterpret_cast<f4*>(copy)[e] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-      wave_sync();
-      // One round pair (even levels, then odd levels) for the tiles tv of one tap column: `u4` is the
-      // u = 4 term per pixel tile, `dst` the lane's cell of level 0 for that column, `odd` the column's sign (bwd_negative).
-      auto rounds = [&](const f4 (&tv)[4], const float (&u4)[4], float* dst, bool odd) {
-        // even levels 2m, m < 6: (nt = m, u = 0) + (m-1, 2) + (m-2, 4)
-        {
-          float e[6], old[6];
-#pragma unroll
-          for (int m = 0; m < 6; ++m) {
-            float acc = 0.0f;
-            if (m < 4) acc = tv[m < 4 ? m : 0][0];
-            if (m >= 1 && m <= 4) acc += tv[m >= 1 ? m - 1 : 0][2];
-            if (m >= 2) acc += u4[m >= 2 ? m - 2 : 0];
-            e[m] = acc;
-            old[m] = dst[2 * DS1_ROW * m];
-          }
-#pragma unroll
-          for (int m = 0; m < 6; ++m) dst[2 * DS1_ROW * m] = fmaf(odd ? -sign : sign, e[m], old[m]);
-        }
-        wave_sync();
-        // odd levels 2m+1, m < 5: (nt = m, u = 1) + (m-1, 3)
-        {
-          float e[5], old[5];
-#pragma unroll
-          for (int m = 0; m < 5; ++m) {
-            float acc = 0.0f;
-            if (m < 4) acc = tv[m < 4 ? m : 0][1];
-            if (m >= 1) acc += tv[m >= 1 ? m - 1 : 0][3];
-            e[m] = acc;
-            old[m] = dst[2 * DS1_ROW * m + DS1_ROW];
-          }
-#pragma unroll
-          for (int m = 0; m < 5; ++m) dst[2 * DS1_ROW * m + DS1_ROW] = fmaf(odd ? sign : -sign, e[m], old[m]);
-        }
-        wave_sync();
-      };
-      // the four pixel tiles of one M tile
-      auto tiles = [&](int tile, f4 (&out)[4]) {
-        u2v a[6];
-#pragma unroll
-        for (int i = 0; i < 6; ++i) a[i] = arow[i][16 * tile * (BWD_REC / 4)];
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-          f4 d = f4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-          for (int k = 0; k < 3; ++k)
-            d = mfma_bf16(__builtin_bit_cast(bf8, u4v{a[2 * k].x, a[2 * k].y, a[2 * k + 1].x, a[2 * k + 1].y}),
-                          __builtin_bit_cast(bf8, u4v{bd[nt][2 * k].x, bd[nt][2 * k].y, bd[nt][2 * k + 1].x, bd[nt][2 * k + 1].y}), d);
-          out[nt] = d;
-        }
-      };
-      f4 tu[4];
-      tiles(BWD_PU, tu);
-      // ---- input maps 4, 5, packed: lane quarters 0, 1 own them for tap columns 0..2 and add into
-      //      d_s1, quarters 2, 3 own them again for columns 3, 4 and add into the copy; in round s a
-      //      lane's column is s or 3 + s (quarters 2, 3 have nothing in round 2: their tile rows are
-      //      zero and they re-write cells with their own values) ----
-      {
-        // (tu: the u = 4 term of round r in register r)
-        float* tgt = q < 2 ? s.pool + W_DS1 + DS1_MAP * (4 + q) + pp : copy + DS1_MAP * (q - 2) + pp + 3;
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-          f4 tv[4];
-          tiles(BWD_PV + r, tv);
-          float u4[4];
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt) u4[nt] = tu[nt][r];
-          rounds(tv, u4, tgt + r, r & 1);
-        }
-      }
-      // ---- input maps 0..3: lane quarter q owns map q; tiles V(0..4) and U4; tap (4, 4) rides in
-      //      register 3 of the packed tile PU of the maps 4, 5 above ----
-      {
-        f4 t4[4];  // taps (4, v), v < 4, in register v
-        tiles(kTileU4, t4);
-        float* tgt = s.pool + W_DS1 + DS1_MAP * q + pp;
-#pragma unroll
-        for (int v = 0; v < 5; ++v) {
-          f4 tv[4];  // taps (u, v), u < 4, in register u
-          tiles(kTileV0 + v, tv);
-          float u4[4];
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt) u4[nt] = v < 4 ? t4[nt][v < 4 ? v : 0] : tu[nt][3];
-          rounds(tv, u4, tgt + v, v & 1);
-        }
-      }
-    }
-
+  // ---- C2 backin into d_s1 -----------------------
+  col2im_split(ops.bwd, reinterpret_cast<const unsigned short*>(s.pool + W_D2), s.pool + W_DS1, sign, phase_lane());
   wave_sync();
   // ---- backavgpool through S1 and the derivative of C1's sigmoid, then C1 backweights as a GEMM over pixel pairs (cnn_wave.h),
   //      column tile by column tile of C1: eight K steps of one row and four pairs.  A tile's error goes to LDS, as
@@ -446,18 +258,18 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
     const int l = phase_lane(), q = l >> 4, n16 = l & 15, a = (n16 >> 1) & 3, bx = n16 >> 3;
     const float* up = s.pool + W_DS1 + a * DS1_ROW + 2 * bx + (q >> 1);
     float* dst = s.pool + W_D1 + (q >> 1) * D1T_HALF + 4 * (n16 & 7) + 2 * bx + (q & 1);
-    float e[2][8];  // the error at S1 over a tile; maps 4 and 5 were summed in two halves (the copy lies over d2)
+    float e[2][6];  // the error at S1 over a tile
     auto fetch = [&](int T) {
       const int o = 4 * DS1_ROW * (T / 3) + 4 * (T % 3);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) e[T & 1][i] = up[i < 6 ? i * DS1_MAP + o : W_D2 - W_DS1 + (i - 6) * DS1_MAP + o];
+      for (int i = 0; i < 6; ++i) e[T & 1][i] = up[i * DS1_MAP + o];
     };
     auto stage = [&](int T) {
 #pragma unroll
       for (int i = 0; i < 6; ++i) {
-        const float c = c1[T][i], d = i < 4 ? e[T & 1][i] : e[T & 1][i] + e[T & 1][i + 2];
+        const float c = c1[T][i];
         // c (1 - c); the pooling's 1/4 is in the weights.  (backbias: the GEMM sums d1 in its padding column.)
-        dst[i * D1T_MAP + (T & 1) * D1T_WORDS] = d * fmaf(-c, c, c);
+        dst[i * D1T_MAP + (T & 1) * D1T_WORDS] = e[T & 1][i] * fmaf(-c, c, c);
       }
     };
     const float* pa = s.pool + W_D1 + ((n16 >> 1) % 6) * D1T_MAP + (q & 1) * D1T_HALF + 2 * (q >> 1) + (n16 & 1);
