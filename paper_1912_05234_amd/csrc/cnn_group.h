@@ -288,7 +288,7 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
 
     if (wave < 4) {
       // ---- C2 input error for input maps 4 cg .. 4 cg + 3 from the pixel tiles nt = 2 h, 2 h + 1
-      //      (col2im rounds of cnn_wave.h restricted to those tiles: levels 4 h .. 4 h + 6) ---------------
+      //      (col2im rounds as in cnn_col2im.h restricted to those tiles: levels 4 h .. 4 h + 6) ---------------
       const int cg = wave & 1, h = wave >> 1;
       float bd[3][2];
 #pragma unroll
