@@ -113,7 +113,7 @@ __global__ __launch_bounds__(64 * FWAVES) void forward_kernel(const float* __res
   for (int i = 0; i < 2; ++i) bias1b[i] = NEG_LOG2E * bias[TAB_BIAS_B1 + 4 + i];
   const float bias3 = bias[TAB_BIAS_B + out_of_lane(l)];
   const bool out_lane = (OUT_LANES >> l) & 1;
-  weights.commit(items);
+  weights.commit(reinterpret_cast<float*>(lds), items);
   __syncthreads();  // the operands are complete; from here on the waves go their own ways
   C1SWeights w1;
   c1s_load_weights(w1, items, l);
@@ -352,9 +352,10 @@ __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 
   if (t < C1G_ONES) ops.ones[t] = 1.0f;
   if (t < FC_PIECES) reinterpret_cast<f4*>(ops.fc)[t] = fc;
   if (t < TAB_BIAS_FLOATS) ops.bias[t] = bias;
-  weights.commit(ops.items, ops.bwd);
-  if (has_images) place_image(s, px);
+  weights.commit(lds[0].pool, ops.items, ops.bwd);
   __syncthreads();  // the operands are complete
+  if (has_images) place_image(s, px);
+  wave_sync();
   st.bias2 = ops.bias[threadIdx.x & 15];
   while (mine.left > 0) {
     const size_t n = image_index(mine.k());

@@ -65,26 +65,15 @@ __global__ __launch_bounds__(THREADS) void forward_kernel(const float* __restric
   __shared__ __align__(16) unsigned planes[WAVES][SPLIT_S1_WORDS];
   const Share<WAVES, 1> mine;
   const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, q = l >> 4, n16 = l & 15;
-  float kv[(NK2 + THREADS - 1) / THREADS];  // the weights of this lane, all in flight at once
-#pragma unroll
-  for (int i = 0; i < (NK2 + THREADS - 1) / THREADS; ++i) kv[i] = k[min(t + THREADS * i, NK2 - 1)];
+  StagedLoad<THREADS, NK2> weights;
+  weights.fetch(k);
   Planes cur;
   if (mine.first < (size_t)B) cur.load(in, mine.first);
-  unsigned short* e = reinterpret_cast<unsigned short*>(items);
-#pragma unroll
-  for (int i = 0; i < (NK2 + THREADS - 1) / THREADS; ++i) {
-    const int p = t + THREADS * i;
-    if (p >= NK2) break;
-    const int j = p / 150, tap = p % 150, c = tap / 25, u = (tap % 25) / 5, kk = 6 * (tap % 5) + c;
-    const Split2 s = split2(kv[i], 0.0f);
-    unsigned short* to = e + 8 * (split_c2_item(u, 0, kk >> 3, j) - SPLIT_C1_ITEMS) + (kk & 7);
-    to[0] = (unsigned short)s.h;
-    to[8 * 48] = (unsigned short)s.m;
-    to[2 * 8 * 48] = (unsigned short)s.l;
-    if (kk >= 28) to[2] = to[8 * 48 + 2] = to[2 * 8 * 48 + 2] = 0;  // slots 30 and 31
-  }
-  pad_planes(planes[wave]);
+  weights.commit(reinterpret_cast<float*>(planes));
   __syncthreads();
+  if (t < C2_TASKS) make_c2_items(items - SPLIT_C1_ITEMS, t, reinterpret_cast<const float*>(planes), 1.0f);
+  __syncthreads();
+  pad_planes(planes[wave]);
   const C2SLane ln = c2s_lane(planes[wave], items - SPLIT_C1_ITEMS, l);
   const float b = bias ? bias[n16 < 12 ? n16 : 0] : 0.0f;
   for (size_t n = mine.first; n < (size_t)B; n += mine.step) {
@@ -229,24 +218,13 @@ __global__ __launch_bounds__(THREADS) void bwd_input_kernel(const float* __restr
   __shared__ __align__(16) float lds[WAVES][REC_WORDS];
   const Share<WAVES, 1> mine;
   const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63;
-  float kv[(NK2 + THREADS - 1) / THREADS];  // the weights of this lane, all in flight at once
-#pragma unroll
-  for (int i = 0; i < (NK2 + THREADS - 1) / THREADS; ++i) kv[i] = k[min(t + THREADS * i, NK2 - 1)];
+  StagedLoad<THREADS, NK2> weights;
+  weights.fetch(k);
   f4 d[4];
   if (mine.first < (size_t)B) load_error(d_out, mine.first, d);
-#pragma unroll
-  for (int i = 0; i < (NK2 + THREADS - 1) / THREADS; ++i) {
-    const int p = t + THREADS * i;
-    if (p >= NK2) break;
-    const int j = p / 150, tap = p % 150, c = tap / 25, u = (tap % 25) / 5, v = tap % 5;
-    const Split2 s = split2(bwd_negative(c, u, v) ? -kv[i] : kv[i], 0.0f);
-    unsigned short* to = rows + BWD_REC * bwd_row(c, u, v) + j;
-    to[0] = (unsigned short)s.h;
-    to[12] = (unsigned short)s.m;
-    to[24] = (unsigned short)s.l;
-  }
-  if (t < BWD_ZERO_ROWS * BWD_REC / 2)
-    reinterpret_cast<unsigned*>(rows + BWD_REC * bwd_zero_row(t / (BWD_REC / 2)))[t % (BWD_REC / 2)] = 0;
+  weights.commit(&lds[0][0]);
+  __syncthreads();
+  if (t < BWD_TASKS) make_bwd_record(rows, t, &lds[0][0], 1.0f);
   __syncthreads();
   float* acc = lds[wave];
   // the 216 fours of an image: where they lie in d_in [6][12][DS1_ROW]

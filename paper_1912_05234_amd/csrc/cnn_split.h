@@ -80,9 +80,27 @@ __host__ __device__ constexpr int bwd_row(int c, int u, int v) {  // row of tap 
 // minus infinity (the mean of T comes out 7e-9 of its mean magnitude too low, a tenth of its rms error), which the sums of
 // the C1 gradients over all pixels and images, where most of T cancels, would show (8e-7 instead of 5e-8 at 700 images).
 __host__ __device__ constexpr bool bwd_negative(int c, int u, int v) { return (u + (c < 4 || v < 3 ? v : v - 3)) & 1; }
-// Rows without a tap: the upper eight of PV(2), two of PU.
-constexpr int BWD_ZERO_ROWS = 10;
-__host__ __device__ constexpr int bwd_zero_row(int k) { return k < 8 ? 16 * (BWD_PV + 2) + 8 + k : 16 * BWD_PU + 10 + 4 * (k - 8); }
+// The tap of a row; false: none (the upper eight rows of PV(2), two of PU), its record is zero.
+__host__ __device__ constexpr bool bwd_tap_of_row(int row, int& c, int& u, int& v) {
+  const int tile = row >> 4, r = row & 15, e = r >> 2, s = r & 3;
+  const int packed = tile - BWD_PV;  // PV(packed) or, at three, PU
+  if (tile < 5) c = e, u = s, v = tile;
+  else if (tile == 5) c = e, u = 4, v = s;
+  else if (packed == 3 && s == 3) c = e, u = 4, v = 4;
+  else c = 4 + (e & 1), u = packed == 3 ? 4 : s, v = (packed == 3 ? s : packed) + (e >= 2 ? 3 : 0);
+  return v < 5;
+}
+constexpr bool bwd_rows_ok() {
+  int rows = 0;
+  for (int row = 0; row < 16 * BWD_TILES; ++row) {
+    int c = 0, u = 0, v = 0;
+    if (!bwd_tap_of_row(row, c, u, v)) continue;
+    if (bwd_row(c, u, v) != row) return false;
+    ++rows;
+  }
+  return rows == 150;
+}
+static_assert(bwd_rows_ok(), "the inverse of bwd_row");
 __host__ __device__ constexpr int bwd_group(int g, bool a) {  // offset of slot group g in a record, in fours
   constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
   return 3 * (a ? PA[g / 3] : PB[g / 3]) + g % 3;
@@ -107,55 +125,90 @@ __host__ __device__ constexpr unsigned bwd_groups(int q, bool a) {  // four bits
   for (int i = 0; i < 6; ++i) w |= (unsigned)bwd_group(BWD_GROUPS[i][q], a) << (4 * i);
   return w;
 }
-// BWD: the records of the input error too.
-template <int THREADS, bool BWD>
-struct SplitLoad {
-  static constexpr int ROUNDS = (OFF_B2 + THREADS - 1) / THREADS;
-  float v[ROUNDS];
+// A thread makes whole items, or a whole record, from the weights staged in LDS, and writes them in pieces of 16 bytes.  (A
+// thread per weight, writing its pieces slot by slot: 3600 clocks of conflicting 2-byte stores and divisions, half of
+// what a workgroup did before its first image.  Gradient of 1000 images 24.8 -> 24.2 us, evaluation of 1100 13.6 -> 13.1 us.)
+constexpr int C2_TASKS = 5 * 4 * 12, BWD_TASKS = 16 * BWD_TILES, C1_TASKS = 5 * 6 * 2;
+// C2: kernel row u, quarter q of map j (k2 staged as it is): elements kk = 8 q + i = 6 v + c, zeros at 30 and 31.
+__device__ __forceinline__ void make_c2_items(u4v* items, int task, const float* k2, float scale) {
+  const int u = task % 5, q = (task / 5) & 3, j = task / 20, c0 = q == 3 ? 0 : 2 * q, v0 = q == 3 ? 4 : q;
+  const float* k = k2 + 150 * j + 5 * u + 25 * c0 + v0;
+  u4v p[3];
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    float x[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      x[i] = h == 3 && q == 3 ? 0.0f : scale * k[h == 3 && q == 3 ? 0 : 25 * (2 * h + i) + (c0 + 2 * h + i >= 6 ? 1 - 150 : 0)];
+    const Split2 s = split2(x[0], x[1]);
+    p[0][h] = s.h, p[1][h] = s.m, p[2][h] = s.l;
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) items[split_c2_item(u, i, q, j)] = p[i];
+}
+// The record of a row of the input error.
+__device__ __forceinline__ void make_bwd_record(unsigned short* bwd, int row, const float* k2, float scale) {
+  int c, u, v;
+  const bool tap = bwd_tap_of_row(row, c, u, v);
+  const float* k = k2 + (tap ? 25 * c + 5 * u + v : 0);
+  const bool negative = bwd_negative(c, u, v);
+  unsigned p[20];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    const float x = scale * k[300 * i], y = scale * k[300 * i + 150];
+    const Split2 s = split2(!tap ? 0.0f : negative ? -x : x, !tap ? 0.0f : negative ? -y : y);
+    p[i] = s.h, p[6 + i] = s.m, p[12 + i] = s.l;
+  }
+  p[18] = p[19] = 0;
+  u4v* to = reinterpret_cast<u4v*>(bwd + BWD_REC * row);
+#pragma unroll
+  for (int i = 0; i < 5; ++i) to[i] = u4v{p[4 * i], p[4 * i + 1], p[4 * i + 2], p[4 * i + 3]};
+}
+// C1: shifts sh and sh + 2, sh < 2, of row u of map m.
+__device__ __forceinline__ void make_c1_items(u4v* items, int task, const float* k1) {
+  const int sh = task & 1, row = task >> 1, u = row % 5, m = row / 5;
+  float x[5];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) x[i] = NEG_LOG2E * k1[5 * row + i];
+  const Split2 a = split2(sh ? 0.0f : x[0], sh ? x[0] : x[1]), b = split2(sh ? x[1] : x[2], sh ? x[2] : x[3]),
+               c = split2(sh ? x[3] : x[4], sh ? x[4] : 0.0f);
+  const unsigned p[3][3] = {{a.h, b.h, c.h}, {a.m, b.m, c.m}, {a.l, b.l, c.l}};
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    items[split_c1_item(i, u, m, sh)] = u4v{p[i][0], p[i][1], p[i][2], 0};
+    items[split_c1_item(i, u, m, sh + 2)] = u4v{0, p[i][0], p[i][1], p[i][2]};
+  }
+}
+// COUNT floats from global memory, all in flight, then in LDS.
+template <int THREADS, int COUNT>
+struct StagedLoad {
+  float v[(COUNT + THREADS - 1) / THREADS];
   __device__ __forceinline__ void fetch(const float* __restrict__ w) {
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
+    for (int r = 0; r * THREADS < COUNT; ++r) {
       const int p = threadIdx.x + THREADS * r;
-      v[r] = w[p < OFF_B2 ? p : 0];
+      v[r] = w[p < COUNT ? p : 0];
     }
   }
-  // Every slot of every item is written by one thread: the zeros of a shifted row by the threads of its first three taps.
-  __device__ __forceinline__ void commit(u4v* items, unsigned short* bwd = nullptr) const {
-    unsigned short* e = reinterpret_cast<unsigned short*>(items);
+  __device__ __forceinline__ void commit(float* stage) const {
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-      const int p = threadIdx.x + THREADS * r;
-      const Split2 s = split2((p < OFF_K2 ? NEG_LOG2E : 0.25f * NEG_LOG2E) * v[r], 0.0f);
-      const unsigned short piece[3] = {(unsigned short)s.h, (unsigned short)s.m, (unsigned short)s.l};
-      if (THREADS * r < OFF_B1 && p < OFF_B1) {
-        const int m = p / 25, u = (p % 25) / 5, x = p % 5;
-        unsigned short* to = e + 8 * split_c1_item(0, u, m, 0);
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-          for (int sh = 0; sh < 4; ++sh) {
-            to[8 * split_c1_item(k, 0, 0, sh) + x + sh] = piece[k];
-            if (x < 3) to[8 * split_c1_item(k, 0, 0, sh) + (x < sh ? x : x + 5)] = 0;
-          }
-      } else if (p >= OFF_K2 && p < OFF_B2) {
-        const int j = (p - OFF_K2) / 150, tap = (p - OFF_K2) % 150, c = tap / 25, u = (tap % 25) / 5, kk = 6 * (tap % 5) + c;
-        unsigned short* to = e + 8 * split_c2_item(u, 0, kk >> 3, j) + (kk & 7);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          to[8 * 48 * k] = piece[k];
-          if (kk >= 28) to[8 * 48 * k + 2] = 0;  // slots 30 and 31
-        }
-        if (BWD) {
-          const Split2 b = split2((bwd_negative(c, u, tap % 5) ? -0.25f : 0.25f) * v[r], 0.0f);
-          unsigned short* rec = bwd + BWD_REC * bwd_row(c, u, tap % 5) + j;
-          rec[0] = (unsigned short)b.h;
-          rec[12] = (unsigned short)b.m;
-          rec[24] = (unsigned short)b.l;
-        }
-      }
-    }
-    if (BWD && threadIdx.x < BWD_ZERO_ROWS * BWD_REC / 2)
-      reinterpret_cast<unsigned*>(bwd + BWD_REC * bwd_zero_row(threadIdx.x / (BWD_REC / 2)))[threadIdx.x % (BWD_REC / 2)] = 0;
+    for (int r = 0; r * THREADS < COUNT; ++r)
+      if ((int)threadIdx.x + THREADS * r < COUNT) stage[threadIdx.x + THREADS * r] = v[r];
+  }
+};
+// All operands from the flat weights.  BWD: the records of the input error too.
+template <int THREADS, bool BWD>
+struct SplitLoad : StagedLoad<THREADS, OFF_B2> {
+  static constexpr int ROW_THREAD = 256, C1_THREAD = 448;  // one task per thread, kinds on whole waves where it fits
+  static_assert(C2_TASKS <= ROW_THREAD && ROW_THREAD + BWD_TASKS <= C1_THREAD && C1_THREAD + C1_TASKS <= THREADS, "one task per thread");
+  // `stage`: OFF_B2 words of LDS that nobody uses until the caller's barrier.
+  __device__ __forceinline__ void commit(float* stage, u4v* items, unsigned short* bwd = nullptr) const {
+    StagedLoad<THREADS, OFF_B2>::commit(stage);
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < C2_TASKS) make_c2_items(items, t, stage + OFF_K2, 0.25f * NEG_LOG2E);
+    if (BWD && t >= ROW_THREAD && t < ROW_THREAD + BWD_TASKS) make_bwd_record(bwd, t - ROW_THREAD, stage + OFF_K2, 0.25f);
+    if (t >= C1_THREAD && t < C1_THREAD + C1_TASKS) make_c1_items(items, t - C1_THREAD, stage + OFF_K1);
   }
 };
 
