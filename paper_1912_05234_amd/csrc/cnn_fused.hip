@@ -26,11 +26,11 @@ using namespace cnn;
 constexpr int TRAIN_BLOCKS = 256;  // most workgroups (= gradient partials) of the large-batch training kernel: one per compute unit
 // Batches up to this size give each image to a workgroup of eight waves (lower latency per image;
 // up to two such workgroups share a compute unit); larger ones give each image to a single wave
-// (more images in flight, no barriers).  Measured crossover: 21.7 against 27.9 us per step at batch
-// 512, 30.8 against 28.8 us at batch 768.
-constexpr int GROUP_MAX_BATCH = 640;
-// The same choice for the forward pass alone: 4.6 us for up to 256 images, 1.8 more for every 256 beyond (8.0 at 768, 9.8 at
-// 1024, 11.7 at 1280) with eight waves per image, 11.1 for any number up to 2048 with one.
+// (more images in flight, no barriers).  Measured crossover, gradient of 512 / 513 / 576 / 640 images: 20.8 / 24.0 / 27.5 /
+// 28.2 us with eight waves per image (a third workgroup has to wait), 23.2 / 23.1 / 23.7 / 23.7 us with one.
+constexpr int GROUP_MAX_BATCH = 512;
+// The same choice for the forward pass alone: evaluation of 512 / 768 / 896 / 1024 images 9.4 / 10.9 / 12.8 / 12.9 us with eight
+// waves per image (1.8 more for every 256), 13.1 for any number up to 2048 with one.
 constexpr int FWD_GROUP_MAX_BATCH = 1024;
 // Device-side epoch loop: one barrier flag per workgroup (a batch of at most EPOCH_MAX_BATCH images:
 // thread t of a 512-thread workgroup polls flag t), one flag nobody sets, the error word.

@@ -1,4 +1,4 @@
-// The training step of more than 640 images: ONE WAVEFRONT (64 lanes) OWNS ONE IMAGE from the pixel load to the last
+// The training step of more than 512 images: ONE WAVEFRONT (64 lanes) OWNS ONE IMAGE from the pixel load to the last
 // gradient term, eight waves to a workgroup, two to a SIMD.  Definitions: arXiv 1912.05234, Section 3 (forward, conv, mconv,
 // sigmoid, avgpool, backweights, backbias, backin, backavgpool); the backward pass is the chain rule over those.
 //

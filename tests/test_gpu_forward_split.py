@@ -1,4 +1,4 @@
-"""The forward pass of more than 1024 images and the gradient of more than 640 (one wave per image, convolutions as products
+"""The forward pass of more than 1024 images and the gradient of more than 512 (one wave per image, convolutions as products
 of bfloat16 pieces) against the fp32 matrix instructions that smaller calls run on: sizes around a whole number of images per wave and workgroup, and
 operands far from 1, where the pieces have to keep a float's range."""
 import numpy as np
@@ -46,7 +46,7 @@ def test_updated_weights_reach_the_pieces():
     assert torch.equal(net.forward(x), fresh.forward(x))
 
 
-@pytest.mark.parametrize("B,pixel,gain", [(641, 1.0, 1.0), (1025, 1e-3, 40.0), (2049, 1.0, 4.0), (1100, 1e30, 1e-30), (700, 1e-30, 1e20)])
+@pytest.mark.parametrize("B,pixel,gain", [(513, 1.0, 1.0), (641, 1.0, 1.0), (1025, 1e-3, 40.0), (2049, 1.0, 4.0), (1100, 1e30, 1e-30), (700, 1e-30, 1e20)])
 def test_gradient_against_the_fp32_instructions(B, pixel, gain):
     images, labels = inputs.make_batch(B, 27)
     w = inputs.make_random_biases(inputs.make_weights(), 28)
@@ -55,8 +55,8 @@ def test_gradient_against_the_fp32_instructions(B, pixel, gain):
     x, lab = torch.from_numpy(images * np.float32(pixel)).to("cuda:0"), torch.from_numpy(labels).to("cuda:0")
     grad, loss = (t.cpu().numpy().astype(np.float64) for t in net.gradient(x, lab))
     want, want_loss = np.zeros_like(grad), 0.0
-    for i in range(0, B, 600):
-        g, n = net.gradient(x[i:i + 600].contiguous(), lab[i:i + 600].contiguous())
+    for i in range(0, B, 500):
+        g, n = net.gradient(x[i:i + 500].contiguous(), lab[i:i + 500].contiguous())
         want += g.cpu().numpy().astype(np.float64)
         want_loss += float(n.cpu().numpy().sum())
     at = 0

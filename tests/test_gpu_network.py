@@ -53,7 +53,7 @@ def test_forward_activations(B):
         np.testing.assert_array_equal(yhat[n], acts["y"][n])
 
 
-# 640 is the last size of the small-batch kernel; 1023 / 1025 / 1500 straddle one image per wave
+# 512 is the last size of the small-batch kernel; 1023 / 1025 / 1500 straddle one image per wave
 @pytest.mark.parametrize("B", [1, 3, 63, 100, 257, 512, 640, 641, 1023, 1025, 1500])
 def test_batch_gradient(B):
     images, labels = inputs.make_batch(B, 22)
@@ -70,11 +70,11 @@ def test_batch_gradient(B):
     np.testing.assert_array_equal(host(net.get_weights_flat()), inputs.flatten(w))
 
 
-@pytest.mark.parametrize("B", [640, 700])
+@pytest.mark.parametrize("B", [512, 640, 700])
 def test_gradient_of_a_repeated_image(B):
     """B copies of ONE image: the batch gradient is B times that image's gradient, so every layer's
     error array of the single image (the bias gradients are its sums per map) is checked against
-    the oracle's, in the small-batch kernel (640) and in the one-wave-per-image kernel (700)."""
+    the oracle's, in the small-batch kernel (512) and in the one-wave-per-image kernel."""
     image, label = inputs.make_batch(1, 27)
     images, labels = np.repeat(image, B, axis=0), np.repeat(label, B)
     w = weights(biases=True)
