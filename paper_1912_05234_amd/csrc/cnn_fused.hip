@@ -270,13 +270,13 @@ constexpr int TWAVES = 8;
 // pattern of SHARE_ROUNDS rounds repeats every SHARE_PERIOD images.  A function of K and the wave
 // alone, so the grouping of the gradient sums (and with it every rounding) is the same in every run.
 // Why not full rounds only: the two waves of a SIMD do not advance at the same rate.  The one in
-// the lower slot wins the issue arbitration more often and needs about 64 thousand clocks per
-// image where its partner needs 88 (51 thousand for a wave that has the SIMD to itself), in every
-// workgroup alike, so an equal split leaves the SIMD to one wave for the last sixth of the kernel.
+// the lower slot wins the issue arbitration more often, in every workgroup alike, so an equal split leaves
+// the SIMD to one wave for the last part of the kernel.  Gradient of 10000 / 20000 images and an epoch of one batch of 60000:
+// 110 / 207 / 591 us with an equal split, 110 / 203 / 585 with 7 images to 6, 105 / 197 / 575 with 4 to 3, 105 / 196 / 570 with 3 to 2.
 // A batch that does not fill the machine (K < 8) still leaves waves 4..7 idle rather than two
 // waves on one SIMD and none on another: the first round is a full one.
-constexpr unsigned SHARE_PATTERN = 0xB;  // rounds F F H F (first round in bit 0): 4 images to 3
-constexpr int SHARE_ROUNDS = 4;
+constexpr unsigned SHARE_PATTERN = 0x5;  // rounds F H F (first round in bit 0): 3 images to 2
+constexpr int SHARE_ROUNDS = 3;
 constexpr bool share_full(int r) { return (SHARE_PATTERN >> r) & 1; }
 constexpr int share_start(int r) {  // first image of round r inside a period
   int at = 0;
