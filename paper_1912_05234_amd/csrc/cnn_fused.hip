@@ -660,7 +660,7 @@ struct Layout {
   size_t w, tabg, dest, partial, eval_partial, fc_hist, sync, total;
 };
 
-// Partial rows a step can write: one per workgroup, in the one-wave-per-image kernel (four waves
+// Partial rows a step can write: one per workgroup, in the one-wave-per-image kernel (eight waves
 // per workgroup) or in the small-batch kernel (one workgroup per image).
 inline int partial_rows_for(int max_batch) {
   const int by_wave = max_batch < TRAIN_BLOCKS ? max_batch : TRAIN_BLOCKS;
