@@ -2,7 +2,7 @@
 // (the shape of the network's second convolution), in the col2im form of `backin` (arXiv
 // 1912.05234, Section 3, "Backpropagating Convolution"):
 //   T[(c,u,v), p] = sum_j k[j,c,u,v] * d_out[j,p],      d_in[c, y(p)+u, x(p)+v] += T[(c,u,v), p]
-// up to 1024 images, two waves per image (more: cnn_layer_split.h).  The 150 rows of T fill ten 16-row tiles of v_mfma_f32_16x16x4_f32 (K = 12
+// one or two waves per image.  The 150 rows of T fill ten 16-row tiles of v_mfma_f32_16x16x4_f32 (K = 12
 // output maps in three steps, four tiles of sixteen pixels): 120 matrix instructions per image, where
 // a forward convolution over the bordered error (cnn_tile.h) needs 414.  T is
 // added into an LDS copy of d_in.  With level = 2 nt + u (nt = pixel tile = row pair of p), two terms of one
@@ -26,13 +26,14 @@ struct __align__(16) Lds {
 };
 constexpr int COUT = 12, CIN = 6, OUT_PIXELS = 64, IN_FLOATS = NS1, OUT_FLOATS = COUT * OUT_PIXELS;
 
-// One wave takes the maps 0..3, its neighbour the maps 4 and 5.
-template <int WAVES>
+// PARTS = 2: one wave takes the maps 0..3, its neighbour the maps 4 and 5.
+template <int WAVES, int PARTS>
 __global__ __launch_bounds__(64 * WAVES) void conv_bwd_input_kernel(const float* __restrict__ d_out,
                                                                     const float* __restrict__ k,
                                                                     float* __restrict__ d_in, int B) {
+  static_assert(PARTS <= 2, "parts are the plain and the packed maps");
   __shared__ Lds<WAVES> lds;
-  const Share<WAVES, 2> mine;
+  const Share<WAVES, PARTS> mine;
   const int t = threadIdx.x, wave = t >> 6, l = t & 63, q = l >> 4, n16 = l & 15;
   // ---- A operands: lane (q, n16) of entry (tile, s) holds k[j = 4 s + q][c][tap] of tile row n16 ----
 #pragma unroll 4
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(64 * WAVES) void conv_bwd_input_kernel(const float*
     };
     f4 tu[4];
     tiles(18 + kTilePU * 3, tu);
-    if (mine.part == 0) {  // maps 0..3: lane quarter q owns map q
+    if (PARTS == 1 || mine.part == 0) {  // maps 0..3: lane quarter q owns map q
       f4 t4[4], tv[4], tn[4];
       tiles(kTileU4 * 3, t4);
       float* tgt = acc + 144 * q + pp;
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(64 * WAVES) void conv_bwd_input_kernel(const float*
         }
       }
     }
-    if (mine.part == 1) {  // maps 4, 5: quarters 0, 1 for the tap columns 0..2 into d_in, quarters 2, 3 for 3, 4 into the copy
+    if (PARTS == 1 || mine.part == 1) {  // maps 4, 5: quarters 0, 1 for the tap columns 0..2 into d_in, quarters 2, 3 for 3, 4 into the copy
       float* tgt = q < 2 ? acc + 144 * (4 + q) + pp : copy + 144 * (q - 2) + pp + 3;
       f4 tv[4], tn[4];
       tiles(18 + kTilePV0 * 3, tv);
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(64 * WAVES) void conv_bwd_input_kernel(const float*
     }
     // ---- d_in of this image (or of this wave's maps): consecutive floats, the two halves of the maps 4, 5 joined ----
     float* dst = d_in + n * IN_FLOATS;
-    const int begin = mine.part == 0 ? 0 : 4 * 144, end = mine.part == 1 ? IN_FLOATS : 4 * 144;
+    const int begin = PARTS == 1 || mine.part == 0 ? 0 : 4 * 144, end = PARTS == 1 || mine.part == 1 ? IN_FLOATS : 4 * 144;
     for (int e = begin + l; e < end; e += 64) {
       float v = acc[e];
       if (e >= 4 * 144) v += copy[e - 4 * 144];

@@ -17,7 +17,7 @@
 //                    in registers over all of a wave's images; the waves of a workgroup are
 //                    added through LDS in a fixed order and the workgroup writes one set of partial
 //                    tiles, which igemm::wgrad_reduce_kernel adds up
-//   (the input gradient of this shape is cnn_col2im.h; more than 1024 images of it: cnn_layer_split.h)
+//   (the input gradient of this shape is cnn_col2im.h)
 // namespace conv1: one input and six output maps, 5 x 5 kernel, 28 x 28 input: forward and weight
 //   gradient as GEMMs over pixel pairs, 144 per image each, and the input gradient on the vector
 //   unit; see there.

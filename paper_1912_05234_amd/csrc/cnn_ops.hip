@@ -15,7 +15,6 @@
 #include "cnn_tile_bf16.h"
 #include "cnn_col2im.h"
 #include "cnn_conv_wave.h"
-#include "cnn_layer_split.h"
 #include "cnn_fc_wave.h"
 
 namespace {
@@ -750,8 +749,7 @@ int launch_tile_wgrad(TileWgradPlan& p, const float* in, const float* d_out, flo
 // One wave per image leaves the machine idle while there are fewer images than SIMDs (1024): a call then takes as long as
 // one image does in one wave, next to seven others of its workgroup.  Up to SPLIT_IMAGES the image's pixels (input
 // gradient: its maps) are shared out among waves, in workgroups of fewer images, as long as all of them are
-// resident at once; beyond, the copies of the image and of the operand tables cost more than the shorter chain gives, and
-// the second layer's calls are those of cnn_layer_split.h (which the last column does not show: 8.4, 11, 10.6 us).
+// resident at once; beyond, the copies of the image and of the operand tables cost more than the shorter chain gives.
 // Kernel times, us, one wave per image -> as below (weight gradients: + 0 .. 2 us of the second kernel, which adds more rows):
 //   images            10              100             250             500             800             2000 (split, not taken)
 //   C1 forward        7.5 -> 3.9      8.5 -> 4.0      8.8 -> 4.2      8.9 -> 5.4      9.3 -> 7.0      10.2 -> 11.1
@@ -768,12 +766,6 @@ constexpr int FEW_IMAGES = NUM_CU, SPLIT_IMAGES = 4 * NUM_CU;
 inline unsigned image_groups(int B, int images) {
   const long long g = ceil_div(B, images);
   return (unsigned)(g < 2 * NUM_CU ? g : 2 * NUM_CU);
-}
-
-// The same for the kernels of cnn_layer_split.h, one workgroup of eight waves per compute unit.
-inline unsigned split_groups(int B) {
-  const long long g = ceil_div(B, conv2_split::WAVES);
-  return (unsigned)(g < NUM_CU ? g : NUM_CU);
 }
 
 template <bool ROUND>
@@ -796,18 +788,19 @@ int launch_conv1_bwd_input(const float* d_out, const float* k, float* d_in, int 
 }
 
 void launch_conv2_fwd(const float* in, const float* k, const float* bias, float* out, int B, hipStream_t st) {
+  // (beyond: two workgroups per compute unit; one, three or four measured the same, the kernel is bound by its matrix instructions)
   if (B <= SPLIT_IMAGES)
     conv2::forward_kernel<8, 4><<<image_groups(B, 2), 64 * 8, 0, st>>>(in, k, bias, out, B);
   else
-    conv2_split::forward_kernel<<<split_groups(B), conv2_split::THREADS, 0, st>>>(in, k, bias, out, B);
+    conv2::forward_kernel<8, 1><<<image_groups(B, 8), 64 * 8, 0, st>>>(in, k, bias, out, B);
 }
 
 void launch_conv2_bwd_input(const float* d_out, const float* k, float* d_in, int B, hipStream_t st) {
-  // col2im form, 120 instead of 414 matrix instructions per image
+  // col2im form, 120 instead of 414 matrix instructions per image; beyond: 112 registers per lane, four waves per SIMD
   if (B <= SPLIT_IMAGES)
-    col2im::conv_bwd_input_kernel<4><<<image_groups(B, 2), 64 * 4, 0, st>>>(d_out, k, d_in, B);
+    col2im::conv_bwd_input_kernel<4, 2><<<image_groups(B, 2), 64 * 4, 0, st>>>(d_out, k, d_in, B);
   else
-    conv2_split::bwd_input_kernel<<<split_groups(B), conv2_split::THREADS, 0, st>>>(d_out, k, d_in, B);
+    col2im::conv_bwd_input_kernel<8, 1><<<image_groups(B, 8), 64 * 8, 0, st>>>(d_out, k, d_in, B);
 }
 
 // Images per round of a workgroup of the weight gradients launched below.
@@ -826,7 +819,7 @@ void launch_conv2_wgrad(const float* in, const float* d_out, float* part, int B,
   switch (conv2_wgrad_images(B)) {
     case 2: conv2::bwd_weight_kernel<4, 2><<<gx, 64 * 4, 0, st>>>(in, d_out, part, B); break;
     case 4: conv2::bwd_weight_kernel<4, 1><<<gx, 64 * 4, 0, st>>>(in, d_out, part, B); break;
-    default: conv2_split::bwd_weight_kernel<<<gx, conv2_split::THREADS, 0, st>>>(in, d_out, part, B); break;
+    default: conv2::bwd_weight_kernel<8, 1><<<gx, 64 * 8, 0, st>>>(in, d_out, part, B); break;
   }
 }
 
@@ -861,9 +854,9 @@ WgradPlan plan_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
   } else if (conv2::shape_fits(Cin, H, W, Cout, KH, KW)) {
     p.kernel = WgradPlan::CONV2;
     p.NT = 10;
-    p.gx = B <= SPLIT_IMAGES ? image_groups(B, conv2_wgrad_images(B)) : split_groups(B);
+    p.gx = image_groups(B, conv2_wgrad_images(B));
     p.workspace_bytes = conv2::bwd_weight_workspace_bytes(p.gx);
-    p.least_bytes = std::min(p.workspace_bytes, conv2::bwd_weight_workspace_bytes(image_groups(B, 8)));
+    p.least_bytes = conv2::bwd_weight_workspace_bytes(image_groups(B, 8));
   } else {
     p.tile = plan_tile_wgrad(B, Cin, H, W, Cout, KH, KW);
     if (p.tile.nt) p.kernel = WgradPlan::TILED;
