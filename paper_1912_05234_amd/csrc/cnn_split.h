@@ -1,11 +1,15 @@
-// The two convolutions of the forward pass on the bfloat16 matrix instruction, in fp32 accuracy.  A float is cut into
+// The network's two convolutions, forward and (the second) backward, on the bfloat16 matrix instruction, in fp32 accuracy.  A float is cut into
 // three bfloat16 pieces, x = h + m + l: eight significant bits each, so nothing of its twenty-four is lost, and the range of a
-// bfloat16 is a float's.  A product of two floats is then the six products of pieces whose sizes are at least 2^-16 of
-// the whole (h h, h m, m h, m m, h l, l h; the others are below a float's last bit), each exact, summed in fp32.  Why: a
+// bfloat16 is a float's.  A product of two floats is then nine products of pieces, each exact, summed in fp32: h h, h m,
+// m h, m m, h l, l h, and of 2^-25 of the whole m l, l m (l l is 2^-34).  Why: a
 // v_mfma_f32_16x16x32_bf16 takes 7.6 ns of a SIMD for 8192 multiply-adds, a v_mfma_f32_16x16x4_f32 14.6 ns for 1024, so
 // six of the former replace eight of the latter in 46 instead of 117 ns, and they run beside the vector instructions of the
-// SIMD's other waves, which the fp32 ones do not.  Error against sums in 64 bits, uniform operands: 0.7 (160 products)
-// to 0.35 (32) times that of the fp32 instructions, because a step of 32 products is rounded once.
+// SIMD's other waves, which the fp32 ones do not.
+// Error against sums in 64 bits.  Left out are m l and l m, where their slots are not free, and l l: at most 2^-24 of a product.
+// The instruction adds sixteen products at a time, cut at 2^-24 of the largest of them and of the sum they are added to,
+// which is rounded each time.  Uniform operands: 0.7 (160 products) to 0.35 (32) times the error of the fp32 instructions.
+// A single product is up to one last bit off (rms 1.3 times that of fp32), sums of four are as exact: fit for this network,
+// whose sums are 25 products and a bias, 150, 12 times up to 25, and 64 per image, not for calls on operands of any kind.
 //
 // Layouts (64 lanes, q = lane / 16, n16 = lane % 16): A[i = n16][k = 8 q ..  8 q + 7], B[k = 8 q .. 8 q + 7][j = n16],
 // D[i = 4 q + r][j = n16] in register r.  An "item" is what a lane supplies to one instruction: eight bfloat16, 16 bytes.
@@ -23,9 +27,10 @@ typedef unsigned u2v __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ f4 mfma_bf16(bf8 a, bf8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 
-// The pieces of x (low half of each word) and y (high half).  h is cut off, not rounded, so that no finite float
-// becomes an infinity; m and l are rounded to nearest, so that what is left out has either sign.  Below 2^-109 (1.5e-33) the
-// last bits of l leave bfloat16's range: an operand is then kept to 2^-134 in place of 24 bits.
+// The pieces of x (low half of each word) and y (high half), each rounded to nearest, so that m is at most 2^-8 and l 2^-17 of
+// x's power of two and both have either sign.  (With h cut off, m and l are twice as large and m has x's sign: one product was
+// off by up to 2^-22, the C1 weight gradient of 40000 images by 5.8e-8 where this gives 4.5e-8 and fp32 instructions 4.6e-8.)
+// Below 2^-109 (1.5e-33) the last bits of l leave bfloat16's range: an operand is then kept to 2^-134 in place of 24 bits.
 struct Split2 {
   unsigned h, m, l;
 };
@@ -34,26 +39,20 @@ __device__ __forceinline__ unsigned pack_bf16(float x, float y) {
   using bf2v = __bf16 __attribute__((ext_vector_type(2)));
   return __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{x, y}, bf2v));
 }
-__device__ __forceinline__ Split2 split2(float x, float y) {
-  const unsigned xi = __float_as_uint(x), yi = __float_as_uint(y);
+__device__ __forceinline__ Split2 split2_rest(float x, float y, unsigned h) {
   Split2 s;
-  s.h = __builtin_amdgcn_perm(yi, xi, 0x07060302u);
-  const float rx = x - __uint_as_float(xi & 0xffff0000u), ry = y - __uint_as_float(yi & 0xffff0000u);
+  s.h = h;
+  const float rx = x - __uint_as_float(h << 16), ry = y - __uint_as_float(h & 0xffff0000u);
   s.m = pack_bf16(rx, ry);
   s.l = pack_bf16(rx - __uint_as_float(s.m << 16), ry - __uint_as_float(s.m & 0xffff0000u));
   return s;
 }
-
-// The same with h rounded to nearest too, for values that are far from the largest floats: m has either sign, so that the
-// products left out (m l, l m) do not add up over many values that meet one weight.  With h cut off, the C1 weight
-// gradient of 40000 images was off by 5.8e-8 where this gives 4.5e-8 and fp32 instructions 4.6e-8.
-__device__ __forceinline__ Split2 split2_nearest(float x, float y) {
-  Split2 s;
-  s.h = pack_bf16(x, y);
-  const float rx = x - __uint_as_float(s.h << 16), ry = y - __uint_as_float(s.h & 0xffff0000u);
-  s.m = pack_bf16(rx, ry);
-  s.l = pack_bf16(rx - __uint_as_float(s.m << 16), ry - __uint_as_float(s.m & 0xffff0000u));
-  return s;
+// For values below 2^127.
+__device__ __forceinline__ Split2 split2_bounded(float x, float y) { return split2_rest(x, y, pack_bf16(x, y)); }
+// For any finite values: h stops at the largest bfloat16, where rounding would make an infinity.
+__device__ __forceinline__ Split2 split2(float x, float y) {
+  const float top = __uint_as_float(0x7f7f0000u);
+  return split2_rest(x, y, pack_bf16(__builtin_amdgcn_fmed3f(x, -top, top), __builtin_amdgcn_fmed3f(y, -top, top)));
 }
 
 // ---- operand items in LDS, shared by the waves of a workgroup -----------------------------------------------------
@@ -68,8 +67,8 @@ __host__ __device__ constexpr int split_c1_item(int piece, int u, int m, int sh)
 __host__ __device__ constexpr int split_c2_item(int u, int piece, int q, int j) { return SPLIT_C1_ITEMS + ((u * 3 + piece) * 4 + q) * 12 + j; }
 // Input error of C2 (training): T[row][pixel] = sum_j W[row][j] * d_c2[j][pixel] over twelve maps, rows as in cnn_wave.h (tiles
 // V(0..4), U4 of the maps 0..3, then the packed PV(0..2), PU), W = k2[j] / 4.  Twelve K elements would leave most of a step
-// of 32 empty, so the six products lie side by side: 72 slots, two steps of 32 and a quarter of a third.  A row is a
-// record [h 12][m 12][l 12][4 unused], and so is a pixel of d_c2; slot group g < 18 (four slots) is part g % 3 of product g / 3.
+// of 32 empty, so eight products (all but l l) lie side by side: 96 slots, three steps of 32.  A row is a
+// record [h 12][m 12][l 12][4 unused], and so is a pixel of d_c2; slot group g < 24 (four slots) is part g % 3 of product g / 3.
 constexpr int BWD_TILES = 10, BWD_REC = 40, BWD_PV = 6, BWD_PU = 9;
 __host__ __device__ constexpr int bwd_row(int c, int u, int v) {  // row of tap (c, u, v), 16 to a tile
   if (c < 4) return u < 4 ? 16 * v + 4 * c + u : v < 4 ? 16 * 5 + 4 * c + v : 16 * BWD_PU + 4 * c + 3;
@@ -102,22 +101,22 @@ constexpr bool bwd_rows_ok() {
 }
 static_assert(bwd_rows_ok(), "the inverse of bwd_row");
 __host__ __device__ constexpr int bwd_group(int g, bool a) {  // offset of slot group g in a record, in fours
-  constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+  constexpr int PA[8] = {2, 1, 2, 0, 1, 1, 0, 0}, PB[8] = {1, 2, 0, 2, 1, 0, 1, 0};
   return 3 * (a ? PA[g / 3] : PB[g / 3]) + g % 3;
 }
-// The group that quarter q supplies as half i of the items (steps of two halves; the third step's two are quarter 0's
-// alone): quarters 0 and 1, and 2 and 3, differ by an odd number in both offsets, so that the sixteen records of both (an
-// odd multiple of four words apart) lie on different banks.
-constexpr int BWD_GROUPS[6][4] = {{0, 1, 2, 6}, {3, 4, 5, 8}, {9, 10, 12, 13}, {11, 14, 7, 16}, {15, 15, 15, 15}, {17, 17, 17, 17}};
+// The group that quarter q supplies as half i of the items (steps of two halves, the small products first): quarters 0 and 1,
+// and 2 and 3, differ by an odd number in both offsets, so that the sixteen records of both (an odd multiple of four
+// words apart) lie on different banks.  (All but the last pair, which is left over.)
+constexpr int BWD_GROUPS[6][4] = {{0, 1, 2, 3}, {4, 5, 6, 7}, {8, 12, 9, 10}, {11, 14, 15, 16}, {17, 18, 19, 20}, {13, 22, 21, 23}};
 constexpr bool bwd_groups_ok() {
   int seen = 0;
-  for (int i = 0; i < 4; ++i)
-    for (int q = 0; q < 4; q += 2)
-      for (int a = 0; a < 2; ++a)
-        if ((bwd_group(BWD_GROUPS[i][q], a) + bwd_group(BWD_GROUPS[i][q + 1], a)) % 2 == 0) return false;
   for (int i = 0; i < 6; ++i)
-    for (int q = 0; q < (i < 4 ? 4 : 1); ++q) seen |= 1 << BWD_GROUPS[i][q];
-  return seen == (1 << 18) - 1;
+    for (int q = 0; q < 4; ++q) {
+      seen |= 1 << BWD_GROUPS[i][q];
+      for (int a = 0; a < 2; ++a)
+        if (q % 2 == 0 && 4 * i + q < 22 && (bwd_group(BWD_GROUPS[i][q], a) + bwd_group(BWD_GROUPS[i][q + 1], a)) % 2 == 0) return false;
+    }
+  return seen == (1 << 24) - 1;
 }
 static_assert(bwd_groups_ok(), "every group once, neighbours on different banks");
 __host__ __device__ constexpr unsigned bwd_groups(int q, bool a) {  // four bits each
@@ -228,8 +227,8 @@ __device__ __forceinline__ void split_store_pixels(unsigned* img, int at, f4 v) 
 // Rows i = 4 sh + m % 4, so that lane (q, n16) of the result holds the maps of ONE pixel, x = 4 X + q: tile 0 the maps 0..3,
 // tile 1 the maps 4, 5 (its other rows repeat them and are not used).  Columns: nine tiles T = 3 ty + tx of sixteen (y, X),
 // y = 8 ty + 2 a + dy, X = 2 tx + bx, n16 = dy + 2 a + 8 bx.  K: an instruction takes four (u, product) pairs, one per lane
-// quarter: quarter q takes row u = q in six instructions, one per product, and row u = 4's six products are two
-// instructions more (two quarters of the last are zero): 16 instructions per column tile, 144 per image.
+// quarter: quarter q takes row u = q in six instructions, one per product, and row u = 4's products (with m l and l m,
+// whose quarters are free) are two instructions more: 16 instructions per column tile, 144 per image.
 struct C1SWeights {
   bf8 row[2][3];    // pieces of row u = q
   bf8 mixed[2][2];  // row u = 4, piece by quarter
@@ -241,11 +240,9 @@ __device__ __forceinline__ void c1s_load_weights(C1SWeights& w, const u4v* items
     const int m = mt == 0 ? n16 & 3 : 4 + (n16 & 1);
 #pragma unroll
     for (int k = 0; k < 3; ++k) w.row[mt][k] = __builtin_bit_cast(bf8, items[split_c1_item(k, q, m, sh)]);
-    // image pieces l, h, m, m | h, h, -, - (c1s_lane) meet weight pieces h, l, m, h | m, h, 0, 0
+    // image pieces l, h, m, m | h, h, l, m (c1s_lane) meet weight pieces h, l, m, h | m, h, m, l
     w.mixed[mt][0] = __builtin_bit_cast(bf8, items[split_c1_item(q == 1 ? 2 : q == 2 ? 1 : 0, 4, m, sh)]);
-    u4v last = items[split_c1_item(q == 0 ? 1 : 0, 4, m, sh)];
-    if (q >= 2) last = u4v{0, 0, 0, 0};
-    w.mixed[mt][1] = __builtin_bit_cast(bf8, last);
+    w.mixed[mt][1] = __builtin_bit_cast(bf8, items[split_c1_item(q == 1 ? 0 : q == 3 ? 2 : 1, 4, m, sh)]);
   }
 }
 struct C1SLane {
@@ -257,7 +254,7 @@ __device__ __forceinline__ C1SLane c1s_lane(const unsigned* img, int l) {
   C1SLane o;
   o.row = at + 14 * q;
   o.mixed0 = at + 14 * 4 + SPLIT_IMG_PLANE * (q == 0 ? 2 : q == 1 ? 0 : 1);
-  o.mixed1 = at + 14 * 4;
+  o.mixed1 = at + 14 * 4 + SPLIT_IMG_PLANE * (q < 2 ? 0 : q == 2 ? 2 : 1);
   return o;
 }
 __host__ __device__ constexpr int c1s_tile_img(int T) { return (T / 3) * 112 + (T % 3) * 4; }  // words
@@ -330,7 +327,7 @@ __device__ __forceinline__ int c1s_lane_s1(int l) {
 // Pieces of two values to two elements; BOTH: of both copies.
 template <bool BOTH>
 __device__ __forceinline__ void split_store_s1(unsigned short* s1, int e0, float v0, int e1, float v1) {
-  const Split2 s = split2_nearest(v0, v1);
+  const Split2 s = split2_bounded(v0, v1);
   const unsigned p[3] = {s.h, s.m, s.l};
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -345,7 +342,7 @@ __device__ __forceinline__ void split_store_s1(unsigned short* s1, int e0, float
 // The same for one value.
 template <bool BOTH>
 __device__ __forceinline__ void split_store_s1_one(unsigned short* s1, int e, float v) {
-  const Split2 s = split2_nearest(v, 0.0f);
+  const Split2 s = split2_bounded(v, 0.0f);
   const unsigned p[3] = {s.h, s.m, s.l};
 #pragma unroll
   for (int k = 0; k < 3; ++k)
@@ -520,7 +517,6 @@ __device__ __forceinline__ void col2im_split(const unsigned short* bwd, const un
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
       bd[nt][i] = b[16 * nt * (BWD_REC / 4)];
-      if (i >= 4 && q >= 1) bd[nt][i] = u2v{0, 0};
     }
   }
   wave_sync();

@@ -234,7 +234,7 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
       st.g_b2 = fmaf(sign, (d[0] + d[1]) + (d[2] + d[3]), st.g_b2);
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const Split2 p = split2_nearest(d[2 * h], d[2 * h + 1]);
+        const Split2 p = split2(d[2 * h], d[2 * h + 1]);
         d2[mt >> 1][0][2 * (mt & 1) + h] = p.h;
         d2[mt >> 1][1][2 * (mt & 1) + h] = p.m;
         d2[mt >> 1][2][2 * (mt & 1) + h] = p.l;

@@ -65,3 +65,28 @@ def test_gradient_against_the_fp32_instructions(B, pixel, gain):
         assert_close(grad[at:at + n], want[at:at + n], RTOL_GRAD, "split grad " + name)
         at += n
     assert abs(loss.sum() - want_loss) <= 1e-5 * want_loss
+
+
+def sigmoid(z):
+    return 1.0 / (1.0 + np.exp(-z))
+
+
+@pytest.mark.parametrize("low", [1.0 + 2.0**-7 - 2.0**-14, 1.0 + 2.0**-8 - 2.0**-17])
+def test_left_out_products_stay_below_a_rounding(low):
+    """Pixels and weights just below the next bfloat16, or just below the middle of two, where what the cut leaves out is largest
+    and of one sign in every product.  Each operand's second and third pieces are at most 2^-8 and 2^-17 of its power of
+    two, so the two products left out are at most 2^-24 of the product's; the constant log2(e), with which the weights are
+    multiplied before the cut, is off by 0.22 x 2^-24 as a float; the other roundings have no common sign.
+    Measured as the factor by which the sums before the sigmoid are off, over all of C1."""
+    rng, B = np.random.default_rng(7), 1025
+    w = {"k1": np.zeros((6, 5, 5), np.float32)}
+    w["k1"][:] = 2.0**-4 * np.where(np.arange(6) % 2, 1.0, -1.0)[:, None, None] * (low + 2.0**-16 * rng.random((6, 5, 5))) / np.log2(np.e)
+    images = (low + 2.0**-16 * rng.random((B, 28, 28))).astype(np.float32)
+    images[:, :, ::2] = 0.0  # sums around 1, where the sigmoid is steep
+    net = binding.CNN(w, max_batch=B)
+    got = net.forward_activations(torch.from_numpy(images).to("cuda:0"))["c1"].cpu().numpy().astype(np.float64)
+    k = torch.from_numpy(w["k1"].astype(np.float64)).view(6, 25)
+    z = torch.matmul(k, torch.nn.functional.unfold(torch.from_numpy(images.astype(np.float64)).view(B, 1, 28, 28), 5)).numpy().reshape(got.shape)
+    steep = z * sigmoid(z) * sigmoid(-z)
+    off = ((got - sigmoid(z)) * steep).sum() / (steep * steep).sum()
+    assert abs(off) <= 1.5 * 2.0**-24, "sums off by %.2f x 2^-24" % (off * 2.0**24)
