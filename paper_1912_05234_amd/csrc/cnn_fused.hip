@@ -67,7 +67,8 @@ __device__ __forceinline__ void judge_lanes(float y, bool out_lane, int label, f
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
   };
   top = fmaxf(fmaxf(from(top, 0), from(top, 16)), from(top, 32));
-  const unsigned long long best = __ballot(out_lane && y == top);  // the lowest lane is the lowest index
+  // the lowest lane is the lowest index; a first output that is NaN stays the answer, as in `judge`
+  const unsigned long long best = __ballot(out_lane && (y == top || (l == 0 && y != y)));
   n_ok += best != 0 && __builtin_ctzll(best) == 16 * (label >> 2) + (label & 3) ? 1.0f : 0.0f;
   loss = fmaf(0.5f, (from(sq, 0) + from(sq, 16)) + from(sq, 32), loss);
 }

@@ -266,6 +266,24 @@ def test_saturated_sigmoids_stay_finite(B):
     assert abs(host(loss)[0] - ref_loss) <= 1e-5 * max(ref_loss, 1.0)
 
 
+@pytest.mark.parametrize("B", [1000, 1025])
+@pytest.mark.parametrize("nan", [(0,), (3,), (0, 5), tuple(range(10))])
+def test_evaluation_of_outputs_that_are_nan(B, nan):
+    """A diverged network counts the same at every size, as the oracle does: only a larger output replaces the first."""
+    images, labels = inputs.make_batch(B, 31)
+    w = weights(biases=True)
+    w["b"][list(nan)] = np.nan
+    net = binding.CNN(w, max_batch=B)
+    yhat = host(net.forward(dev(images)))
+    assert np.isnan(yhat[:, list(nan)]).all() and np.isnan(yhat).sum() == B * len(nan)
+    best = np.zeros(B, np.int64)
+    for o in range(1, 10):
+        best[yhat[:, o] > yhat[np.arange(B), best]] = o
+    n_ok, loss = net.evaluate(dev(images), dev(labels))
+    assert int(host(n_ok)[0]) == int((best == labels).sum())
+    assert np.isnan(host(loss)[0])
+
+
 def test_kernel_timing_aid():
     """cnn_profile_begin / cnn_profile_read: one reading per recorded step, only the first
     `capacity` steps are recorded, readings are positive and of a plausible size, and recording
