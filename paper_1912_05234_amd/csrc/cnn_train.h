@@ -168,6 +168,7 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
   }
   wave_sync();
   s1_second_copy(s.pool);
+  wave_sync();
   touch_pixels(next_image);
   // ---- C2 = sigmoid(mconv(S1, k2, b2)), S2 = avgpool(C2): a lane's four result registers are one window -------------
   f4 c2v[4];
