@@ -148,15 +148,6 @@ __host__ __device__ constexpr int bwd_packed_source(int tile, int qi, int ri) {
   if (qi < 2) return 25 * c + 20 + ri;
   return ri < 2 ? 25 * c + 23 + ri : -1;
 }
-// Slot of the expanded table (float index) that holds what lane `lane` of packed entry e = tile*3 + s
-// needs, or -1 for a zero: the same weight sits in the plain tiles of AB (maps 0..3) or AB1 (maps 4..7).
-__host__ __device__ constexpr int packed_table_slot(int e, int lane) {
-  const int sidx = e % 3, q = lane >> 4, n16 = lane & 15, src = bwd_packed_source(e / 3, n16 >> 2, n16 & 3);
-  if (src < 0) return -1;
-  const int c = src / 25, tap = src % 25;
-  const int tile = tap < 20 ? tap % 5 : tap < 24 ? (int)kTileU4 : (int)kTileC, ri = tap < 20 ? tap / 5 : tap < 24 ? tap - 20 : 0;
-  return ((c < 4 ? TAB_AB : TAB_AB1) + tile * 3 + sidx) * 64 + q * 16 + (c & 3) * 4 + ri;
-}
 // ---- C1 forward as a GEMM (16x16x4 MFMA) -----------------------------------------------------------
 // Output pixels are taken in horizontal pairs x = 2X + sh (sh = 0, 1).  With v' = v + sh the image
 // factor img[y+u][2X+v'] does not depend on sh:
