@@ -12,7 +12,9 @@ then one call over the first n * batch images for the rest), so no per-step Pyth
 timed region and the figure does not depend on --steps.  Prints ONE JSON line.  Besides the
 contract fields it carries
   roofline      the fused forward+backward kernel's algorithmic flop rate against MI355X's fp32
-                peak, from HIP events recorded around that kernel on its own stream;
+                peak, from HIP events recorded around that kernel on its own stream; batches above 512
+                run their convolutions as products of bfloat16 pieces, which that peak does not
+                bind: there it is a yardstick for fp32 work only;
   cpu_baseline  the single-threaded CPU oracle timed on this host on a bounded sample;
   sweep         the same step at batch 1000 / 10000 / 60000, the forward-only evaluation pass, and the
                 stateless per-op calls at the layer shapes (matrix cores, vector unit alone, bf16):
@@ -41,7 +43,7 @@ GROUP_MAX_BATCH = 512                 # batches up to this size run train_group_
 # what the counters read for a plain 256 MiB copy (FETCH x2.0, WRITE x1.0).  Taken from profiles/,
 # not read in this run; only for the batch sizes that were profiled with the kernels as they are
 # now, null otherwise.
-MEASURED_TRAFFIC_BYTES = {100: 2370765, 60000: 305109402}
+MEASURED_TRAFFIC_BYTES = {100: 2370765, 60000: 309032981}
 
 
 def main():

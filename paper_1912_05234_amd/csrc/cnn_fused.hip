@@ -77,9 +77,9 @@ __device__ __forceinline__ void judge_lanes(float y, bool out_lane, int label, f
 // waves per workgroup (they share the operands), one workgroup per compute unit; wave w of workgroup b takes the images
 // b + blocks * (w + FWAVES k).
 // What bounds it: a SIMD's issue.  264 matrix instructions at 6 ns (7.6 alone; a vector instruction hides under half of
-// one), about 570 vector instructions at 1.25 and 140 exponentials and reciprocals at 3.45 are 2.8 us of the 3.8 us that
+// one), about 560 vector instructions at 1.25 and 140 exponentials and reciprocals at 3.45 are 2.8 us of the 3.8 us that
 // an image takes a SIMD with two waves; three waves (with fewer registers each) take the same.  In fp32 (152 matrix, 2134
-// vector instructions) it was 6.3 us: evaluation of 10000 images 68 -> 45.7 us, of 60000 373 -> 228 us.
+// vector instructions) it was 6.3 us: evaluation of 10000 images 68 -> 42.2 us, of 60000 373 -> 214 us.
 constexpr int FWAVES = 8;
 struct __align__(16) SplitForwardLds {  // of one wave
   unsigned img[3 * SPLIT_IMG_PLANE];
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(64 * GWAVES) void forward_group_kernel(const float*
   }
 }
 
-// Sums the G (count, loss) pairs: 1024 interleaved strands (at most three pairs each for the 3072
+// Sums the G (count, loss) pairs: 1024 interleaved strands (at most two pairs each for the 2048
 // waves of the forward kernel, so the loads are one memory round trip), then a fixed tree over the
 // strands.  The counts are whole numbers (each wave's is far below 2^24, so exact in its float) and
 // are added as 64-bit integers.
@@ -272,8 +272,15 @@ constexpr int TWAVES = 8;
 // alone, so the grouping of the gradient sums (and with it every rounding) is the same in every run.
 // Why not full rounds only: the two waves of a SIMD do not advance at the same rate.  The one in
 // the lower slot wins the issue arbitration more often, in every workgroup alike, so an equal split leaves
-// the SIMD to one wave for the last part of the kernel.  Gradient of 10000 / 20000 images and an epoch of one batch of 60000:
-// 110 / 207 / 591 us with an equal split, 110 / 203 / 585 with 7 images to 6, 105 / 197 / 575 with 4 to 3, 105 / 196 / 570 with 3 to 2.
+// the SIMD to one wave for the last part of the kernel.  Where the last rounds are not full ones, the longest wave decides.
+// Gradient of so many images, us, an equal split / 4 images to 3 (F F H F) / 3 to 2:
+//   2048 and 3072, the same       32 / 32 / 32 and 41 / 41 / 41
+//   3073 .. 4096 (13 .. 16 each)  48.5 .. 51.4 / 48.8 .. 51.7 / 51.1 .. 53.9: three to two gives the lower waves a third image
+//   4608, 5120, 6144              57.5, 59.2, 72.4 / 57.9, 59.6, 72.3 / 57.3, 59.3, 71.3
+//   8448, 9216 (33, 36 each)      97.0, 100.1 / 98.4, 101.1 / 99.4, 103.0
+//   10000, 12000                  113, 136 / 110, 131 / 109, 132
+//   20000, 60000                  222, 588 / 213, 577 / 211, 575
+// One pattern for all sizes, the best of the three from 10000 images on.
 // A batch that does not fill the machine (K < 8) still leaves waves 4..7 idle rather than two
 // waves on one SIMD and none on another: the first round is a full one.
 constexpr unsigned SHARE_PATTERN = 0x5;  // rounds F H F (first round in bit 0): 3 images to 2

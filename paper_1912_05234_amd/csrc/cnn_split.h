@@ -500,8 +500,8 @@ __device__ __forceinline__ void add_column(float& lo, float& hi, float e) {
 // the same lanes, and an odd level shares its rows half and half with the two even ones beside it.  What is added over levels
 // is shifted by v within the quarter (one map) and added over v.  With the sums in
 // LDS, in sixteen dependent rounds of reads, additions and writes (its clearing, a second copy of the maps 4 and 5), an image
-// kept the LDS busy for 1000 clocks, eight waves 8000 of 13000; training on 60000 images took 588 us instead of 572, the
-// input gradient alone of as many 160 us instead of 137.  The input maps 0..3 and 4, 5 are taken one after the other: half the registers.
+// kept the LDS busy for 1000 clocks, eight waves 8000 of 13000; training on 60000 images took 588 us instead of 572.
+// The input maps 0..3 and 4, 5 are taken one after the other: half the registers.
 // d_in may lie over the records; its columns 12..15 get zeros.  `sign`: what d was taken with.
 __device__ __forceinline__ void col2im_split(const unsigned short* bwd, const unsigned short* rec, float* d_in, float sign, int l) {
   const int q = l >> 4, n16 = l & 15;

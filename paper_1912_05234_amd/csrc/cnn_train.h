@@ -5,17 +5,16 @@
 // Where the arithmetic runs
 //   C1, C2 forward        v_mfma_f32_16x16x32_bf16 on the pieces of the operands (cnn_split.h)
 //   C2 weight gradient    the same: M = 12(16) maps, N = 30(32) neighbouring elements of S1 per kernel row, K = 64 pixels
-//   C2 input error        v_mfma_f32_16x16x4_f32: T[tap,pixel] = k2^T * d_c2 (K = 12 maps), then T is
-//                         added into d_s1 at (y+u, x+v) (the col2im form of `backin`: no zero padding)
-//                         in rounds of plain LDS read-add-write whose targets cannot collide
+//   C2 input error        the same: T[tap,pixel] = k2^T * d_c2 (K = 12 maps, eight products side by side), then T is
+//                         summed over the taps in registers (the col2im form of `backin`: no zero padding)
 //   C1 weight gradient    v_mfma_f32_16x16x4_f32: M = 12(16) rows (map, x parity), N = 30(32) shifted taps,
 //                         K = 288 pixel pairs; the C1 error is staged in LDS by column tiles of C1
 //   FC weight gradient    v_mfma_f32_16x16x4_f32, once per wave over all its images
 //   FC, pooling, sigmoid  fp32 VALU
-// What bounds it, 60000 images in 585 us (830 with fp32 instructions throughout), 22.5 thousand clocks of a SIMD per image:
-// 507 bfloat16 and 144 fp32 matrix instructions are 12.8 thousand of them, about 1580 vector instructions of three clocks
-// another 4.7 (few of them under a matrix instruction, see cnn_split.h), the rest are waits that the SIMD's other wave does
-// not cover; the LDS is busy for 60 % of the time.  The C1 weight gradient stays on the fp32 instruction: as products of
+// What bounds it, 60000 images in 577 us (830 with fp32 instructions throughout), 21.8 thousand clocks of a SIMD per image:
+// 507 bfloat16 and 144 fp32 matrix instructions are 12.8 thousand of them, about 1810 vector instructions of three clocks
+// another 5.4 (few of them under a matrix instruction, see cnn_split.h), the rest are waits that the SIMD's other wave does
+// not cover; the LDS is busy for half of the time.  The C1 weight gradient stays on the fp32 instruction: as products of
 // pieces it needs 180 instructions, 300 vector instructions for the cutting, and gains nothing.
 // The waves of a workgroup share the operands in LDS and nothing else; after the barrier that completes them they do
 // not synchronise until they join their gradient sums at the end of the kernel.

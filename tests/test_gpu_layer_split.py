@@ -31,14 +31,14 @@ def test_against_the_plain_kernels(B, scale):
     for bias in (None, b):
         want = host(binding.conv_fwd(x, k, None if bias is None else dev(b), valu=True))
         got = binding.conv_fwd(xs, k, None if bias is None else dev(b * scale))
-        assert_close(host(got) / scale, want, RTOL_ACT, "pieces conv_fwd")
+        assert_close(host(got) / scale, want, RTOL_ACT, "many images conv_fwd")
     assert_close(host(binding.conv_bwd_input(ds, k, 12, 12)) / scale, host(binding.conv_bwd_input(d, k, 12, 12, valu=True)), RTOL_ACT,
-                 "pieces conv_bwd_input")
+                 "many images conv_bwd_input")
     p_k, p_b = binding.conv_bwd_weight(x, d, workspace=False)
     for in_, d_out in ((xs, d), (x, ds)):
         d_k, d_b = binding.conv_bwd_weight(in_, d_out)
-        assert_close(host(d_k) / scale, host(p_k), RTOL_GRAD, "pieces conv_bwd_weight")
-        assert_close(host(d_b) / (scale if d_out is ds else 1.0), host(p_b), RTOL_GRAD, "pieces conv_bwd_bias")
+        assert_close(host(d_k) / scale, host(p_k), RTOL_GRAD, "many images conv_bwd_weight")
+        assert_close(host(d_b) / (scale if d_out is ds else 1.0), host(p_b), RTOL_GRAD, "many images conv_bwd_bias")
 
 
 def test_weight_gradient_stays_in_its_workspace():
@@ -53,8 +53,8 @@ def test_weight_gradient_stays_in_its_workspace():
         d_k, d_b = torch.empty_like(p_k), torch.empty_like(p_b)
         stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
         assert L.cnn_conv_bwd_weight(ptr(x), ptr(d), ptr(d_k), ptr(d_b), B, 6, 12, 12, 12, 5, 5, ptr(ws), ctypes.c_size_t(size), stream) == 0
-        assert_close(host(d_k), host(p_k), RTOL_GRAD, "pieces conv_bwd_weight")
-        assert_close(host(d_b), host(p_b), RTOL_GRAD, "pieces conv_bwd_bias")
+        assert_close(host(d_k), host(p_k), RTOL_GRAD, "many images conv_bwd_weight")
+        assert_close(host(d_b), host(p_b), RTOL_GRAD, "many images conv_bwd_bias")
         used = (ws != 255).nonzero()
         assert used.numel() == 0 or int(used.max()) < size
 

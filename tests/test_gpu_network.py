@@ -34,7 +34,7 @@ def oracle_grad(images, labels, wflat):
     return loss, g
 
 
-# 6149 = 2 * 3072 + 5: more images than the forward kernel has waves, so every wave walks several
+# 6149 = 3 * 2048 + 5: more images than the forward kernel has waves, so every wave walks several
 # images (the hand-over of the prefetched pixels, the activation dump of later images) and the last
 # round is ragged; every image is compared
 @pytest.mark.parametrize("B", [1, 7, 64, 6149])
