@@ -62,8 +62,8 @@ size_t cnn_workspace_bytes(int max_batch);
  *
  * Calls of a context on more than 1024 images (forward pass, evaluation) or 512 (gradient, training) take the
  * operands of the convolutions as sums of three bfloat16 numbers, exact from 2^-109 (1.5e-33) up; what is smaller is
- * kept to 2^-134.  There a pixel times a weight of k1 beyond a float's range may make the image's outputs NaN, where smaller
- * calls saturate to 0 or 1. */
+ * kept to 2^-134.  There a pixel times a weight of k1 beyond 2^136 (a float ends at 2^128) may make the image's outputs NaN,
+ * where smaller calls saturate to 0 or 1. */
 int cnn_init(cnn_ctx** out, void* workspace, size_t workspace_bytes, int max_batch,
              const float* k1, const float* b1, const float* k2, const float* b2,
              const float* fc, const float* b, void* hip_stream);
