@@ -72,8 +72,8 @@ def test_gradient_against_the_fp32_instructions(B, pixel, gain):
     assert abs(loss.sum() - want_loss) <= 1e-5 * want_loss
 
 
-# A product that is left out has a share of 1.  The results' own rounding, of another pattern than any product, gives the
-# 1800 (150) weights of a gradient shares of 0.02 and the activations' of 0.001.
+# A product that is left out has a share of 1.  The results' own rounding, of another pattern than any product, gives shares of up
+# to 0.05 in the gradients (150 and 1800 weights) and 0.005 in the activations.
 SHARE = 0.25
 
 
