@@ -656,7 +656,9 @@ size_t tile_layout_bytes(int B, int Cin, int H, int W, int Cout, int KH, int KW)
   return 0;
 }
 
-TileWgradPlan search_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
+// Five and nine tap tiles of a workgroup: only for unpacked fp32 plans.  With rounded operands they are slower than the fit says
+// (305 images 21 -> 12, 33 x 23, 4 x 4 43.6 -> 46.6 us), packed ones too (850 images 24 -> 1, 19 x 11, 5 x 5 19.7 -> 25.1).
+TileWgradPlan search_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW, bool rounded) {
   TileWgradPlan best, p;
   tile::WgradArgs& a = p.a;
   a.in = a.d_out = nullptr, a.out_k = a.out_b = nullptr;
@@ -675,7 +677,8 @@ TileWgradPlan search_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, 
     if ((P & (P - 1)) && P != 16 / Cout && a.Wo % P) continue;
     for (int mt = 1; mt <= (Cout > 16 ? 2 : 1); ++mt) {
       const int NT = up(Cin * KH * (KW + P - 1), 16);
-      for (int nt : {1, 2, 3, 4, 6, 8, 12}) {
+      for (int nt : {1, 2, 3, 4, 5, 6, 8, 9, 12}) {
+        if ((nt == 5 || nt == 9) && (P > 1 || rounded)) continue;
         if (nt * mt > 16 || (nt > 1 && nt / 2 >= NT) || 16 * nt < KW + P - 1 || !tile_wgrad_form(p, best, P, mt, nt)) continue;
         auto consider = [&](int NB, int TH) { tile_wgrad_candidates(best, p, NB, TH, B > 64 ? 1 : 0, tiny ? 0 : 4); };
         for (long long NB = 1; NB <= B && NB * a.Ho * a.WOP <= 1536; NB = NB < 4 ? NB + 1 : 2 * NB) consider((int)NB, a.Ho);
@@ -693,10 +696,10 @@ TileWgradPlan search_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, 
   return best;
 }
 
-TileWgradPlan plan_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
-  static PlanMemo<TileWgradPlan, 7> memo;
-  return memo.get({B, Cin, H, W, Cout, KH, KW}, [&] {
-    TileWgradPlan p = search_tile_wgrad(B, Cin, H, W, Cout, KH, KW);
+TileWgradPlan plan_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW, bool rounded) {
+  static PlanMemo<TileWgradPlan, 8> memo;
+  return memo.get({B, Cin, H, W, Cout, KH, KW, rounded}, [&] {
+    TileWgradPlan p = search_tile_wgrad(B, Cin, H, W, Cout, KH, KW, rounded);
     p.interface_bytes = tile_layout_bytes(B, Cin, H, W, Cout, KH, KW);
     return p;
   });
@@ -739,9 +742,16 @@ int launch_tile_wgrad(TileWgradPlan& p, const float* in, const float* d_out, flo
     CNN_TILE_WGRAD(2, 4, 2, false);
     CNN_TILE_WGRAD(2, 6, 2, false);
     CNN_TILE_WGRAD(2, 8, 2, false);
-    default: return CNN_EINVAL;
-  }
 #undef CNN_TILE_WGRAD
+    default:
+      if constexpr (ROUND) {
+        return CNN_EINVAL;
+      } else {
+        if (p.a.P > 1 || (p.nt != 5 && (p.nt != 9 || p.mt != 1))) return CNN_EINVAL;
+        launch_tiled(p.nt == 9 ? tile::wgrad_kernel<9, 1, false, false> : p.mt == 1 ? tile::wgrad_kernel<5, 1, false, false> : tile::wgrad_kernel<5, 2, false, false>,
+                     p.grid, p.lds_bytes, st, p.a);
+      }
+  }
   return launch_reduce_rows(part, G, p.a.RS, nk, d_k, d_bias, st);
 }
 
@@ -858,7 +868,7 @@ WgradPlan plan_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
     p.workspace_bytes = conv2::bwd_weight_workspace_bytes(p.gx);
     p.least_bytes = conv2::bwd_weight_workspace_bytes(image_groups(B, 8));
   } else {
-    p.tile = plan_tile_wgrad(B, Cin, H, W, Cout, KH, KW);
+    p.tile = plan_tile_wgrad(B, Cin, H, W, Cout, KH, KW, false);
     if (p.tile.nt) p.kernel = WgradPlan::TILED;
     if (p.tile.nt) p.workspace_bytes = std::max({p.tile.workspace_bytes, p.tile.interface_bytes, NO_PARTIAL_SUMS_BYTES});
     p.least_bytes = p.workspace_bytes;
@@ -1150,7 +1160,7 @@ struct Wgrad16Plan {
 Wgrad16Plan plan_wgrad16(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
   Wgrad16Plan p;
   p.eight = plan_tile16_wgrad(B, Cin, H, W, Cout, KH, KW);
-  p.rounded = plan_tile_wgrad(B, Cin, H, W, Cout, KH, KW);
+  p.rounded = plan_tile_wgrad(B, Cin, H, W, Cout, KH, KW, true);
   return p;
 }
 

@@ -29,9 +29,9 @@
 // What bounds it (timed plans, cnn_ops.hip): a block of a column tile costs 144 clocks of its SIMD against the
 // 128 of its matrix instructions; around that a unit pays about 500 + 83 NT clocks of staging, addressing and
 // stores, and a workgroup one memory round trip (1700 clocks) per unit, the largest share for layers with few
-// channels.  500 images 3 -> 16 maps, 32 x 32, 5 x 5: forward 25 us, input gradient 36 us, weight gradient 24.5 + 4.6 us (the
+// channels.  500 images 3 -> 16 maps, 32 x 32, 5 x 5: forward 25 us, input gradient 36 us, weight gradient 21.2 + 4.6 us (the
 // kernels before, which needed whole images in LDS: 26, 290 and 1540 us); 256 images 16 -> 32, 28 x 28, 3 x 3: 28,
-// 35, 38 + 5 us (364, 460, 2020 us).  Without its matrix instructions and operand reads the input gradient of the first
+// 35, 33 + 5 us (364, 460, 2020 us).  Without its matrix instructions and operand reads the input gradient of the first
 // takes 25 of 46 us, without the weights' way into LDS 33, without staging 40, without stores 45 (before the weights
 // were loaded as below).  Small calls are bound by what comes before the first matrix instruction.
 #pragma once
@@ -806,34 +806,35 @@ __global__ __launch_bounds__(THREADS) void wgrad_kernel(const WgradArgs g) {
     const char* xb = reinterpret_cast<const char*>(buf + L.x);
     const int last = g.NBK - 1;
     if (wave < g.NBK) {
-      // the NT reads of step s + 1 are issued under the instructions of step s, a block's dense operand
-      // and slot offsets one block ahead
-      i4 k = pq[wave];
-      f4 a[MT];
-#pragma unroll
-      for (int m = 0; m < MT; ++m) a[m] = *reinterpret_cast<const f4*>(buf + arow[m] + 16 * wave);
+      // Two blocks a trip; the NT reads of step s + 1 are issued under the instructions of step s, a block's dense operand
+      // and slot offsets one block ahead.  Left to itself the compiler puts every read right before its use, and a wave waits
+      // for the LDS in every step.  Kernel times, us, with five and nine tap tiles (before: six and three): 500 images 3 -> 16, 32 x 32,
+      // 5 x 5 24.6 -> 21.2; 256 images 16 -> 32, 28 x 28, 3 x 3 39 -> 33.  (Reading two neighbouring slots as one item of eight bytes
+      // took 38 and 57: an LDS item that is not aligned to its size is slow.  Taps in another order and planes a few floats further
+      // apart, so that no two of a tile share a bank: no gain.)
+      i4 k0 = pq[wave], k1;
+      f4 a0[MT], a1[MT];
       float b[2][NT];
+      auto dense = [&](f4 (&a)[MT], int blk) {
 #pragma unroll
-      for (int i = 0; i < NT; ++i) b[0][i] = *reinterpret_cast<const float*>(xb + k[0] + toff[i]);
-#pragma unroll 1
-      for (int blk = wave; blk < g.NBK; blk += WAVES) {
-        if (ROUND) {
+        for (int m = 0; m < MT; ++m) a[m] = *reinterpret_cast<const f4*>(buf + arow[m] + 16 * blk);
+      };
+      auto gather = [&](float (&v)[NT], int at) {
 #pragma unroll
-          for (int m = 0; m < MT; ++m) a[m] = f4{round_bf16(a[m][0]), round_bf16(a[m][1]), round_bf16(a[m][2]), round_bf16(a[m][3])};
-        }
-        const int nblk = min(blk + WAVES, last);
-        const i4 kn = pq[nblk];
-        f4 an[MT];
+        for (int i = 0; i < NT; ++i) v[i] = *reinterpret_cast<const float*>(xb + at + toff[i]);
+      };
+      auto block = [&](const f4 (&read)[MT], const i4& k, f4 (&an)[MT], i4& kn, int next) {
+        f4 a[MT];
 #pragma unroll
-        for (int m = 0; m < MT; ++m) an[m] = *reinterpret_cast<const f4*>(buf + arow[m] + 16 * nblk);
+        for (int m = 0; m < MT; ++m) a[m] = f4{operand<ROUND>(read[m][0]), operand<ROUND>(read[m][1]), operand<ROUND>(read[m][2]), operand<ROUND>(read[m][3])};
+        kn = pq[next];
+        dense(an, next);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          const int ko = s < 3 ? k[s < 3 ? s + 1 : 0] : kn[0];
-#pragma unroll
-          for (int i = 0; i < NT; ++i) b[(s + 1) & 1][i] = *reinterpret_cast<const float*>(xb + ko + toff[i]);
+          gather(b[(s + 1) & 1], s < 3 ? k[s < 3 ? s + 1 : 0] : kn[0]);
 #pragma unroll
           for (int i = 0; i < NT; ++i) {
-            const float bi = ROUND ? round_bf16(b[s & 1][i]) : b[s & 1][i];
+            const float bi = operand<ROUND>(b[s & 1][i]);
 #pragma unroll
             for (int m = 0; m < MT; ++m) acc[m][i] = mfma16(a[m][s], bi, acc[m][i]);
           }
@@ -842,10 +843,24 @@ __global__ __launch_bounds__(THREADS) void wgrad_kernel(const WgradArgs g) {
 #pragma unroll
           for (int m = 0; m < MT; ++m) asum[m] += (a[m][0] + a[m][1]) + (a[m][2] + a[m][3]);
         }
-        k = kn;
+        if (!ROUND) {  // (with the rounding in between it is slower: 1083 images 17 -> 5, 13 x 34, 4 x 4 60 -> 70 us)
+          __builtin_amdgcn_sched_group_barrier(0x100, 1 + MT, 0);
 #pragma unroll
-        for (int m = 0; m < MT; ++m) a[m] = an[m];
+          for (int r = 0; r < 4 * NT; ++r) {  // one LDS read before every MT matrix instructions
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, MT, 0);
+          }
+        }
+      };
+      dense(a0, wave);
+      gather(b[0], k0[0]);
+      int blk = wave;
+#pragma unroll 1
+      for (; blk + WAVES < g.NBK; blk += 2 * WAVES) {
+        block(a0, k0, a1, k1, blk + WAVES);
+        block(a1, k1, a0, k0, min(blk + 2 * WAVES, last));
       }
+      if (blk < g.NBK) block(a0, k0, a1, k1, last);
     }
   }
   finish_wgrad<NT, MT>(g, acc, asum, lds, row0, rows, tap0, taps, sums_bias);
