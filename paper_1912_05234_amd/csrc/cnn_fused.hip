@@ -29,6 +29,8 @@ constexpr int TRAIN_BLOCKS = 256;  // most workgroups (= gradient partials) of t
 // (more images in flight, no barriers).  Measured crossover, gradient of 512 / 513 / 576 / 640 images: 20.8 / 24.0 / 27.5 /
 // 28.2 us with eight waves per image (a third workgroup has to wait), 23.2 / 23.1 / 23.7 / 23.7 us with one.
 constexpr int GROUP_MAX_BATCH = 512;
+// Up to this size there are two compute units per image, and two workgroups share it.
+constexpr int GROUP_PAIR_MAX_BATCH = 128;
 // The same choice for the forward pass alone: evaluation of 512 / 768 / 896 / 1024 images 9.4 / 10.9 / 12.8 / 12.9 us with eight
 // waves per image (1.8 more for every 256), 13.1 for any number up to 2048 with one.
 constexpr int FWD_GROUP_MAX_BATCH = 1024;
@@ -434,6 +436,8 @@ __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 
 }
 
 // Small batches: eight waves share one image (cnn_group.h); one partial row per workgroup.
+// PAIR: two workgroups per image, blocks 0 .. B - 1 and B .. 2 B - 1 (GroupPart).
+template <bool PAIR>
 __global__ __launch_bounds__(64 * GWAVES) void train_group_kernel(const float* __restrict__ images,
                                                               const int32_t* __restrict__ labels, int B,
                                                               const float* __restrict__ tabg,
@@ -442,8 +446,16 @@ __global__ __launch_bounds__(64 * GWAVES) void train_group_kernel(const float* _
   __shared__ TrainLds s;
   __shared__ __align__(16) float d_s1b[D_S1B_FLOATS];
   __shared__ float ybuf[16];
-  group_train<false>(images + (size_t)blockIdx.x * NI, labels + blockIdx.x, tabg,
-                     partial + (size_t)blockIdx.x * PSTRIDE, tab, s, d_s1b, ybuf);
+  const bool upper = PAIR && blockIdx.x >= (unsigned)B;
+  const size_t n = blockIdx.x - (upper ? B : 0);
+  const float* image = images + n * NI;
+  float* row = partial + n * PSTRIDE;
+  if (!PAIR)
+    group_train<false, WHOLE>(image, labels + n, tabg, row, tab, s, d_s1b, ybuf);
+  else if (!upper)
+    group_train<false, LOWER>(image, labels + n, tabg, row, tab, s, d_s1b, ybuf);
+  else
+    group_train<false, UPPER>(image, labels + n, tabg, row, tab, s, d_s1b, ybuf);
 }
 
 // Expanded operand table from the flat parameter vector: tabg[i] = table_scale(i) * w[table_source(i)] or 0.
@@ -617,7 +629,7 @@ __global__ __launch_bounds__(64 * GWAVES) void train_epoch_kernel(const float* _
   float* row = partial + (size_t)blockIdx.x * PSTRIDE;
   for (int k = 0; k < steps; ++k) {
     const size_t n = (size_t)k * B + blockIdx.x;
-    group_train<true>(images + n * NI, labels + n, tabg, row, tab, s, d_s1b, ybuf);
+    group_train<true, WHOLE>(images + n * NI, labels + n, tabg, row, tab, s, d_s1b, ybuf);
     if (!grid_barrier(gs, &dead)) return;  // every row of the step is in memory
     for (int j = blockIdx.x; j < PSTRIDE / 64; j += gridDim.x) {  // (a batch below 61 images: several blocks each)
       reduce_update_block<64 * GWAVES, true>(j, red, partial, B, scale, w, dest, tabg, nullptr,
@@ -719,11 +731,13 @@ int run_backward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B
   const bool grouped = B <= GROUP_MAX_BATCH;
   // small batches: one workgroup per image; large ones: one workgroup of eight waves per compute unit
   const int blocks = grouped ? B : (B < TRAIN_BLOCKS ? B : TRAIN_BLOCKS);
-  const int G = blocks;  // one partial row per workgroup in both kernels
+  const int G = blocks;  // one partial row per workgroup, or per pair of workgroups
   const bool timed = (size_t)(2 * ctx->ev_used + 1) < ctx->ev.size();
   if (timed) CNN_HIP_TRY(hipEventRecord(ctx->ev[2 * ctx->ev_used], ctx->stream));
-  if (grouped)
-    train_group_kernel<<<blocks, 64 * GWAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, ctx->partial);
+  if (grouped && B <= GROUP_PAIR_MAX_BATCH)
+    train_group_kernel<true><<<2 * blocks, 64 * GWAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, ctx->partial);
+  else if (grouped)
+    train_group_kernel<false><<<blocks, 64 * GWAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, ctx->partial);
   else
     train_kernel<<<blocks, 64 * TWAVES, 0, ctx->stream>>>(images, labels, B, ctx->w, ctx->tabg, ctx->partial, ctx->fc_hist);
   if (hipGetLastError() != hipSuccess) return CNN_EHIP;

@@ -29,9 +29,19 @@ constexpr int GWAVES = 8;  // waves per workgroup of the small-batch kernel
 // rewrite with themselves (+ 0.0), as they do behind the first target inside TrainLds.
 constexpr int D_S1B_FLOATS = NS1 + 304;
 
-// Tap tiles of the C2 weight gradient owned by wave 4 + i: first tile and count.
-__host__ __device__ constexpr int k2_first(int i) { return i < 2 ? 2 * i : 3 * i - 2; }
-__host__ __device__ constexpr int k2_count(int i) { return i < 2 ? 2 : 3; }
+// What a workgroup does of its image's step.  WHOLE: everything.  Where there are two compute units per image (GROUP_PAIR_MAX_BATCH),
+// two workgroups share it: both run the forward pass, then LOWER takes the C2 input error and the C1 gradient, UPPER
+// the FC and C2 gradients and the loss, and each writes its part of the image's partial row.  Every sum is made in the
+// same order in all of them.
+enum GroupPart { WHOLE, LOWER, UPPER };
+
+// Tap tiles of the C2 weight gradient owned by wave 4 + i: first tile and count; of UPPER, by wave i.
+template <GroupPart PART>
+__host__ __device__ constexpr int k2_first(int i) {
+  return PART == UPPER ? (i < 2 ? 2 * i : i + 2) : i < 2 ? 2 * i : 3 * i - 2;
+}
+template <GroupPart PART>
+__host__ __device__ constexpr int k2_count(int i) { return PART == UPPER ? (i < 2 ? 2 : 1) : i < 2 ? 2 : 3; }
 
 struct GroupState {
   float bias2;      // b2[n16]
@@ -153,7 +163,7 @@ __device__ __forceinline__ void put_row(float* p, float v) {
 // The whole step for the workgroup's image (`image`, `label` point at it); one partial row, `out`.
 // `d_s1b` is the second col2im target (D_S1B_FLOATS floats), `ybuf` 16 floats of LDS for the network
 // output.  COHERENT: see put_row and TableLoad.
-template <bool COHERENT>
+template <bool COHERENT, GroupPart PART>
 __device__ __forceinline__ void group_train(const float* __restrict__ image,
                                             const int32_t* __restrict__ label_ptr,
                                             const float* __restrict__ tabg, float* __restrict__ out,
@@ -172,7 +182,7 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
   table.fetch(tabg);
   // every LDS cell that padded GEMM steps may read starts finite, and both col2im targets start at
   // zero (the image area is written below, before the first barrier, so it is left alone here)
-  for (int e = t; e < D_S1B_FLOATS / 4; e += 64 * GWAVES) {
+  for (int e = t; PART != UPPER && e < D_S1B_FLOATS / 4; e += 64 * GWAVES) {
     if (e < NS1 / 4) reinterpret_cast<f4*>(s.d_s1)[e] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     reinterpret_cast<f4*>(d_s1b)[e] = f4{0.0f, 0.0f, 0.0f, 0.0f};
   }
@@ -237,6 +247,13 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
         if (l == 0) ybuf[o] = yo;
       }
     }
+    // (read before the barrier: what the error at C2 needs of the FC weights)
+    float fcw[NY];
+    if (wave < 4) {
+      const int i = n16 * 16 + 4 * wave + q;
+#pragma unroll
+      for (int o = 0; o < NY; ++o) fcw[o] = tab.e[(TAB_FCW + (i >> 6) + 3 * o) * 64 + (i & 63)];
+    }
     CNN_GROUP_MARK(5);
     __syncthreads();  // (4) yhat complete
     if (wave < 4) {
@@ -252,7 +269,7 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
         }
         if (wave == 0) st.loss = fmaf(0.5f, lsum, st.loss);
       }
-      if (wave < 3) {  // FC backweights / backbias, row tile mt = wave
+      if (PART != LOWER && wave < 3) {  // FC backweights / backbias, row tile mt = wave
         float d[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -270,11 +287,9 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
       // ---- error at C2 for this wave's tile: the lane's own element of the error at S2,
       //      d_s2[i] = sum_o fc[o][i] delta[o] with i = 16 n16 + 4 wave + q, then backavgpool and sigmoid' --
       {
-        const int i = n16 * 16 + 4 * wave + q;
-        const float* fcw = tab.e + (TAB_FCW + (i >> 6)) * 64 + (i & 63);
         float up = 0.0f;
 #pragma unroll
-        for (int o = 0; o < 10; ++o) up = fmaf(fcw[3 * o * 64], delta[o], up);
+        for (int o = 0; o < 10; ++o) up = fmaf(fcw[o], delta[o], up);
         up *= 0.25f;
         f4 d2v;
 #pragma unroll
@@ -283,55 +298,50 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
         st.g_b2 += (d2v[0] + d2v[1]) + (d2v[2] + d2v[3]);
       }
     }
+    // (read before the barrier: the weights of the C2 input error, for input maps 4 cg .. 4 cg + 3)
+    const int cg = wave & 1, h = (wave >> 1) & 1;
+    float wt[7][3];
+    if (PART != UPPER && wave < 4) {
+      const float* ta = tl + (cg ? TAB_AB1 : TAB_AB) * 64;
+#pragma unroll
+      for (int tile = 0; tile < 7; ++tile)
+#pragma unroll
+        for (int sidx = 0; sidx < 3; ++sidx) wt[tile][sidx] = ta[(tile * 3 + sidx) * 64];
+    }
     CNN_GROUP_MARK(6);
     __syncthreads();  // (5) d_c2 complete
 
-    if (wave < 4) {
+    if (PART != UPPER && wave < 4) {
       // ---- C2 input error for input maps 4 cg .. 4 cg + 3 from the pixel tiles nt = 2 h, 2 h + 1
       //      (col2im rounds as in cnn_col2im.h restricted to those tiles: levels 4 h .. 4 h + 6) ---------------
-      const int cg = wave & 1, h = wave >> 1;
       float bd[3][2];
 #pragma unroll
       for (int sidx = 0; sidx < 3; ++sidx)
 #pragma unroll
         for (int j = 0; j < 2; ++j) bd[sidx][j] = s.pool[P_D2 + (4 * sidx + q) * D2S + 16 * (2 * h + j) + n16];
-      const float* ta = tl + (cg ? TAB_AB1 : TAB_AB) * 64;
       f4 t4[2];
       float t44[2];
-      {
-        float au[3], ac[3];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        f4 a = f4{0.0f, 0.0f, 0.0f, 0.0f}, c = a;
 #pragma unroll
         for (int sidx = 0; sidx < 3; ++sidx) {
-          au[sidx] = ta[(kTileU4 * 3 + sidx) * 64];
-          ac[sidx] = ta[(kTileC * 3 + sidx) * 64];
+          a = mfma16(wt[kTileU4][sidx], bd[sidx][j], a);
+          c = mfma16(wt[kTileC][sidx], bd[sidx][j], c);
         }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          f4 a = f4{0.0f, 0.0f, 0.0f, 0.0f}, c = a;
-#pragma unroll
-          for (int sidx = 0; sidx < 3; ++sidx) {
-            a = mfma16(au[sidx], bd[sidx][j], a);
-            c = mfma16(ac[sidx], bd[sidx][j], c);
-          }
-          t4[j] = a;
-          t44[j] = c[0];
-        }
+        t4[j] = a;
+        t44[j] = c[0];
       }
       float* tgt = (h ? d_s1b : s.d_s1) + 144 * q + pp + 576 * cg + 48 * h;
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         f4 tv[2];
-        {
-          float av[3];
 #pragma unroll
-          for (int sidx = 0; sidx < 3; ++sidx) av[sidx] = ta[((kTileV0 + v) * 3 + sidx) * 64];
+        for (int j = 0; j < 2; ++j) {
+          f4 a = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            f4 a = f4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int sidx = 0; sidx < 3; ++sidx) a = mfma16(av[sidx], bd[sidx][j], a);
-            tv[j] = a;
-          }
+          for (int sidx = 0; sidx < 3; ++sidx) a = mfma16(wt[kTileV0 + v][sidx], bd[sidx][j], a);
+          tv[j] = a;
         }
         const float tu4[2] = {v < 4 ? t4[0][v < 4 ? v : 0] : t44[0], v < 4 ? t4[1][v < 4 ? v : 0] : t44[1]};
         {  // even levels 2 (2 h + mm), mm < 4: (j = mm, u = 0) + (mm - 1, 2) + (mm - 2, 4)
@@ -353,9 +363,11 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
         }
         wave_sync();
       }
-    } else {
+    }
+    constexpr int K2_WAVE = PART == UPPER ? 0 : 4;  // the first wave that has tiles of the C2 weight gradient
+    if (PART != LOWER && wave >= K2_WAVE) {
       // ---- C2 weight gradient: this wave's tap tiles over all four pixel tiles ---------------------------
-      const int first = k2_first(wave - 4), count = k2_count(wave - 4);  // wave-uniform
+      const int first = k2_first<PART>(wave - K2_WAVE), count = k2_count<PART>(wave - K2_WAVE);  // wave-uniform
       const float* bsrc[3];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -365,11 +377,13 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
       }
       if (count == 3)
         group_k2_gradient<3>(st.acc_k2, s, bsrc);
-      else
+      else if (count == 2)
         group_k2_gradient<2>(st.acc_k2, s, bsrc);
+      else
+        group_k2_gradient<1>(st.acc_k2, s, bsrc);
     }
     CNN_GROUP_MARK(7);
-    __syncthreads();  // (6) both d_s1 copies complete; s1, d_c2 no longer needed
+    if (PART != UPPER) __syncthreads();  // (6) both d_s1 copies complete; s1, d_c2 no longer needed
 
     // ---- C1 error for this wave's tiles, then the K steps of the C1 weight gradient GEMM that belong
     //      to the same tiles: a wave reads only the d1 cells it staged itself, so no barrier -------------
@@ -381,7 +395,8 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
       d1t[k] = s.pool + c1f_tile_c1(T);
       imgt[k] = s.img + c1f_tile_img(T);
     }
-    if (wave < 2) {
+    if (PART == UPPER) {
+    } else if (wave < 2) {
       group_c1_error<3>(st, s, d_s1b, wave, ln, c1);
       wave_sync();
       c1g_accumulate_tiles<3>(st.acc_k1, d1t, imgt);
@@ -394,29 +409,33 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
   }
 
   // ---- one partial row per workgroup: cross-wave sums through LDS in a fixed order -------------------
-  // Nothing has read the operand table since barrier (6); its storage takes the parked values.
+  // The parked values take the storage of the operand table, which nothing has read since barrier (5) but the lower waves of WHOLE
+  // and LOWER, and barrier (6) is behind those.
   float* k1s = tab.e;                               // [8 waves][16][32]: parked C1 weight GEMM results
   float* b1s = tab.e + GWAVES * C1G_PARK;           // [8 waves][8]: C1 bias sums (256 floats reserved)
   float* b2s = b1s + 256;                           // [4 waves][64]: per-lane C2 bias sums
   static_assert(GWAVES * C1G_PARK + 256 + 256 <= TAB_TRAIN_ENTRIES * 64, "flush scratch fits the table");
-  c1g_park(st.acc_k1, k1s + wave * C1G_PARK);
-  CNN_GROUP_MARK(11);
+  if (PART != UPPER) {
+    c1g_park(st.acc_k1, k1s + wave * C1G_PARK);
+    CNN_GROUP_MARK(11);
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {  // C1 biases: lanes (q, .) hold maps 2q, 2q + 1
-    float v = st.g_b1[k];
-    v += quad_xor1(v);
-    v += quad_xor2(v);
-    v += dpp_row_half_mirror(v);
-    v += dpp_row_mirror(v);
-    if (n16 == 0 && q < 3) b1s[wave * 8 + 2 * q + k] = v;
+    for (int k = 0; k < 2; ++k) {  // C1 biases: lanes (q, .) hold maps 2q, 2q + 1
+      float v = st.g_b1[k];
+      v += quad_xor1(v);
+      v += quad_xor2(v);
+      v += dpp_row_half_mirror(v);
+      v += dpp_row_mirror(v);
+      if (n16 == 0 && q < 3) b1s[wave * 8 + 2 * q + k] = v;
+    }
   }
-  if (wave < 4) b2s[wave * 64 + l] = st.g_b2;  // lane (q, j) of this wave's pixel tile
+  if (PART != LOWER && wave < 4) b2s[wave * 64 + l] = st.g_b2;  // lane (q, j) of this wave's pixel tile
   CNN_GROUP_MARK(9);
   __syncthreads();
   CNN_GROUP_MARK(12);
   // (stores grouped by the lanes that take part: one branch per group, not one per store)
-  if (wave >= 4) {  // C2 weights: every wave stores the columns (tap tiles) it owns; rows j = 4 q + r < 12
-    const int first = k2_first(wave - 4), count = k2_count(wave - 4);
+  constexpr int K2_WAVE = PART == UPPER ? 0 : 4;
+  if (PART != LOWER && wave >= K2_WAVE) {  // C2 weights: every wave stores the columns (tap tiles) it owns; rows j = 4 q + r < 12
+    const int first = k2_first<PART>(wave - K2_WAVE), count = k2_count<PART>(wave - K2_WAVE);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       const int tap = 16 * (first + k) + n16;
@@ -427,7 +446,7 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
       }
     }
   }
-  if (wave < 3) {  // FC rows o = 4 wave + r < 10: wave 2 has two
+  if (PART != LOWER && wave < 3) {  // FC rows o = 4 wave + r < 10: wave 2 has two
     float* dst = out + OFF_FC + 4 * wave * NS2 + l;
 #pragma unroll
     for (int k = 0; k < 3; ++k)
@@ -442,10 +461,11 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
     if (l < 4 && 4 * wave + l < 10) put_row<COHERENT>(out + OFF_B + 4 * wave + l, st.g_bq);
   }
   CNN_GROUP_MARK(13);
-  if (wave >= 6 || (wave == 3 && l >= 32)) {
-    // one thread per C1 weight (waves 6, 7 have nothing else to store; 22 lanes of wave 3 take the
+  const bool k1_lane = PART == LOWER ? t < 150 : wave >= 6 || (wave == 3 && l >= 32);
+  if (PART != UPPER && k1_lane) {
+    // one thread per C1 weight (of WHOLE, waves 6, 7 have nothing else to store; 22 lanes of wave 3 take the
     // rest): the eight waves' shares of the GEMM, both shifted halves
-    const int e = wave >= 6 ? t - 384 : 96 + l;
+    const int e = PART == LOWER ? t : wave >= 6 ? t - 384 : 96 + l;
     if (e < 150) {
       float x[GWAVES];
 #pragma unroll
@@ -454,12 +474,12 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
     }
   }
   if (wave == 3) {
-    if (l < 6) {  // C1 biases: the eight waves' sums
+    if (PART != UPPER && l < 6) {  // C1 biases: the eight waves' sums
       float x[GWAVES];
 #pragma unroll
       for (int k = 0; k < GWAVES; ++k) x[k] = b1s[k * 8 + l];
       put_row<COHERENT>(out + OFF_B1 + l, ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7])));
-    } else if (l >= 16 && l < 28) {  // C2 biases: 4 waves x 4 lane quarters
+    } else if (PART != LOWER && l >= 16 && l < 28) {  // C2 biases: 4 waves x 4 lane quarters
       const int j = l - 16;
       float x[16];
 #pragma unroll
@@ -469,7 +489,7 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
       put_row<COHERENT>(out + OFF_B2 + j, (x[0] + x[4]) + (x[8] + x[12]));
     }
   }
-  if (t == 0) put_row<COHERENT>(out + LOSS_SLOT, st.loss);
+  if (PART != LOWER && t == 0) put_row<COHERENT>(out + LOSS_SLOT, st.loss);
   CNN_GROUP_MARK(10);
 }
 
