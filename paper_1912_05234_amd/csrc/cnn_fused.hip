@@ -445,17 +445,16 @@ __global__ __launch_bounds__(64 * GWAVES) void train_group_kernel(const float* _
   __shared__ OperandTable<TAB_TRAIN_ENTRIES> tab;
   __shared__ TrainLds s;
   __shared__ __align__(16) float d_s1b[D_S1B_FLOATS];
-  __shared__ float ybuf[16];
   const bool upper = PAIR && blockIdx.x >= (unsigned)B;
   const size_t n = blockIdx.x - (upper ? B : 0);
   const float* image = images + n * NI;
   float* row = partial + n * PSTRIDE;
   if (!PAIR)
-    group_train<false, WHOLE>(image, labels + n, tabg, row, tab, s, d_s1b, ybuf);
+    group_train<false, WHOLE>(image, labels + n, tabg, row, tab, s, d_s1b);
   else if (!upper)
-    group_train<false, LOWER>(image, labels + n, tabg, row, tab, s, d_s1b, ybuf);
+    group_train<false, LOWER>(image, labels + n, tabg, row, tab, s, d_s1b);
   else
-    group_train<false, UPPER>(image, labels + n, tabg, row, tab, s, d_s1b, ybuf);
+    group_train<false, UPPER>(image, labels + n, tabg, row, tab, s, d_s1b);
 }
 
 // Expanded operand table from the flat parameter vector: tabg[i] = table_scale(i) * w[table_source(i)] or 0.
@@ -618,7 +617,6 @@ __global__ __launch_bounds__(64 * GWAVES) void train_epoch_kernel(const float* _
   __shared__ OperandTable<TAB_TRAIN_ENTRIES> tab;
   __shared__ TrainLds s;
   __shared__ __align__(16) float d_s1b[D_S1B_FLOATS];
-  __shared__ float ybuf[16];
   __shared__ float red[RSTRANDS][64];
   __shared__ int dead;
   if (threadIdx.x == 0) dead = 0;
@@ -629,7 +627,7 @@ __global__ __launch_bounds__(64 * GWAVES) void train_epoch_kernel(const float* _
   float* row = partial + (size_t)blockIdx.x * PSTRIDE;
   for (int k = 0; k < steps; ++k) {
     const size_t n = (size_t)k * B + blockIdx.x;
-    group_train<true, WHOLE>(images + n * NI, labels + n, tabg, row, tab, s, d_s1b, ybuf);
+    group_train<true, WHOLE>(images + n * NI, labels + n, tabg, row, tab, s, d_s1b);
     if (!grid_barrier(gs, &dead)) return;  // every row of the step is in memory
     for (int j = blockIdx.x; j < PSTRIDE / 64; j += gridDim.x) {  // (a batch below 61 images: several blocks each)
       reduce_update_block<64 * GWAVES, true>(j, red, partial, B, scale, w, dest, tabg, nullptr,

@@ -6,21 +6,21 @@
 //
 //   C1 forward and C1 error      GEMM tiles T = wave, wave + 8 (waves 0, 1 also T = wave + 16), cnn_wave.h
 //   C1 weight gradient           the GEMM's K steps that belong to the wave's own C1 tiles
-//   C2 forward, C2 error         waves 0..3: pixel tile mt = wave
-//   output layer                 outputs o = wave and wave + 8
-//   FC weight gradient           waves 0..2 take the three 4-output row tiles
+//   C2 forward                   waves 0..3: pixel tile mt = wave
+//   output layer, C2 error       waves 4..7: each all ten outputs, and pixel tile mt = wave - 4
+//   FC weight gradient           waves 4..6 take the three 4-output row tiles
 //   C2 input error (col2im)      waves 0..3: input maps 4 cg .. 4 cg + 3, cg = wave % 2, and pixel tiles
 //                                nt = 2 h, 2 h + 1, h = wave / 2; half h adds into its own copy of d_s1,
 //                                so no two waves ever touch the same cell; the C1 error reads both copies
 //   C2 weight gradient           waves 4..7: tap tiles nt = 0-1, 2-3, 4-6, 7-9 over all 64 pixels (each wave
 //                                owns whole columns of the result, so nothing has to be added across waves)
 //
-// Phases that hand data between waves are separated by workgroup barriers (six, plus one in the
+// Phases that hand data between waves are separated by workgroup barriers (five, plus one in the
 // final cross-wave sums).  A workgroup handles exactly one image: the grid is one workgroup per
 // image of the batch.
 #pragma once
 
-#include "cnn_wave.h"
+#include "cnn_split.h"
 
 namespace cnn {
 
@@ -47,10 +47,10 @@ struct GroupState {
   float bias2;      // b2[n16]
   f4 acc_k2[3];     // waves 4..7: C2 weight gradient tiles nt = k2_first(wave - 4) + k
   f4 acc_k1[2];     // C1 weight gradient GEMM over the K steps of this wave's tiles, T[(m,sh)][c]
-  f4 acc_fc[3];     // waves 0..2: FC weight gradient rows o = 4 wave + r, columns lane + 64 k
-  float g_bq;       // waves 0..2: FC bias gradient b[4 wave + lane % 4]
+  f4 acc_fc[3];     // waves 4..6: FC weight gradient rows o = 4 fw + r, columns lane + 64 k
+  float g_bq;       // waves 4..6: FC bias gradient b[4 fw + lane % 4]
   float g_b1[2];    // C1 bias gradient of maps 2q, 2q + 1 over this lane's pixels
-  float g_b2, loss;
+  float g_b2, loss;  // (loss: the lane's output's share)
 };
 
 // C1 forward + S1 for this wave's NT tiles T = wave + 8 k of the C1 GEMM (cnn_wave.h): returns the
@@ -160,15 +160,19 @@ __device__ __forceinline__ void put_row(float* p, float v) {
     *p = v;
 }
 
+// What another compute unit may have written during this kernel (COHERENT).
+template <bool COHERENT>
+__device__ __forceinline__ float get_shared(const float* p) {
+  return COHERENT ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+
 // The whole step for the workgroup's image (`image`, `label` point at it); one partial row, `out`.
-// `d_s1b` is the second col2im target (D_S1B_FLOATS floats), `ybuf` 16 floats of LDS for the network
-// output.  COHERENT: see put_row and TableLoad.
+// `d_s1b` is the second col2im target (D_S1B_FLOATS floats).  COHERENT: see put_row and TableLoad.
 template <bool COHERENT, GroupPart PART>
 __device__ __forceinline__ void group_train(const float* __restrict__ image,
                                             const int32_t* __restrict__ label_ptr,
                                             const float* __restrict__ tabg, float* __restrict__ out,
-                                            OperandTable<TAB_TRAIN_ENTRIES>& tab, TrainLds& s, float* d_s1b,
-                                            float* ybuf) {
+                                            OperandTable<TAB_TRAIN_ENTRIES>& tab, TrainLds& s, float* d_s1b) {
   const int t = threadIdx.x, wave = t >> 6, l = t & 63, q = l >> 4, n16 = l & 15, sub = l & 3;
   const int pp = 12 * ((n16 & 3) >> 1) + 2 * (n16 >> 2) + (n16 & 1);
   const float* tl = tab.e + l;
@@ -178,7 +182,9 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
   f4 px = reinterpret_cast<const f4*>(image)[pix];
   const int label = *label_ptr;  // in flight during the set-up too
   // the C1 forward operands (the table's last entries) and the biases come first: see barrier (1)
-  TableLoad<TAB_TRAIN_ENTRIES, 64 * GWAVES, COHERENT, TAB_TRAIN_ENTRIES, TAB_C1A> table;
+  // (the FC weights go to the upper waves' registers; UPPER has no C2 input error)
+  constexpr int SKIPPED = (PART == UPPER ? TAB_C1A : TAB_AB) - TAB_FCW;
+  TableLoad<TAB_TRAIN_ENTRIES, 64 * GWAVES, COHERENT, TAB_TRAIN_ENTRIES, TAB_C1A, TAB_FCW, SKIPPED> table;
   table.fetch(tabg);
   // every LDS cell that padded GEMM steps may read starts finite, and both col2im targets start at
   // zero (the image area is written below, before the first barrier, so it is left alone here)
@@ -210,6 +216,8 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
     CNN_GROUP_MARK(2);
     __syncthreads();  // (1) image, C1 forward operands and biases in LDS
     st.bias2 = tab.bias[n16];
+    const int fw = wave & 3;
+    const float bias3 = tab.bias[TAB_BIAS_B + out_of_lane(l)];
 
     // ---- C1 forward + S1 for this wave's tiles ---------------------------------------------------------
     f4 c1[3];
@@ -218,6 +226,15 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
     else
       group_c1_forward<2>(tab.e + TAB_C1A * 64, tab.bias, s.img, s.pool + P_S1, wave, ln, c1);
     table.commit_rest(tab);
+    // The output layer is the upper waves', each for itself (one hand-over between waves costs more than ten outputs): they wait
+    // while the lower ones are busy with C2, and their lanes hold the weights of the inputs lane, lane + 64, lane + 128.
+    float fcw[NY][3];
+    if (wave >= 4) {
+#pragma unroll
+      for (int o = 0; o < NY; ++o)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) fcw[o][k] = get_shared<COHERENT>(tabg + (TAB_FCW + 3 * o + k) * 64 + l);
+    }
     CNN_GROUP_MARK(3);
     __syncthreads();  // (2) S1 and the operand table complete
 
@@ -228,74 +245,56 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
 #pragma unroll
       for (int r = 0; r < 4; ++r) c2v[r] = logistic_of_scaled(c2v[r]);
       if (n16 < 12) s.pool[P_S2 + n16 * 16 + 4 * wave + q] = 0.25f * ((c2v[0] + c2v[1]) + (c2v[2] + c2v[3]));
+      *reinterpret_cast<f4*>(&s.pool[P_D2 + n16 * D2S + 16 * wave + 4 * q]) = c2v;  // its error takes this place
     }
     CNN_GROUP_MARK(4);
-    __syncthreads();  // (3) S2 complete
+    __syncthreads();  // (3) S2 and C2 complete
 
-    // ---- output layer: this wave's outputs o = wave, wave + 8 -----------------------------------------
-    float sv[3];
+    // ---- output layer, its error, and the error at C2 for pixel tile fw (waves 4..7) ------------------------
+    if (wave >= 4) {
+      float sv[3], p[NY];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) sv[k] = s.pool[P_S2 + l + 64 * k];
+      for (int k = 0; k < 3; ++k) sv[k] = s.pool[P_S2 + l + 64 * k];
+      f4* const d2 = reinterpret_cast<f4*>(&s.pool[P_D2 + n16 * D2S + 16 * fw + 4 * q]);
+      const f4 c2 = *d2;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int o = wave + GWAVES * j;  // wave-uniform
-      if (o < NY) {
-        float p = tl[(TAB_FCW + 3 * o) * 64] * sv[0];
-        p = fmaf(tl[(TAB_FCW + 3 * o + 1) * 64], sv[1], p);
-        p = fmaf(tl[(TAB_FCW + 3 * o + 2) * 64], sv[2], p);
-        const float yo = logistic(wave_sum(p) + tab.bias[TAB_BIAS_B + o]);
-        if (l == 0) ybuf[o] = yo;
-      }
-    }
-    // (read before the barrier: what the error at C2 needs of the FC weights)
-    float fcw[NY];
-    if (wave < 4) {
-      const int i = n16 * 16 + 4 * wave + q;
-#pragma unroll
-      for (int o = 0; o < NY; ++o) fcw[o] = tab.e[(TAB_FCW + (i >> 6) + 3 * o) * 64 + (i & 63)];
-    }
-    CNN_GROUP_MARK(5);
-    __syncthreads();  // (4) yhat complete
-    if (wave < 4) {
-      float delta[10];
+      for (int o = 0; o < NY; ++o) p[o] = fmaf(fcw[o][2], sv[2], fmaf(fcw[o][1], sv[1], fcw[o][0] * sv[0]));
+      const bool out_lane = (OUT_LANES >> l) & 1;
+      const float y = logistic(wave_sum10(p) + bias3);
+      const float e = out_lane ? y - (out_of_lane(l) == label ? 1.0f : 0.0f) : 0.0f;
+      const float mine = e * fmaf(-y, y, y);  // y (1 - y) as y - y^2: one instruction
+      if (PART != LOWER && fw == 0) st.loss = 0.5f * e * e;
+      auto from = [&](int lane) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine), lane)); };
+      // the error at S2, of which the lane takes on element 16 n16 + 4 fw + q; then backavgpool and sigmoid'
+      float* const d_s2 = s.pool + P_END + NS2 * fw;
       {
-        float lsum = 0.0f;
+        float up[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int o = 0; o < 10; ++o) {
-          const float yo = ybuf[o];
-          const float e = yo - (o == label ? 1.0f : 0.0f);
-          lsum = fmaf(e, e, lsum);
-          delta[o] = e * yo * (1.0f - yo);
+        for (int o = 0; o < NY; ++o) {
+          const float delta = from(o < 8 ? 16 * (o >> 2) + (o & 3) : 24 + o);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) up[k] = fmaf(fcw[o][k], delta, up[k]);
         }
-        if (wave == 0) st.loss = fmaf(0.5f, lsum, st.loss);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) d_s2[l + 64 * k] = up[k];
       }
-      if (PART != LOWER && wave < 3) {  // FC backweights / backbias, row tile mt = wave
-        float d[4];
+      wave_sync();
+      const float up = 0.25f * d_s2[(n16 < 12 ? 16 * n16 : 0) + 4 * fw + q];
+      f4 d2v;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float v = 0.0f;
-#pragma unroll
-          for (int mt = 0; mt < 3; ++mt)
-            if (4 * mt + r < 10) v = wave == mt ? delta[4 * mt + r] : v;
-          d[r] = v;
-        }
-        const float aq = (sub & 2) ? ((sub & 1) ? d[3] : d[2]) : ((sub & 1) ? d[1] : d[0]);
-        st.g_bq += aq;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) st.acc_fc[k] = mfma4(aq, sv[k], st.acc_fc[k]);
-      }
-      // ---- error at C2 for this wave's tile: the lane's own element of the error at S2,
-      //      d_s2[i] = sum_o fc[o][i] delta[o] with i = 16 n16 + 4 wave + q, then backavgpool and sigmoid' --
-      {
-        float up = 0.0f;
-#pragma unroll
-        for (int o = 0; o < 10; ++o) up = fmaf(fcw[o], delta[o], up);
-        up *= 0.25f;
-        f4 d2v;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) d2v[r] = n16 < 12 ? up * c2v[r] * (1.0f - c2v[r]) : 0.0f;
-        *reinterpret_cast<f4*>(&s.pool[P_D2 + n16 * D2S + 16 * wave + 4 * q]) = d2v;
+      for (int r = 0; r < 4; ++r) d2v[r] = n16 < 12 ? up * c2[r] * (1.0f - c2[r]) : 0.0f;
+      *d2 = d2v;
+      if (PART != LOWER) {
         st.g_b2 += (d2v[0] + d2v[1]) + (d2v[2] + d2v[3]);
+        if (fw < 3) {  // FC backweights / backbias, row tile mt = fw: outputs 4 fw .. 4 fw + 3 (lanes 34, 35 hold zeros)
+          float d[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) d[r] = from(16 * fw + r);
+          const float aq = (sub & 2) ? ((sub & 1) ? d[3] : d[2]) : ((sub & 1) ? d[1] : d[0]);
+          st.g_bq += aq;
+#pragma unroll
+          for (int k = 0; k < 3; ++k) st.acc_fc[k] = mfma4(aq, sv[k], st.acc_fc[k]);
+        }
       }
     }
     // (read before the barrier: the weights of the C2 input error, for input maps 4 cg .. 4 cg + 3)
@@ -309,7 +308,7 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
         for (int sidx = 0; sidx < 3; ++sidx) wt[tile][sidx] = ta[(tile * 3 + sidx) * 64];
     }
     CNN_GROUP_MARK(6);
-    __syncthreads();  // (5) d_c2 complete
+    __syncthreads();  // (4) d_c2 complete
 
     if (PART != UPPER && wave < 4) {
       // ---- C2 input error for input maps 4 cg .. 4 cg + 3 from the pixel tiles nt = 2 h, 2 h + 1
@@ -383,7 +382,7 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
         group_k2_gradient<1>(st.acc_k2, s, bsrc);
     }
     CNN_GROUP_MARK(7);
-    if (PART != UPPER) __syncthreads();  // (6) both d_s1 copies complete; s1, d_c2 no longer needed
+    if (PART != UPPER) __syncthreads();  // (5) both d_s1 copies complete; s1, d_c2 no longer needed
 
     // ---- C1 error for this wave's tiles, then the K steps of the C1 weight gradient GEMM that belong
     //      to the same tiles: a wave reads only the d1 cells it staged itself, so no barrier -------------
@@ -408,9 +407,10 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
     CNN_GROUP_MARK(8);
   }
 
+  const int fw = wave & 3;
   // ---- one partial row per workgroup: cross-wave sums through LDS in a fixed order -------------------
-  // The parked values take the storage of the operand table, which nothing has read since barrier (5) but the lower waves of WHOLE
-  // and LOWER, and barrier (6) is behind those.
+  // The parked values take the storage of the operand table, which nothing has read since barrier (4) but the lower waves of WHOLE
+  // and LOWER, and barrier (5) is behind those.
   float* k1s = tab.e;                               // [8 waves][16][32]: parked C1 weight GEMM results
   float* b1s = tab.e + GWAVES * C1G_PARK;           // [8 waves][8]: C1 bias sums (256 floats reserved)
   float* b2s = b1s + 256;                           // [4 waves][64]: per-lane C2 bias sums
@@ -428,7 +428,7 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
       if (n16 == 0 && q < 3) b1s[wave * 8 + 2 * q + k] = v;
     }
   }
-  if (PART != LOWER && wave < 4) b2s[wave * 64 + l] = st.g_b2;  // lane (q, j) of this wave's pixel tile
+  if (PART != LOWER && wave >= 4) b2s[fw * 64 + l] = st.g_b2;  // lane (q, j) of this wave's pixel tile
   CNN_GROUP_MARK(9);
   __syncthreads();
   CNN_GROUP_MARK(12);
@@ -446,26 +446,24 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
       }
     }
   }
-  if (PART != LOWER && wave < 3) {  // FC rows o = 4 wave + r < 10: wave 2 has two
-    float* dst = out + OFF_FC + 4 * wave * NS2 + l;
+  if (PART != LOWER && wave >= 4 && fw < 3) {  // FC rows o = 4 fw + r < 10: the last wave has two
+    float* dst = out + OFF_FC + 4 * fw * NS2;
 #pragma unroll
     for (int k = 0; k < 3; ++k)
 #pragma unroll
-      for (int r = 0; r < 2; ++r) put_row<COHERENT>(dst + r * NS2 + 64 * k, st.acc_fc[k][r]);
-    if (wave < 2) {
+      for (int r = 0; r < 2; ++r) put_row<COHERENT>(dst + r * NS2 + l + 64 * k, st.acc_fc[k][r]);
+    if (fw < 2) {
 #pragma unroll
       for (int k = 0; k < 3; ++k)
 #pragma unroll
-        for (int r = 2; r < 4; ++r) put_row<COHERENT>(dst + r * NS2 + 64 * k, st.acc_fc[k][r]);
+        for (int r = 2; r < 4; ++r) put_row<COHERENT>(dst + r * NS2 + l + 64 * k, st.acc_fc[k][r]);
     }
-    if (l < 4 && 4 * wave + l < 10) put_row<COHERENT>(out + OFF_B + 4 * wave + l, st.g_bq);
+    if (l < 4 && 4 * fw + l < 10) put_row<COHERENT>(out + OFF_B + 4 * fw + l, st.g_bq);
   }
   CNN_GROUP_MARK(13);
-  const bool k1_lane = PART == LOWER ? t < 150 : wave >= 6 || (wave == 3 && l >= 32);
-  if (PART != UPPER && k1_lane) {
-    // one thread per C1 weight (of WHOLE, waves 6, 7 have nothing else to store; 22 lanes of wave 3 take the
-    // rest): the eight waves' shares of the GEMM, both shifted halves
-    const int e = PART == LOWER ? t : wave >= 6 ? t - 384 : 96 + l;
+  if (PART != UPPER && wave < 3) {
+    // one thread per C1 weight: the eight waves' shares of the GEMM, both shifted halves
+    const int e = t;
     if (e < 150) {
       float x[GWAVES];
 #pragma unroll
@@ -489,7 +487,10 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
       put_row<COHERENT>(out + OFF_B2 + j, (x[0] + x[4]) + (x[8] + x[12]));
     }
   }
-  if (PART != LOWER && t == 0) put_row<COHERENT>(out + LOSS_SLOT, st.loss);
+  if (PART != LOWER && wave == 4) {
+    const float loss = wave_sum(st.loss);
+    if (l == 0) put_row<COHERENT>(out + LOSS_SLOT, loss);
+  }
   CNN_GROUP_MARK(10);
 }
 

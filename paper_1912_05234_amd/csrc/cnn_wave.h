@@ -41,7 +41,7 @@ constexpr int D1_MAP = 24 * 24 + 4;
 // The same in chunks of eight rows, d1c[6][8][24] (the kernels with one wave per image).
 constexpr int D1C_MAP = 8 * 24 + 4;
 constexpr int POOL_FLOATS = 6 * D1_MAP + 32;
-static_assert(POOL_FLOATS >= P_END, "pool holds the forward/C2 arrays");
+static_assert(POOL_FLOATS >= P_END + 4 * NS2, "pool holds the forward/C2 arrays and the upper waves' errors at S2");
 struct __align__(16) TrainLds {
   float d_s1[NS1];  // error at S1 (col2im target)
   float img[NI];
@@ -293,21 +293,22 @@ constexpr int table_max_multiplicity() {
 // ENTRIES counts the entries of the LDS copy, of which the first LOADED come from global memory.
 // FIRST: the entry whose pieces are fetched first; `commit_first` stores those (one round of loads)
 // and the tail, `commit_rest` the others, each followed by a barrier of the caller's.
-template <int ENTRIES, int THREADS, bool COHERENT = false, int LOADED = ENTRIES, int FIRST = 0>
+// Of the entries, SKIPPED from SKIP on (before FIRST) stay where they are.
+template <int ENTRIES, int THREADS, bool COHERENT = false, int LOADED = ENTRIES, int FIRST = 0, int SKIP = 0, int SKIPPED = 0>
 struct TableLoad {
-  static constexpr int PIECES = LOADED * 16, ROUNDS = (PIECES + THREADS - 1) / THREADS;
+  static constexpr int PIECES = (LOADED - SKIPPED) * 16, ROUNDS = (PIECES + THREADS - 1) / THREADS;
   static constexpr int TAIL = TAB_BIAS_FLOATS / 4;
   typedef OperandTable<ENTRIES> Table;
   static_assert(TAIL <= THREADS, "one thread per piece of the tail");
-  static_assert(FIRST >= 0 && FIRST < LOADED, "the entry fetched first is one of the loaded ones");
+  static_assert(FIRST >= SKIP + SKIPPED && FIRST < LOADED, "the entry fetched first is one of the loaded ones");
   f4 v[ROUNDS], tail;
   // 16-byte piece of the table that this thread moves in round r (the same in global memory and in
   // LDS), or -1: the pieces are taken in the order FIRST * 16, .., PIECES - 1, 0, .., FIRST * 16 - 1, so
   // that round 0 brings the entries from FIRST on (what the caller needs first) and loads return in
   // the order they are issued
   static __device__ __forceinline__ int piece(int r) {
-    const int i = r * THREADS + (int)threadIdx.x, at = i + FIRST * 16;
-    return i < PIECES ? (at < PIECES ? at : at - PIECES) : -1;
+    const int i = r * THREADS + (int)threadIdx.x, at = i + (FIRST - SKIPPED) * 16, of = at < PIECES ? at : at - PIECES;
+    return i < PIECES ? (of < SKIP * 16 ? of : of + SKIPPED * 16) : -1;
   }
   // Issue order: round 0, the tail (biases), the other rounds.
   __device__ __forceinline__ void fetch(const float* __restrict__ tabg) {
