@@ -29,7 +29,8 @@ constexpr int TRAIN_BLOCKS = 256;  // most workgroups (= gradient partials) of t
 // (more images in flight, no barriers).  Measured crossover, gradient of 512 / 513 / 576 / 640 images: 20.8 / 24.0 / 27.5 /
 // 28.2 us with eight waves per image (a third workgroup has to wait), 23.2 / 23.1 / 23.7 / 23.7 us with one.
 constexpr int GROUP_MAX_BATCH = 512;
-// Up to this size there are two compute units per image, and two workgroups share it.
+// Up to this size there are two compute units per image, and two workgroups share it.  Step with one workgroup / two, us: 64
+// images 11.6 / 10.5, 128 12.1 / 11.0, 129 12.3 / 13.2, 256 13.6 / 15.0, 512 20.7 / 25.8.
 constexpr int GROUP_PAIR_MAX_BATCH = 128;
 // The same choice for the forward pass alone: evaluation of 512 / 768 / 896 / 1024 images 9.4 / 10.9 / 12.8 / 12.9 us with eight
 // waves per image (1.8 more for every 256), 13.1 for any number up to 2048 with one.
