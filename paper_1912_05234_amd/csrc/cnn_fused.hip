@@ -172,7 +172,7 @@ __global__ __launch_bounds__(64 * FWAVES) void forward_kernel(const float* __res
     f4 c2[4];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) c2[mt] = f4{bias2, bias2, bias2, bias2};
-    c2s_gemm(c2, ln2);
+    c2s_gemm<0, 4>(c2, ln2);
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
 #pragma unroll
@@ -336,6 +336,9 @@ struct WaveShare {
     }
   }
 };
+// PAIR: at most four images per workgroup, one for each SIMD; waves w and w + 4 share image w (cnn_train.h).  All waves pass all
+// barriers: a pair without an image goes through the first one's and drops what it finds.
+template <bool PAIR>
 __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void train_kernel(
     const float* __restrict__ images, const int32_t* __restrict__ labels, int B, const float* __restrict__ w,
     const float* __restrict__ tabg, float* __restrict__ partial, float* fc_hist) {
@@ -346,11 +349,12 @@ __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 
   WaveState st;
   const int K = B > (int)blockIdx.x ? (B - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x : 0;
   WaveShare mine(K, wave);
-  const bool has_images = mine.left > 0;
+  const bool has_images = PAIR ? (wave & 3) < K : mine.left > 0;
   const float sign = wave & 1 ? -1.0f : 1.0f;  // see wave_image
   auto image_index = [&](int k) { return (size_t)blockIdx.x + (size_t)gridDim.x * (size_t)k; };
   // every load of the set-up is issued before anything waits for one
-  const Pixels px = load_pixels(images + (has_images ? image_index(mine.k()) : 0) * NI);
+  const size_t first = has_images ? image_index(PAIR ? wave & 3 : mine.k()) : PAIR ? image_index(0) : 0;
+  const Pixels px = load_pixels(images + first * NI);
   SplitLoad<64 * TWAVES, true> weights;
   weights.fetch(w);
   constexpr int FC_PIECES = 30 * 16;
@@ -359,20 +363,34 @@ __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 
   const f4 fc = reinterpret_cast<const f4*>(tabg)[TAB_FCW * 16 + (t < FC_PIECES ? t : 0)];
   const float bias = tabg[TABG_BIAS + (t < TAB_BIAS_FLOATS ? t : 0)];
   // waves without images skip their set-up and their row
-  if (has_images) wave_init(st);
+  if (PAIR || has_images) wave_init(st);
   if (t < C1G_ONES) ops.ones[t] = 1.0f;
   if (t < FC_PIECES) reinterpret_cast<f4*>(ops.fc)[t] = fc;
   if (t < TAB_BIAS_FLOATS) ops.bias[t] = bias;
   weights.commit(lds[0].pool, ops.items, ops.bwd);
   __syncthreads();  // the operands are complete
-  if (has_images) place_image(s, px);
-  wave_sync();
-  st.bias2 = ops.bias[threadIdx.x & 15];
-  while (mine.left > 0) {
-    const size_t n = image_index(mine.k());
-    mine.advance();
-    const size_t nn = mine.left > 0 ? image_index(mine.k()) : n;
-    wave_image(st, s, ops, images + nn * NI, labels[n], sign, fc_hist + n * FC_HIST);
+  if constexpr (PAIR) {
+    WaveTrainLds& area = lds[wave & 3];
+    if (wave < 4)
+      place_image<FIRST>(area, px);
+    else
+      place_image<SECOND>(area, px);
+    __syncthreads();
+    st.bias2 = ops.bias[threadIdx.x & 15];
+    if (wave < 4)
+      wave_image<FIRST>(st, area, s, ops, images, labels[first], sign, fc_hist + first * FC_HIST, has_images);
+    else
+      wave_image<SECOND>(st, area, s, ops, images, labels[first], sign, fc_hist + first * FC_HIST, has_images);
+  } else {
+    if (has_images) place_image<LONE>(s, px);
+    wave_sync();
+    st.bias2 = ops.bias[threadIdx.x & 15];
+    while (mine.left > 0) {
+      const size_t n = image_index(mine.k());
+      mine.advance();
+      const size_t nn = mine.left > 0 ? image_index(mine.k()) : n;
+      wave_image<LONE>(st, s, s, ops, images + nn * NI, labels[n], sign, fc_hist + n * FC_HIST, true);
+    }
   }
   // FC weight gradient: a second walk over this wave's images, four per K step (the history rows
   // have left the L2 cache by now; a wave that is done early does this while the others still work)
@@ -430,7 +448,7 @@ __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 
     for (int i = threadIdx.x; i < RF4; i += 64 * TWAVES) {
       f4 v[TWAVES];
 #pragma unroll
-      for (int k = 0; k < TWAVES; ++k) v[k] = K > k ? r[i + k * RF4] : zero;
+      for (int k = 0; k < TWAVES; ++k) v[k] = K > (PAIR ? k & 3 : k) ? r[i + k * RF4] : zero;
       dst[i] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     }
   }
@@ -737,8 +755,10 @@ int run_backward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B
     train_group_kernel<true><<<2 * blocks, 64 * GWAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, ctx->partial);
   else if (grouped)
     train_group_kernel<false><<<blocks, 64 * GWAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, ctx->partial);
+  else if (B <= 4 * TRAIN_BLOCKS)
+    train_kernel<true><<<blocks, 64 * TWAVES, 0, ctx->stream>>>(images, labels, B, ctx->w, ctx->tabg, ctx->partial, ctx->fc_hist);
   else
-    train_kernel<<<blocks, 64 * TWAVES, 0, ctx->stream>>>(images, labels, B, ctx->w, ctx->tabg, ctx->partial, ctx->fc_hist);
+    train_kernel<false><<<blocks, 64 * TWAVES, 0, ctx->stream>>>(images, labels, B, ctx->w, ctx->tabg, ctx->partial, ctx->fc_hist);
   if (hipGetLastError() != hipSuccess) return CNN_EHIP;
   if (timed) {
     CNN_HIP_TRY(hipEventRecord(ctx->ev[2 * ctx->ev_used + 1], ctx->stream));

@@ -374,25 +374,31 @@ __device__ __forceinline__ C2SLane c2s_lane(const unsigned* s1, const u4v* items
 }
 // One piece of the image after the other (l, m, h), so that seven rows of items are in registers and not all of them; a step's
 // new row, and the next piece's first rows, are read a step ahead.
-__device__ __forceinline__ void c2s_gemm(f4 (&d)[4], const C2SLane& ln) {
-  bf8 x[2][11];
-  auto load_row = [&](int k, int row) { x[k & 1][row] = item8(ln.s1 + 36 * row + k * SPLIT_S1_PLANE); };
+// The pixel tiles M0 .. M0 + N - 1.
+template <int M0, int N>
+__device__ __forceinline__ void c2s_gemm(f4 (&d)[N], const C2SLane& ln) {
+  constexpr int ROWS = 2 * N + 3;  // rows 2 M0 .. of S1
+  bf8 x[2][ROWS];
+  auto load_row = [&](int k, int row) {
+    if (row < ROWS) x[k & 1][row] = item8(ln.s1 + 36 * (2 * M0 + row) + k * SPLIT_S1_PLANE);
+  };
 #pragma unroll
-  for (int row = 0; row < 7; ++row) load_row(2, row);
+  for (int row = 0; row < 2 * N - 1; ++row) load_row(2, row);
 #pragma unroll
   for (int k = 2; k >= 0; --k)  // piece l meets h; m meets m, h; h meets l, m, h
 #pragma unroll
     for (int u = 0; u < 5; ++u) {
-      if (u < 4) load_row(k, u + 7);
+      if (u < 4) load_row(k, u + 2 * N - 1);
       if (k > 0 && u >= 1) {
-        load_row(k - 1, 2 * u - 2);
-        if (u < 4) load_row(k - 1, 2 * u - 1);
+        // (what the first kernel row of the next piece needs; its other rows follow under its products)
+        load_row(k - 1, 2 * u - 2 < 2 * N - 1 ? 2 * u - 2 : ROWS);
+        if (u < 4) load_row(k - 1, 2 * u - 1 < 2 * N - 1 ? 2 * u - 1 : ROWS);
       }
 #pragma unroll
       for (int j = 2 - k; j >= 0; --j) {
         const bf8 b = __builtin_bit_cast(bf8, ln.w[(u * 3 + j) * 48]);
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) d[mt] = mfma_bf16(x[k & 1][u + 2 * mt], b, d[mt]);
+        for (int mt = 0; mt < N; ++mt) d[mt] = mfma_bf16(x[k & 1][u + 2 * mt], b, d[mt]);
       }
     }
 }
@@ -403,6 +409,8 @@ __device__ __forceinline__ void c2s_gemm(f4 (&d)[4], const C2SLane& ln) {
 // stand.  The columns of kernel row u are the thirty elements s1[y+u][x .. x+4][0..5], two tiles; a transposing
 // read brings four pixels (rows, twelve bytes apart) of sixteen columns: lane 4 r + i of a quarter gives the address of
 // pixel r's columns 4 i .. 4 i + 3 and receives column n16 of all four.
+// Over the pixel tiles 2 S and 2 S + 1, S0 <= S < S0 + NS.
+template <int S0, int NS>
 __device__ __forceinline__ void k2_gradient(f4 (&acc)[10], const u4v (&d2)[2][3], const unsigned* s1, int l) {
   typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
   typedef bf4 __attribute__((address_space(3)))* LdsQuad;
@@ -410,7 +418,7 @@ __device__ __forceinline__ void k2_gradient(f4 (&acc)[10], const u4v (&d2)[2][3]
   LdsQuad at = (LdsQuad)(reinterpret_cast<const unsigned short*>(s1 + (dx ? SPLIT_S1B : 0)) + 6 * (12 * (r >> 1) + 2 * q + dx) + 4 * (n16 & 3));
   bf8 a[2][3];
 #pragma unroll
-  for (int S = 0; S < 2; ++S)
+  for (int S = S0; S < S0 + NS; ++S)
 #pragma unroll
     for (int k = 0; k < 3; ++k) a[S][k] = __builtin_bit_cast(bf8, d2[S][k]);
   // Rows R = u + 4 S and R + 2 of the image plane make an operand.  Every one is read afresh (two operands may share a row, but
@@ -418,7 +426,7 @@ __device__ __forceinline__ void k2_gradient(f4 (&acc)[10], const u4v (&d2)[2][3]
   // their own and then added: steps onto the sums over all images would be rounded, and cut, at their size.
   bf8 x[2][2][3];
   auto load = [&](int n) {
-    const int R = (n >> 1) + 4 * (n & 1);
+    const int R = n / NS + 4 * (S0 + n % NS);
     LdsQuad from = at;
     asm volatile("" : "+v"(from));
 #pragma unroll
@@ -434,19 +442,19 @@ __device__ __forceinline__ void k2_gradient(f4 (&acc)[10], const u4v (&d2)[2][3]
   load(0);
   f4 sum[2];
 #pragma unroll
-  for (int n = 0; n < 10; ++n) {  // u = n / 2, S = n % 2
-    if (n < 9) load(n + 1);
-    if (!(n & 1)) sum[0] = sum[1] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int n = 0; n < 5 * NS; ++n) {  // u = n / NS, S = S0 + n % NS
+    if (n < 5 * NS - 1) load(n + 1);
+    if (n % NS == 0) sum[0] = sum[1] = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int k = 0; k < 6; ++k)
 #pragma unroll
-      for (int t = 0; t < 2; ++t) sum[t] = mfma_bf16(a[n & 1][PA[k]], x[n & 1][t][PX[k]], sum[t]);
-    if (n & 1)
+      for (int t = 0; t < 2; ++t) sum[t] = mfma_bf16(a[S0 + n % NS][PA[k]], x[n & 1][t][PX[k]], sum[t]);
+    if (n % NS == NS - 1)
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[(n & ~1) + t][r] += sum[t][r];
-        asm volatile("" : "+v"(acc[(n & ~1) + t]));  // now: the compiler would keep the sums and the old `acc` until the end of the image
+        for (int r = 0; r < 4; ++r) acc[2 * (n / NS) + t][r] += sum[t][r];
+        asm volatile("" : "+v"(acc[2 * (n / NS) + t]));  // now: the compiler would keep the sums and the old `acc` until the end of the image
       }
   }
 }
@@ -457,12 +465,13 @@ __device__ __forceinline__ void k2_gradient(f4 (&acc)[10], const u4v (&d2)[2][3]
 constexpr int DS1_ROW = 16, DS1_MAP = 12 * DS1_ROW + 8;
 // Records of an image's d from its pieces d2[S][piece] (result layout: register r of tile 2 S + mt % 2 is pixel
 // (2 mt + r / 2, 2 q + r % 2)).  Record 16 mt + 2 x + y % 2 is pixel (y, x): the two rows of a tile alternate, see col2im_split.
+template <int S0, int NS>
 __device__ __forceinline__ void store_records(unsigned short* recs, const u4v (&d2)[2][3], int l) {
   const int q = l >> 4, n16 = l & 15;
   unsigned short* rec = recs + 4 * q * BWD_REC + n16;
   if (n16 < 12) {
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 2 * S0; mt < 2 * (S0 + NS); ++mt)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -503,6 +512,8 @@ __device__ __forceinline__ void add_column(float& lo, float& hi, float e) {
 // kept the LDS busy for 1000 clocks, eight waves 8000 of 13000; training on 60000 images took 588 us instead of 572.
 // The input maps 0..3 and 4, 5 are taken one after the other: half the registers.
 // d_in may lie over the records; its columns 12..15 get zeros.  `sign`: what d was taken with.
+// LOW, HIGH: with the input maps 0..3, with 4 and 5.
+template <bool LOW, bool HIGH>
 __device__ __forceinline__ void col2im_split(const unsigned short* bwd, const unsigned short* rec, float* d_in, float sign, int l) {
   const int q = l >> 4, n16 = l & 15;
   // this quarter's slot groups of a row record and of a pixel record
@@ -565,7 +576,7 @@ __device__ __forceinline__ void col2im_split(const unsigned short* bwd, const un
   // ---- input maps 4, 5, packed: lane quarters 0, 1 have them for tap columns 0..2 and quarters 2, 3 for columns 3, 4, in
   //      round s column s or 3 + s (quarters 2, 3 have nothing in round 2: their tile rows are zero).  tu: the u = 4 term of
   //      round s in register s ----
-  {
+  if constexpr (HIGH) {
     auto round = [&](auto sc) {
       constexpr int S = decltype(sc)::value;
       f4 tv[4];
@@ -591,7 +602,7 @@ __device__ __forceinline__ void col2im_split(const unsigned short* bwd, const un
   }
   // ---- input maps 0..3: lane quarter q owns map q; tiles V(0..4) and U4; tap (4, 4) rides in
   //      register 3 of the packed tile PU of the maps 4, 5 above ----
-  {
+  if constexpr (LOW) {
     f4 t4[4];  // taps (4, v), v < 4, in register v
     tiles(kTileU4, t4);
     auto round = [&](auto vc) {

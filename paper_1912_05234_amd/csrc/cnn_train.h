@@ -87,15 +87,22 @@ __device__ __forceinline__ int phase_lane() {
   asm volatile("" : "+v"(l));
   return l;
 }
+// What a wave does of an image.  LONE: everything.  Where there is a SIMD for every image and more waves than images
+// (train_kernel, PAIR), two waves of a SIMD share one: they take different column tiles of C1, pixel tiles of C2, pixels of the C2 weight
+// gradient and input maps of the C2 input error, both make the outputs, and hand over at workgroup barriers.
+enum WavePart { LONE, FIRST, SECOND };
 // The image into LDS, as it is and in pieces.
+template <WavePart PART>
 __device__ __forceinline__ void place_image(WaveTrainLds& s, const Pixels& px) {
   const int l = threadIdx.x & 63;
-  store_pixels(s.img, px);
+  if (PART != SECOND) store_pixels(s.img, px);
   unsigned* pieces = reinterpret_cast<unsigned*>(s.pool) + W_PIECES;
-  split_store_pixels(pieces, l, px.a);
-  split_store_pixels(pieces, l + 64, px.b);
-  split_store_pixels(pieces, l + 128, px.c);
-  if (l < 4) split_store_pixels(pieces, l + 192, px.d);
+  if (PART != SECOND) split_store_pixels(pieces, l, px.a);
+  if (PART != FIRST) {
+    split_store_pixels(pieces, l + 64, px.b);
+    split_store_pixels(pieces, l + 128, px.c);
+    if (l < 4) split_store_pixels(pieces, l + 192, px.d);
+  }
 }
 // Touches the 25 cache lines of an image so that they are on their way into the L2 cache; the value
 // is not used (the asm keeps the load alive and costs no instruction).
@@ -106,30 +113,44 @@ __device__ __forceinline__ void touch_pixels(const float* __restrict__ image) {
 }
 
 // The second copy of S1's pieces (cnn_split.h), a word per lane: contiguous, where wider stores would not be aligned.
+template <WavePart PART>
 __device__ __forceinline__ void s1_second_copy(float* pool) {
   const int l = threadIdx.x & 63;
   const unsigned* from = reinterpret_cast<const unsigned*>(pool) + W_S1 + l;
   unsigned* to = reinterpret_cast<unsigned*>(pool) + W_S1 + SPLIT_S1B + l;
   constexpr int WHOLE = SPLIT_S1_COPY / 64, REST = SPLIT_S1_COPY % 64;
+  constexpr int K0 = PART == SECOND ? WHOLE / 2 : 0, K1 = PART == FIRST ? WHOLE / 2 : WHOLE;
   unsigned v[WHOLE + 1];
 #pragma unroll
-  for (int k = 0; k < WHOLE; ++k) v[k] = from[64 * k];
-  if (l < REST) v[WHOLE] = from[64 * WHOLE];
+  for (int k = K0; k < K1; ++k) v[k] = from[64 * k];
+  if (PART != FIRST && l < REST) v[WHOLE] = from[64 * WHOLE];
 #pragma unroll
-  for (int k = 0; k < WHOLE; ++k) to[64 * k] = v[k];
-  if (l < REST) to[64 * WHOLE] = v[WHOLE];
+  for (int k = K0; k < K1; ++k) to[64 * k] = v[k];
+  if (PART != FIRST && l < REST) to[64 * WHOLE] = v[WHOLE];
 }
 
 // One image through forward and backward.  The image is in s (place_image) on entry and `next_image` (any valid image when
 // there is no next one) on return; `hist` is the image's history row (FC_HIST floats).  `sign` (1 or -1): what d_c2 is taken
 // with in the bfloat16 products, another in every other wave: the instruction cuts what it aligns towards minus infinity
 // (cnn_split.h, bwd_negative), and the sums over images would add that up.
-__device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const TrainOperands& ops,
-                                           const float* __restrict__ next_image, int label, float sign, float* hist) {
+// FIRST and SECOND: `s` is the image's area, `own` the wave's (LONE: the same); no next image; `keeps`: whether the
+// image's history row is written (a pair without an image goes through another's, and drops what it finds).
+template <WavePart PART>
+__device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, WaveTrainLds& own, const TrainOperands& ops,
+                                           const float* __restrict__ next_image, int label, float sign, float* hist, bool keeps) {
+  constexpr int T0 = PART == SECOND ? 5 : 0, T1 = PART == FIRST ? 5 : 9;  // column tiles of C1
+  constexpr int M0 = PART == SECOND ? 2 : 0, MN = PART == LONE ? 4 : 2;   // pixel tiles of C2
+  constexpr int S0 = M0 / 2, SN = MN / 2;
+  auto hand_over = [&]() {
+    if (PART == LONE)
+      wave_sync();
+    else
+      __syncthreads();
+  };
   unsigned short* s1 = reinterpret_cast<unsigned short*>(s.pool + W_S1);
   // ---- C1 = sigmoid(mconv(I, k1, b1)), S1 = sums of avgpool's windows (cnn_split.h): lane (q, n16) keeps the six maps
   //      of pixel y = 8 ty + n16 % 8, x = 8 tx + 4 (n16 / 8) + q of the column tiles T = 3 ty + tx --------------------
-  float c1[9][6];
+  float c1[9][6];  // (of the wave's tiles)
   {
     const int l = phase_lane(), n16 = l & 15;
     const C1SLane ln = c1s_lane(reinterpret_cast<const unsigned*>(s.pool) + W_PIECES, l);
@@ -143,19 +164,19 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
     for (int i = 0; i < 2; ++i) bias1b[i] = NEG_LOG2E * ops.bias[TAB_BIAS_B1 + 4 + i];
     float low = 0.0f, high = 0.0f;  // of the pair's first tile
     C1SItems it[2];
-    c1s_load(it[0], ln, 0);
+    c1s_load(it[T0 & 1], ln, T0);
 #pragma unroll
-    for (int T = 0; T < 9; ++T) {
-      if (T < 8) c1s_load(it[(T + 1) & 1], ln, T + 1);
+    for (int T = T0; T < T1; ++T) {
+      if (T < T1 - 1) c1s_load(it[(T + 1) & 1], ln, T + 1);
       f4 d0 = bias1a, d1 = bias1b;
       c1s_gemm(w, it[T & 1], d0, d1);
 #pragma unroll
       for (int i = 0; i < 6; ++i) c1[T][i] = logistic_of_scaled(i < 4 ? d0[i & 3] : d1[i & 3]);
       float lo, hi;
       c1s_pool(c1[T], lo, hi);
-      if (T == 8) {
+      if (T == T1 - 1 && ((T1 - T0) & 1)) {
         split_store_s1<false>(s1, es + c1s_tile_s1(T), lo, eh + c1s_tile_s1(T), c1s_pool_rows(hi, hi));
-      } else if (T & 1) {
+      } else if ((T - T0) & 1) {
         split_store_s1<false>(s1, es + c1s_tile_s1(T - 1), low, es + c1s_tile_s1(T), lo);
         split_store_s1_one<false>(s1, eh + ((n16 & 1) ? c1s_tile_s1(T) : c1s_tile_s1(T - 1)), c1s_pool_rows(high, hi));
       }
@@ -163,27 +184,27 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
       high = hi;
     }
     // the words behind the planes are read by the last items and meet zero weights (the second copy takes them along)
-    if (l < 4) s.pool[W_S1 + 3 * SPLIT_S1_PLANE + l] = 0.0f;
+    if (PART != SECOND && l < 4) s.pool[W_S1 + 3 * SPLIT_S1_PLANE + l] = 0.0f;
   }
-  wave_sync();
-  s1_second_copy(s.pool);
-  wave_sync();
-  touch_pixels(next_image);
+  hand_over();
+  s1_second_copy<PART>(s.pool);
+  hand_over();
+  if (PART == LONE) touch_pixels(next_image);
   // ---- C2 = sigmoid(mconv(S1, k2, b2)), S2 = avgpool(C2): a lane's four result registers are one window -------------
-  f4 c2v[4];
+  f4 c2v[MN];
   {
     const int l = phase_lane(), q = l >> 4, n16 = l & 15;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) c2v[mt] = f4{st.bias2, st.bias2, st.bias2, st.bias2};
-    c2s_gemm(c2v, c2s_lane(reinterpret_cast<const unsigned*>(s.pool + W_S1), ops.items, l));
+    for (int mt = 0; mt < MN; ++mt) c2v[mt] = f4{st.bias2, st.bias2, st.bias2, st.bias2};
+    c2s_gemm<M0, MN>(c2v, c2s_lane(reinterpret_cast<const unsigned*>(s.pool + W_S1), ops.items, l));
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
+    for (int mt = 0; mt < MN; ++mt) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) c2v[mt][r] = logistic_of_scaled(c2v[mt][r]);
-      if (n16 < 12) s.pool[W_S2 + n16 * S2_MAP + 4 * mt + q] = 0.25f * ((c2v[mt][0] + c2v[mt][1]) + (c2v[mt][2] + c2v[mt][3]));
+      if (n16 < 12) s.pool[W_S2 + n16 * S2_MAP + 4 * (M0 + mt) + q] = 0.25f * ((c2v[mt][0] + c2v[mt][1]) + (c2v[mt][2] + c2v[mt][3]));
     }
   }
-  wave_sync();
+  hand_over();
   // ---- output = sigmoid(mconv(S2, fc, b)), its error, FC backweights / backbias / backin: the lane owns the inputs lane,
   //      lane + 64, lane + 128 and the output out_of_lane(lane) --------------------------------------------------------
   {
@@ -198,13 +219,17 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
     const float y = logistic(wave_sum10(p) + ops.bias[TAB_BIAS_B + out_of_lane(l)]);
     const float e = out_lane ? y - (out_of_lane(l) == label ? 1.0f : 0.0f) : 0.0f;
     const float mine = e * fmaf(-y, y, y);  // y (1 - y) as y - y^2: one instruction
-    st.loss = fmaf(0.5f * e, e, st.loss);
-    st.g_b += mine;
+    if (PART != SECOND) {
+      st.loss = fmaf(0.5f * e, e, st.loss);
+      st.g_b += mine;
+    }
     // s2 and delta go to the image's history row, the products are taken once per wave
+    if (PART == LONE || (PART == FIRST && keeps)) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) hist[l + 64 * k] = sv[k];
-    if (out_lane) hist[FC_HIST_DELTA + out_of_lane(l)] = mine;
-    if (l >= 4 && l < 10) hist[FC_HIST_DELTA + 6 + l] = 0.0f;
+      for (int k = 0; k < 3; ++k) hist[l + 64 * k] = sv[k];
+      if (out_lane) hist[FC_HIST_DELTA + out_of_lane(l)] = mine;
+      if (l >= 4 && l < 10) hist[FC_HIST_DELTA + 6 + l] = 0.0f;
+    }
     float delta[NY];
 #pragma unroll
     for (int o = 0; o < NY; ++o)
@@ -214,7 +239,7 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
       float d = 0.0f;
 #pragma unroll
       for (int o = 0; o < NY; ++o) d = fmaf(fc[(3 * o + k) * 64], delta[o], d);
-      s.pool[W_DS2 + s2_at(l + 64 * k)] = d;
+      own.pool[W_DS2 + s2_at(l + 64 * k)] = d;
     }
   }
   wave_sync();
@@ -223,12 +248,12 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
   {
     const int l = phase_lane(), q = l >> 4, n16 = l & 15;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const float up = s.pool[W_DS2 + (n16 < 12 ? n16 : 0) * S2_MAP + 4 * mt + q] * (0.25f * sign);  // (padding rows: map 0's)
+    for (int mt = M0; mt < M0 + MN; ++mt) {
+      const float up = own.pool[W_DS2 + (n16 < 12 ? n16 : 0) * S2_MAP + 4 * mt + q] * (0.25f * sign);  // (padding rows: map 0's)
       f4 d;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float c = c2v[mt][r];
+        const float c = c2v[mt - M0][r];
         d[r] = up * fmaf(-c, c, c);
       }
       st.g_b2 = fmaf(sign, (d[0] + d[1]) + (d[2] + d[3]), st.g_b2);
@@ -240,16 +265,16 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
         d2[mt >> 1][2][2 * (mt & 1) + h] = p.l;
       }
     }
-    k2_gradient(st.acc_k2, d2, reinterpret_cast<const unsigned*>(s.pool + W_S1), l);
+    k2_gradient<S0, SN>(st.acc_k2, d2, reinterpret_cast<const unsigned*>(s.pool + W_S1), l);
   }
-  wave_sync();
+  hand_over();
   // S1 is dead: d_c2 as records of its pixels
-  store_records(reinterpret_cast<unsigned short*>(s.pool + W_D2), d2, phase_lane());
-  wave_sync();
+  store_records<S0, SN>(reinterpret_cast<unsigned short*>(s.pool + W_D2), d2, phase_lane());
+  hand_over();
 
   // ---- C2 backin into d_s1 -----------------------
-  col2im_split(ops.bwd, reinterpret_cast<const unsigned short*>(s.pool + W_D2), s.pool + W_DS1, sign, phase_lane());
-  wave_sync();
+  col2im_split<PART != SECOND, PART != FIRST>(ops.bwd, reinterpret_cast<const unsigned short*>(s.pool + W_D2), s.pool + W_DS1, sign, phase_lane());
+  hand_over();
   // ---- backavgpool through S1 and the derivative of C1's sigmoid, then C1 backweights as a GEMM over pixel pairs (cnn_wave.h),
   //      column tile by column tile of C1: eight K steps of one row and four pairs.  A tile's error goes to LDS, as
   //      d1[6][x / 2 % 2][8][x / 4][x % 2] with the parts D1T_HALF and D1T_MAP apart (stores and loads of 32 lanes on 32
@@ -257,7 +282,7 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
   {
     const int l = phase_lane(), q = l >> 4, n16 = l & 15, a = (n16 >> 1) & 3, bx = n16 >> 3;
     const float* up = s.pool + W_DS1 + a * DS1_ROW + 2 * bx + (q >> 1);
-    float* dst = s.pool + W_D1 + (q >> 1) * D1T_HALF + 4 * (n16 & 7) + 2 * bx + (q & 1);
+    float* dst = own.pool + W_D1 + (q >> 1) * D1T_HALF + 4 * (n16 & 7) + 2 * bx + (q & 1);
     float e[2][6];  // the error at S1 over a tile
     auto fetch = [&](int T) {
       const int o = 4 * DS1_ROW * (T / 3) + 4 * (T % 3);
@@ -272,7 +297,7 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
         dst[i * D1T_MAP + (T & 1) * D1T_WORDS] = e[T & 1][i] * fmaf(-c, c, c);
       }
     };
-    const float* pa = s.pool + W_D1 + ((n16 >> 1) % 6) * D1T_MAP + (q & 1) * D1T_HALF + 2 * (q >> 1) + (n16 & 1);
+    const float* pa = own.pool + W_D1 + ((n16 >> 1) % 6) * D1T_MAP + (q & 1) * D1T_HALF + 2 * (q >> 1) + (n16 & 1);
     const int c0 = n16, c1x = 16 + n16;
     const float* pb0 = s.img + (c0 / 6) * 28 + c0 % 6 + 2 * q;
     const float* pb1 = n16 >= 14 ? ops.ones + 2 * q : s.img + (c1x / 6) * 28 + c1x % 6 + 2 * q;
@@ -288,27 +313,27 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
         ob1[T & 1][y] = b1[28 * y];
       }
     };
-    fetch(0);
-    fetch(1);
-    stage(0);
+    fetch(T0);
+    fetch(T0 + 1);
+    stage(T0);
     wave_sync();
-    load(0);
-    fetch(2);
-    stage(1);
+    load(T0);
+    fetch(T0 + 2);
+    stage(T0 + 1);
     wave_sync();
     Pixels nx;
     f4 sum[2] = {f4{0.0f, 0.0f, 0.0f, 0.0f}, f4{0.0f, 0.0f, 0.0f, 0.0f}};  // the image's own, as in k2_gradient
     // The products of tile T, the loads of tile T + 1, the stores of tile T + 2 (into the buffer whose loads are done)
     // and the error at S1 for tile T + 3
 #pragma unroll
-    for (int T = 0; T < 9; ++T) {
-      if (T < 6) fetch(T + 3);
-      if (T < 7) stage(T + 2);
-      if (T < 8) load(T + 1);
+    for (int T = T0; T < T1; ++T) {
+      if (T + 3 < T1) fetch(T + 3);
+      if (T + 2 < T1) stage(T + 2);
+      if (T + 1 < T1) load(T + 1);
       // the next image's pixels (touched into the L2 cache long ago) are fetched under the last products, when the
       // fewest registers are in use (through an offset the compiler cannot see before this point: it would otherwise
       // start the loads, and occupy their sixteen registers, phases earlier)
-      if (T == 7) {
+      if (PART == LONE && T == 7) {
         int zero = 0;
         asm volatile("" : "+v"(zero));
         nx = load_pixels(next_image + zero);
@@ -321,9 +346,9 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
 #pragma unroll
       for (int y = 0; y < 8; ++y) {
         __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-        if (T < 7) __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
-        if (T < 7) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-        if (T < 8) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+        if (T + 2 < T1) __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+        if (T + 2 < T1) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+        if (T + 1 < T1) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
       }
       wave_sync();
       __builtin_amdgcn_sched_barrier(0);
@@ -332,8 +357,10 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, const
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) st.acc_k1[t][r] += sum[t][r];
-    place_image(s, nx);
-    wave_sync();
+    if (PART == LONE) {
+      place_image<LONE>(s, nx);
+      wave_sync();
+    }
   }
 }
 
