@@ -369,6 +369,7 @@ __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 
   if (t < TAB_BIAS_FLOATS) ops.bias[t] = bias;
   weights.commit(lds[0].pool, ops.items, ops.bwd);
   __syncthreads();  // the operands are complete
+  float fc_grad[NY][3];  // (PAIR)
   if constexpr (PAIR) {
     WaveTrainLds& area = lds[wave & 3];
     if (wave < 4)
@@ -378,9 +379,9 @@ __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 
     __syncthreads();
     st.bias2 = ops.bias[threadIdx.x & 15];
     if (wave < 4)
-      wave_image<FIRST>(st, area, s, ops, images, labels[first], sign, fc_hist + first * FC_HIST, has_images);
+      wave_image<FIRST>(st, area, s, ops, images, labels[first], sign, nullptr, fc_grad);
     else
-      wave_image<SECOND>(st, area, s, ops, images, labels[first], sign, fc_hist + first * FC_HIST, has_images);
+      wave_image<SECOND>(st, area, s, ops, images, labels[first], sign, nullptr, fc_grad);
   } else {
     if (has_images) place_image<LONE>(s, px);
     wave_sync();
@@ -389,13 +390,13 @@ __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 
       const size_t n = image_index(mine.k());
       mine.advance();
       const size_t nn = mine.left > 0 ? image_index(mine.k()) : n;
-      wave_image<LONE>(st, s, s, ops, images + nn * NI, labels[n], sign, fc_hist + n * FC_HIST, true);
+      wave_image<LONE>(st, s, s, ops, images + nn * NI, labels[n], sign, fc_hist + n * FC_HIST, fc_grad);
     }
   }
   // FC weight gradient: a second walk over this wave's images, four per K step (the history rows
   // have left the L2 cache by now; a wave that is done early does this while the others still work)
   f4 g_fc[12];
-  if (has_images) {
+  if (!PAIR && has_images) {
 #pragma unroll
     for (int nt = 0; nt < 12; ++nt) g_fc[nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     // this wave's stores to its history rows are complete before it reads them back
@@ -434,9 +435,13 @@ __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 
     if (again.left > 0) steps(std::integral_constant<int, 1>());
     if (again.left > 0) steps(std::integral_constant<int, 1>());
   }
+  static_assert(OFF_FC % 4 == 0 && OFF_B % 4 == 0, "whole items");
   __syncthreads();  // every wave is done with the operands: their storage parks the C1 GEMM results
   static_assert(TWAVES * C1G_PARK * sizeof(float) <= sizeof(ops.items), "the parked results fit");
-  if (has_images) wave_flush(st, sign, g_fc, reinterpret_cast<float*>(&s), reinterpret_cast<float*>(ops.items) + wave * C1G_PARK);
+  float *const row = reinterpret_cast<float*>(&s), *const park = reinterpret_cast<float*>(ops.items) + wave * C1G_PARK;
+  if (!PAIR && has_images) wave_flush<LONE>(st, sign, g_fc, fc_grad, row, park);
+  if (PAIR && has_images && wave < 4) wave_flush<FIRST>(st, sign, g_fc, fc_grad, row, park);
+  if (PAIR && has_images && wave >= 4) wave_flush<SECOND>(st, sign, g_fc, fc_grad, row, park);
   __syncthreads();
   {
     // rows of the waves that had images in a fixed tree; an idle wave's row counts as zeros (the
@@ -448,7 +453,10 @@ __global__ __launch_bounds__(64 * TWAVES) __attribute__((amdgpu_waves_per_eu(2, 
     for (int i = threadIdx.x; i < RF4; i += 64 * TWAVES) {
       f4 v[TWAVES];
 #pragma unroll
-      for (int k = 0; k < TWAVES; ++k) v[k] = K > (PAIR ? k & 3 : k) ? r[i + k * RF4] : zero;
+      for (int k = 0; k < TWAVES; ++k) {
+        const bool have = K > (PAIR ? k & 3 : k) && !(PAIR && k < 4 && i >= OFF_FC / 4 && i < OFF_B / 4);  // (FIRST has no FC weights)
+        v[k] = have ? r[i + k * RF4] : zero;
+      }
       dst[i] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     }
   }

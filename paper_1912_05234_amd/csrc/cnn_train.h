@@ -133,11 +133,11 @@ __device__ __forceinline__ void s1_second_copy(float* pool) {
 // there is no next one) on return; `hist` is the image's history row (FC_HIST floats).  `sign` (1 or -1): what d_c2 is taken
 // with in the bfloat16 products, another in every other wave: the instruction cuts what it aligns towards minus infinity
 // (cnn_split.h, bwd_negative), and the sums over images would add that up.
-// FIRST and SECOND: `s` is the image's area, `own` the wave's (LONE: the same); no next image; `keeps`: whether the
-// image's history row is written (a pair without an image goes through another's, and drops what it finds).
+// FIRST and SECOND: `s` is the image's area, `own` the wave's (LONE: the same); no next image and no history: SECOND leaves the FC
+// weight gradient of its one image in `fc`, of output o and input lane + 64 k.
 template <WavePart PART>
 __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, WaveTrainLds& own, const TrainOperands& ops,
-                                           const float* __restrict__ next_image, int label, float sign, float* hist, bool keeps) {
+                                           const float* __restrict__ next_image, int label, float sign, float* hist, float (&fc_grad)[NY][3]) {
   constexpr int T0 = PART == SECOND ? 5 : 0, T1 = PART == FIRST ? 5 : 9;  // column tiles of C1
   constexpr int M0 = PART == SECOND ? 2 : 0, MN = PART == LONE ? 4 : 2;   // pixel tiles of C2
   constexpr int S0 = M0 / 2, SN = MN / 2;
@@ -224,7 +224,7 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, WaveT
       st.g_b += mine;
     }
     // s2 and delta go to the image's history row, the products are taken once per wave
-    if (PART == LONE || (PART == FIRST && keeps)) {
+    if (PART == LONE) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) hist[l + 64 * k] = sv[k];
       if (out_lane) hist[FC_HIST_DELTA + out_of_lane(l)] = mine;
@@ -234,6 +234,11 @@ __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, WaveT
 #pragma unroll
     for (int o = 0; o < NY; ++o)
       delta[o] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine), o < 8 ? 16 * (o >> 2) + (o & 3) : 24 + o));
+    if (PART == SECOND)
+#pragma unroll
+      for (int o = 0; o < NY; ++o)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) fc_grad[o][k] = delta[o] * sv[k];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       float d = 0.0f;
@@ -389,14 +394,22 @@ __device__ __forceinline__ void fc_step_mfma(f4 (&g_fc)[12], const FcStepOperand
 // Writes the wave's gradient sums as one partial row (PSTRIDE floats in parameter order, the loss
 // in LOSS_SLOT, zeros after it) to `row`, every slot by exactly one lane.  `row` may be the start
 // of the wave's own LDS area (all of it is dead once the wave's images are done); `park` is
-// C1G_PARK floats of LDS outside the row that no other wave uses; `g_fc` is wave_fc_gradient's result.
-__device__ __forceinline__ void wave_flush(WaveState& st, float sign, const f4 (&g_fc)[12], float* row, float* park) {
+// C1G_PARK floats of LDS outside the row that no other wave uses; the FC weight gradient is `g_fc` (LONE) or `fc_grad` (SECOND; FIRST
+// has none, and its row no FC weights).
+template <WavePart PART>
+__device__ __forceinline__ void wave_flush(WaveState& st, float sign, const f4 (&g_fc)[12], const float (&fc_grad)[NY][3], float* row, float* park) {
   const int l = threadIdx.x & 63, q = l >> 4, n16 = l & 15;
   // The stores are grouped by the lanes that take part (one branch per group, not one per store):
   // FC rows o = 4 q + r < 10 are registers 0, 1 of the quarters 0..2 and registers 2, 3 of the quarters
   // 0, 1; C2 rows j = 4 q + r < 12 are every register of the quarters 0..2, and of the last tap tile
   // only the columns n16 < 6 are taps.
-  {
+  if (PART == SECOND) {
+#pragma unroll
+    for (int o = 0; o < NY; ++o)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) row[OFF_FC + o * NS2 + l + 64 * k] = fc_grad[o][k];
+  }
+  if (PART == LONE) {
     float* fc = row + OFF_FC + 4 * q * NS2 + n16;
     if (q < 3) {
 #pragma unroll
