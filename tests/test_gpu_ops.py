@@ -240,6 +240,17 @@ def test_fc(B, I, O):
         assert_close(host(d_b), ref_db, RTOL_ACT, "fc_bwd_bias")
 
 
+# Rows of an odd and of an even number of outputs (one and two per thread): exact, by the definition's own order of additions.
+@pytest.mark.parametrize("shape", [(1, 1, 2, 2), (3, 2, 2, 4), (2, 3, 6, 10), (5, 1, 4, 12), (17, 6, 24, 24), (9, 3, 22, 22), (300, 5, 2, 6)])
+def test_avgpool_items(shape):
+    B, C, H, W = shape
+    x, d = inputs.make_signed(shape, 123), inputs.make_signed((B, C, H // 2, W // 2), 124)
+    ref = (x[:, :, 0::2, 0::2] + x[:, :, 0::2, 1::2] + x[:, :, 1::2, 0::2] + x[:, :, 1::2, 1::2]) * np.float32(0.25)
+    assert np.array_equal(host(binding.avgpool_fwd(dev(x))), ref)
+    assert np.array_equal(host(binding.avgpool_bwd(dev(d))), (d * np.float32(0.25)).repeat(2, axis=2).repeat(2, axis=3))
+
+
+
 def test_fc_of_the_network_with_looping_waves():
     """The network's own fully connected shape has kernels in which a wave takes sixteen rows (four for
     the weight gradient) at a time; 70001 rows make their waves loop and leave a ragged last tile.  The
