@@ -1225,7 +1225,13 @@ int launch_wgrad(WgradPlan& p, const float* in, const float* d_out, float* d_k, 
                  int KH, int KW, float* part, hipStream_t st) {
   switch (p.kernel) {
     case WgradPlan::TILED: return launch_tile_wgrad<false>(p.tile, in, d_out, d_k, d_bias, part, st);
-    case WgradPlan::FC: fc::bwd_weight_kernel<<<p.gx, fc::WGRAD_THREADS, 0, st>>>(in, d_out, part, B); break;
+    case WgradPlan::FC:
+      if (B <= fc::DIRECT_MAX_ROWS) {
+        fc::bwd_weight_direct_kernel<<<fc::NT, fc::WGRAD_THREADS, 0, st>>>(in, d_out, d_k, d_bias, B);
+        return launched();
+      }
+      fc::bwd_weight_kernel<<<p.gx, fc::WGRAD_THREADS, 0, st>>>(in, d_out, part, B);
+      break;
     case WgradPlan::CONV1: launch_conv1_wgrad(in, d_out, part, B, p.gx, st); break;
     case WgradPlan::CONV2: launch_conv2_wgrad(in, d_out, part, B, p.gx, st); break;
     default: return CNN_EINVAL;

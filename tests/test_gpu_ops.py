@@ -240,6 +240,19 @@ def test_fc(B, I, O):
         assert_close(host(d_b), ref_db, RTOL_ACT, "fc_bwd_bias")
 
 
+# The network's weight gradient of few rows in one kernel (up to 2048): less than a step, whole and ragged steps, a wave's loads
+# in one round, in two and just beyond, and the first size of the two kernels.  Against float64; 2048 products of magnitude 1
+# summed in fp32 stay within 2^-24 sqrt(2048) of the scale of the sums.
+@pytest.mark.parametrize("B", [1, 3, 4, 31, 33, 256, 257, 2047, 2048, 2049])
+def test_fc_weight_gradient_of_few_rows(B):
+    x, d = inputs.make_signed((B, 192), 121), inputs.make_signed((B, 10), 122)
+    d_w, d_b = binding.fc_bwd_weight(dev(x), dev(d))
+    assert_close(host(d_w), d.astype(np.float64).T @ x.astype(np.float64), RTOL_GRAD, "fc_bwd_weight of few rows")
+    assert_close(host(d_b), d.astype(np.float64).sum(0), RTOL_GRAD, "fc_bwd_bias of few rows")
+    again, none = binding.fc_bwd_weight(dev(x), dev(d), want_bias=False)
+    assert none is None and torch.equal(again, d_w)
+
+
 # Rows of an odd and of an even number of outputs (one and two per thread): exact, by the definition's own order of additions.
 @pytest.mark.parametrize("shape", [(1, 1, 2, 2), (3, 2, 2, 4), (2, 3, 6, 10), (5, 1, 4, 12), (17, 6, 24, 24), (9, 3, 22, 22), (300, 5, 2, 6)])
 def test_avgpool_items(shape):
