@@ -76,7 +76,7 @@ __device__ __forceinline__ void judge_lanes(float y, bool out_lane, int label, f
   loss = fmaf(0.5f, (from(sq, 0) + from(sq, 16)) + from(sq, 32), loss);
 }
 
-// Forward-only: yhat[B,10], optional activation dump, optional (count, loss) per wave.  One wave per image, FWAVES
+// Forward-only: yhat[B,10], optional activation dump, optional (count, loss) per workgroup.  One wave per image, FWAVES
 // waves per workgroup (they share the operands), one workgroup per compute unit; wave w of workgroup b takes the images
 // b + blocks * (w + FWAVES k).
 // What bounds it: a SIMD's issue.  264 matrix instructions at 6 ns (7.6 alone; a vector instruction hides under half of
@@ -199,10 +199,15 @@ __global__ __launch_bounds__(64 * FWAVES) void forward_kernel(const float* __res
     if (labels) judge_lanes(y, out_lane, labels[n], n_ok, loss);
     wave_sync();
   }
-  if (eval_partial && l == 0) {
-    const size_t gw = (size_t)blockIdx.x * FWAVES + wave;
-    eval_partial[2 * gw] = n_ok;  // exact: far fewer than 2^24 images per wave
-    eval_partial[2 * gw + 1] = loss;
+  if (!eval_partial) return;
+  __shared__ float2 sums[FWAVES];
+  if (l == 0) sums[wave] = float2{n_ok, loss};  // (exact: far fewer than 2^24 images per workgroup)
+  __syncthreads();
+  if (t == 0) {
+    float2 all = sums[0];
+#pragma unroll
+    for (int k = 1; k < FWAVES; ++k) all.x += sums[k].x, all.y += sums[k].y;
+    reinterpret_cast<float2*>(eval_partial)[blockIdx.x] = all;
   }
 }
 
@@ -227,37 +232,38 @@ __global__ __launch_bounds__(64 * GWAVES) void forward_group_kernel(const float*
   }
 }
 
-// Sums the G (count, loss) pairs: 1024 interleaved strands (at most two pairs each for the 2048
-// waves of the forward kernel, so the loads are one memory round trip), then a fixed tree over the
-// strands.  The counts are whole numbers (each wave's is far below 2^24, so exact in its float) and
-// are added as 64-bit integers.
-constexpr int EVAL_REDUCE_THREADS = 1024;
+// Sums the G (count, loss) pairs, one per workgroup of the forward kernel: strand t takes the pairs t, t + 256, .. (at most four,
+// one memory round trip), then a fixed tree over a wave's lanes and the waves in order.  The counts are whole numbers (each far
+// below 2^24, so exact in its float; together no more than the images, which an int counts).  It is bound by the launch and a round trip:
+// sixteen waves with a barrier per level of the tree, over a pair per wave, took 0.8 us more from 1025 images on.
+constexpr int EVAL_REDUCE_THREADS = 256;
 __global__ __launch_bounds__(EVAL_REDUCE_THREADS) void eval_reduce_kernel(const float* __restrict__ eval_partial,
                                                                           int G, int64_t* __restrict__ n_correct,
                                                                           float* __restrict__ loss_sum) {
-  __shared__ long long counts[EVAL_REDUCE_THREADS];
-  __shared__ float losses[EVAL_REDUCE_THREADS];
+  constexpr int ROUNDS = FWD_GROUP_MAX_BATCH / EVAL_REDUCE_THREADS, WAVES = EVAL_REDUCE_THREADS / 64;
+  __shared__ int counts[WAVES];
+  __shared__ float losses[WAVES];
   const int t = threadIdx.x;
-  long long ok = 0;
+  float2 pair[ROUNDS];
+#pragma unroll
+  for (int k = 0; k < ROUNDS; ++k) {
+    const int g = t + EVAL_REDUCE_THREADS * k;
+    pair[k] = g < G ? reinterpret_cast<const float2*>(eval_partial)[g] : float2{0.0f, 0.0f};
+  }
+  int ok = 0;
   float loss = 0.0f;
-  for (int g = t; g < G; g += EVAL_REDUCE_THREADS) {
-    const float2 pair = reinterpret_cast<const float2*>(eval_partial)[g];
-    ok += (long long)pair.x;
-    loss += pair.y;
+#pragma unroll
+  for (int k = 0; k < ROUNDS; ++k) ok += (int)pair[k].x, loss += pair[k].y;
+#pragma unroll
+  for (int step = 1; step < 64; step *= 2) {
+    ok += __shfl_xor(ok, step);
+    loss += __shfl_xor(loss, step);
   }
-  counts[t] = ok;
-  losses[t] = loss;
+  if ((t & 63) == 0) counts[t >> 6] = ok, losses[t >> 6] = loss;
   __syncthreads();
-  for (int half = EVAL_REDUCE_THREADS / 2; half >= 1; half >>= 1) {
-    if (t < half) {
-      counts[t] += counts[t + half];
-      losses[t] += losses[t + half];
-    }
-    __syncthreads();
-  }
   if (t == 0) {
-    if (n_correct) *n_correct = (int64_t)counts[0];
-    if (loss_sum) *loss_sum = losses[0];
+    if (n_correct) *n_correct = (int64_t)counts[0] + counts[1] + counts[2] + counts[3];
+    if (loss_sum) *loss_sum = (losses[0] + losses[1]) + (losses[2] + losses[3]);
   }
 }
 
@@ -675,7 +681,7 @@ struct cnn_ctx {
   float* tabg;          // [TABG_FLOATS]: the operand table expanded from w, kept in step with it
   int32_t* dest;        // [PSTRIDE][TABLE_MAX_DEST]: slots of tabg that hold parameter p
   float* partial;       // [partial_rows_for(max_batch)][PSTRIDE]
-  float* eval_partial;  // [eval_pairs(max_batch)][2]: one pair per wave, or per image
+  float* eval_partial;  // [eval_pairs(max_batch)][2]: a pair per workgroup
   float* fc_hist;       // [max_batch][FC_HIST] when max_batch > GROUP_MAX_BATCH: per image, what the FC weight gradient needs
   unsigned* sync;       // [SYNC_WORDS]: barrier flags of the device-side epoch loop, then its error word
   int epoch_mode = 0;         // 1: cnn_train_epoch runs as one kernel where it can
@@ -694,11 +700,10 @@ constexpr size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // Waves of the forward-only kernel for B images: whole workgroups, at most one of FWAVES waves per compute unit.
 inline int forward_blocks(int B) { return B < FWAVES * TRAIN_BLOCKS ? (B + FWAVES - 1) / FWAVES : TRAIN_BLOCKS; }
 
-// (count, loss) pairs an evaluation can write: one per image (eight waves share one) or one per wave.
+// (count, loss) pairs an evaluation can write: one per workgroup.
 inline int eval_pairs(int max_batch) {
-  const int by_group = max_batch < FWD_GROUP_MAX_BATCH ? max_batch : FWD_GROUP_MAX_BATCH;
-  const int by_wave = forward_blocks(max_batch) * FWAVES;
-  return by_wave > by_group ? by_wave : by_group;
+  static_assert(TRAIN_BLOCKS <= FWD_GROUP_MAX_BATCH, "of one wave per image there are fewer");
+  return max_batch < FWD_GROUP_MAX_BATCH ? max_batch : FWD_GROUP_MAX_BATCH;
 }
 
 struct Layout {
@@ -748,7 +753,7 @@ int run_forward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B,
   auto kernel = dumps ? forward_kernel<true> : forward_kernel<false>;
   kernel<<<blocks, 64 * FWAVES, 0, ctx->stream>>>(images, labels, B, ctx->w, ctx->tabg, yhat, dump, pairs);
   if (hipGetLastError() != hipSuccess) return CNN_EHIP;
-  return blocks * FWAVES;
+  return blocks;
 }
 
 int run_backward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B, float scale,
