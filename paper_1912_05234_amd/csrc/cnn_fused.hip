@@ -502,12 +502,17 @@ __global__ __launch_bounds__(256) void expand_kernel(const float* __restrict__ w
 // Adds the G partial rows in a fixed order (sixteen interleaved strands, each summed in row
 // order, then a fixed tree over the strands) and either applies  w <- w - scale * g  (grad_out ==
 // nullptr) or stores g.  An updated parameter is also written to its slots of the expanded operand
-// table, dest[p][0..3] (-1 = none).  One block of work per 64 parameters, `block` < PSTRIDE / 64; the
-// lanes of a wave read 64 consecutive floats of a row, and a strand keeps eight row reads in flight.
-// THREADS = 1024: one strand per wave; 512: every wave takes strands s and s + 8, one after the
+// table, dest[p][0..3] (-1 = none).  One block of work per P parameters, `block` < PSTRIDE / P; neighbouring
+// lanes read P consecutive floats of a row, and a strand keeps sixteen row reads in flight.
+// THREADS = 16 P: one strand per thread; half of that: every thread takes strands s and s + 8, one after the
 // other (same sums, same order).  COHERENT (device-side epoch loop: rows, weights and table are
 // written and read by different compute units within one kernel): agent-scope loads and stores.
-constexpr int RSTRANDS = 16;
+// What bounds it: the launch and one memory round trip; the rows come from memory, at the rate of the compute units that ask for
+// them.  With P = 32 (a cache line of a row) twice as many ask as with 64, and all 256 rows of the largest calls are one trip.
+// Step of 256 / 512 / 1000 images, us, with P = 64 13.17 / 20.33 / 22.43, 32 13.08 / 19.96 / 22.27, 16 (half lines) 13.63 /
+// 21.13 / 22.88; up to 128 images 32 is as fast as 64.
+constexpr int RSTRANDS = 16, REDUCE_PARAMS = 32;
+static_assert(PSTRIDE % REDUCE_PARAMS == 0, "whole blocks of parameters");
 template <bool COHERENT>
 __device__ __forceinline__ float ld_shared(const float* p) {
   return COHERENT ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
@@ -519,43 +524,53 @@ __device__ __forceinline__ void st_shared(float* p, float v) {
   else
     *p = v;
 }
-template <int THREADS, bool COHERENT>
-__device__ __forceinline__ void reduce_update_block(int block, float (&red)[RSTRANDS][64],
+template <int P, int THREADS, bool COHERENT>
+__device__ __forceinline__ void reduce_update_block(int block, float (&red)[RSTRANDS][P],
                                                     const float* __restrict__ partial, int G, float scale,
                                                     float* __restrict__ w, const int32_t* __restrict__ dest,
                                                     float* __restrict__ tabg, float* __restrict__ grad_out,
                                                     float* __restrict__ loss_sum) {
-  static_assert(THREADS == 64 * RSTRANDS || THREADS == 32 * RSTRANDS, "one or two strands per wave");
-  constexpr int WAVES_HERE = THREADS / 64, PASSES = RSTRANDS / WAVES_HERE;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int p = block * 64 + lane;
+  static_assert(THREADS == P * RSTRANDS || THREADS == P * RSTRANDS / 2, "one or two strands per thread");
+  constexpr int TOGETHER = THREADS / P, PASSES = RSTRANDS / TOGETHER;
+  const int lane = threadIdx.x % P, first = threadIdx.x / P;
+  const int p = block * P + lane;
   // what the update needs besides the sum is fetched first, so that it arrives during the reduction
   float w_old = 0.0f;
   int4 d = int4{-1, -1, -1, -1};
-  if (wave == 0 && !grad_out && p < NPARAM) {
+  if (first == 0 && !grad_out && p < NPARAM) {
     w_old = ld_shared<COHERENT>(w + p);
     d = reinterpret_cast<const int4*>(dest)[p];
   }
   const float* src = partial + p;
 #pragma unroll
   for (int pass = 0; pass < PASSES; ++pass) {
-    const int strand = wave + WAVES_HERE * pass;
-    // eight row reads in flight per strand; a row index past G reads nothing and adds 0.0
+    const int strand = first + TOGETHER * pass;
+    // up to sixteen row reads in flight per strand; a row index past G reads nothing and adds 0.0
     float a[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    for (int g = strand; g < G; g += 8 * RSTRANDS) {
-      float r[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int row = g + k * RSTRANDS;
+    for (int g = 0; g < G; g += 16 * RSTRANDS) {
+      const bool both = g + 8 * RSTRANDS < G;
+      float r[16];
+      auto fetch = [&](int k) {
+        const int row = g + strand + k * RSTRANDS;
         r[k] = row < G ? ld_shared<COHERENT>(src + (size_t)row * PSTRIDE) : 0.0f;
+      };
+#pragma unroll
+      for (int k = 0; k < 8; ++k) fetch(k);
+      if (both) {
+#pragma unroll
+        for (int k = 8; k < 16; ++k) fetch(k);
       }
 #pragma unroll
       for (int k = 0; k < 8; ++k) a[k] += r[k];
+      if (both) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) a[k] += r[8 + k];
+      }
     }
     red[strand][lane] = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
   }
   __syncthreads();
-  if (wave == 0) {
+  if (first == 0) {
     float t[RSTRANDS];
 #pragma unroll
     for (int k = 0; k < RSTRANDS; ++k) t[k] = red[k][lane];
@@ -581,14 +596,15 @@ __device__ __forceinline__ void reduce_update_block(int block, float (&red)[RSTR
   }
 }
 
-__global__ __launch_bounds__(64 * RSTRANDS) void reduce_update_kernel(const float* __restrict__ partial, int G,
+template <int P>
+__global__ __launch_bounds__(P * RSTRANDS) void reduce_update_kernel(const float* __restrict__ partial, int G,
                                                                      float scale, float* __restrict__ w,
                                                                      const int32_t* __restrict__ dest,
                                                                      float* __restrict__ tabg,
                                                                      float* __restrict__ grad_out,
                                                                      float* __restrict__ loss_sum) {
-  __shared__ float red[RSTRANDS][64];
-  reduce_update_block<64 * RSTRANDS, false>(blockIdx.x, red, partial, G, scale, w, dest, tabg, grad_out, loss_sum);
+  __shared__ float red[RSTRANDS][P];
+  reduce_update_block<P, P * RSTRANDS, false>(blockIdx.x, red, partial, G, scale, w, dest, tabg, grad_out, loss_sum);
 }
 
 // ---- device-side epoch loop ---------------------------------------------------------------------------
@@ -663,7 +679,7 @@ __global__ __launch_bounds__(64 * GWAVES) void train_epoch_kernel(const float* _
     group_train<true, WHOLE>(images + n * NI, labels + n, tabg, row, tab, s, d_s1b);
     if (!grid_barrier(gs, &dead)) return;  // every row of the step is in memory
     for (int j = blockIdx.x; j < PSTRIDE / 64; j += gridDim.x) {  // (a batch below 61 images: several blocks each)
-      reduce_update_block<64 * GWAVES, true>(j, red, partial, B, scale, w, dest, tabg, nullptr,
+      reduce_update_block<64, 64 * GWAVES, true>(j, red, partial, B, scale, w, dest, tabg, nullptr,
                                             loss_sums ? loss_sums + k : nullptr);
       __syncthreads();  // `red` is free again
     }
@@ -777,7 +793,8 @@ int run_backward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B
     CNN_HIP_TRY(hipEventRecord(ctx->ev[2 * ctx->ev_used + 1], ctx->stream));
     ++ctx->ev_used;
   }
-  reduce_update_kernel<<<PSTRIDE / 64, 64 * RSTRANDS, 0, ctx->stream>>>(ctx->partial, G, scale, ctx->w, ctx->dest,
+  constexpr int P = REDUCE_PARAMS;
+  reduce_update_kernel<P><<<PSTRIDE / P, P * RSTRANDS, 0, ctx->stream>>>(ctx->partial, G, scale, ctx->w, ctx->dest,
                                                               ctx->tabg, grad_out, loss_sum);
   if (hipGetLastError() != hipSuccess) return CNN_EHIP;
   return CNN_OK;
