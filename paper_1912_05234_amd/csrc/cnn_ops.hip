@@ -747,9 +747,9 @@ TileWgradPlan plan_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, in
 // The second kernel of a weight gradient with more than one workgroup column.
 int launch_reduce_rows(const float* part, int G, int RS, int nk, float* d_k, float* d_bias, hipStream_t st) {
   if (G > 1 && RS > 8192)
-    tile::reduce_rows_kernel<64><<<(unsigned)ceil_div(RS, 64), 1024, 0, st>>>(part, G, RS, nk, d_k, d_bias);
+    tile::reduce_rows_kernel<64><<<(unsigned)ceil_div(RS, 64), tile::REDUCE_THREADS, 0, st>>>(part, G, RS, nk, d_k, d_bias);
   else if (G > 1)
-    tile::reduce_rows_kernel<16><<<(unsigned)ceil_div(RS, 16), 1024, 0, st>>>(part, G, RS, nk, d_k, d_bias);
+    tile::reduce_rows_kernel<16><<<(unsigned)ceil_div(RS, 16), tile::REDUCE_THREADS, 0, st>>>(part, G, RS, nk, d_k, d_bias);
   return launched();
 }
 
@@ -878,10 +878,10 @@ constexpr size_t NO_PARTIAL_SUMS_BYTES = 16;
 
 struct WgradPlan {
   // which kernel: cnn_tile.h by the plan in `tile`, or one of the network's own layers (gx workgroups that leave partial
-  // 16 x 16 tiles, MT x NT of them with P shifts, for igemm::wgrad_reduce_kernel)
+  // 16 x 16 tiles, NT of them, for igemm::wgrad_reduce_kernel)
   enum { PLAIN, TILED, CONV1, CONV2, FC } kernel = PLAIN;
   TileWgradPlan tile;
-  int P = 1, MT = 1, NT = 0;
+  int NT = 0;
   unsigned gx = 0;
   size_t workspace_bytes = 0;  // what the plan uses
   size_t least_bytes = 0;      // what it can run with
@@ -891,7 +891,7 @@ WgradPlan plan_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
   WgradPlan p;
   if (conv1::shape_fits(Cin, H, W, Cout, KH, KW)) {
     p.kernel = WgradPlan::CONV1;
-    p.P = 2, p.NT = 2;  // rows (map, x parity), columns the shifted taps: what the second kernel joins
+    p.NT = 2;  // rows (map, x parity), columns the shifted taps: what the second kernel joins
     p.gx = image_groups(B, conv1_wgrad_images(B));
     p.workspace_bytes = conv1::bwd_weight_workspace_bytes(p.gx);
     p.least_bytes = conv1::bwd_weight_workspace_bytes(image_groups(B, 8));
@@ -1237,9 +1237,9 @@ int launch_wgrad(WgradPlan& p, const float* in, const float* d_out, float* d_k, 
     default: return CNN_EINVAL;
   }
   const size_t outputs = (size_t)Cout * Cin * KH * KW + Cout;
-  const int epw = outputs >= 2048 ? 16 : outputs >= 512 ? 8 : 4;  // outputs per workgroup of the second kernel
-  igemm::wgrad_reduce_kernel<<<(unsigned)((outputs + epw - 1) / epw), igemm::THREADS, 0, st>>>(
-      part, (int)p.gx, p.MT, p.NT, Cout, Cin, KH, KW, p.P, epw, d_k, d_bias);
+  const int epw = p.kernel == WgradPlan::CONV1 ? 4 : 8;  // outputs per workgroup of the second kernel: 156 of the first layer, 1812 and 1930
+  const auto second = p.kernel == WgradPlan::CONV1 ? igemm::wgrad_reduce_kernel<4, 2> : igemm::wgrad_reduce_kernel<8, 1>;
+  second<<<(unsigned)((outputs + epw - 1) / epw), igemm::THREADS, 0, st>>>(part, (int)p.gx, p.NT, Cout, Cin, KH, KW, d_k, d_bias);
   return launched();
 }
 
