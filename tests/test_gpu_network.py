@@ -70,6 +70,32 @@ def test_batch_gradient(B):
     np.testing.assert_array_equal(host(net.get_weights_flat()), inputs.flatten(w))
 
 
+# Where the training kernels change (two workgroups per image up to 128, two waves per image from 513 to 1024, compute units with
+# two to four images) and where the update kernel's rows end (strands of sixteen, one trip or two of them).
+@pytest.mark.parametrize("B", [2, 16, 17, 127, 128, 129, 145, 255, 256, 513, 514, 767, 769, 1024])
+def test_gradient_at_the_edges_of_the_kernels(B):
+    images, labels = inputs.make_batch(B, 28)
+    w = weights(biases=True)
+    grad, loss = binding.CNN(w, max_batch=B).gradient(dev(images), dev(labels))
+    ref_loss, ref_g = oracle_grad(images, labels, inputs.flatten(w))
+    g, r = inputs.unflatten(host(grad)), inputs.unflatten(ref_g)
+    for name in ("k1", "b1", "k2", "b2", "fc", "b"):
+        assert_close(g[name], r[name], RTOL_GRAD, "grad %s (B=%d)" % (name, B))
+    assert abs(host(loss)[0] - ref_loss) <= 1e-5 * ref_loss
+
+
+# Sums of an evaluation, a pair per workgroup: one image per workgroup up to 1024, eight beyond, the last of them with fewer.
+@pytest.mark.parametrize("B", [1, 63, 64, 255, 256, 257, 1023, 1024, 1025, 1032, 2047, 2048, 2049])
+def test_evaluation_sums(B):
+    images, labels = inputs.make_batch(B, 29)
+    net = binding.CNN(weights(biases=True), max_batch=B)
+    yhat = host(net.forward(dev(images))).astype(np.float64)
+    right, loss = net.evaluate(dev(images), dev(labels))
+    assert int(host(right)[0]) == int((yhat.argmax(axis=1) == labels).sum())
+    want = 0.5 * np.square(yhat - np.eye(10)[labels]).sum()
+    assert abs(host(loss)[0] - want) <= 1e-5 * want
+
+
 @pytest.mark.parametrize("B", [512, 640, 700])
 def test_gradient_of_a_repeated_image(B):
     """B copies of ONE image: the batch gradient is B times that image's gradient, so every layer's

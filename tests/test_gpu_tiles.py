@@ -116,6 +116,18 @@ def test_unpacked_weight_gradients(case, bf16):
     assert_close(host(d_b), p_b, RTOL_ACT, "unpacked conv_bwd_bias")
 
 
+# Second kernels of the weight gradients: more rows of partial sums than one trip takes, and columns of sixteen and of 64.
+@pytest.mark.parametrize("case", [(1000, 3, 32, 32, 16, 5, 5), (90, 16, 28, 28, 64, 3, 3), (700, 2, 30, 30, 5, 3, 3)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_second_kernels(case, bf16):
+    B, Cin, H, W, Cout, KH, KW = case
+    x, d = inputs.make_signed((B, Cin, H, W), 112), inputs.make_signed((B, Cout, H - KH + 1, W - KW + 1), 113)
+    p_k, p_b = weight_gradient(oracle.round_bf16(x) if bf16 else x, oracle.round_bf16(d) if bf16 else d, KH, KW)
+    d_k, d_b = binding.conv_bwd_weight(dev(x), dev(d), bf16=bf16)
+    assert_close(host(d_k), p_k, RTOL_ACT, "conv_bwd_weight of many rows")
+    assert_close(host(d_b), p_b, RTOL_ACT, "conv_bwd_bias of many rows")
+
+
 # Packed columns whose taps lie in runs of two or four: with and without a border, ragged rows, bands and channel chunks,
 # whole images per unit, and (the last two) rows of odd length, which have no runs without a border.
 @pytest.mark.parametrize("case", [(33, 3, 28, 32, 3, 5, 5), (500, 3, 32, 32, 15, 5, 5), (130, 2, 20, 11, 25, 5, 5), (18, 5, 33, 33, 2, 3, 3),
