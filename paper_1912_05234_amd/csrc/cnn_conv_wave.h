@@ -154,7 +154,7 @@ struct __align__(16) WgradLds {
   float bsum[WAVES][64];
 };
 // part: [gridDim.x][10 tiles][16 rows j][16 columns] then the bias rows [gridDim.x][16] (the layout
-// igemm::wgrad_reduce_kernel reads with MT = 1, NT = 10, P = 1).
+// igemm::wgrad_reduce_kernel reads with NT = 10, P = 1).
 template <int WAVES, int PARTS>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 4))) void bwd_weight_kernel(const float* __restrict__ in,
                                                              const float* __restrict__ d_out,

@@ -137,7 +137,7 @@ struct __align__(16) WgradLds {
   float bsum[WGRAD_WAVES][64];
 };
 // part: [gridDim.x][12 tiles][16 rows o][16 columns] then the bias rows [gridDim.x][16] (the layout
-// igemm::wgrad_reduce_kernel reads with MT = 1, NT = 12, P = 1).
+// igemm::wgrad_reduce_kernel reads with NT = 12, P = 1).
 __global__ __launch_bounds__(WGRAD_THREADS) void bwd_weight_kernel(const float* __restrict__ in,
                                                                    const float* __restrict__ d_out,
                                                                    float* __restrict__ part, int B) {
