@@ -573,6 +573,7 @@ int launch_tile_conv_rounded(const TileConvPlan& p, hipStream_t stream) {
 struct TileWgradPlan {
   tile::WgradArgs a;
   int nt = 0, mt = 0;
+  bool rounded = false;  // with operands rounded to bfloat16
   dim3 grid;
   size_t lds_bytes = 0, workspace_bytes = 0, interface_bytes = 0;
   double cost = 0.0;
@@ -639,8 +640,7 @@ void tile_wgrad_candidates(TileWgradPlan& best, TileWgradPlan& p, int NB, int TH
   if (a.bands == 1 && a.NTG == 1 && (long long)a.Cin * plane % 4 == 0) a.vec_x = 16;  // (runs of whole images)
   const long long end = tile::wgrad_end_floats(nt, mt), all = tile::wgrad_lds(a).total, lds = 4 * (all > end ? all : end);
   if (lds > TILE_LDS_LIMIT) return;
-  const int regs = 4 * nt * mt + 3 * nt + 60;  // registers a wave needs, roughly
-  const int resident = std::min(CU_LDS / ((int)lds + 512), 512 / regs);
+  const int resident = std::min(CU_LDS / ((int)lds + 512), tile::wgrad_residency(nt, mt, p.rounded));
   auto loads = [&](int floats) { return a.vec_x == 16 ? k.x16 * up(floats, 256) : k.x4 * up(floats, 64); };
   const double around = per_unit + NB * (a.bands == 1 ? loads(a.LI) : a.CG * loads(a.LP));
   for (int res = few; res <= most && res <= resident && (res <= 1 || (long long)a.units * gy > NUM_CU * (res - 1)); ++res) {
@@ -699,6 +699,7 @@ size_t tile_layout_bytes(int B, int Cin, int H, int W, int Cout, int KH, int KW)
 // (305 images 21 -> 12, 33 x 23, 4 x 4 43.6 -> 46.6 us), packed ones too (850 images 24 -> 1, 19 x 11, 5 x 5 19.7 -> 25.1).
 TileWgradPlan search_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW, bool rounded) {
   TileWgradPlan best, p;
+  p.rounded = rounded;
   tile::WgradArgs& a = p.a;
   a.in = a.d_out = nullptr, a.out_k = a.out_b = nullptr;
   a.B = B, a.Cin = Cin, a.H = H, a.W = W, a.Cout = Cout, a.KH = KH, a.KW = KW, a.Ho = H - KH + 1, a.Wo = W - KW + 1;

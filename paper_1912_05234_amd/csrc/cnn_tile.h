@@ -696,6 +696,15 @@ __device__ __forceinline__ void stage_slots(const WgradArgs& g, const float* d, 
   }
 }
 
+// Waves per SIMD (= workgroups per compute unit) the registers allow, which plans count on: sums, the taps' operands and addresses,
+// and with ROUND a block's rounded operands beside those read.  Left unbounded the compiler took up to 28 registers more for two row
+// tiles, of eight tap tiles two workgroups were resident instead of three, and plans that asked for three ran a second
+// turn: 9770 images 2 -> 23, 8 x 21, 7 x 7 55 us, with the bound 42; 450 images 28 -> 17, 18 x 34, 2 x 2 61 and 43.
+__host__ __device__ constexpr int wgrad_residency(int nt, int mt, bool round) {
+  const int fit = 512 / (4 * nt * mt + 3 * nt + 60 + (round ? 4 * mt : 0));
+  return fit < 4 ? fit : 4;
+}
+
 // ROUND: the reduced-precision form for few images (cnn_tile_bf16.h needs eight to fill its operands): operands are
 // rounded to bfloat16 as they are read, their products, exact in fp32, are summed as in the fp32 form.
 // PACKED: P > 1, a row of d_out is every P-th pixel and is staged float by float.  Otherwise the slots of an image are its
@@ -703,7 +712,7 @@ __device__ __forceinline__ void stage_slots(const WgradArgs& g, const float* d, 
 // us, float by float -> 16 bytes: 1000 images 1 -> 32, 28 x 28, 3 x 3 47 -> 38; 500 images 3 -> 64, 32 x 32, 3 x 3 68 -> 52;
 // 2000 images 4 -> 16, 14 x 14, one tap 22.4 -> 17.6.
 template <int NT, int MT, bool ROUND, bool PACKED>
-__global__ __launch_bounds__(THREADS) void wgrad_kernel(const WgradArgs g) {
+__global__ __launch_bounds__(THREADS, wgrad_residency(NT, MT, ROUND)) void wgrad_kernel(const WgradArgs g) {
   extern __shared__ __align__(16) float lds[];
   const WgradLds L = wgrad_lds(g);
   int* pb = reinterpret_cast<int*>(lds + L.pb);
