@@ -615,6 +615,12 @@ bool tile_wgrad_form(TileWgradPlan& p, const TileWgradPlan& best, int P, int mt,
   return k.scale * (9500.0 + 256.0 * nt * mt + rounds * (64.0 * nt * mt + k.tile * nt + k.block + (P == 1 ? k.d16 / 4.0 : k.d4) * a.R)) < best.cost;
 }
 
+// Five tap tiles of a workgroup: where it takes a unit after the other, at most two of them per compute unit.  The fit counts the matrix
+// instructions that six tiles waste and not what more of them cost before a first unit.  Against plans without them, over random
+// layers that would take them: one unit per workgroup 0.94 to 1.03 times as fast (403 images 3 -> 20, 18 x 15, 7 x 7 15.0 -> 19.2 us),
+// from one and three quarters on 1.06 to 1.10 (worst 0.96) with two workgroups per compute unit, 1.03 to 1.05 (worst 0.88) with more.
+inline bool five_tiles_pay(int units, int gx, int gy) { return 4ll * units >= 7ll * gx && (long long)gx * gy <= 2 * NUM_CU; }
+
 // Keeps the best of one unit of p's form, `few` .. `most` workgroups per compute unit; 0: one workgroup column, which needs
 // no second kernel.
 void tile_wgrad_candidates(TileWgradPlan& best, TileWgradPlan& p, int NB, int TH, int few, int most) {
@@ -645,6 +651,7 @@ void tile_wgrad_candidates(TileWgradPlan& best, TileWgradPlan& p, int NB, int TH
   const double around = per_unit + NB * (a.bands == 1 ? loads(a.LI) : a.CG * loads(a.LP));
   for (int res = few; res <= most && res <= resident && (res <= 1 || (long long)a.units * gy > NUM_CU * (res - 1)); ++res) {
     const int gx = tile_columns(a.units, gy, res);
+    if (nt == 5 && !five_tiles_pay(a.units, gx, gy)) continue;
     const long long total = (long long)gx * gy, wgs = total > NUM_CU ? ceil_div(total, NUM_CU) : 1;
     const double share = total > NUM_CU ? (double)total / NUM_CU : 1.0, turns = up(a.units, gx);
     const double cost = k.scale * (9500.0 + 256.0 * wgs * nt * mt + turns * (share * (mfma * (wgs == 1 ? 2.0 : wgs == 2 ? 0.9 : 0.5) + around) + k.turn) + second_kernel(gx));
@@ -695,8 +702,10 @@ size_t tile_layout_bytes(int B, int Cin, int H, int W, int Cout, int KH, int KW)
   return 0;
 }
 
-// Five and nine tap tiles of a workgroup: only for unpacked fp32 plans.  With rounded operands they are slower than the fit says
-// (305 images 21 -> 12, 33 x 23, 4 x 4 43.6 -> 46.6 us), packed ones too (850 images 24 -> 1, 19 x 11, 5 x 5 19.7 -> 25.1).
+// Five tap tiles of a workgroup: only for unpacked fp32 plans (five_tiles_pay).  With rounded operands they are slower than the fit
+// says (305 images 21 -> 12, 33 x 23, 4 x 4 43.6 -> 46.6 us), packed ones too (850 images 24 -> 1, 19 x 11, 5 x 5 19.7 -> 25.1).  Nine
+// were no gain: 1.02 times as fast as without where a workgroup takes several units, 0.93 where it takes one (509 images
+// 16 -> 12, 13 x 33, 5 x 5 37.4 -> 47.4 us).
 TileWgradPlan search_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW, bool rounded) {
   TileWgradPlan best, p;
   p.rounded = rounded;
@@ -717,8 +726,8 @@ TileWgradPlan search_tile_wgrad(int B, int Cin, int H, int W, int Cout, int KH, 
     if ((P & (P - 1)) && P != 16 / Cout && a.Wo % P) continue;
     for (int mt = 1; mt <= (Cout > 16 ? 2 : 1); ++mt) {
       const int NT = up(Cin * KH * (KW + P - 1), 16);
-      for (int nt : {1, 2, 3, 4, 5, 6, 8, 9, 12}) {
-        if ((nt == 5 || nt == 9) && (P > 1 || rounded)) continue;
+      for (int nt : {1, 2, 3, 4, 5, 6, 8, 12}) {
+        if (nt == 5 && (P > 1 || rounded)) continue;
         if (nt * mt > 16 || (nt > 1 && nt / 2 >= NT) || 16 * nt < KW + P - 1 || !tile_wgrad_form(p, best, P, mt, nt)) continue;
         auto consider = [&](int NB, int TH) { tile_wgrad_candidates(best, p, NB, TH, B > 64 ? 1 : 0, tiny ? 0 : 4); };
         for (long long NB = 1; NB <= B && NB * a.Ho * a.WOP <= 1536; NB = NB < 4 ? NB + 1 : 2 * NB) consider((int)NB, a.Ho);
@@ -787,9 +796,8 @@ int launch_tile_wgrad(TileWgradPlan& p, const float* in, const float* d_out, flo
       if constexpr (ROUND) {
         return CNN_EINVAL;
       } else {
-        if (p.a.P > 1 || (p.nt != 5 && (p.nt != 9 || p.mt != 1))) return CNN_EINVAL;
-        launch_tiled(p.nt == 9 ? tile::wgrad_kernel<9, 1, false, false> : p.mt == 1 ? tile::wgrad_kernel<5, 1, false, false> : tile::wgrad_kernel<5, 2, false, false>,
-                     p.grid, p.lds_bytes, st, p.a);
+        if (p.a.P > 1 || p.nt != 5) return CNN_EINVAL;
+        launch_tiled(p.mt == 1 ? tile::wgrad_kernel<5, 1, false, false> : tile::wgrad_kernel<5, 2, false, false>, p.grid, p.lds_bytes, st, p.a);
       }
   }
   return launch_reduce_rows(part, G, p.a.RS, nk, d_k, d_bias, st);

@@ -29,6 +29,15 @@ def test_only_plain_shapes_ask_for_no_workspace():
     assert L.cnn_conv_bwd_weight_workspace_bytes(1, 18, 27, 34, 2, 5, 5) == 0
 
 
+def test_layers_of_one_unit_per_workgroup_take_no_five_tap_tiles():
+    """Columns of partial sums, which is what these layers ask for: with five tap tiles they were 48, 36 and 52, and such calls
+    up to a fifth slower."""
+    L = binding.lib()
+    for shape, columns in (((16, 24, 30, 37, 17, 7, 7), 30), ((12, 16, 28, 36, 27, 7, 7), 20), ((13, 16, 36, 37, 14, 5, 5), 39)):
+        B, Cin, H, W, Cout, KH, KW = shape
+        assert L.cnn_conv_bwd_weight_workspace_bytes(*shape) == columns * 4 * (Cout * Cin * KH * KW + Cout)
+
+
 def test_plans_do_not_depend_on_what_was_planned_before():
     """More layers than the table of plans holds, from eight threads, each in an order of its own."""
     L = binding.lib()
