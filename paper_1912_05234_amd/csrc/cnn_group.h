@@ -160,12 +160,6 @@ __device__ __forceinline__ void put_row(float* p, float v) {
     *p = v;
 }
 
-// What another compute unit may have written during this kernel (COHERENT).
-template <bool COHERENT>
-__device__ __forceinline__ float get_shared(const float* p) {
-  return COHERENT ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
-}
-
 // The whole step for the workgroup's image (`image`, `label` point at it); one partial row, `out`.
 // `d_s1b` is the second col2im target (D_S1B_FLOATS floats).  COHERENT: see put_row and TableLoad.
 template <bool COHERENT, GroupPart PART>
@@ -182,8 +176,8 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
   f4 px = reinterpret_cast<const f4*>(image)[pix];
   const int label = *label_ptr;  // in flight during the set-up too
   // the C1 forward operands (the table's last entries) and the biases come first: see barrier (1)
-  // (the FC weights go to the upper waves' registers; UPPER has no C2 input error)
-  constexpr int SKIPPED = (PART == UPPER ? TAB_C1A : TAB_AB) - TAB_FCW;
+  // (the FC weights go to the upper waves' registers, with COHERENT by way of LDS; UPPER has no C2 input error)
+  constexpr int SKIPPED = COHERENT ? 0 : (PART == UPPER ? TAB_C1A : TAB_AB) - TAB_FCW;
   TableLoad<TAB_TRAIN_ENTRIES, 64 * GWAVES, COHERENT, TAB_TRAIN_ENTRIES, TAB_C1A, TAB_FCW, SKIPPED> table;
   table.fetch(tabg);
   // every LDS cell that padded GEMM steps may read starts finite, and both col2im targets start at
@@ -227,16 +221,19 @@ __device__ __forceinline__ void group_train(const float* __restrict__ image,
       group_c1_forward<2>(tab.e + TAB_C1A * 64, tab.bias, s.img, s.pool + P_S1, wave, ln, c1);
     table.commit_rest(tab);
     // The output layer is the upper waves', each for itself (one hand-over between waves costs more than ten outputs): they wait
-    // while the lower ones are busy with C2, and their lanes hold the weights of the inputs lane, lane + 64, lane + 128.
+    // while the lower ones are busy with C2, and their lanes hold the weights of the inputs lane, lane + 64, lane + 128.  They come
+    // past LDS, in flight over the barrier, but with COHERENT: beside what that loop over steps keeps they did not fit the registers.
     float fcw[NY][3];
-    if (wave >= 4) {
+    auto fetch_fcw = [&](const float* from) {
 #pragma unroll
       for (int o = 0; o < NY; ++o)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) fcw[o][k] = get_shared<COHERENT>(tabg + (TAB_FCW + 3 * o + k) * 64 + l);
-    }
+        for (int k = 0; k < 3; ++k) fcw[o][k] = from[(TAB_FCW + 3 * o + k) * 64 + l];
+    };
+    if (!COHERENT && wave >= 4) fetch_fcw(tabg);
     CNN_GROUP_MARK(3);
     __syncthreads();  // (2) S1 and the operand table complete
+    if (COHERENT && wave >= 4) fetch_fcw(tab.e);
 
     // ---- C2 forward for pixel tile mt = wave, S2 (waves 0..3) -----------------------------------------
     f4 c2v = f4{st.bias2, st.bias2, st.bias2, st.bias2};
