@@ -32,6 +32,8 @@ constexpr int GROUP_MAX_BATCH = 512;
 // Up to this size there are two compute units per image, and two workgroups share it.  Step with one workgroup / two, us: 64
 // images 11.6 / 10.5, 128 12.1 / 11.0, 129 12.3 / 13.2, 256 13.6 / 15.0, 512 20.7 / 25.8.
 constexpr int GROUP_PAIR_MAX_BATCH = 128;
+// Beyond GROUP_MAX_BATCH and up to this size there is a SIMD for every image, and two waves of it share one (train_kernel<true>).
+constexpr int WAVE_PAIR_MAX_BATCH = 4 * TRAIN_BLOCKS;
 // The same choice for the forward pass alone: evaluation of 512 / 768 / 896 / 1024 images 9.4 / 10.9 / 12.8 / 12.9 us with eight
 // waves per image (1.8 more for every 256), 13.1 for any number up to 2048 with one.
 constexpr int FWD_GROUP_MAX_BATCH = 1024;
@@ -698,7 +700,7 @@ struct cnn_ctx {
   int32_t* dest;        // [PSTRIDE][TABLE_MAX_DEST]: slots of tabg that hold parameter p
   float* partial;       // [partial_rows_for(max_batch)][PSTRIDE]
   float* eval_partial;  // [eval_pairs(max_batch)][2]: a pair per workgroup
-  float* fc_hist;       // [max_batch][FC_HIST] when max_batch > GROUP_MAX_BATCH: per image, what the FC weight gradient needs
+  float* fc_hist;       // [max_batch][FC_HIST] when max_batch > WAVE_PAIR_MAX_BATCH: per image, what the FC weight gradient needs
   unsigned* sync;       // [SYNC_WORDS]: barrier flags of the device-side epoch loop, then its error word
   int epoch_mode = 0;         // 1: cnn_train_epoch runs as one kernel where it can
   long long wait_ticks = 0;   // longest wait at a grid barrier, in ticks of the 100 MHz wall clock
@@ -743,8 +745,8 @@ inline Layout layout_for(int max_batch) {
   l.partial = align_up(l.dest + sizeof(int32_t) * TABLE_MAX_DEST * PSTRIDE, 256);
   l.eval_partial = align_up(l.partial + sizeof(float) * PSTRIDE * g, 256);
   l.fc_hist = align_up(l.eval_partial + sizeof(float) * 2 * (size_t)eval_pairs(max_batch), 256);
-  // only the large-batch kernel keeps sums in global memory; it never launches more workgroups than images
-  const size_t hist_rows = max_batch > GROUP_MAX_BATCH ? (size_t)max_batch : 0;
+  // only the kernel with one wave per image writes history rows
+  const size_t hist_rows = max_batch > WAVE_PAIR_MAX_BATCH ? (size_t)max_batch : 0;
   l.sync = align_up(l.fc_hist + sizeof(float) * FC_HIST * hist_rows, 256);
   l.total = align_up(l.sync + sizeof(unsigned) * SYNC_WORDS, 256);
   return l;
@@ -784,7 +786,7 @@ int run_backward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B
     train_group_kernel<true><<<2 * blocks, 64 * GWAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, ctx->partial);
   else if (grouped)
     train_group_kernel<false><<<blocks, 64 * GWAVES, 0, ctx->stream>>>(images, labels, B, ctx->tabg, ctx->partial);
-  else if (B <= 4 * TRAIN_BLOCKS)
+  else if (B <= WAVE_PAIR_MAX_BATCH)
     train_kernel<true><<<blocks, 64 * TWAVES, 0, ctx->stream>>>(images, labels, B, ctx->w, ctx->tabg, ctx->partial, ctx->fc_hist);
   else
     train_kernel<false><<<blocks, 64 * TWAVES, 0, ctx->stream>>>(images, labels, B, ctx->w, ctx->tabg, ctx->partial, ctx->fc_hist);

@@ -39,6 +39,9 @@ def test_error_strings_and_workspace_size():
     assert 0 < small <= big
     # the partial count is capped; beyond it the size grows by one KiB per image (the per-image history rows)
     assert L.cnn_workspace_bytes(10 ** 7) - L.cnn_workspace_bytes(10 ** 6) == 1024 * (10 ** 7 - 10 ** 6)
+    # a kilobyte per image only where a kernel writes it: one wave per image, beyond 1024 of them
+    assert L.cnn_workspace_bytes(1025) - L.cnn_workspace_bytes(1024) == 1024 * 1025
+    assert L.cnn_workspace_bytes(1024) - L.cnn_workspace_bytes(512) <= 512 * 8 + 256  # evaluation pairs
 
 
 def test_bad_arguments_are_rejected_on_the_host():
