@@ -120,8 +120,9 @@ def test_unpacked_weight_gradients(case, bf16):
     assert_close(host(d_b), p_b, RTOL_ACT, "unpacked conv_bwd_bias")
 
 
-# Second kernels of the weight gradients: more rows of partial sums than one trip takes, and columns of sixteen and of 64.
-@pytest.mark.parametrize("case", [(1000, 3, 32, 32, 16, 5, 5), (90, 16, 28, 28, 64, 3, 3), (700, 2, 30, 30, 5, 3, 3)])
+# Second kernels of the weight gradients: columns of sixteen, of which a trip takes 512 rows (there are 512 of them, or 768 with rounded
+# operands, and 700), and of 64, of which it takes 128 (128, and 153).
+@pytest.mark.parametrize("case", [(1000, 3, 32, 32, 16, 5, 5), (700, 2, 30, 30, 5, 3, 3), (90, 16, 28, 28, 64, 3, 3), (200, 32, 20, 20, 32, 3, 3)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_second_kernels(case, bf16):
     B, Cin, H, W, Cout, KH, KW = case
