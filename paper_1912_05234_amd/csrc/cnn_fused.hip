@@ -4,13 +4,13 @@
 // backin, backavgpool) and Section 2 (batch gradient descent,
 // w := w - eta * sum_i grad F_i).
 //
-// Large batches: one wavefront owns one image at a time (cnn_train.h, cnn_split.h): the pixels, every
-// activation and every error array stay in that wave's LDS and registers; the
+// Large batches: one wavefront owns one image at a time (cnn_train.h, cnn_split.h; of 513 to 1024 images
+// two waves own one): the pixels, every activation and every error array stay in LDS and registers; the
 // only HBM traffic per image is its 3136-byte pixel block and its label.  Each wave
 // keeps its 3898 gradient sums in registers, so no atomics touch memory shared between
 // waves and a partial's value does not depend on scheduling.  A second kernel
-// adds the partials in a fixed order and applies the update.  Small batches: eight waves
-// share an image (cnn_group.h).
+// adds the partials in a fixed order and applies the update.  Small batches: eight or sixteen
+// waves share an image (cnn_group.h).
 #include <new>
 #include <vector>
 
@@ -25,17 +25,19 @@ using namespace cnn;
 
 constexpr int TRAIN_BLOCKS = 256;  // most workgroups (= gradient partials) of the large-batch training kernel: one per compute unit
 // Batches up to this size give each image to a workgroup of eight waves (lower latency per image;
-// up to two such workgroups share a compute unit); larger ones give each image to a single wave
-// (more images in flight, no barriers).  Measured crossover, gradient of 512 / 513 / 576 / 640 images: 20.8 / 24.0 / 27.5 /
-// 28.2 us with eight waves per image (a third workgroup has to wait), 23.2 / 23.1 / 23.7 / 23.7 us with one.
+// up to two such workgroups share a compute unit); larger ones give each image to two waves (train_kernel<true>, more images in
+// flight).  Gradient of 257 / 384 / 512 / 513 / 576 / 640 images, us: 16.1 / 18.4 / 19.6 / 23.1 / 26.1 / 26.6 with eight waves
+// per image (from 513 on a third workgroup has to wait), 21.3 / 21.2 / 21.2 / 21.3 / 21.4 / 21.4 with two.
 constexpr int GROUP_MAX_BATCH = 512;
 // Up to this size there are two compute units per image, and two workgroups share it.  Step with one workgroup / two, us: 64
-// images 11.6 / 10.5, 128 12.1 / 11.0, 129 12.3 / 13.2, 256 13.6 / 15.0, 512 20.7 / 25.8.
+// images 11.6 / 10.5, 128 12.1 / 11.0, 129 12.3 / 13.2, 256 13.6 / 15.0, 512 20.7 / 25.8.  Gradient with nothing in the caches:
+// 16 images 13.6 / 12.4, 64 13.9 / 12.8, 128 14.6 / 13.6.
 constexpr int GROUP_PAIR_MAX_BATCH = 128;
 // Beyond GROUP_MAX_BATCH and up to this size there is a SIMD for every image, and two waves of it share one (train_kernel<true>).
 constexpr int WAVE_PAIR_MAX_BATCH = 4 * TRAIN_BLOCKS;
-// The same choice for the forward pass alone: evaluation of 512 / 768 / 896 / 1024 images 9.4 / 10.9 / 12.8 / 12.9 us with eight
-// waves per image (1.8 more for every 256), 13.1 for any number up to 2048 with one.
+// The same choice for the forward pass alone: evaluation of 512 / 768 / 896 / 1024 / 1025 / 1280 images 10.0 / 11.1 / 13.1 / 13.1 /
+// 14.6 / 15.3 us with eight waves per image, 12.7 to 13.2 for any number up to 2048 with one (896 and 1024: 12.8, which is 0.3
+// less; the line is from before both of them added their pairs in one small workgroup).
 constexpr int FWD_GROUP_MAX_BATCH = 1024;
 // Device-side epoch loop: one barrier flag per workgroup (a batch of at most EPOCH_MAX_BATCH images:
 // thread t of a 512-thread workgroup polls flag t), one flag nobody sets, the error word.
@@ -236,8 +238,9 @@ __global__ __launch_bounds__(64 * GWAVES) void forward_group_kernel(const float*
 
 // Sums the G (count, loss) pairs, one per workgroup of the forward kernel: strand t takes the pairs t, t + 256, .. (at most four,
 // one memory round trip), then a fixed tree over a wave's lanes and the waves in order.  The counts are whole numbers (each far
-// below 2^24, so exact in its float; together no more than the images, which an int counts).  It is bound by the launch and a round trip:
-// sixteen waves with a barrier per level of the tree, over a pair per wave, took 0.8 us more from 1025 images on.
+// below 2^24, so exact in its float; together no more than the images, which an int counts).  It is bound by the launch and a round trip.
+// Evaluation of 1025 / 2048 / 10000 images, us: 13.4 / 14.1 / 42.0 with sixteen waves, a barrier per level of the tree and a pair per
+// wave, 13.0 / 13.3 / 41.2 with this.
 constexpr int EVAL_REDUCE_THREADS = 256;
 __global__ __launch_bounds__(EVAL_REDUCE_THREADS) void eval_reduce_kernel(const float* __restrict__ eval_partial,
                                                                           int G, int64_t* __restrict__ n_correct,
@@ -715,7 +718,7 @@ namespace {
 
 constexpr size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Waves of the forward-only kernel for B images: whole workgroups, at most one of FWAVES waves per compute unit.
+// Workgroups of the forward-only kernel for B images: at most one, of FWAVES waves, per compute unit.
 inline int forward_blocks(int B) { return B < FWAVES * TRAIN_BLOCKS ? (B + FWAVES - 1) / FWAVES : TRAIN_BLOCKS; }
 
 // (count, loss) pairs an evaluation can write: one per workgroup.
@@ -728,8 +731,8 @@ struct Layout {
   size_t w, tabg, dest, partial, eval_partial, fc_hist, sync, total;
 };
 
-// Partial rows a step can write: one per workgroup, in the one-wave-per-image kernel (eight waves
-// per workgroup) or in the small-batch kernel (one workgroup per image).
+// Partial rows a step can write: one per workgroup of eight waves in the kernels of large batches, one per image in the
+// small-batch kernel (one or two workgroups per image).
 inline int partial_rows_for(int max_batch) {
   const int by_wave = max_batch < TRAIN_BLOCKS ? max_batch : TRAIN_BLOCKS;
   const int by_group = max_batch < GROUP_MAX_BATCH ? max_batch : GROUP_MAX_BATCH;
@@ -777,7 +780,7 @@ int run_forward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B,
 int run_backward(cnn_ctx* ctx, const float* images, const int32_t* labels, int B, float scale,
                  float* grad_out, float* loss_sum) {
   const bool grouped = B <= GROUP_MAX_BATCH;
-  // small batches: one workgroup per image; large ones: one workgroup of eight waves per compute unit
+  // small batches: one or two workgroups per image; large ones: one workgroup of eight waves per compute unit
   const int blocks = grouped ? B : (B < TRAIN_BLOCKS ? B : TRAIN_BLOCKS);
   const int G = blocks;  // one partial row per workgroup, or per pair of workgroups
   const bool timed = (size_t)(2 * ctx->ev_used + 1) < ctx->ev.size();

@@ -908,6 +908,7 @@ WgradPlan plan_wgrad(int B, int Cin, int H, int W, int Cout, int KH, int KW) {
     p.kernel = WgradPlan::FC;
     p.NT = fc::NT;
     p.gx = image_groups(B, 4 * fc::AHEAD * fc::WGRAD_WAVES);  // a wave takes fc::AHEAD steps of four images per memory round trip
+    // (up to fc::DIRECT_MAX_ROWS nothing is left there, but a call with less of it is the plain kernel, as for any shape)
     p.workspace_bytes = p.least_bytes = fc::bwd_weight_workspace_bytes(p.gx);
   } else if (conv2::shape_fits(Cin, H, W, Cout, KH, KW)) {
     p.kernel = WgradPlan::CONV2;

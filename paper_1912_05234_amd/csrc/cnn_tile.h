@@ -818,7 +818,7 @@ __global__ __launch_bounds__(THREADS, wgrad_residency(NT, MT, ROUND)) void wgrad
       // Two blocks a trip; the NT reads of step s + 1 are issued under the instructions of step s, a block's dense operand
       // and slot offsets one block ahead.  Left to itself the compiler puts every read right before its use, and a wave waits
       // for the LDS in every step.  Kernel times, us, with the five tap tiles they now have (before: six and three): 500 images 3 -> 16, 32 x 32,
-      // 5 x 5 24.6 -> 21.2; 256 images 16 -> 32, 28 x 28, 3 x 3 39 -> 33.  (Reading two neighbouring slots as one item of eight bytes
+      // 5 x 5 24.6 -> 21.2; 256 images 16 -> 32, 28 x 28, 3 x 3 38 -> 33.  (Reading two neighbouring slots as one item of eight bytes
       // took 38 and 57: an LDS item that is not aligned to its size is slow.  Taps in another order and planes a few floats further
       // apart, so that no two of a tile share a bank: no gain.)
       i4 k0 = pq[wave], k1;

@@ -1,6 +1,7 @@
 // The training step of more than 512 images: ONE WAVEFRONT (64 lanes) OWNS ONE IMAGE from the pixel load to the last
-// gradient term, eight waves to a workgroup, two to a SIMD.  Definitions: arXiv 1912.05234, Section 3 (forward, conv, mconv,
-// sigmoid, avgpool, backweights, backbias, backin, backavgpool); the backward pass is the chain rule over those.
+// gradient term, eight waves to a workgroup, two to a SIMD; up to 1024 images, of which a SIMD has one, its two waves share it
+// (WavePart).  Definitions: arXiv 1912.05234, Section 3 (forward, conv, mconv, sigmoid, avgpool, backweights, backbias, backin,
+// backavgpool); the backward pass is the chain rule over those.
 //
 // Where the arithmetic runs
 //   C1, C2 forward        v_mfma_f32_16x16x32_bf16 on the pieces of the operands (cnn_split.h)
@@ -9,15 +10,16 @@
 //                         summed over the taps in registers (the col2im form of `backin`: no zero padding)
 //   C1 weight gradient    v_mfma_f32_16x16x4_f32: M = 12(16) rows (map, x parity), N = 30(32) shifted taps,
 //                         K = 288 pixel pairs; the C1 error is staged in LDS by column tiles of C1
-//   FC weight gradient    v_mfma_f32_16x16x4_f32, once per wave over all its images
+//   FC weight gradient    v_mfma_f32_16x16x4_f32, once per wave over all its images (of a shared one: products in registers)
 //   FC, pooling, sigmoid  fp32 VALU
 // What bounds it, 60000 images in 577 us (830 with fp32 instructions throughout), 21.8 thousand clocks of a SIMD per image:
 // 507 bfloat16 and 144 fp32 matrix instructions are 12.8 thousand of them, about 1810 vector instructions of three clocks
 // another 5.4 (few of them under a matrix instruction, see cnn_split.h), the rest are waits that the SIMD's other wave does
 // not cover; the LDS is busy for half of the time.  The C1 weight gradient stays on the fp32 instruction: as products of
 // pieces it needs 180 instructions, 300 vector instructions for the cutting, and gains nothing.
-// The waves of a workgroup share the operands in LDS and nothing else; after the barrier that completes them they do
-// not synchronise until they join their gradient sums at the end of the kernel.
+// Waves with images of their own share the operands in LDS and nothing else; after the barrier that completes them they do
+// not synchronise until they join their gradient sums at the end of the kernel.  What two waves of a shared image write, and
+// which barrier hands it over, stands at WavePart.
 #pragma once
 
 #include "cnn_split.h"
@@ -34,7 +36,8 @@ struct __align__(16) TrainOperands {
   float bias[TAB_BIAS_FLOATS];
   float ones[C1G_ONES];  // 1.0: B operand of the padding columns of the C1 weight-gradient GEMM (c1g_accumulate)
 };
-// Per wave: the image, and 3120 words that the phases use in turn, exactly one partial row together.
+// Per wave: the image, and 3120 words that the phases use in turn, exactly one partial row together.  (A shared image has those of
+// its FIRST wave; in SECOND's own are the parts that each wave makes for itself.)
 //   C1 forward          S1's pieces (first copy) at 0, the image's pieces behind them
 //   C2 forward, FC      both copies of S1, s2, d_s2
 //   C2 gradients        both copies of S1; then d_s1 and the records of d_c2
@@ -89,7 +92,16 @@ __device__ __forceinline__ int phase_lane() {
 }
 // What a wave does of an image.  LONE: everything.  Where there is a SIMD for every image and more waves than images
 // (train_kernel, PAIR), two waves of a SIMD share one: they take different column tiles of C1, pixel tiles of C2, pixels of the C2 weight
-// gradient and input maps of the C2 input error, both make the outputs, and hand over at workgroup barriers.
+// gradient and input maps of the C2 input error, both make the outputs, and hand over at workgroup barriers (all waves of the workgroup
+// pass all of them):
+//   in the image's area     written                         read by both behind
+//   image and its pieces    place_image, half each          the barrier in train_kernel
+//   S1, first copy          C1 forward, tiles 0-4 / 5-8     the first barrier here: the second copy, and with the next one C2
+//   S1, second copy         over the image's pieces, halves the second
+//   s2                      C2 forward, two pixel tiles each  the third
+//   records of d_c2         over S1, which both have done with at the fourth; two pixel tiles each  the fifth
+//   d_s1                    col2im, maps 0-3 / 4, 5         the sixth
+// and in each wave's own: its d_s2 and its tiles of the C1 error.
 enum WavePart { LONE, FIRST, SECOND };
 // The image into LDS, as it is and in pieces.
 template <WavePart PART>
@@ -133,8 +145,8 @@ __device__ __forceinline__ void s1_second_copy(float* pool) {
 // there is no next one) on return; `hist` is the image's history row (FC_HIST floats).  `sign` (1 or -1): what d_c2 is taken
 // with in the bfloat16 products, another in every other wave: the instruction cuts what it aligns towards minus infinity
 // (cnn_split.h, bwd_negative), and the sums over images would add that up.
-// FIRST and SECOND: `s` is the image's area, `own` the wave's (LONE: the same); no next image and no history: SECOND leaves the FC
-// weight gradient of its one image in `fc`, of output o and input lane + 64 k.
+// FIRST and SECOND: `s` is the image's area, `own` the wave's (LONE and FIRST: the same); no next image and no history: SECOND leaves the FC
+// weight gradient of its one image in `fc_grad`, of output o and input lane + 64 k.
 template <WavePart PART>
 __device__ __forceinline__ void wave_image(WaveState& st, WaveTrainLds& s, WaveTrainLds& own, const TrainOperands& ops,
                                            const float* __restrict__ next_image, int label, float sign, float* hist, float (&fc_grad)[NY][3]) {

@@ -4,8 +4,8 @@
 // A call of the library with small tensors is over in about 5 us on the GPU, less than Python needed to make it: 10.5 us
 // for a convolution, of which 3.4 are the launch itself, 2.9 the lookup of the current stream, 1.7 each allocation and
 // the rest the conversion of a dozen arguments by ctypes.  Here the same call takes 4.2 us, or 5 to 6 where the host's
-// processor runs slower (both occur on one machine).  A network made of single operations at batch 100 (18 calls, 22
-// launches, 73 us of kernels) is still limited by the host: 90 or 120 us a pass, 211 before.
+// processor runs slower (both occur on one machine).  A network made of single operations at batch 100 (18 calls, 21
+// launches, 67 us of kernels) is still limited by the host: 98 to 107 us a pass, 211 before.
 // Arguments arrive positionally from the wrappers in binding.py, which hold the names, the defaults and the
 // descriptions.  The interpreter lock is released around each call of the library, as ctypes does.
 #include <torch/csrc/autograd/python_variable.h>
